@@ -134,23 +134,6 @@ __device__ __forceinline__ uint64_t edge_code(int32_t a, int32_t b) {
     return ((uint64_t)lo << 32) | hi;
 }
 
-// Hash of an embedding's ascending key (see gpm_list in gpm.h).
-template <int L>
-__device__ __forceinline__ uint64_t key_hash(uint64_t (&k)[L]) {
-#pragma unroll
-    for (int i = 1; i < L; i++)
-#pragma unroll
-        for (int j = L - 1; j >= i; j--) {
-            const uint64_t a = k[j - 1], b = k[j];
-            k[j - 1] = a < b ? a : b;
-            k[j] = a < b ? b : a;
-        }
-    uint64_t h = (uint64_t)L;
-#pragma unroll
-    for (int i = 0; i < L; i++) h = fmix64((h ^ k[i]) + 0x9E3779B97F4A7C15ull);
-    return h;
-}
-
 // Must be reached by the whole wave; `active` lanes emit (a, b, c, d).
 __device__ __forceinline__ void emit4(Emitter &em, bool active, int32_t a, int32_t b, int32_t c,
                                       int32_t d, uint64_t h) {
@@ -174,12 +157,21 @@ __device__ __forceinline__ void emit4(Emitter &em, bool active, int32_t a, int32
     }
 }
 
+// A cycle x - y1 - z - y2 has the keys of its two middles, each middle y
+// giving edge_code(y, lo) < edge_code(y, hi) with lo, hi = min, max of x and
+// z.  Both grow with y, so the smaller middle's first key is the smallest and
+// the larger one's second key the largest: one compare of the two keys left
+// sorts all four.
 __device__ __forceinline__ void emit_c4(Emitter &em, bool active, int32_t x, int32_t y1,
                                         int32_t z, int32_t y2) {
     uint64_t h = 0;
     if (active) {
-        uint64_t k[4] = {edge_code(x, y1), edge_code(y1, z), edge_code(z, y2), edge_code(y2, x)};
-        h = key_hash<4>(k);
+        const int32_t lo = min(x, z), hi = max(x, z), ya = min(y1, y2), yb = max(y1, y2);
+        const uint64_t p = edge_code(ya, hi), q = edge_code(yb, lo);
+        const uint64_t k[4] = {edge_code(ya, lo), p < q ? p : q, p < q ? q : p, edge_code(yb, hi)};
+        h = 4;
+#pragma unroll
+        for (int i = 0; i < 4; i++) h = fmix64((h ^ k[i]) + 0x9E3779B97F4A7C15ull);
     }
     emit4(em, active, x, y1, z, y2, h);
 }
@@ -908,23 +900,111 @@ __global__ void __launch_bounds__(kBlock) k_c4_light_list(const int32_t *__restr
     emitter_flush(em, result);
 }
 
-// Heavy apexes, listing: workgroup per (apex, z-part); counts per z, then
-// the part's wedges grouped by z in a per-workgroup HBM buffer (in z
-// sub-ranges that fit it), then every pair of middles per z.
+// Pairs [qa, qz) of the 64 groups held in the wave's LDS arrays: group l has
+// end gz[l], middles mids[go[l]] .. mids[go[l + 1] - 1] and, as its first
+// pair, gp[l].  Each lane takes kListUnroll consecutive pairs per step: it
+// decodes the first and steps through the rest (a new group's pairs start at
+// (0, 1)), and their middles' loads go out together before any is hashed.
+// The whole wave must call it.
+__device__ __forceinline__ void emit_pairs(Emitter &em, int32_t x, const int32_t *mids,
+                                           const int64_t *gp, const int32_t *go,
+                                           const int32_t *gz, int64_t qa, int64_t qz) {
+    const int lane = lane_id();
+    for (int64_t qb = qa; qb < qz; qb += kWave * kListUnroll) {
+        const int64_t q0 = qb + (int64_t)lane * kListUnroll;
+        int32_t y1[kListUnroll], y2[kListUnroll], zz[kListUnroll];
+        int32_t l = 0, o = 0, c = 0, i = 0, j = 0, z = 0;
+        // the group holding pair q: last l with gp[l] <= q
+        auto find = [&](int64_t q) {
+            l = 0;
+#pragma unroll
+            for (int h = kWave / 2; h > 0; h >>= 1)
+                if (gp[l + h] <= q) l += h;
+            o = go[l];
+            c = go[l + 1] - o;
+            z = gz[l];
+        };
+        if (q0 < qz) {
+            find(q0);
+            // r -> (i, j), i < j, r = j (j - 1) / 2 + i; the single-precision
+            // root is off by at most one here
+            const int64_t r = q0 - gp[l];
+            int64_t jj = (int64_t)((1.0f + sqrtf(1.0f + 8.0f * (float)r)) * 0.5f);
+            while (jj * (jj - 1) / 2 > r) jj--;
+            while ((jj + 1) * jj / 2 <= r) jj++;
+            j = (int32_t)jj;
+            i = (int32_t)(r - jj * (jj - 1) / 2);
+        }
+#pragma unroll
+        for (int u = 0; u < kListUnroll; u++) {
+            const int64_t q = q0 + u;
+            y1[u] = y2[u] = zz[u] = 0;
+            if (q < qz) {
+                if (u > 0 && ++i == j) {
+                    i = 0;
+                    if (++j == c) {   // this group's pairs are done
+                        find(q);
+                        j = 1;
+                    }
+                }
+                zz[u] = z;
+                y1[u] = mids[o + i];
+                y2[u] = mids[o + j];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kListUnroll; u++) emit_c4(em, q0 + u < qz, x, y1[u], zz[u], y2[u]);
+    }
+}
+
+// A grouped task whose pairs are listed by k_c4_big_list: apex x, its
+// `groups` groups of at least two middles at arena + at (the ends gz[groups],
+// the groups' first middles go[groups + 1], the first unit of every 64
+// groups, then the middles), and its share [unit0, unit0 + units) of the
+// units of all such tasks.
+struct BigTask {
+    int64_t at, unit0;
+    int32_t x, groups, units, pad;
+};
+constexpr int kMaxBig = 1 << 16;
+constexpr int kUnitPairs = 4096;                // pairs per unit
+constexpr int kZBlocks = kPartZ / kWave;        // 64-group blocks of a task
+constexpr uint64_t kArenaWords = 1ull << 27;    // 512 MiB
+constexpr int kUnitBits = 40;                   // big_ctr: tasks above, units below
+// at most 2^30 units a task (kListBlocks tasks at once: 2^39)
+constexpr uint64_t kBigPairsMax = ((1ull << 30) - kZBlocks) * kUnitPairs;
+
+// Heavy apexes, listing: workgroup per (apex, z-part) counts the wedges per
+// z and groups the middles of every z with at least two.  A task of fewer
+// than big_pairs pairs groups into the workgroup's HBM buffer (in z
+// sub-ranges that fit it) and lists its pairs at once.  On a power-law graph
+// a few tasks hold most pairs (RMAT-15: the largest of some 60K tasks kept
+// its four waves busy for 100 of the call's 107 ms, with the chip idle), so a
+// larger task leaves its groups in the arena and its pairs to
+// k_c4_big_list, unless the arena or the task list is full.
 __global__ void __launch_bounds__(kBlock) k_c4_heavy_list(const int32_t *__restrict__ off,
                                                           const int32_t *__restrict__ adj,
                                                           const int32_t *__restrict__ deg,
                                                           const int32_t *__restrict__ list,
                                                           const int32_t *__restrict__ count_p,
                                                           int32_t nparts, uint32_t *cursor,
-                                                          int32_t *wedge_buf, Emitter em,
+                                                          int32_t *wedge_buf, int32_t *arena,
+                                                          uint64_t arena_words,
+                                                          unsigned long long *arena_used,
+                                                          uint64_t big_pairs, BigTask *big,
+                                                          unsigned long long *big_ctr, Emitter em,
                                                           unsigned long long *result) {
-    __shared__ int32_t cnt[kPartZ + 1];     // counts, then prefix offsets
+    constexpr int PER = kPartZ / kBlock;
+    __shared__ int32_t cnt[kPartZ + 1];     // counts, then prefix offsets of the kept groups
     __shared__ uint32_t cur[kPartZ];
     __shared__ int32_t s_pre[kYChunk + 1];
     __shared__ int32_t s_start[kYChunk];
-    __shared__ int32_t s_sum[kWPB];
-    __shared__ int64_t s_pp[kWPB][kWave];   // per wave: first pair of each of its 64 z
+    __shared__ int32_t s_sum[kWPB], s_grp[kWPB];
+    __shared__ int64_t s_pp[kWPB][kWave];   // per wave: the 64 groups of emit_pairs
+    __shared__ int32_t s_go[kWPB][kWave + 1], s_gz[kWPB][kWave];
+    __shared__ unsigned long long s_zp[kZBlocks], s_pairs;
+    __shared__ int32_t s_zu[kZBlocks + 1];
+    __shared__ int64_t s_at;
     __shared__ uint32_t s_task, s_z;
     const int tid = threadIdx.x, lane = lane_id(), wid = tid / kWave;
     const uint64_t ntasks = (uint64_t)(*count_p) * (uint64_t)nparts;
@@ -933,7 +1013,10 @@ __global__ void __launch_bounds__(kBlock) k_c4_heavy_list(const int32_t *__restr
     em.count = 0;
     em.hsum = 0;
     for (;;) {
-        if (tid == 0) s_task = atomicAdd(cursor, 1u);
+        if (tid == 0) {
+            s_task = atomicAdd(cursor, 1u);
+            s_pairs = 0;
+        }
         __syncthreads();
         const uint64_t t = s_task;
         __syncthreads();
@@ -943,10 +1026,11 @@ __global__ void __launch_bounds__(kBlock) k_c4_heavy_list(const int32_t *__restr
         const int32_t z0 = part * kPartZ;
         const int32_t s = off[x], dx = off[x + 1] - s;
         for (int i = tid; i <= kPartZ; i += kBlock) cnt[i] = 0;
+        if (tid < kZBlocks) s_zp[tid] = 0;
         __syncthreads();
         // wedges of this task restricted to z in [za, zb); pass 0 counts,
-        // pass 1 places y into buf by z.
-        auto walk = [&](int32_t za, int32_t zb, int pass) {
+        // pass 1 places the middles of kept groups into dst by z.
+        auto walk = [&](int32_t za, int32_t zb, int pass, int32_t *dst) {
             for (int32_t c0 = 0; c0 < dx; c0 += kYChunk) {
                 const int32_t i = c0 + tid;
                 int32_t len = 0, start = 0, y = 0;
@@ -980,36 +1064,113 @@ __global__ void __launch_bounds__(kBlock) k_c4_heavy_list(const int32_t *__restr
                         const int32_t zi = z - z0;
                         if (pass == 0) {
                             atomicAdd(&cnt[zi], 1);
-                        } else {
-                            const int32_t yj = adj[s + c0 + j];
-                            const int32_t pos = cnt[zi] - cnt[za - z0] + (int32_t)atomicAdd(&cur[zi], 1u);
-                            buf[pos] = yj;
+                        } else if (cnt[zi + 1] > cnt[zi]) {
+                            dst[cnt[zi] - cnt[za - z0] + (int32_t)atomicAdd(&cur[zi], 1u)] =
+                                adj[s + c0 + j];
                         }
                     }
                 }
                 __syncthreads();
             }
         };
-        walk(z0, z0 + kPartZ, 0);
-        // exclusive prefix of the counts (in place, cnt[kPartZ] = total)
+        walk(z0, z0 + kPartZ, 0, nullptr);
+        // the kept groups (at least two middles): exclusive prefix of their
+        // counts (in place, cnt[kPartZ] = total), their number, and the pairs
+        // of every 64 of them
+        int32_t ngroups = 0, g0 = 0;
         {
-            constexpr int PER = kPartZ / kBlock;
-            int32_t v[PER], sum = 0;
+            int32_t v[PER], sum = 0, grp = 0;
+            uint64_t pairs = 0;
             for (int q = 0; q < PER; q++) {
-                v[q] = cnt[tid * PER + q];
+                const int32_t c = cnt[tid * PER + q];
+                v[q] = c > 1 ? c : 0;
                 sum += v[q];
+                grp += c > 1;
             }
-            const int32_t inc = wave_incl_scan(sum);
-            if (lane == 63) s_sum[wid] = inc;
+            const int32_t inc = wave_incl_scan(sum), ginc = wave_incl_scan(grp);
+            if (lane == 63) {
+                s_sum[wid] = inc;
+                s_grp[wid] = ginc;
+            }
             __syncthreads();
             int32_t run = inc - sum;
-            for (int q = 0; q < wid; q++) run += s_sum[q];
+            g0 = ginc - grp;
+            for (int q = 0; q < kWPB; q++) {
+                run += q < wid ? s_sum[q] : 0;
+                g0 += q < wid ? s_grp[q] : 0;
+                ngroups += s_grp[q];
+            }
+            int32_t g = g0;
             for (int q = 0; q < PER; q++) {
                 cnt[tid * PER + q] = run;
                 run += v[q];
+                if (v[q]) {
+                    const uint64_t p = (uint64_t)v[q] * (uint64_t)(v[q] - 1) / 2;
+                    atomicAdd(&s_zp[g >> 6], (unsigned long long)p);
+                    pairs += p;
+                    g++;
+                }
             }
             if (tid == kBlock - 1) cnt[kPartZ] = run;
+            pairs = wave_sum(pairs);
+            if (lane == 0 && pairs) atomicAdd(&s_pairs, (unsigned long long)pairs);
             __syncthreads();
+        }
+        if (s_pairs >= big_pairs && s_pairs < kBigPairsMax) {
+            // units of every 64 groups, and room for the groups in the arena
+            const int32_t nzb = (ngroups + kWave - 1) / kWave;
+            if (wid == 0) {
+                int32_t carry = 0;
+                for (int32_t b0 = 0; b0 < kZBlocks; b0 += kWave) {
+                    const int32_t units =
+                        (int32_t)((s_zp[b0 + lane] + kUnitPairs - 1) / kUnitPairs);
+                    const int32_t inc = wave_incl_scan(units);
+                    s_zu[b0 + lane] = carry + inc - units;
+                    carry += __shfl(inc, 63, 64);
+                }
+                if (lane == 0) {
+                    s_zu[kZBlocks] = carry;
+                    const uint64_t words = (uint64_t)(2 * ngroups + 1 + nzb + 1 + cnt[kPartZ]);
+                    int64_t at = -1;
+                    // unit numbers stay below 2^40 with every workgroup's task added
+                    const uint64_t units_now = *(volatile unsigned long long *)big_ctr &
+                                               ((1ull << kUnitBits) - 1);
+                    if (*(volatile unsigned long long *)arena_used + words <= arena_words &&
+                        units_now < (1ull << (kUnitBits - 1))) {
+                        const uint64_t a = atomicAdd(arena_used, (unsigned long long)words);
+                        if (a + words <= arena_words) {
+                            // the task's number and its first unit from one
+                            // counter, so that units ascend with the tasks
+                            const unsigned long long c = atomicAdd(
+                                big_ctr, (1ull << kUnitBits) + (unsigned long long)carry);
+                            const uint64_t slot = c >> kUnitBits;
+                            if (slot < (uint64_t)kMaxBig) {
+                                at = (int64_t)a;
+                                big[slot] = {at, (int64_t)(c & ((1ull << kUnitBits) - 1)), x,
+                                             ngroups, carry, 0};
+                            }
+                        }
+                    }
+                    s_at = at;
+                }
+            }
+            for (int i = tid; i < kPartZ; i += kBlock) cur[i] = 0u;
+            __syncthreads();
+            if (s_at >= 0) {
+                int32_t *gz = arena + s_at, *go = gz + ngroups, *zu = go + ngroups + 1;
+                for (int32_t b = tid; b <= nzb; b += kBlock) zu[b] = s_zu[b];
+                int32_t g = g0;
+                for (int q = 0; q < PER; q++) {
+                    const int32_t zi = tid * PER + q;
+                    if (cnt[zi + 1] > cnt[zi]) {
+                        gz[g] = z0 + zi;
+                        go[g++] = cnt[zi];
+                    }
+                }
+                if (tid == 0) go[ngroups] = cnt[kPartZ];
+                walk(z0, z0 + kPartZ, 1, zu + nzb + 1);
+                continue;
+            }
         }
         int32_t za = 0;   // relative to z0
         while (za < kPartZ && cnt[za] < cnt[kPartZ]) {
@@ -1022,75 +1183,29 @@ __global__ void __launch_bounds__(kBlock) k_c4_heavy_list(const int32_t *__restr
             const int32_t zb = lo;
             for (int i = tid; i < kPartZ; i += kBlock) cur[i] = 0u;
             __syncthreads();
-            walk(z0 + za, z0 + zb, 1);
+            walk(z0 + za, z0 + zb, 1, buf);
             // emit: waves take 64 consecutive z of [za, zb) at a time and
-            // share out the pairs of middles of all of them, one per lane
-            // (most groups hold one or two pairs, so a wave per z would
-            // leave most lanes idle)
+            // share out the pairs of middles of all of them (most groups
+            // hold one or two pairs, so a wave per z would leave most lanes
+            // idle)
             if (tid == 0) s_z = (uint32_t)za;
             __syncthreads();
-            int64_t *pp = s_pp[wid];
             for (;;) {
                 uint32_t z1 = 0;
                 if (lane == 0) z1 = atomicAdd(&s_z, (uint32_t)kWave);
                 z1 = __shfl(z1, 0, 64);
                 if ((int32_t)z1 >= zb) break;
                 const int32_t zl = (int32_t)z1 + lane;
-                const int32_t cl = zl < zb ? cnt[zl + 1] - cnt[zl] : 0;
-                const int64_t npl = (int64_t)cl * (cl - 1) / 2;
+                const int32_t o = cnt[min(zl, zb)] - cnt[za], o1 = cnt[min(zl + 1, zb)] - cnt[za];
+                const int64_t npl = (int64_t)(o1 - o) * (o1 - o - 1) / 2;
                 const int64_t incl = wave_incl_scan(npl);
-                pp[lane] = incl - npl;   // first pair of this lane's z
+                s_pp[wid][lane] = incl - npl;   // first pair of this lane's z
+                s_go[wid][lane] = o;
+                s_gz[wid][lane] = z0 + zl;
+                if (lane == kWave - 1) s_go[wid][kWave] = o1;
                 const int64_t total = __shfl(incl, kWave - 1, 64);
                 wave_sync();
-                // each lane takes kListUnroll consecutive pairs per step:
-                // it decodes the first and steps through the rest (a new z's
-                // pairs start at (0, 1)), and their middles' loads go out
-                // together before any is hashed
-                for (int64_t qb = 0; qb < total; qb += kWave * kListUnroll) {
-                    const int64_t q0 = qb + (int64_t)lane * kListUnroll;
-                    int32_t y1[kListUnroll], y2[kListUnroll], zz[kListUnroll];
-                    int32_t l = 0, o = 0, c = 0, i = 0, j = 0;
-                    // the lane (z) holding pair q: last l with pp[l] <= q
-                    auto find = [&](int64_t q) {
-                        l = 0;
-#pragma unroll
-                        for (int h = kWave / 2; h > 0; h >>= 1)
-                            if (pp[l + h] <= q) l += h;
-                        o = cnt[(int32_t)z1 + l] - cnt[za];
-                        c = cnt[(int32_t)z1 + l + 1] - cnt[(int32_t)z1 + l];
-                    };
-                    if (q0 < total) {
-                        find(q0);
-                        // r -> (i, j), i < j, r = j (j - 1) / 2 + i; the
-                        // single-precision root is off by at most one here
-                        const int64_t r = q0 - pp[l];
-                        int64_t jj = (int64_t)((1.0f + sqrtf(1.0f + 8.0f * (float)r)) * 0.5f);
-                        while (jj * (jj - 1) / 2 > r) jj--;
-                        while ((jj + 1) * jj / 2 <= r) jj++;
-                        j = (int32_t)jj;
-                        i = (int32_t)(r - jj * (jj - 1) / 2);
-                    }
-#pragma unroll
-                    for (int u = 0; u < kListUnroll; u++) {
-                        const int64_t q = q0 + u;
-                        y1[u] = y2[u] = zz[u] = 0;
-                        if (q < total) {
-                            if (u > 0 && ++i == j) {
-                                i = 0;
-                                if (++j == c) {   // this z's pairs are done
-                                    find(q);
-                                    j = 1;
-                                }
-                            }
-                            zz[u] = (int32_t)z1 + l;
-                            y1[u] = buf[o + i];
-                            y2[u] = buf[o + j];
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < kListUnroll; u++)
-                        emit_c4(em, q0 + u < total, x, y1[u], z0 + zz[u], y2[u]);
-                }
+                emit_pairs(em, x, buf, s_pp[wid], s_go[wid], s_gz[wid], 0, total);
                 wave_sync();
             }
             __syncthreads();
@@ -1101,18 +1216,89 @@ __global__ void __launch_bounds__(kBlock) k_c4_heavy_list(const int32_t *__restr
     emitter_flush(em, result);
 }
 
+// Last i in [0, count) with key(i) <= x, for ascending keys with key(0) <= x:
+// 64 probes per step.
+template <class F>
+__device__ __forceinline__ int32_t wave_last_le(int32_t count, int64_t x, F &&key) {
+    int32_t lo = 0, len = count;
+    while (len > 1) {
+        const int32_t step = (len + kWave - 1) / kWave;
+        const int32_t at = lane_id() * step;
+        const uint64_t m = __ballot(at < len && key(lo + min(at, len - 1)) <= x);
+        const int32_t k = 63 - __builtin_clzll(m);   // probe 0 always passes
+        lo += k * step;
+        len = min(step, len - k * step);
+    }
+    return lo;
+}
+
+// The pairs of the tasks left in the arena, in units of kUnitPairs pairs of
+// 64 groups; waves take `grab` units at a time from a cursor.  Bound by the
+// checksum: four 64-bit mixes an embedding, 24 quarter-rate multiplies.
+__global__ void __launch_bounds__(kBlock) k_c4_big_list(const int32_t *__restrict__ arena,
+                                                        const BigTask *__restrict__ big,
+                                                        const unsigned long long *big_ctr,
+                                                        unsigned long long *cursor, Emitter em,
+                                                        unsigned long long *result) {
+    __shared__ int64_t s_pp[kWPB][kWave];
+    __shared__ int32_t s_go[kWPB][kWave + 1], s_gz[kWPB][kWave];
+    const int lane = lane_id(), wid = threadIdx.x / kWave;
+    const int32_t nbig = (int32_t)min<unsigned long long>(*big_ctr >> kUnitBits, kMaxBig);
+    const int64_t total = nbig ? big[nbig - 1].unit0 + big[nbig - 1].units : 0;
+    const int64_t waves = (int64_t)gridDim.x * kWPB;
+    const int32_t grab = (int32_t)min<int64_t>(8, max<int64_t>(1, total / (waves * 16)));
+    em.cached = 0;
+    em.count = 0;
+    em.hsum = 0;
+    for (;;) {
+        unsigned long long u0 = 0;
+        if (lane == 0) u0 = atomicAdd(cursor, (unsigned long long)grab);
+        u0 = __shfl(u0, 0, 64);
+        if ((int64_t)u0 >= total) break;
+        const int64_t uz = min<int64_t>(total, (int64_t)u0 + grab);
+        for (int64_t u = (int64_t)u0; u < uz; u++) {
+            const int32_t e = wave_last_le(nbig, u, [&](int32_t i) { return big[i].unit0; });
+            const BigTask T = big[e];
+            const int32_t *gz = arena + T.at, *go = gz + T.groups, *zu = go + T.groups + 1;
+            const int32_t nzb = (T.groups + kWave - 1) / kWave;
+            const int32_t *mids = zu + nzb + 1;
+            const int32_t lu = (int32_t)(u - T.unit0);
+            const int32_t b = wave_last_le(nzb, lu, [&](int32_t i) { return (int64_t)zu[i]; });
+            const int32_t g = b * kWave + lane;
+            const int32_t o = go[min(g, T.groups)], o1 = go[min(g + 1, T.groups)];
+            const int64_t npl = (int64_t)(o1 - o) * (o1 - o - 1) / 2;
+            const int64_t incl = wave_incl_scan(npl);
+            s_pp[wid][lane] = incl - npl;
+            s_go[wid][lane] = o;
+            s_gz[wid][lane] = gz[min(g, T.groups - 1)];
+            if (lane == kWave - 1) s_go[wid][kWave] = o1;
+            const int64_t qa = (int64_t)(lu - zu[b]) * kUnitPairs;
+            const int64_t qz = min<int64_t>(__shfl(incl, kWave - 1, 64), qa + kUnitPairs);
+            wave_sync();
+            emit_pairs(em, T.x, mids, s_pp[wid], s_go[wid], s_gz[wid], qa, qz);
+            wave_sync();
+        }
+    }
+    emitter_flush(em, result);
+}
+
 __global__ void k_finish(unsigned long long *result, const unsigned long long *slot_ctr,
                          uint64_t cap) {
     if (threadIdx.x == 0 && blockIdx.x == 0) result[1] = *slot_ctr < cap ? *slot_ctr : cap;
 }
 
 struct C4Ws {
-    uint32_t *ctl;                 // [0] heavy cursor; counts [1] light, [2] heavy, [3] medium
+    uint32_t *ctl;                 // [0] heavy cursor; counts [1] light, [2] heavy, [3] medium;
+                                   // [4..5] cursor of the large listing tasks' units
     unsigned long long *slot;      // listing slot counter
     unsigned long long *sum;       // counting: 128-bit total
     int32_t *deg, *cls, *flag, *pos, *light, *heavy, *med;
     int64_t *scan_tmp;
     int32_t *wedges;               // listing: per-workgroup wedge buffers
+    int32_t *arena;                // listing: groups of the large tasks
+    uint64_t arena_words;
+    BigTask *big;
+    unsigned long long *big_ctr;   // [0] large tasks and units, [1] arena words used
     int2 *seg;                     // counting: part table (null when too large)
     // counting: the graph relabelled by rank (see above) and its build
     int32_t *rank, *perm, *rdeg, *roff, *radj, *nin, *dcnt, *dstart, *dcur;
@@ -1151,7 +1337,16 @@ C4Ws c4_layout(const gpm_graph *g, bool list, void *base) {
     W.light = c.take<int32_t>(n1);
     W.heavy = c.take<int32_t>(n1);
     W.scan_tmp = c.take<int64_t>(scan_tmp_words(n1));
-    if (list) W.wedges = c.take<int32_t>((uint64_t)kListBlocks * kWedgeCap);
+    if (list) {
+        W.wedges = c.take<int32_t>((uint64_t)kListBlocks * kWedgeCap);
+        // a wedge is an arc y -> z with its arc x -> y: at most m * max_degree
+        // of them, two words a kept one
+        W.arena_words = std::min<uint64_t>(
+            kArenaWords, 4 * (uint64_t)g->m * (uint64_t)std::max(g->max_degree, 1) + 4096);
+        W.arena = c.take<int32_t>(W.arena_words);
+        W.big = c.take<BigTask>(kMaxBig);
+        W.big_ctr = c.take<unsigned long long>(2);
+    }
     if (!list) {
         const uint64_t arcs = (uint64_t)std::max<int64_t>(2 * g->m, 1);
         W.med = c.take<int32_t>(n1);
@@ -1296,12 +1491,26 @@ gpm_status c4_run(const gpm_graph *g, bool list, void *ws, uint64_t ws_bytes,
     if (rc) return rc;
     const int32_t nparts = (n + kPartZ - 1) / kPartZ;
     Emitter em{W.slot, d_buf, d_buf ? cap : 0, 0, 0, 0};
+    GPM_HIP(fill_u32(W.big_ctr, 0, 4, st));
     {
         Span sp("k_c4_heavy_list", st);
+        // tasks of at least this many pairs are shared out: 32,768 keep a
+        // workgroup busy for 0.15 ms, and larger graphs have tasks enough
+        // above it to fill the arena, so the line grows with them
+        const uint64_t big_pairs = (uint64_t)std::max<int64_t>(1 << 15, g->m / 16);
         hipLaunchKernelGGL(k_c4_heavy_list, dim3(kListBlocks), dim3(kBlock), 0, st, g->off, g->adj,
-                           W.deg, W.heavy, cnt_heavy, nparts, W.ctl + 0, W.wedges, em, d_result);
+                           W.deg, W.heavy, cnt_heavy, nparts, W.ctl + 0, W.wedges, W.arena,
+                           W.arena_words, W.big_ctr + 1, big_pairs, W.big, W.big_ctr, em,
+                           d_result);
     }
     GPM_LAUNCH_CHECK("k_c4_heavy_list");
+    {
+        Span sp("k_c4_big_list", st);
+        hipLaunchKernelGGL(k_c4_big_list, dim3((unsigned)persistent_blocks(kWPB, 8)), dim3(kBlock),
+                           0, st, W.arena, W.big, W.big_ctr,
+                           reinterpret_cast<unsigned long long *>(W.ctl + 4), em, d_result);
+    }
+    GPM_LAUNCH_CHECK("k_c4_big_list");
     {
         Span sp("k_c4_light_list", st);
         hipLaunchKernelGGL(k_c4_light_list, dim3((unsigned)persistent_blocks(kWPB, 4)), dim3(kBlock),
