@@ -39,11 +39,22 @@ constexpr int kWPB = kBlock / kWave;
 constexpr int kLightW = 512;         // wedge work of a light apex
 constexpr int kMedW = 8192;          // counting: wedge work of a medium apex (hashed task)
 constexpr int kHashSlots = 1024;     // per-wave LDS hash (load <= 1/2)
-constexpr int kPartZ = 8192;         // z-range per heavy task (LDS counters)
+// listing: ids per z-part of a heavy task (LDS counters).  Each part of an
+// apex scans its in-neighbours again, so graphs of more than kFineIds ids take
+// the large parts; below, a hub's few large parts were the last to finish
+// (RMAT-15: the grouping kernel 4.9 ms with 8192, 3.4 ms with 2048)
+constexpr int kPartZ = 8192, kPartZFine = 2048;
+constexpr int32_t kFineIds = 1 << 16;
 constexpr int kYChunk = kBlock;      // in-neighbours staged per round
 constexpr int kListBlocks = 512;     // workgroups of the heavy listing kernel
+constexpr int kListBlocksFine = 1024;
 constexpr int kWedgeCap = 1 << 18;   // per-workgroup wedge buffer (>= max degree)
+constexpr int kWedgeCapFine = 1 << 17;
+static_assert((int64_t)kListBlocks * kWedgeCap == (int64_t)kListBlocksFine * kWedgeCapFine &&
+                  kWedgeCapFine >= kFineIds,
+              "both forms share the wedge buffers, and a row fits one");
 constexpr int kListUnroll = 8;       // pairs per lane in flight when listing
+constexpr int kWalkUnroll = 8;       // wedges per thread in flight when grouping
 
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -968,11 +979,10 @@ struct BigTask {
 };
 constexpr int kMaxBig = 1 << 16;
 constexpr int kUnitPairs = 4096;                // pairs per unit
-constexpr int kZBlocks = kPartZ / kWave;        // 64-group blocks of a task
 constexpr uint64_t kArenaWords = 1ull << 27;    // 512 MiB
 constexpr int kUnitBits = 40;                   // big_ctr: tasks above, units below
-// at most 2^30 units a task (kListBlocks tasks at once: 2^39)
-constexpr uint64_t kBigPairsMax = ((1ull << 30) - kZBlocks) * kUnitPairs;
+// at most 2^29 units a task (1024 tasks at once: 2^39)
+constexpr uint64_t kBigPairsMax = (1ull << 28) * kUnitPairs;
 
 // Heavy apexes, listing: workgroup per (apex, z-part) counts the wedges per
 // z and groups the middles of every z with at least two.  A task of fewer
@@ -982,6 +992,7 @@ constexpr uint64_t kBigPairsMax = ((1ull << 30) - kZBlocks) * kUnitPairs;
 // its four waves busy for 100 of the call's 107 ms, with the chip idle), so a
 // larger task leaves its groups in the arena and its pairs to
 // k_c4_big_list, unless the arena or the task list is full.
+template <int PZ>
 __global__ void __launch_bounds__(kBlock) k_c4_heavy_list(const int32_t *__restrict__ off,
                                                           const int32_t *__restrict__ adj,
                                                           const int32_t *__restrict__ deg,
@@ -994,9 +1005,12 @@ __global__ void __launch_bounds__(kBlock) k_c4_heavy_list(const int32_t *__restr
                                                           uint64_t big_pairs, BigTask *big,
                                                           unsigned long long *big_ctr, Emitter em,
                                                           unsigned long long *result) {
-    constexpr int PER = kPartZ / kBlock;
-    __shared__ int32_t cnt[kPartZ + 1];     // counts, then prefix offsets of the kept groups
-    __shared__ uint32_t cur[kPartZ];
+    constexpr int PER = PZ / kBlock;
+    constexpr int kZBlocks = PZ / kWave;   // blocks of 64 groups
+    static_assert(kZBlocks <= kBlock && PZ % kBlock == 0, "a thread per block of 64 groups");
+    constexpr int kCap = PZ == kPartZ ? kWedgeCap : kWedgeCapFine;
+    __shared__ int32_t cnt[PZ + 1];     // counts, then prefix offsets of the kept groups
+    __shared__ uint32_t cur[PZ];
     __shared__ int32_t s_pre[kYChunk + 1];
     __shared__ int32_t s_start[kYChunk];
     __shared__ int32_t s_sum[kWPB], s_grp[kWPB];
@@ -1008,7 +1022,7 @@ __global__ void __launch_bounds__(kBlock) k_c4_heavy_list(const int32_t *__restr
     __shared__ uint32_t s_task, s_z;
     const int tid = threadIdx.x, lane = lane_id(), wid = tid / kWave;
     const uint64_t ntasks = (uint64_t)(*count_p) * (uint64_t)nparts;
-    int32_t *buf = wedge_buf + (int64_t)blockIdx.x * kWedgeCap;
+    int32_t *buf = wedge_buf + (int64_t)blockIdx.x * kCap;
     em.cached = 0;
     em.count = 0;
     em.hsum = 0;
@@ -1023,9 +1037,9 @@ __global__ void __launch_bounds__(kBlock) k_c4_heavy_list(const int32_t *__restr
         if (t >= ntasks) break;
         const int32_t x = list[t / nparts];
         const int32_t part = (int32_t)(t % nparts);
-        const int32_t z0 = part * kPartZ;
+        const int32_t z0 = part * PZ;
         const int32_t s = off[x], dx = off[x + 1] - s;
-        for (int i = tid; i <= kPartZ; i += kBlock) cnt[i] = 0;
+        for (int i = tid; i <= PZ; i += kBlock) cnt[i] = 0;
         if (tid < kZBlocks) s_zp[tid] = 0;
         __syncthreads();
         // wedges of this task restricted to z in [za, zb); pass 0 counts,
@@ -1057,25 +1071,43 @@ __global__ void __launch_bounds__(kBlock) k_c4_heavy_list(const int32_t *__restr
                 s_start[tid] = start;
                 if (tid == 0) s_pre[0] = 0;
                 __syncthreads();
-                for (int32_t q = tid; q < total; q += kBlock) {
-                    const int32_t j = last_le_i32(s_pre, kYChunk + 1, q);
-                    const int32_t z = adj[s_start[j] + (q - s_pre[j])];
-                    if (rank_less(deg[z], z, dx, x)) {
-                        const int32_t zi = z - z0;
+                // kWalkUnroll wedges in flight per thread: their searches
+                // advance together, then the ends' loads, then the degrees'
+                for (int32_t qb = tid; qb < total; qb += kBlock * kWalkUnroll) {
+                    int32_t jj[kWalkUnroll], z[kWalkUnroll], dz[kWalkUnroll];
+#pragma unroll
+                    for (int u = 0; u < kWalkUnroll; u++) jj[u] = 0;
+#pragma unroll
+                    for (int h = kYChunk / 2; h > 0; h >>= 1)
+#pragma unroll
+                        for (int u = 0; u < kWalkUnroll; u++)
+                            if (s_pre[jj[u] + h] <= qb + u * kBlock) jj[u] += h;
+#pragma unroll
+                    for (int u = 0; u < kWalkUnroll; u++) {
+                        const int32_t q = qb + u * kBlock;
+                        z[u] = q < total ? adj[s_start[jj[u]] + (q - s_pre[jj[u]])] : x;
+                    }
+#pragma unroll
+                    for (int u = 0; u < kWalkUnroll; u++) dz[u] = deg[z[u]];
+#pragma unroll
+                    for (int u = 0; u < kWalkUnroll; u++) {
+                        // x itself (lanes past the end) is not below x
+                        if (!rank_less(dz[u], z[u], dx, x)) continue;
+                        const int32_t zi = z[u] - z0;
                         if (pass == 0) {
                             atomicAdd(&cnt[zi], 1);
                         } else if (cnt[zi + 1] > cnt[zi]) {
                             dst[cnt[zi] - cnt[za - z0] + (int32_t)atomicAdd(&cur[zi], 1u)] =
-                                adj[s + c0 + j];
+                                adj[s + c0 + jj[u]];
                         }
                     }
                 }
                 __syncthreads();
             }
         };
-        walk(z0, z0 + kPartZ, 0, nullptr);
+        walk(z0, z0 + PZ, 0, nullptr);
         // the kept groups (at least two middles): exclusive prefix of their
-        // counts (in place, cnt[kPartZ] = total), their number, and the pairs
+        // counts (in place, cnt[PZ] = total), their number, and the pairs
         // of every 64 of them
         int32_t ngroups = 0, g0 = 0;
         {
@@ -1111,7 +1143,7 @@ __global__ void __launch_bounds__(kBlock) k_c4_heavy_list(const int32_t *__restr
                     g++;
                 }
             }
-            if (tid == kBlock - 1) cnt[kPartZ] = run;
+            if (tid == kBlock - 1) cnt[PZ] = run;
             pairs = wave_sum(pairs);
             if (lane == 0 && pairs) atomicAdd(&s_pairs, (unsigned long long)pairs);
             __syncthreads();
@@ -1122,15 +1154,16 @@ __global__ void __launch_bounds__(kBlock) k_c4_heavy_list(const int32_t *__restr
             if (wid == 0) {
                 int32_t carry = 0;
                 for (int32_t b0 = 0; b0 < kZBlocks; b0 += kWave) {
+                    const int32_t b = b0 + lane;
                     const int32_t units =
-                        (int32_t)((s_zp[b0 + lane] + kUnitPairs - 1) / kUnitPairs);
+                        b < kZBlocks ? (int32_t)((s_zp[b] + kUnitPairs - 1) / kUnitPairs) : 0;
                     const int32_t inc = wave_incl_scan(units);
-                    s_zu[b0 + lane] = carry + inc - units;
+                    if (b < kZBlocks) s_zu[b] = carry + inc - units;
                     carry += __shfl(inc, 63, 64);
                 }
                 if (lane == 0) {
                     s_zu[kZBlocks] = carry;
-                    const uint64_t words = (uint64_t)(2 * ngroups + 1 + nzb + 1 + cnt[kPartZ]);
+                    const uint64_t words = (uint64_t)(2 * ngroups + 1 + nzb + 1 + cnt[PZ]);
                     int64_t at = -1;
                     // unit numbers stay below 2^40 with every workgroup's task added
                     const uint64_t units_now = *(volatile unsigned long long *)big_ctr &
@@ -1154,7 +1187,7 @@ __global__ void __launch_bounds__(kBlock) k_c4_heavy_list(const int32_t *__restr
                     s_at = at;
                 }
             }
-            for (int i = tid; i < kPartZ; i += kBlock) cur[i] = 0u;
+            for (int i = tid; i < PZ; i += kBlock) cur[i] = 0u;
             __syncthreads();
             if (s_at >= 0) {
                 int32_t *gz = arena + s_at, *go = gz + ngroups, *zu = go + ngroups + 1;
@@ -1167,21 +1200,21 @@ __global__ void __launch_bounds__(kBlock) k_c4_heavy_list(const int32_t *__restr
                         go[g++] = cnt[zi];
                     }
                 }
-                if (tid == 0) go[ngroups] = cnt[kPartZ];
-                walk(z0, z0 + kPartZ, 1, zu + nzb + 1);
+                if (tid == 0) go[ngroups] = cnt[PZ];
+                walk(z0, z0 + PZ, 1, zu + nzb + 1);
                 continue;
             }
         }
         int32_t za = 0;   // relative to z0
-        while (za < kPartZ && cnt[za] < cnt[kPartZ]) {
-            // largest zb with cnt[zb] - cnt[za] <= kWedgeCap (at least za + 1)
-            int32_t lo = za + 1, hi = kPartZ;
+        while (za < PZ && cnt[za] < cnt[PZ]) {
+            // largest zb with cnt[zb] - cnt[za] <= kCap (at least za + 1)
+            int32_t lo = za + 1, hi = PZ;
             while (lo < hi) {
                 const int32_t mid = (lo + hi + 1) >> 1;
-                if (cnt[mid] - cnt[za] <= kWedgeCap) lo = mid; else hi = mid - 1;
+                if (cnt[mid] - cnt[za] <= kCap) lo = mid; else hi = mid - 1;
             }
             const int32_t zb = lo;
-            for (int i = tid; i < kPartZ; i += kBlock) cur[i] = 0u;
+            for (int i = tid; i < PZ; i += kBlock) cur[i] = 0u;
             __syncthreads();
             walk(z0 + za, z0 + zb, 1, buf);
             // emit: waves take 64 consecutive z of [za, zb) at a time and
@@ -1489,7 +1522,8 @@ gpm_status c4_run(const gpm_graph *g, bool list, void *ws, uint64_t ws_bytes,
     GPM_LAUNCH_CHECK("k_c4_work");
     gpm_status rc = split_classes();
     if (rc) return rc;
-    const int32_t nparts = (n + kPartZ - 1) / kPartZ;
+    const bool fine = n <= kFineIds;
+    const int32_t pz = fine ? kPartZFine : kPartZ, nparts = (n + pz - 1) / pz;
     Emitter em{W.slot, d_buf, d_buf ? cap : 0, 0, 0, 0};
     GPM_HIP(fill_u32(W.big_ctr, 0, 4, st));
     {
@@ -1498,8 +1532,9 @@ gpm_status c4_run(const gpm_graph *g, bool list, void *ws, uint64_t ws_bytes,
         // workgroup busy for 0.15 ms, and larger graphs have tasks enough
         // above it to fill the arena, so the line grows with them
         const uint64_t big_pairs = (uint64_t)std::max<int64_t>(1 << 15, g->m / 16);
-        hipLaunchKernelGGL(k_c4_heavy_list, dim3(kListBlocks), dim3(kBlock), 0, st, g->off, g->adj,
-                           W.deg, W.heavy, cnt_heavy, nparts, W.ctl + 0, W.wedges, W.arena,
+        hipLaunchKernelGGL(fine ? k_c4_heavy_list<kPartZFine> : k_c4_heavy_list<kPartZ>,
+                           dim3(fine ? kListBlocksFine : kListBlocks), dim3(kBlock), 0, st, g->off,
+                           g->adj, W.deg, W.heavy, cnt_heavy, nparts, W.ctl + 0, W.wedges, W.arena,
                            W.arena_words, W.big_ctr + 1, big_pairs, W.big, W.big_ctr, em,
                            d_result);
     }
