@@ -231,12 +231,15 @@ gpm_status gpm_graph_orient(gpm_graph *g, int32_t order, void *d_scratch, uint64
 
 /* Task granularity of the plain path, kept per graph handle (Section 4.1
  * splits the work into tasks and leaves their size open).  Triangle
- * counting (and the per-edge triangle counts of local counting) splits the
- * (root, out-neighbour) pair space of each out-degree class, (1, 64],
- * (64, 256] and (256, 1024], into chunks of tc_tau pairs that
- * cu_count * tc_blocks_per_cu persistent workgroups take from an atomic
- * cursor; 5-clique counting splits each root of out-degree above 256 into
- * tasks of about lg5_slice local triangles; k-cliques (k >= 4) at roots of
+ * counting (and the per-edge triangle counts of local counting) gives every
+ * arc to its end of larger out-degree; a root of out-degree d above 32 is
+ * split into tasks of about 8 tc_tau / d of its neighbours (at least 256;
+ * tc_tau[0], [1], [2] for d up to 64, up to 256 and above), roughly tc_tau
+ * candidate pairs, that cu_count * max(tc_blocks_per_cu[1], [2]) persistent
+ * workgroups take from an atomic cursor, and the arcs between shorter lists
+ * are merged, a lane per arc, by at most cu_count * tc_blocks_per_cu[0]
+ * workgroups; 5-clique counting splits each root of out-degree above 256
+ * into tasks of about lg5_slice local triangles; k-cliques (k >= 4) at roots of
  * out-degree up to 64 are counted a wave per root, roots dealt round robin
  * to cu_count * clique_wave_blocks_per_cu one-wave workgroups.  Counts never
  * depend on these.  A new handle starts at tc_tau = {8192, 16384, 65536},
@@ -245,7 +248,7 @@ gpm_status gpm_graph_orient(gpm_graph *g, int32_t order, void *d_scratch, uint64
  * them after changing it (a workspace sized before a smaller tc_tau gives
  * GPM_OUT_OF_MEMORY). */
 typedef struct gpm_tuning {
-    int64_t tc_tau[3];            /* pairs per chunk, [2048, 2^24] */
+    int64_t tc_tau[3];            /* pairs per task, [2048, 2^24] */
     int32_t tc_blocks_per_cu[3];  /* workgroups per CU, [1, 64] */
     int32_t clique_wave_blocks_per_cu;   /* [8, 1024] */
     int64_t lg5_slice;            /* local triangles per task, [2^14, 2^28] */

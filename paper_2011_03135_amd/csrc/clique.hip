@@ -8,15 +8,15 @@
 // filtering, Section 4.3).
 //
 // Kernels:
-//   k_tc_block      triangles.  The work of root u is the list of pairs
-//                   (v, w), v in N+(u), w in N+(v); all pairs of the roots of
-//                   one out-degree class form one flattened index space cut
-//                   into fixed-size chunks that blocks pop from an atomic
-//                   cursor, so a hub's pairs are shared among many blocks.
-//                   N+(u) sits in LDS as a hash table next to the pair
-//                   prefix of its out-neighbours; each pair is a membership
-//                   test of w in N+(u).  Optionally adds 1 to the triangle
-//                   count of each of the triangle's three arcs.
+//   k_tc_arcs, k_tc_seg  triangles.  Every arc u -> v belongs to its end of
+//                   larger out-degree, x (the root on a tie), and counts the
+//                   entries of the other end's out-list that lie in N+(x):
+//                   sum over arcs of min(d+(u), d+(v)) tests instead of
+//                   sum of d+(v) (RMAT-20: 2.2e9 instead of 5.0e9).  Arcs
+//                   between short lists are merged, a lane per arc; for the
+//                   other roots x N+(x) sits in LDS as a hash table and x's
+//                   neighbours' lists run past it.  Optionally adds 1 to the
+//                   triangle count of each of the triangle's three arcs.
 //   k_clique_wave   k = 4..9, roots with out-degree <= 64: one wave builds
 //                   the local graph on N+(u) as 64-bit adjacency rows in LDS
 //                   and counts cliques with AND + popcount.
@@ -36,9 +36,10 @@ namespace gpm {
 
 gpm_status lg_workspace_bytes(const gpm_graph *g, int32_t k, uint64_t *bytes);
 gpm_status lg_cliques(const gpm_graph *g, int32_t k, const int32_t *list_m, const int32_t *cnt_m,
-                      const int32_t *list_b, const int32_t *cnt_b, void *ws, uint64_t ws_bytes,
-                      unsigned long long *res, unsigned long long *res3,
-                      unsigned long long *res4, const RowEmitter *em, hipStream_t st);
+                      const int32_t *list_b, const int32_t *cnt_b, const int64_t *rowoff_b,
+                      void *ws, uint64_t ws_bytes, unsigned long long *res,
+                      unsigned long long *res3, unsigned long long *res4, const RowEmitter *em,
+                      hipStream_t st);
 
 namespace {
 
@@ -61,16 +62,6 @@ __device__ __forceinline__ int lower_bound_i32(const int32_t *a, int n, int32_t 
     return lo;
 }
 
-// Largest j in [0, n) with a[j] <= x, for ascending a with a[0] <= x.
-__device__ __forceinline__ int last_le_i32(const int32_t *a, int n, int32_t x) {
-    int lo = 0, hi = n;  // invariant: a[lo] <= x
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (a[mid] <= x) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
 __device__ __forceinline__ int64_t last_le_i64(const int64_t *a, int64_t n, int64_t x) {
     int64_t lo = 0, hi = n;
     while (hi - lo > 1) {
@@ -85,201 +76,504 @@ __device__ __forceinline__ int64_t last_le_i64(const int64_t *a, int64_t n, int6
 // Classes of roots by out-degree.
 enum RootClass : int { RC_NONE = 0, RC_SMALL = 1, RC_MID = 2, RC_BIG = 3, RC_HUB = 4 };
 
-// Per root: class and pair work W_u = sum over v in N+(u) of d+(v).  Roots
-// above big_max are hubs (their arcs become tasks of their own; no work sum).
-__global__ void __launch_bounds__(kBlock) k_root_work(const int32_t *__restrict__ dag_off,
-                                                      const int32_t *__restrict__ dag_adj,
-                                                      int32_t n, int32_t min_out, int32_t small_max,
-                                                      int32_t mid_max, int32_t big_max,
-                                                      int32_t *work, int32_t *cls) {
-    const int lane = lane_id();
-    const int64_t wave0 = (int64_t)blockIdx.x * kWPB + threadIdx.x / kWave;
-    const int64_t nwaves = (int64_t)gridDim.x * kWPB;
-    for (int64_t r = wave0; r < n; r += nwaves) {
-        const int32_t s = dag_off[r], d = dag_off[r + 1] - s;
-        int c = RC_NONE;
-        if (d >= min_out && d <= big_max) c = d <= small_max ? RC_SMALL : (d <= mid_max ? RC_MID : RC_BIG);
-        if (d >= min_out && d > big_max) {
-            if (lane == 0) {
-                cls[r] = RC_HUB;
-                work[r] = 0;
-            }
-            continue;
-        }
-        int64_t w = 0;
-        if (c != RC_NONE)
-            for (int32_t i = lane; i < d; i += kWave) {
-                int32_t v = dag_adj[s + i];
-                w += dag_off[v + 1] - dag_off[v];
-            }
-        w = wave_sum(w);
-        if (lane == 0) {
-            cls[r] = (c != RC_NONE && w > 0) ? c : RC_NONE;
-            work[r] = (int32_t)w;
-        }
+constexpr int kRootsPer = 4;                      // roots per thread
+constexpr int kRootsBlock = kBlock * kRootsPer;   // roots per workgroup
+
+// Block-wide exclusive scan of one 64-bit value per thread (kBlock threads);
+// returns the block's total in `total`.  Two barriers.
+__device__ __forceinline__ uint64_t block_excl64(uint64_t x, uint64_t *s_sum, uint64_t &total) {
+    const int lane = lane_id(), wid = threadIdx.x / kWave;
+    const uint64_t inc = wave_incl_scan(x);
+    __syncthreads();
+    if (lane == 63) s_sum[wid] = inc;
+    __syncthreads();
+    uint64_t before = inc - x;
+    total = 0;
+#pragma unroll
+    for (int q = 0; q < kWPB; q++) {
+        before += q < wid ? s_sum[q] : 0;
+        total += s_sum[q];
     }
+    return before;
 }
 
-// flag[r] = (cls[r] == want)
-__global__ void k_class_flag(const int32_t *cls, int32_t n, int32_t want, int32_t *flag) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) flag[i] = cls[i] == want ? 1 : 0;
+// The lists of the roots of every class, in blocks of ascending ids (the
+// order of the blocks is that of their arrival): one pass and one atomic per
+// workgroup and class, where a flag, scan and compaction per class took ten
+// launches a class.
+struct RootLists {
+    int32_t *list[4];              // small, mid, big, hub
+    int32_t *count;                // their lengths (zero on entry)
+    int64_t *rowoff;               // big: first word of the root's stored rows (may be null)
+    unsigned long long *words;     // big: row words handed out (zero on entry)
+    int64_t *hpre;                 // hub: out-arcs of the hubs before this one
+    unsigned long long *hub;       // hub: count << 32 | out-arcs (zero on entry)
+};
+
+// Words of a stored local graph: d rows of ceil(d / 64), then d vertex ids.
+__device__ __forceinline__ int32_t row_words(int32_t d) {
+    return d * ((d + 63) >> 6) + (d + 1) / 2;
 }
 
-// Compacts the flagged roots: list[pos[r]] = r, lwork[pos[r]] = work[r].
-__global__ void k_compact_roots(const int32_t *cls, const int32_t *pos, const int32_t *work,
-                                int32_t n, int32_t want, int32_t *list, int32_t *lwork) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride)
-        if (cls[i] == want) {
-            list[pos[i]] = (int32_t)i;
-            if (lwork) lwork[pos[i]] = work[i];
+__global__ void __launch_bounds__(kBlock) k_clique_roots(const int32_t *__restrict__ dag_off,
+                                                         int32_t n, int32_t min_out,
+                                                         int32_t small_max, int32_t mid_max,
+                                                         int32_t big_max, RootLists L) {
+    __shared__ uint64_t s_sum[kWPB];
+    __shared__ uint64_t s_base[6];   // list bases, row words, hub arcs
+    for (int64_t r0 = (int64_t)blockIdx.x * kRootsBlock; r0 < n;
+         r0 += (int64_t)gridDim.x * kRootsBlock) {
+        const int64_t r = r0 + (int64_t)threadIdx.x * kRootsPer;
+        int32_t d[kRootsPer], c[kRootsPer];
+        uint64_t num = 0, words = 0, arcs = 0;   // num: 16 bits per class
+        int32_t at = r < n ? dag_off[r] : 0;
+#pragma unroll
+        for (int q = 0; q < kRootsPer; q++) {
+            const int32_t next = r + q < n ? dag_off[r + q + 1] : at;
+            d[q] = next - at;
+            at = next;
+            c[q] = d[q] < min_out || d[q] == 0 ? RC_NONE
+                   : d[q] > big_max ? RC_HUB
+                   : d[q] > mid_max ? RC_BIG : (d[q] > small_max ? RC_MID : RC_SMALL);
+            if (c[q] != RC_NONE) num += 1ull << (16 * (c[q] - 1));
+            if (c[q] == RC_BIG) words += (uint64_t)row_words(d[q]);
+            if (c[q] == RC_HUB) arcs += (uint64_t)d[q];
         }
-}
-
-// Chunk map of a flattened pair space: chunk c starts inside active root a
-// iff wpre[a] <= c*tau < wpre[a+1]; first[c] = a.
-__global__ void k_chunk_map(const int64_t *wpre, const int32_t *pos_total, int64_t tau,
-                            int32_t *first, uint32_t *ctl, unsigned long long *total_pairs) {
-    const int32_t nact = *pos_total;
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    if (i == 0) {
-        ctl[0] = (uint32_t)nact;
-        ctl[1] = (uint32_t)((wpre[nact] + tau - 1) / tau);
-        *total_pairs = (unsigned long long)wpre[nact];
-    }
-    for (; i < nact; i += stride) {
-        int64_t c0 = (wpre[i] + tau - 1) / tau, c1 = (wpre[i + 1] + tau - 1) / tau;
-        for (int64_t c = c0; c < c1; c++) first[c] = (int32_t)i;
+        uint64_t total, wtotal = 0, htotal = 0, wbefore = 0, hbefore = 0;
+        const uint64_t before = block_excl64(num, s_sum, total);
+        if (total >> 32) {   // big roots or hubs in this block
+            wbefore = block_excl64(words, s_sum, wtotal);
+            hbefore = block_excl64(arcs, s_sum, htotal);
+        }
+        if (threadIdx.x < 3) {
+            const int32_t t = (int32_t)((total >> (16 * threadIdx.x)) & 0xffffu);
+            s_base[threadIdx.x] = t ? (uint64_t)atomicAdd(&L.count[threadIdx.x], t) : 0;
+        } else if (threadIdx.x == 3) {
+            // a hub's place and its first arc come from one counter, so that
+            // the arcs ascend along the list
+            const uint64_t t = total >> 48;
+            const unsigned long long h =
+                t ? atomicAdd(L.hub, (unsigned long long)(t << 32 | htotal)) : 0;
+            s_base[3] = h >> 32;
+            s_base[5] = h & 0xffffffffull;
+        } else if (threadIdx.x == 4) {
+            s_base[4] = wtotal && L.words ? atomicAdd(L.words, (unsigned long long)wtotal) : 0;
+        }
+        __syncthreads();
+        uint64_t pos = before;
+#pragma unroll
+        for (int q = 0; q < kRootsPer; q++) {
+            if (c[q] == RC_NONE) continue;
+            const int k = c[q] - 1;
+            const uint64_t p = s_base[k] + ((pos >> (16 * k)) & 0xffffu);
+            L.list[k][p] = (int32_t)(r + q);
+            if (c[q] == RC_BIG && L.rowoff) {
+                L.rowoff[p] = (int64_t)(s_base[4] + wbefore);
+                wbefore += (uint64_t)row_words(d[q]);
+            }
+            if (c[q] == RC_HUB) {
+                L.hpre[p] = (int64_t)(s_base[5] + hbefore);
+                hbefore += (uint64_t)d[q];
+            }
+            pos += 1ull << (16 * k);
+        }
+        __syncthreads();
     }
 }
 
 // ---------------------------------------------------------- triangles ---
 
-// What k_tc_block does with each triangle (u, v, w), u -> v -> w, u -> w.
+// What the triangle kernels do with each triangle (u, v, w), u -> v -> w, u -> w.
 enum TcMode : int {
     TC_COUNT = 0,   // count only
     TC_ARCS = 1,    // also +1 on the triangle count of each of its three arcs
     TC_LIST = 2,    // list: emit (u, v, w)
 };
 
-// Triangles of the roots of one out-degree class (d+(u) <= DMAX), NT
-// threads per block.  A block pops a chunk of tau pairs of the class's
-// flattened pair space; for each root u the chunk touches it stages, in LDS,
-//   pre[j]   the pair prefix over N+(u) (pairs of v_j start at pre[j]),
-//   offj[j]  dag_off[v_j] - pre[j], so pair q of segment j is arc offj[j] + q,
-//   a hash table of N+(u) (key v_j, value j; load factor <= 1/4);
-// then every wave takes a contiguous run of the chunk's pairs of u.  Lane q
-// finds its segment by walking forward from the segment of the previous
-// tile's last pair (segments are long on power-law graphs, so a tile
-// crosses few boundaries) and tests w in N+(u) with the hash.  In TC_ARCS
-// mode the two arcs out of u are counted in LDS and flushed once per root
-// and chunk; the arc v -> w takes a global atomic.
-template <int DMAX, int NT, int MODE, int U>
-__global__ void __launch_bounds__(NT) k_tc_block(const int32_t *__restrict__ dag_off,
-                                                 const int32_t *__restrict__ dag_adj,
-                                                 const int32_t *__restrict__ act,
-                                                 const int64_t *__restrict__ wpre,
-                                                 const int32_t *__restrict__ first,
-                                                 const uint32_t *__restrict__ ctl,
-                                                 uint32_t *cursor, int64_t tau,
-                                                 unsigned long long *result, uint32_t *te,
-                                                 RowEmitter em) {
-    constexpr int NW = NT / kWave;
-    constexpr int F = DMAX <= 256 ? 16 : 4;   // slots per out-neighbour
-    constexpr int H = F * DMAX;
-    constexpr int PER = (DMAX + NT - 1) / NT;
-    static_assert(DMAX <= 32767, "local indices are kept as int16");
-    __shared__ __align__(16) int32_t keys[H];
-    __shared__ int16_t vals[MODE == TC_ARCS ? H : 1];
-    __shared__ int32_t pre[DMAX + 1];
-    __shared__ int32_t offj[DMAX];
-    __shared__ uint32_t cnt[MODE == TC_ARCS ? DMAX : 1];
-    __shared__ int32_t verts[MODE == TC_LIST ? DMAX : 1];
-    __shared__ int32_t s_sum[NW];
-    __shared__ uint32_t s_chunk;
-    __shared__ unsigned long long s_acc[NW];
-    const int tid = threadIdx.x, lane = lane_id(), wid = tid / kWave;
-    const int32_t nact = (int32_t)ctl[0];
-    const uint32_t nchunks = ctl[1];
-    const int64_t total = wpre[nact];
-    if (MODE == TC_ARCS)
-        for (int i = tid; i < DMAX; i += NT) cnt[i] = 0;
-    uint64_t acc = 0;
-    for (;;) {
-        if (tid == 0) s_chunk = atomicAdd(cursor, 1u);
-        __syncthreads();
-        const uint32_t c = s_chunk;
-        if (c >= nchunks) break;
-        int64_t p = (int64_t)c * tau;
-        const int64_t p1 = min(p + tau, total);
-        int32_t a = first[c];
-        while (p < p1) {
-            const int64_t w0 = wpre[a], w1 = wpre[a + 1];
-            const int32_t u = act[a];
-            const int32_t s = dag_off[u], d = dag_off[u + 1] - s;
-            const int32_t hb = lds_hash_bits(d, F);
-            for (int i = tid; i < (1 << hb); i += NT) keys[i] = -1;
-            stage_root<NT, PER>(dag_off, dag_adj, s, d, keys, MODE == TC_ARCS ? vals : nullptr,
-                                hb, pre, offj, s_sum, nullptr,
-                                MODE == TC_LIST ? verts : nullptr);
-            const int32_t q0 = (int32_t)(p - w0);
-            const int32_t q1 = (int32_t)(min(p1, w1) - w0);
-            // wave wid takes pairs [qa, qz), whole steps except the last
-            const int32_t per_wave =
-                ((q1 - q0 + NW - 1) / NW + U * kWave - 1) / (U * kWave) * (U * kWave);
-            const int32_t qa = min(q1, q0 + wid * per_wave);
-            const int32_t qz = min(q1, qa + per_wave);
-            if constexpr (MODE == TC_COUNT) {
-                const uint64_t c = walk_count<U>(pre, offj, dag_adj, d, qa, qz, keys, hb);
-                if (lane == 0) acc += c;
-            } else {
-                walk_lookup<U>(pre, offj, dag_adj, d, qa, qz, keys, hb,
-                        [&](int32_t jj, int32_t e_vw, int32_t w, int32_t slot) {
-                    if (slot >= 0) {
-                        acc++;
-                        if (MODE == TC_ARCS) {
-                            atomicAdd(&cnt[jj], 1u);
-                            atomicAdd(&cnt[vals[slot]], 1u);
-                            atomicAdd(&te[e_vw], 1u);
-                        }
-                        if (MODE == TC_LIST) {
-                            const int32_t tri[3] = {u, verts[jj], w};
-                            emit_vertices<3>(em, tri);
-                        }
-                    }
-                });
+// Arcs whose ends both have at most this out-degree are merged by
+// k_tc_arcs; roots above it are staged by k_tc_seg, up to kTcMaxD in LDS.
+constexpr int32_t kTcArcMax = 32, kTcMaxD = 1024;
+constexpr int kTcUnit = 16;   // list entries a 16-lane group tests at once
+
+struct Tau {
+    int64_t t[3];   // gpm_graph::tc_tau
+};
+
+// Neighbours per task of a staged root of out-degree d: about eight times
+// tau / d, since a segment is at most d long, most are shorter, and fewer
+// than half of the neighbours have one.
+__host__ __device__ inline int32_t tc_task_nbrs(int32_t d, const Tau &tau) {
+    const int64_t t = tau.t[d <= 64 ? 0 : (d <= 256 ? 1 : 2)];
+    const int64_t k = 8 * t / d / kBlock * kBlock;
+    return (int32_t)(k < kBlock ? kBlock : (k > (1 << 20) ? (1 << 20) : k));
+}
+
+// A run of tc_task_nbrs neighbours of the staged root x, from the c0-th.
+struct TcTask {
+    int32_t x, c0;
+};
+
+// The tasks of every root of out-degree above kTcArcMax; those of roots
+// above kTcMaxD go to `hub`.  num[0], num[1]: their numbers (zero on entry).
+__global__ void __launch_bounds__(kBlock) k_tc_tasks(const int32_t *__restrict__ off,
+                                                     const int32_t *__restrict__ dag_off,
+                                                     int32_t n, Tau tau, TcTask *tasks,
+                                                     TcTask *hub, uint32_t *num) {
+    __shared__ uint64_t s_sum[kWPB];
+    __shared__ uint32_t s_base[2];
+    for (int64_t r0 = (int64_t)blockIdx.x * kRootsBlock; r0 < n;
+         r0 += (int64_t)gridDim.x * kRootsBlock) {
+        const int64_t r = r0 + (int64_t)threadIdx.x * kRootsPer;
+        int32_t d[kRootsPer], nt[kRootsPer];
+        uint64_t mine = 0;   // tasks, hub tasks << 32
+        int32_t at = r < n ? dag_off[r] : 0;
+#pragma unroll
+        for (int q = 0; q < kRootsPer; q++) {
+            const int32_t next = r + q < n ? dag_off[r + q + 1] : at;
+            d[q] = next - at;
+            at = next;
+            nt[q] = 0;
+            if (d[q] > kTcArcMax) {
+                const int32_t nb = tc_task_nbrs(d[q], tau);
+                nt[q] = (off[r + q + 1] - off[r + q] + nb - 1) / nb;
+                mine += (uint64_t)nt[q] << (d[q] > kTcMaxD ? 32 : 0);
             }
+        }
+        uint64_t total;
+        uint64_t before = block_excl64(mine, s_sum, total);
+        if (threadIdx.x < 2) {
+            const uint32_t t = (uint32_t)(total >> (32 * threadIdx.x));
+            s_base[threadIdx.x] = t ? atomicAdd(&num[threadIdx.x], t) : 0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kRootsPer; q++) {
+            if (nt[q] == 0) continue;
+            const bool h = d[q] > kTcMaxD;
+            const int32_t nb = tc_task_nbrs(d[q], tau);
+            TcTask *o = h ? hub + s_base[1] + (uint32_t)(before >> 32)
+                          : tasks + s_base[0] + (uint32_t)before;
+            for (int32_t i = 0; i < nt[q]; i++) o[i] = {(int32_t)(r + q), i * nb};
+            before += (uint64_t)nt[q] << (h ? 32 : 0);
+        }
+        __syncthreads();
+    }
+}
+
+// Adds the block's per-wave counts (one per wave, in lane 0) to *result.
+template <int NW>
+__device__ __forceinline__ void block_add(uint64_t acc, unsigned long long *result) {
+    __shared__ unsigned long long s_acc[NW];
+    if (lane_id() == 0) s_acc[threadIdx.x / kWave] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long t = 0;
+        for (int q = 0; q < NW; q++) t += s_acc[q];
+        if (t) atomicAdd(result, t);
+    }
+}
+
+struct __attribute__((aligned(4))) Int4u {
+    int32_t x, y, z, w;
+};
+
+// Arcs between short lists, a lane per arc u -> v: the two out-lists
+// (d+(u), d+(v) <= kTcArcMax) are merged four entries against four, the
+// block with the smaller last entry making way.  Loads of four entries may
+// run past a list's end (and past the last list into the arc sources that
+// follow it in the graph's storage); what lies there is masked.  Bound by
+// the gathers of v's offsets and list, one line each per arc.
+template <int MODE>
+__global__ void __launch_bounds__(kBlock) k_tc_arcs(const int32_t *__restrict__ dag_off,
+                                                    const int32_t *__restrict__ dag_adj,
+                                                    const int32_t *__restrict__ dag_src,
+                                                    int64_t m, unsigned long long *result,
+                                                    uint32_t *te, RowEmitter em) {
+    uint32_t acc = 0;   // below 2^32: at most kTcArcMax per arc, m < 2^30 over the grid
+    uint64_t total = 0;
+    const int64_t stride = (int64_t)gridDim.x * kBlock;
+    for (int64_t e0 = (int64_t)blockIdx.x * kBlock + threadIdx.x; e0 < m; e0 += stride) {
+        const int32_t u = dag_src[e0];
+        int32_t a = dag_off[u];
+        const int32_t az = dag_off[u + 1];
+        if (az - a > kTcArcMax || az - a < 2) continue;
+        const int32_t v = dag_adj[e0];
+        int32_t b = dag_off[v];
+        const int32_t bz = dag_off[v + 1];
+        if (bz - b > kTcArcMax) continue;
+        uint32_t mine = 0;
+        auto load = [&](int32_t at, int32_t end, int32_t pad) {
+            Int4u x = *reinterpret_cast<const Int4u *>(dag_adj + at);
+            x.y = at + 1 < end ? x.y : pad;
+            x.z = at + 2 < end ? x.z : pad;
+            x.w = at + 3 < end ? x.w : pad;
+            return x;
+        };
+        Int4u A{}, B{};
+        if (b < bz) {
+            A = load(a, az, -1);
+            B = load(b, bz, -2);
+        }
+        while (a < az && b < bz) {
+            const int32_t x[4] = {A.x, A.y, A.z, A.w}, y[4] = {B.x, B.y, B.z, B.w};
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const bool hit = x[i] == y[0] || x[i] == y[1] || x[i] == y[2] || x[i] == y[3];
+                mine += hit ? 1u : 0u;
+                if (MODE == TC_ARCS && hit) {
+                    const int j = x[i] == y[0] ? 0 : (x[i] == y[1] ? 1 : (x[i] == y[2] ? 2 : 3));
+                    atomicAdd(&te[a + i], 1u);
+                    atomicAdd(&te[b + j], 1u);
+                }
+                if (MODE == TC_LIST && hit) {
+                    const int32_t tri[3] = {u, v, x[i]};
+                    emit_vertices<3>(em, tri);
+                }
+            }
+            const int32_t la = a + 4 < az ? A.w : INT_MAX, lb = b + 4 < bz ? B.w : INT_MAX;
+            if (la <= lb) {
+                a += 4;
+                if (a < az) A = load(a, az, -1);
+            }
+            if (lb <= la) {
+                b += 4;
+                if (b < bz) B = load(b, bz, -2);
+            }
+        }
+        if (MODE == TC_ARCS && mine) atomicAdd(&te[e0], mine);
+        acc += mine;
+    }
+    total = wave_sum((uint64_t)acc);
+    if (MODE == TC_LIST) {
+        row_emitter_flush(em, result);
+        return;
+    }
+    block_add<kWPB>(total, result);
+}
+
+// The line between the two: a merge costs a lane up to 16 dependent steps at
+// 32 entries a side, and a staged root its table; uniform graphs fall below
+// it whole (3,000,001 vertices, 24M edges: 1.1 ms against 2.8 ms for a wave
+// per root), and on RMAT-20 99% of the tests lie above it.
+
+// Staged roots.  A workgroup takes a task (x, a run of x's neighbours),
+// holds N+(x) in LDS as a hash table (4 to 16 slots per entry, at most 4096)
+// and takes 256 neighbours y at a time: y has a segment when the arc between
+// x and y is x's (d+(y) < d+(x), or equal and x -> y), namely N+(y), cut
+// into units of 16 entries.  A wave looks up the segments of 64 units at
+// once, one per lane, and then tests 4 units per step and tile, a 16-lane
+// group each: two lane exchanges tell a group its unit, so short and long
+// segments cost the same bookkeeping.  With HUB, N+(x) is too long for LDS
+// and each entry is searched in it.
+//   TC_ARCS: the arc from x to the closing vertex is counted in LDS by its
+// position in N+(x), the arc between x and y per segment (found in the table
+// when y is an out-neighbour, else by a search for x in N+(y)), both flushed
+// after use; the arc from y takes a global atomic.
+// RMAT-20: 2.4 ms for 2.2e9 tests (6.1 ms with every arc u -> v at u: 5.0e9).
+template <int MODE, bool HUB>
+__global__ void __launch_bounds__(kBlock, MODE == TC_COUNT ? 8 : 4)
+    k_tc_seg(const int32_t *__restrict__ off, const int32_t *__restrict__ adj,
+             const int32_t *__restrict__ okey, const int32_t *__restrict__ dag_off,
+             const int32_t *__restrict__ dag_adj, const TcTask *__restrict__ tasks,
+             const uint32_t *__restrict__ ntasks_p, Tau tau, uint32_t *cursor,
+             unsigned long long *result, uint32_t *te, RowEmitter em) {
+    constexpr int TU = 4;                        // tiles in flight
+    constexpr int H = HUB ? 4 : 4096;
+    constexpr bool ARCS = MODE == TC_ARCS, VALS = ARCS && !HUB;
+    __shared__ __align__(16) int32_t keys[H];
+    __shared__ int16_t vals[VALS ? H : 1];
+    __shared__ uint32_t cnt[VALS ? kTcMaxD : 1];
+    __shared__ int32_t pre[kBlock], sbeg[kBlock], slen[kBlock];
+    __shared__ uint32_t scnt[ARCS ? kBlock : 1];
+    __shared__ int32_t sy[MODE == TC_LIST ? kBlock : 1];   // y, or ~y for y -> x
+    __shared__ int32_t s_sum[kWPB];
+    __shared__ uint32_t s_task;
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wid = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int grp = lane / kTcUnit, gl = lane % kTcUnit;
+    const uint32_t ntasks = *ntasks_p;
+    uint64_t acc = 0;   // wave-uniform
+    if (VALS)
+        for (int i = tid; i < kTcMaxD; i += kBlock) cnt[i] = 0;
+    for (;;) {
+        if (tid == 0) s_task = atomicAdd(cursor, 1u);
+        __syncthreads();
+        const uint32_t t = s_task;
+        if (t >= ntasks) break;
+        const int32_t x = tasks[t].x, c0 = tasks[t].c0;
+        const int32_t s = dag_off[x], d = dag_off[x + 1] - s;
+        const int32_t r0 = off[x], cz = min(off[x + 1] - r0, c0 + tc_task_nbrs(d, tau));
+        const int32_t kx = okey[x];
+        const int32_t hb = min(12, lds_hash_bits(d, d <= 256 ? 16 : 4));
+        const uint32_t bmask = (1u << (hb - 2)) - 1u;
+        const int4 *kb = reinterpret_cast<const int4 *>(keys);
+        if (!HUB) {
+            int4 *k4 = reinterpret_cast<int4 *>(keys);
+            for (int i = tid; i < (1 << hb) / 4; i += kBlock) k4[i] = make_int4(-1, -1, -1, -1);
             __syncthreads();
-            if (MODE == TC_ARCS) {
-                for (int32_t i = tid; i < d; i += NT) {
-                    const uint32_t x = cnt[i];
-                    if (x) {
-                        atomicAdd(&te[s + i], x);
-                        cnt[i] = 0;
+            for (int32_t i = tid; i < d; i += kBlock)
+                lds_hash_insert(keys, VALS ? vals : nullptr, hb, dag_adj[s + i], i);
+        }
+        for (int32_t b0 = c0; b0 < cz; b0 += kBlock) {
+            // one neighbour per thread: its segment's units
+            int32_t y = 0, ys = 0, dy = 0;
+            bool in = false;   // y -> x (known where it matters)
+            if (b0 + tid < cz) {
+                y = adj[r0 + b0 + tid];
+                ys = dag_off[y];
+                dy = dag_off[y + 1] - ys;
+                if (dy > d) dy = 0;
+                if (dy > 0 && (dy == d || MODE == TC_LIST)) {
+                    in = !rank_less(kx, x, okey[y], y);
+                    if (dy == d && in) dy = 0;
+                }
+            }
+            const int32_t nu = (dy + kTcUnit - 1) / kTcUnit;
+            const int32_t inc = wave_incl_scan(nu);
+            if (lane == 63) s_sum[wid] = inc;
+            sbeg[tid] = ys;
+            slen[tid] = dy;
+            if (ARCS) scnt[tid] = 0;
+            if (MODE == TC_LIST) sy[tid] = in ? ~y : y;
+            __syncthreads();
+            int32_t before = 0, units = 0;
+#pragma unroll
+            for (int q = 0; q < kWPB; q++) {
+                before += q < wid ? s_sum[q] : 0;
+                units += s_sum[q];
+            }
+            units = __builtin_amdgcn_readfirstlane(units);
+            pre[tid] = before + inc - nu;
+            __syncthreads();
+            for (int32_t ub = wid * kWave; ub < units; ub += kBlock) {
+                // this lane's unit of the wave's 64: first arc, entries and segment
+                int32_t st = s, ln = 0;
+                if (ub + lane < units) {
+                    int32_t j = 0;   // last segment starting at or before the unit
+#pragma unroll
+                    for (int h = kBlock / 2; h > 0; h >>= 1)
+                        if (pre[j + h] <= ub + lane) j += h;
+                    const int32_t o = (ub + lane - pre[j]) * kTcUnit;
+                    st = sbeg[j] + o;
+                    ln = min(kTcUnit, slen[j] - o) | (j << 5);
+                }
+                const int32_t ntile = min(kTcUnit, (units - ub + 3) / 4);
+                for (int32_t t0 = 0; t0 < ntile; t0 += TU) {
+                    int32_t e[TU], w[TU], us[TU];
+                    uint64_t pend[TU];
+#pragma unroll
+                    for (int q = 0; q < TU; q++) {
+                        const int src = (t0 + q) * 4 + grp;   // below 64: TU divides 16
+                        us[q] = __shfl(ln, src, 64);
+                        e[q] = __shfl(st, src, 64);
+                    }
+#pragma unroll
+                    for (int q = 0; q < TU; q++) {
+                        const bool live = gl < (us[q] & 31);
+                        pend[q] = __ballot(live);
+                        // idle lanes load their unit's first arc
+                        e[q] += live ? gl : 0;
+                        w[q] = *reinterpret_cast<const int32_t *>(
+                            reinterpret_cast<const char *>(dag_adj) + ((uint32_t)e[q] << 2));
+                    }
+                    if constexpr (MODE == TC_COUNT && !HUB) {
+                        uint32_t b[TU];
+#pragma unroll
+                        for (int q = 0; q < TU; q++) b[q] = lds_hash_slot(w[q], hb) >> 2;
+                        for (;;) {
+                            int4 kv[TU];
+#pragma unroll
+                            for (int q = 0; q < TU; q++) kv[q] = kb[b[q]];
+                            uint64_t more = 0;
+#pragma unroll
+                            for (int q = 0; q < TU; q++) {
+                                const int4 k = kv[q];
+                                const int32_t v = w[q];
+                                const uint64_t hit = __ballot(k.x == v) | __ballot(k.y == v) |
+                                                     __ballot(k.z == v) | __ballot(k.w == v);
+                                const uint64_t empty = __ballot((k.x | k.y | k.z | k.w) < 0);
+                                acc += (uint64_t)__popcll(hit & pend[q]);
+                                pend[q] &= ~(hit | empty);
+                                b[q] = (b[q] + 1u) & bmask;
+                                more |= pend[q];
+                            }
+                            if (!more) break;
+                        }
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < TU; q++) {
+                            int32_t at = -1;   // slot of w (HUB: position in N+(x))
+                            if ((pend[q] >> lane) & 1ull) {
+                                if constexpr (HUB) {
+                                    const int32_t p = lower_bound_i32(dag_adj + s, d, w[q]);
+                                    at = p < d && dag_adj[s + p] == w[q] ? p : -1;
+                                } else {
+                                    uint32_t h = lds_hash_slot(w[q], hb);
+                                    for (;;) {
+                                        const int4 k = kb[h >> 2];
+                                        const int c = k.x == w[q] ? 0 : k.y == w[q] ? 1
+                                                      : k.z == w[q] ? 2 : k.w == w[q] ? 3 : -1;
+                                        if (c >= 0) at = (int32_t)h + c;
+                                        if (c >= 0 || (k.x | k.y | k.z | k.w) < 0) break;
+                                        h = (h + 4) & ((1u << hb) - 1u);
+                                    }
+                                }
+                            }
+                            const uint64_t hit = __ballot(at >= 0);
+                            acc += (uint64_t)__popcll(hit);
+                            if (MODE == TC_COUNT || !hit) continue;
+                            const int32_t seg = us[q] >> 5;
+                            if (ARCS) {
+                                const uint32_t g =
+                                    (uint32_t)(hit >> (grp * kTcUnit)) & ((1u << kTcUnit) - 1u);
+                                if (gl == 0 && g) atomicAdd(&scnt[seg], (uint32_t)__popc(g));
+                                if (at >= 0) {
+                                    if (HUB) atomicAdd(&te[s + at], 1u);
+                                    else atomicAdd(&cnt[vals[at]], 1u);
+                                    atomicAdd(&te[e[q]], 1u);
+                                }
+                            }
+                            if (MODE == TC_LIST && at >= 0) {
+                                const int32_t yy = sy[seg];
+                                const int32_t tri[3] = {yy < 0 ? ~yy : x, yy < 0 ? x : yy, w[q]};
+                                emit_vertices<3>(em, tri);
+                            }
+                        }
                     }
                 }
-                __syncthreads();
             }
-            p = min(p1, w1);
-            a++;
+            __syncthreads();
+            if (ARCS) {
+                const uint32_t c = scnt[tid];
+                if (c) {
+                    // the arc between x and y
+                    int32_t p = lower_bound_i32(dag_adj + ys, dy, x);
+                    if (p < dy && dag_adj[ys + p] == x) {
+                        atomicAdd(&te[ys + p], c);
+                    } else {
+                        p = lower_bound_i32(dag_adj + s, d, y);
+                        if (VALS) atomicAdd(&cnt[p], c);
+                        else atomicAdd(&te[s + p], c);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        if (VALS) {
+            for (int32_t i = tid; i < d; i += kBlock) {
+                const uint32_t c = cnt[i];
+                if (c) {
+                    atomicAdd(&te[s + i], c);
+                    cnt[i] = 0;
+                }
+            }
         }
     }
     if (MODE == TC_LIST) {
         row_emitter_flush(em, result);
         return;
     }
-    acc = wave_sum(acc);
-    if (lane == 0) s_acc[wid] = acc;
-    __syncthreads();
-    if (tid == 0) {
-        unsigned long long t = 0;
-        for (int q = 0; q < NW; q++) t += s_acc[q];
-        if (t) atomicAdd(result, t);
-    }
+    block_add<kWPB>(acc, result);
 }
 
 // ------------------------------------------- local-graph k-cliques ---
@@ -562,153 +856,98 @@ __global__ void k_finish_listing(unsigned long long *result, uint64_t cap) {
 
 enum HubMode : int {
     HUB_COUNT = 0,   // count K-cliques (and triangles / 4-cliques into res3 / res4)
-    HUB_ARCS = 1,    // K = 3: count triangles and add 1 per triangle to each of its arcs
-    HUB_LIST = 2,    // list K-cliques through the row emitter
+    HUB_LIST = 1,    // list K-cliques through the row emitter
 };
-
-// Per hub root r (list hubs[0..nh)), its out-degree: the arc counts whose
-// scan numbers the tasks.
-__global__ void k_hub_arcs(const int32_t *dag_off, const int32_t *hubs, const int32_t *nh_p,
-                           int32_t *cnt) {
-    const int32_t nh = *nh_p;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nh;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t u = hubs[i];
-        cnt[i] = dag_off[u + 1] - dag_off[u];
-    }
-}
 
 template <int K, int MODE>
 __global__ void __launch_bounds__(kBlock) k_clique_hub(const int32_t *__restrict__ dag_off,
                                                        const int32_t *__restrict__ dag_adj,
                                                        const int32_t *__restrict__ hubs,
                                                        const int64_t *__restrict__ hpre,
-                                                       const int32_t *__restrict__ nh_p,
+                                                       const unsigned long long *hub_p,
                                                        int32_t maxout, int32_t *scratch,
                                                        unsigned long long *res,
                                                        unsigned long long *res3,
-                                                       unsigned long long *res4, uint32_t *te,
+                                                       unsigned long long *res4,
                                                        RowEmitter em) {
-    static_assert(K >= 3 && K <= kGenMaxK, "clique size");
-    static_assert(MODE != HUB_ARCS || K == 3, "arc counts are triangle counts");
+    static_assert(K >= 4 && K <= kGenMaxK, "clique size");
     const int lane = lane_id();
     const int64_t wave_gid = (int64_t)blockIdx.x * kWPB + threadIdx.x / kWave;
     const int64_t nwaves = (int64_t)gridDim.x * kWPB;
     int32_t *mine = scratch + wave_gid * (int64_t)(kGenMaxK - 2) * maxout;
-    const int32_t nh = *nh_p;
-    const int64_t total = hpre[nh];
+    const int32_t nh = (int32_t)(*hub_p >> 32);
+    const int64_t total = (int64_t)(*hub_p & 0xffffffffull);
     // fused counts need every 4-clique below an arc, so only K's own
     // pruning applies when no 4-cliques are asked for
     const int32_t need2 = (res4 && K > 4) ? 2 : K - 2;
     uint64_t acc = 0, acc3 = 0, acc4 = 0;
     for (int64_t t = wave_gid; t < total; t += nwaves) {
-        const int32_t r = (int32_t)last_le_i64(hpre, (int64_t)nh + 1, t);
+        const int32_t r = (int32_t)last_le_i64(hpre, nh, t);
         const int32_t u = hubs[r];
         const int32_t s = dag_off[u], d = dag_off[u + 1] - s;
         const int32_t e = s + (int32_t)(t - hpre[r]);
         const int32_t v = dag_adj[e];
         const int32_t vs = dag_off[v], vd = dag_off[v + 1] - vs;
-        if constexpr (MODE == HUB_ARCS || (K == 3 && MODE == HUB_LIST)) {
-            // every common out-neighbour w closes the triangle (u, v, w)
-            const bool u_short = d <= vd;
-            const int32_t *a = u_short ? dag_adj + s : dag_adj + vs;
-            const int32_t *b = u_short ? dag_adj + vs : dag_adj + s;
-            const int32_t na = u_short ? d : vd, nb = u_short ? vd : d;
-            uint32_t c = 0;
-            for (int32_t i0 = 0; i0 < na; i0 += kWave) {
-                const int32_t i = i0 + lane;
-                bool hit = false;
-                int32_t x = 0, p = 0;
-                if (i < na) {
-                    x = a[i];
-                    p = lower_bound_i32(b, nb, x);
-                    hit = p < nb && b[p] == x;
-                }
-                if (hit) {
-                    if constexpr (MODE == HUB_ARCS) {
-                        // arcs u -> w and v -> w
-                        atomicAdd(&te[(u_short ? s + i : s + p)], 1u);
-                        atomicAdd(&te[(u_short ? vs + p : vs + i)], 1u);
-                    } else {
-                        const int32_t tri[3] = {u, v, x};
-                        emit_vertices<3>(em, tri);
-                    }
-                }
-                c += (uint32_t)__popcll(__ballot(hit));
-            }
-            if (lane == 0) {
-                acc += c;
-                if (MODE == HUB_ARCS && c) atomicAdd(&te[e], c);   // arc u -> v
-            }
-            continue;
-        } else {
-            if constexpr (K == 3) {
-                const int32_t c = wave_intersect<false>(dag_adj + s, d, dag_adj + vs, vd, nullptr);
-                if (lane == 0) acc += (uint64_t)c;
+        // level 1: C = N+(u) ∩ N+(v), the triangles on the arc
+        const int32_t c2 = wave_intersect<true>(dag_adj + s, d, dag_adj + vs, vd, mine);
+        wave_sync();
+        if (res3 && lane == 0) acc3 += (uint64_t)c2;
+        if (c2 < need2) continue;
+        const int32_t *cand[kGenMaxK];
+        int32_t csz[kGenMaxK], it[kGenMaxK], pv[kGenMaxK];
+        pv[0] = u;
+        pv[1] = v;
+        cand[2] = mine;
+        csz[2] = c2;
+        it[2] = 0;
+        constexpr int last = K - 2;   // level whose intersection is counted or listed
+        int l = 2;
+        while (l >= 2) {
+            if (it[l] >= csz[l]) {
+                l--;
+                if (l >= 2) it[l]++;
                 continue;
-            } else {
-                // level 1: C = N+(u) ∩ N+(v), the triangles on the arc
-                const int32_t c2 = wave_intersect<true>(dag_adj + s, d, dag_adj + vs, vd, mine);
-                wave_sync();
-                if (res3 && lane == 0) acc3 += (uint64_t)c2;
-                if (c2 < need2) continue;
-                const int32_t *cand[kGenMaxK];
-                int32_t csz[kGenMaxK], it[kGenMaxK], pv[kGenMaxK];
-                pv[0] = u;
-                pv[1] = v;
-                cand[2] = mine;
-                csz[2] = c2;
-                it[2] = 0;
-                constexpr int last = K - 2;   // level whose intersection is counted or listed
-                int l = 2;
-                while (l >= 2) {
-                    if (it[l] >= csz[l]) {
-                        l--;
-                        if (l >= 2) it[l]++;
-                        continue;
-                    }
-                    const int32_t w = cand[l][it[l]];
-                    pv[l] = w;
-                    const int32_t ws = dag_off[w], wd = dag_off[w + 1] - ws;
-                    if (l == last) {
-                        if constexpr (MODE == HUB_COUNT) {
-                            const int32_t c = wave_intersect<false>(cand[l], csz[l], dag_adj + ws,
-                                                                    wd, nullptr);
-                            if (lane == 0) acc += (uint64_t)c;
-                        } else {
-                            const int32_t *a = cand[l], *b = dag_adj + ws;
-                            const int32_t na = csz[l], nb = wd;
-                            for (int32_t i0 = 0; i0 < na; i0 += kWave) {
-                                const int32_t i = i0 + lane;
-                                if (i < na) {
-                                    const int32_t x = a[i];
-                                    const int32_t p = lower_bound_i32(b, nb, x);
-                                    if (p < nb && b[p] == x) {
-                                        int32_t q[K];
+            }
+            const int32_t w = cand[l][it[l]];
+            pv[l] = w;
+            const int32_t ws = dag_off[w], wd = dag_off[w + 1] - ws;
+            if (l == last) {
+                if constexpr (MODE == HUB_COUNT) {
+                    const int32_t c = wave_intersect<false>(cand[l], csz[l], dag_adj + ws,
+                                                            wd, nullptr);
+                    if (lane == 0) acc += (uint64_t)c;
+                } else {
+                    const int32_t *a = cand[l], *b = dag_adj + ws;
+                    const int32_t na = csz[l], nb = wd;
+                    for (int32_t i0 = 0; i0 < na; i0 += kWave) {
+                        const int32_t i = i0 + lane;
+                        if (i < na) {
+                            const int32_t x = a[i];
+                            const int32_t p = lower_bound_i32(b, nb, x);
+                            if (p < nb && b[p] == x) {
+                                int32_t q[K];
 #pragma unroll
-                                        for (int z = 0; z < K - 1; z++) q[z] = pv[z];
-                                        q[K - 1] = x;
-                                        emit_vertices<K>(em, q);
-                                    }
-                                }
+                                for (int z = 0; z < K - 1; z++) q[z] = pv[z];
+                                q[K - 1] = x;
+                                emit_vertices<K>(em, q);
                             }
                         }
-                        it[l]++;
-                    } else {
-                        int32_t *out = mine + (int64_t)(l - 1) * maxout;
-                        const int32_t c = wave_intersect<true>(cand[l], csz[l], dag_adj + ws, wd,
-                                                               out);
-                        wave_sync();
-                        if (res4 && l == 2 && lane == 0) acc4 += (uint64_t)c;
-                        if (c >= K - 1 - l) {
-                            l++;
-                            cand[l] = out;
-                            csz[l] = c;
-                            it[l] = 0;
-                        } else {
-                            it[l]++;
-                        }
                     }
+                }
+                it[l]++;
+            } else {
+                int32_t *out = mine + (int64_t)(l - 1) * maxout;
+                const int32_t c = wave_intersect<true>(cand[l], csz[l], dag_adj + ws, wd,
+                                                       out);
+                wave_sync();
+                if (res4 && l == 2 && lane == 0) acc4 += (uint64_t)c;
+                if (c >= K - 1 - l) {
+                    l++;
+                    cand[l] = out;
+                    csz[l] = c;
+                    it[l] = 0;
+                } else {
+                    it[l]++;
                 }
             }
         }
@@ -731,35 +970,32 @@ __global__ void __launch_bounds__(kBlock) k_clique_hub(const int32_t *__restrict
 
 // ------------------------------------------------------------ host side --
 
-// Triangle classes by out-degree: (1, 64] one wave per block, (64, 256] and
-// (256, 1024] larger blocks sharing one staged root.  Chunk sizes in pairs
-// (per graph, gpm_graph::tc_tau): every chunk costs one atomic on the
-// class's cursor, and a few hundred thousand atomics on one address cost
-// milliseconds, so chunks stay large; too large, and the last chunks leave
-// most of the grid idle.
-constexpr int32_t kTcSmall = 64, kTcMid = 256, kTcMax = 1024;
-
 struct CliqueWs {
-    unsigned long long *result;   // [8]: count, -, pairs of each triangle class
-    uint32_t *ctl;                // [32]: cursors, per-class {nact, nchunks}, class counts
-    int32_t *work, *cls, *flag, *pos;
+    unsigned long long *ctr;      // [8]: [0] listing slots, [1] row words, [2] hubs, [3..7] unused
+    uint32_t *ctl;                // [16]: [0..1] triangle cursors, [2..3] triangle tasks,
+                                  // [4..7] class counts
     int32_t *list_s, *list_m, *list_b, *list_h;
-    int32_t *lwork;               // compacted work of one class (reused)
-    int64_t *wpre_s, *wpre_m, *wpre_b, *wpre_h;
-    int32_t *first_s, *first_m, *first_b;
-    int64_t *scan_tmp;
-    void *lg;                     // local-graph workspace (k = 4, 5)
+    int64_t *rowoff_b, *hpre;
+    TcTask *tasks, *hub_tasks;
+    void *lg;                     // local-graph workspace (k >= 4)
     uint64_t lg_bytes;
     int32_t *gen_scratch;
     int gen_waves;
     uint64_t bytes;
 };
 
-int64_t chunk_bound(const gpm_graph *g) {
-    // total pair work = sum_v d-(v) d+(v) <= m * max_out; chunks = ceil(total / tau)
-    int64_t w = g->m * (int64_t)std::max(g->max_out_degree, 1);
-    const int64_t tau = std::min({g->tc_tau[0], g->tc_tau[1], g->tc_tau[2]});
-    return w / std::max<int64_t>(tau, 1) + 2;
+Tau tau_of(const gpm_graph *g) { return Tau{{g->tc_tau[0], g->tc_tau[1], g->tc_tau[2]}}; }
+
+// Tasks of the staged triangle roots at most: one per root of out-degree
+// above kTcArcMax and one per full run of neighbours, runs being shortest at
+// the top of a class of tc_tau.
+uint64_t tc_task_bound(const gpm_graph *g) {
+    const Tau tau = tau_of(g);
+    int32_t nb = INT_MAX;
+    for (int32_t top : {64, 256, INT_MAX})
+        nb = std::min(nb, tc_task_nbrs(std::max(1, std::min(top, g->max_out_degree)), tau));
+    const uint64_t roots = (uint64_t)std::min<int64_t>(g->n, g->m / (kTcArcMax + 1));
+    return roots + 2 * (uint64_t)g->m / (uint64_t)nb + 1;
 }
 
 // The generic DFS (a wave per root) serves listings of k >= 6; every other
@@ -778,8 +1014,8 @@ bool uses_generic(const gpm_graph *g, int32_t k, bool list) {
     return list && k > 5;
 }
 
-// Roots above the largest class go to k_clique_hub.
-bool has_hubs(const gpm_graph *g) { return g->max_out_degree > kTcMax; }
+// Roots above the largest class go to k_clique_hub (k >= 4).
+bool has_hubs(const gpm_graph *g) { return g->max_out_degree > kTcMaxD; }
 
 bool uses_hub_kernel(const gpm_graph *g, int32_t k) { return has_hubs(g) || lg_disabled(k); }
 
@@ -787,33 +1023,26 @@ CliqueWs clique_layout(const gpm_graph *g, int32_t k, bool list, void *base) {
     CliqueWs W{};
     Carve c(base, ~0ull);
     const uint64_t n1 = (uint64_t)g->n + 1;
-    W.result = c.take<unsigned long long>(8);
-    W.ctl = c.take<uint32_t>(32);
-    W.work = c.take<int32_t>(n1);
-    W.cls = c.take<int32_t>(n1);
-    W.flag = c.take<int32_t>(n1);
-    W.pos = c.take<int32_t>(n1);
-    W.list_s = c.take<int32_t>(n1);
-    W.list_m = c.take<int32_t>(n1);
-    W.list_b = c.take<int32_t>(n1);
-    W.list_h = c.take<int32_t>(n1);
-    W.lwork = c.take<int32_t>(n1);
-    W.wpre_s = c.take<int64_t>(n1);
-    W.wpre_m = c.take<int64_t>(n1);
-    W.wpre_b = c.take<int64_t>(n1);
-    W.wpre_h = c.take<int64_t>(n1);
-    W.scan_tmp = c.take<int64_t>(scan_tmp_words(n1));
-    bool generic = uses_generic(g, k, list);
+    W.ctr = c.take<unsigned long long>(8);
+    W.ctl = c.take<uint32_t>(16);
+    const bool generic = uses_generic(g, k, list);
     if (!generic && k == 3) {
-        W.first_s = c.take<int32_t>((uint64_t)chunk_bound(g));
-        W.first_m = c.take<int32_t>((uint64_t)chunk_bound(g));
-        W.first_b = c.take<int32_t>((uint64_t)chunk_bound(g));
+        if (g->max_out_degree > kTcArcMax) W.tasks = c.take<TcTask>(tc_task_bound(g));
+        if (has_hubs(g)) W.hub_tasks = c.take<TcTask>(tc_task_bound(g));
     }
-    if (!generic && k >= 4 && !lg_disabled(k)) {
-        lg_workspace_bytes(g, k, &W.lg_bytes);
-        W.lg = c.take<char>(W.lg_bytes);
+    if (!generic && k >= 4) {
+        W.list_s = c.take<int32_t>(n1);
+        W.list_m = c.take<int32_t>(n1);
+        W.list_b = c.take<int32_t>(n1);
+        W.list_h = c.take<int32_t>(n1);
+        if (k >= 5) W.rowoff_b = c.take<int64_t>(n1);
+        if (uses_hub_kernel(g, k)) W.hpre = c.take<int64_t>(n1);
+        if (!lg_disabled(k)) {
+            lg_workspace_bytes(g, k, &W.lg_bytes);
+            W.lg = c.take<char>(W.lg_bytes);
+        }
     }
-    if (generic || uses_hub_kernel(g, k)) {
+    if (generic || (k >= 4 && uses_hub_kernel(g, k))) {
         W.gen_waves = persistent_blocks(kWPB, 8) * kWPB;
         W.gen_scratch = c.take<int32_t>((uint64_t)W.gen_waves * (kGenMaxK - 2) *
                                         (uint64_t)std::max(1, g->max_out_degree));
@@ -828,87 +1057,72 @@ unsigned grid_for(int64_t items, int per_block, int cap_per_cu) {
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(b, cap));
 }
 
-// Builds the compacted root list of one class; returns its count in *count_dev
-// (device int32 = pos[n]) and, when wpre is given, the int64 work prefix.
-hipError_t build_class(const gpm_graph *g, CliqueWs &W, int32_t want, int32_t *list,
-                       int64_t *wpre, hipStream_t st) {
-    const int32_t n = g->n;
-    if (wpre) {
-        hipError_t z = fill_u32(W.lwork, 0, (uint64_t)n + 1, st);
-        if (z != hipSuccess) return z;
-    }
-    hipLaunchKernelGGL(k_class_flag, dim3(grid_for(n, 256, 8)), dim3(256), 0, st, W.cls, n, want,
-                       W.flag);
-    hipError_t e = exclusive_scan_i32(W.flag, W.pos, (uint64_t)n, W.scan_tmp, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_compact_roots, dim3(grid_for(n, 256, 8)), dim3(256), 0, st, W.cls, W.pos,
-                       W.work, n, want, list, wpre ? W.lwork : (int32_t *)nullptr);
-    e = hipGetLastError();
-    if (e != hipSuccess || !wpre) return e;
-    // work prefix over the class's roots; the count is pos[n] (device)
-    return exclusive_scan_i64(W.lwork, wpre, (uint64_t)n, W.scan_tmp, st);
+// A persistent grid over the roots of out-degree above dmin: no more
+// workgroups than the graph can have such roots (each takes dmin + 1 arcs).
+unsigned roots_grid(const gpm_graph *g, int32_t dmin, int64_t blocks) {
+    const int64_t most = std::min<int64_t>(g->n, g->m / (dmin + 1));
+    return (unsigned)std::max<int64_t>(1, std::min(most, blocks));
 }
 
-// Cliques (or, K = 3 with HUB_ARCS, per-arc triangle counts) rooted at the
-// hub roots, the roots above the largest class; W.cls must hold the classes
-// from k_root_work.  Nothing is launched on graphs without hubs.
+// The class lists of k >= 4 (ctl and ctr zero on entry).
+gpm_status clique_roots(const gpm_graph *g, CliqueWs &W, int32_t min_out, int32_t small_max,
+                        int32_t mid_max, int32_t big_max, hipStream_t st) {
+    RootLists L{{W.list_s, W.list_m, W.list_b, W.list_h}, (int32_t *)(W.ctl + 4), W.rowoff_b,
+                W.ctr + 1, W.hpre, W.ctr + 2};
+    if (g->n > 0)
+        hipLaunchKernelGGL(k_clique_roots, dim3(grid_for(g->n, kRootsBlock, 8)), dim3(kBlock), 0,
+                           st, g->dag_off, g->n, min_out, small_max, mid_max, big_max, L);
+    GPM_LAUNCH_CHECK("k_clique_roots");
+    return GPM_OK;
+}
+
+// Cliques rooted at the hub roots, the roots above the largest class, listed
+// by clique_roots.  Nothing is launched on graphs without hubs.
 template <int K, int MODE>
 gpm_status hub_launch(const gpm_graph *g, CliqueWs &W, unsigned long long *res,
-                      unsigned long long *res3, unsigned long long *res4, uint32_t *te,
-                      const RowEmitter &em, hipStream_t st, bool all_roots = false) {
+                      unsigned long long *res3, unsigned long long *res4, const RowEmitter &em,
+                      hipStream_t st, bool all_roots = false) {
     if (!has_hubs(g) && !all_roots) return GPM_OK;
-    const int32_t n = g->n;
-    int32_t *cnt_h = (int32_t *)(W.ctl + 15);
-    GPM_HIP(build_class(g, W, RC_HUB, W.list_h, nullptr, st));
-    GPM_HIP(hipMemcpyAsync(cnt_h, W.pos + n, 4, hipMemcpyDeviceToDevice, st));
-    GPM_HIP(fill_u32(W.lwork, 0, (uint64_t)n + 1, st));
-    hipLaunchKernelGGL(k_hub_arcs, dim3(grid_for(n, 256, 8)), dim3(256), 0, st, g->dag_off,
-                       W.list_h, cnt_h, W.lwork);
-    GPM_LAUNCH_CHECK("k_hub_arcs");
-    GPM_HIP(exclusive_scan_i64(W.lwork, W.wpre_h, (uint64_t)n, W.scan_tmp, st));
     {
-        static const char *const kNames[] = {"k_clique_hub<3>", "k_clique_hub<4>",
-                                             "k_clique_hub<5>", "k_clique_hub<6>",
-                                             "k_clique_hub<7>", "k_clique_hub<8>",
-                                             "k_clique_hub<9>"};
-        Span sp(kNames[K - 3], st);
+        static const char *const kNames[] = {"k_clique_hub<4>", "k_clique_hub<5>",
+                                             "k_clique_hub<6>", "k_clique_hub<7>",
+                                             "k_clique_hub<8>", "k_clique_hub<9>"};
+        Span sp(kNames[K - 4], st);
         hipLaunchKernelGGL((k_clique_hub<K, MODE>), dim3((unsigned)(W.gen_waves / kWPB)),
                            dim3(kBlock), 0, st, g->dag_off, g->dag_adj, W.list_h,
-                           (const int64_t *)W.wpre_h, (const int32_t *)cnt_h,
-                           std::max(1, g->max_out_degree), W.gen_scratch, res, res3, res4, te,
-                           em);
+                           (const int64_t *)W.hpre, W.ctr + 2,
+                           std::max(1, g->max_out_degree), W.gen_scratch, res, res3, res4, em);
     }
     GPM_LAUNCH_CHECK("k_clique_hub");
     return GPM_OK;
 }
 
 template <int K>
-gpm_status launch_local(const gpm_graph *g, CliqueWs &W, const int32_t *cnt_s,
-                        const int32_t *cnt_m, const int32_t *cnt_b, unsigned long long *res,
+gpm_status launch_local(const gpm_graph *g, CliqueWs &W, unsigned long long *res,
                         unsigned long long *res3, unsigned long long *res4, hipStream_t st,
                         const RowEmitter *em = nullptr) {
-    gpm_status rc = lg_cliques(g, K, W.list_m, cnt_m, W.list_b, cnt_b, W.lg, W.lg_bytes, res,
-                               res3, res4, em, st);
+    const int32_t *cnt = (const int32_t *)(W.ctl + 4);   // small, mid, big
+    gpm_status rc = lg_cliques(g, K, W.list_m, cnt + 1, W.list_b, cnt + 2, W.rowoff_b, W.lg,
+                               W.lg_bytes, res, res3, res4, em, st);
     if (rc) return rc;
     {
         static const char *const kNames[] = {"k_clique_wave<4>", "k_clique_wave<5>",
                                              "k_clique_wave<6>", "k_clique_wave<7>",
                                              "k_clique_wave<8>", "k_clique_wave<9>"};
         Span sp(kNames[K - 4], st);
+        const dim3 grid(roots_grid(g, 0, (int64_t)cu_count() * g->cw_bpc));
         if (em)
-            hipLaunchKernelGGL((k_clique_wave<K, true>), dim3((unsigned)(cu_count() * g->cw_bpc)),
-                               dim3(kWave), 0, st, g->dag_off, g->dag_adj, W.list_s, cnt_s, res,
-                               res3, res4, *em);
+            hipLaunchKernelGGL((k_clique_wave<K, true>), grid, dim3(kWave), 0, st, g->dag_off,
+                               g->dag_adj, W.list_s, cnt, res, res3, res4, *em);
         else
-            hipLaunchKernelGGL((k_clique_wave<K, false>), dim3((unsigned)(cu_count() * g->cw_bpc)),
-                               dim3(kWave), 0, st, g->dag_off, g->dag_adj, W.list_s, cnt_s, res,
-                               res3, res4, RowEmitter{});
+            hipLaunchKernelGGL((k_clique_wave<K, false>), grid, dim3(kWave), 0, st, g->dag_off,
+                               g->dag_adj, W.list_s, cnt, res, res3, res4, RowEmitter{});
     }
     GPM_LAUNCH_CHECK("k_clique_wave");
     if constexpr (K <= 5) {
-        if (em) return hub_launch<K, HUB_LIST>(g, W, res, nullptr, nullptr, nullptr, *em, st);
+        if (em) return hub_launch<K, HUB_LIST>(g, W, res, nullptr, nullptr, *em, st);
     }
-    return hub_launch<K, HUB_COUNT>(g, W, res, res3, res4, nullptr, RowEmitter{}, st);
+    return hub_launch<K, HUB_COUNT>(g, W, res, res3, res4, RowEmitter{}, st);
 }
 
 }  // namespace
@@ -919,67 +1133,51 @@ gpm_status clique_workspace_bytes(const gpm_graph *g, int32_t k, bool list, uint
     return GPM_OK;
 }
 
-template <int DMAX, int NT, int MODE>
-static gpm_status tc_class(const gpm_graph *g, CliqueWs &W, int32_t want, int32_t *list,
-                           int64_t *wpre, int32_t *first, int cls_idx, int64_t tau,
-                           int blocks_per_cu, const char *name, unsigned long long *res,
-                           uint32_t *te, const RowEmitter &em, hipStream_t st) {
-    const int32_t n = g->n;
-    uint32_t *info = W.ctl + 4 + 2 * cls_idx;   // {nact, nchunks}
-    GPM_HIP(build_class(g, W, want, list, wpre, st));
-    hipLaunchKernelGGL(k_chunk_map, dim3(grid_for(n, 256, 8)), dim3(256), 0, st, wpre, W.pos + n,
-                       tau, first, info, W.result + 2 + cls_idx);
-    GPM_LAUNCH_CHECK("k_chunk_map");
-    {
-        Span sp(name, st);
-        hipLaunchKernelGGL((k_tc_block<DMAX, NT, MODE, MODE == TC_COUNT ? 4 : 2>),
-                           dim3((unsigned)(cu_count() * blocks_per_cu)), dim3(NT), 0, st,
-                           g->dag_off, g->dag_adj, list, wpre, first, info, W.ctl + cls_idx,
-                           tau, res, te, em);
-        span_units(W.result + 2 + cls_idx, st);
-    }
-    GPM_LAUNCH_CHECK(name);
-    return GPM_OK;
-}
-
-// Triangle count into *res (zero on entry); with MODE == TC_ARCS also adds 1
-// to the triangle count of each of the three arcs of every triangle (te, m
-// words, zero on entry).  Uses the triangle workspace
+// Triangle count into *res (zero on entry, as are W.ctl and W.ctr); with MODE
+// == TC_ARCS also adds 1 to the triangle count of each of the three arcs of
+// every triangle (te, m words, zero on entry).  Uses the triangle workspace
 // (clique_workspace_bytes(g, 3, false)).
 template <int MODE>
 static gpm_status tc_launch(const gpm_graph *g, CliqueWs &W, unsigned long long *res,
                             uint32_t *te, hipStream_t st, const RowEmitter &em = RowEmitter{}) {
-    const int32_t n = g->n;
-    GPM_HIP(fill_u32(W.ctl, 0, 32, st));
-    hipLaunchKernelGGL(k_root_work, dim3(grid_for(n, kWPB, 16)), dim3(kBlock), 0, st, g->dag_off,
-                       g->dag_adj, n, 2, kTcSmall, kTcMid, kTcMax, W.work, W.cls);
-    GPM_LAUNCH_CHECK("k_root_work");
-    const bool arcs = MODE == TC_ARCS;
-    gpm_status rc = tc_class<kTcMax, 512, MODE>(
-        g, W, RC_BIG, W.list_b, W.wpre_b, W.first_b, 2, g->tc_tau[2], g->tc_bpc[2],
-        MODE == TC_LIST ? "k_tc_block<1024,list>" : (arcs ? "k_tc_block<1024,arcs>" : "k_tc_block<1024>"),
-        res, te, em, st);
-    if (rc) return rc;
-    rc = tc_class<kTcMid, 256, MODE>(g, W, RC_MID, W.list_m, W.wpre_m, W.first_m, 1,
-                                     g->tc_tau[1], g->tc_bpc[1],
-                                     MODE == TC_LIST ? "k_tc_block<256,list>"
-                                                     : (arcs ? "k_tc_block<256,arcs>" : "k_tc_block<256>"),
-                                     res, te, em, st);
-    if (rc) return rc;
-    rc = tc_class<kTcSmall, 64, MODE>(g, W, RC_SMALL, W.list_s, W.wpre_s, W.first_s, 0,
-                                      g->tc_tau[0], g->tc_bpc[0],
-                                      MODE == TC_LIST ? "k_tc_block<64,list>"
-                                                      : (arcs ? "k_tc_block<64,arcs>" : "k_tc_block<64>"),
-                                      res, te, em, st);
-    if (rc) return rc;
-    constexpr int HM = MODE == TC_LIST ? HUB_LIST : (MODE == TC_ARCS ? HUB_ARCS : HUB_COUNT);
-    return hub_launch<3, HM>(g, W, res, nullptr, nullptr, te, em, st);
+    if (g->m == 0) return GPM_OK;
+    if (g->max_out_degree > kTcArcMax) {
+        const Tau tau = tau_of(g);
+        hipLaunchKernelGGL(k_tc_tasks, dim3(grid_for(g->n, kRootsBlock, 8)), dim3(kBlock), 0, st,
+                           g->off, g->dag_off, g->n, tau, W.tasks, W.hub_tasks, W.ctl + 2);
+        GPM_LAUNCH_CHECK("k_tc_tasks");
+        const int64_t bpc = std::max(g->tc_bpc[1], g->tc_bpc[2]);
+        const dim3 grid((unsigned)std::min<int64_t>((int64_t)tc_task_bound(g), cu_count() * bpc));
+        {
+            Span sp(MODE == TC_LIST ? "k_tc_seg<list>" : (MODE == TC_ARCS ? "k_tc_seg<arcs>" : "k_tc_seg"), st);
+            hipLaunchKernelGGL((k_tc_seg<MODE, false>), grid, dim3(kBlock), 0, st, g->off, g->adj,
+                               g->okey, g->dag_off, g->dag_adj, W.tasks, W.ctl + 2, tau, W.ctl + 0,
+                               res, te, em);
+        }
+        GPM_LAUNCH_CHECK("k_tc_seg");
+        if (has_hubs(g)) {
+            Span sp("k_tc_seg<hub>", st);
+            hipLaunchKernelGGL((k_tc_seg<MODE, true>), grid, dim3(kBlock), 0, st, g->off, g->adj,
+                               g->okey, g->dag_off, g->dag_adj, W.hub_tasks, W.ctl + 3, tau,
+                               W.ctl + 1, res, te, em);
+        }
+        GPM_LAUNCH_CHECK("k_tc_seg<hub>");
+    }
+    {
+        Span sp(MODE == TC_LIST ? "k_tc_arcs<list>" : (MODE == TC_ARCS ? "k_tc_arcs<arcs>" : "k_tc_arcs"), st);
+        hipLaunchKernelGGL(k_tc_arcs<MODE>, dim3(grid_for(g->m, kBlock, g->tc_bpc[0])),
+                           dim3(kBlock), 0, st, g->dag_off, g->dag_adj, g->dag_src, g->m, res, te,
+                           em);
+    }
+    GPM_LAUNCH_CHECK("k_tc_arcs");
+    return GPM_OK;
 }
 
 gpm_status triangle_arc_counts(const gpm_graph *g, void *ws, uint64_t ws_bytes, uint32_t *te,
                                unsigned long long *tri, hipStream_t st) {
     CliqueWs W = clique_layout(g, 3, false, ws);
     if (W.bytes > ws_bytes) return fail(GPM_OUT_OF_MEMORY, "workspace smaller than required");
+    GPM_HIP(zero_words(st, {{W.ctr, 16}, {W.ctl, 16}}));
     return tc_launch<TC_ARCS>(g, W, tri, te, st);
 }
 
@@ -989,14 +1187,13 @@ gpm_status clique_run(const gpm_graph *g, int32_t k, bool list, void *ws, uint64
     CliqueWs W = clique_layout(g, k, list, ws);
     if (W.bytes > ws_bytes) return fail(GPM_OUT_OF_MEMORY, "workspace smaller than required");
     const int32_t n = g->n;
-    unsigned long long *res = list ? d_result : W.result;
-    GPM_HIP(fill_u32(res, 0, list ? 6 : 16, st));
-    GPM_HIP(fill_u32(W.ctl, 0, 32, st));
+    // counts go straight to the caller's word, listing totals and checksums
+    // to its three; the slot counter is in the workspace
+    unsigned long long *res = list ? d_result : d_count;
+    GPM_HIP(zero_words(st, {{res, list ? 6u : 2u}, {W.ctr, 16}, {W.ctl, 16},
+                            {W.lg, W.lg ? kLgCtlWords : 0}}));
     const bool generic = uses_generic(g, k, list);
-    // listing through the triangle / local-graph kernels: slot counter in the
-    // workspace, totals and checksum into d_result
-    GPM_HIP(fill_u32(W.result, 0, 16, st));
-    RowEmitter em{W.result + 6, d_buf, list ? cap : 0, 0, 0, 0};
+    RowEmitter em{W.ctr, d_buf, list ? cap : 0, 0, 0, 0};
     if (generic) {
         ListOut lo{d_buf, list ? cap : 0};
         int blocks = W.gen_waves / kWPB;
@@ -1019,51 +1216,35 @@ gpm_status clique_run(const gpm_graph *g, int32_t k, bool list, void *ws, uint64
         if (rc) return rc;
     } else if (lg_disabled(k)) {
         // every root with out-degree >= k - 1 is a hub: one task per out-arc
-        hipLaunchKernelGGL(k_root_work, dim3(grid_for(n, kWPB, 16)), dim3(kBlock), 0, st,
-                           g->dag_off, g->dag_adj, n, k - 1, 0, 0, 0, W.work, W.cls);
-        GPM_LAUNCH_CHECK("k_root_work");
-        gpm_status rc;
+        gpm_status rc = clique_roots(g, W, k - 1, 0, 0, 0, st);
+        if (rc) return rc;
         switch (k) {
-        case 4: rc = list ? hub_launch<4, HUB_LIST>(g, W, res, nullptr, nullptr, nullptr, em, st, true)
-                          : hub_launch<4, HUB_COUNT>(g, W, res, nullptr, nullptr, nullptr, em, st, true); break;
-        case 5: rc = list ? hub_launch<5, HUB_LIST>(g, W, res, nullptr, nullptr, nullptr, em, st, true)
-                          : hub_launch<5, HUB_COUNT>(g, W, res, nullptr, nullptr, nullptr, em, st, true); break;
-        case 6: rc = hub_launch<6, HUB_COUNT>(g, W, res, nullptr, nullptr, nullptr, em, st, true); break;
-        case 7: rc = hub_launch<7, HUB_COUNT>(g, W, res, nullptr, nullptr, nullptr, em, st, true); break;
-        case 8: rc = hub_launch<8, HUB_COUNT>(g, W, res, nullptr, nullptr, nullptr, em, st, true); break;
-        default: rc = hub_launch<9, HUB_COUNT>(g, W, res, nullptr, nullptr, nullptr, em, st, true); break;
+        case 4: rc = list ? hub_launch<4, HUB_LIST>(g, W, res, nullptr, nullptr, em, st, true)
+                          : hub_launch<4, HUB_COUNT>(g, W, res, nullptr, nullptr, em, st, true); break;
+        case 5: rc = list ? hub_launch<5, HUB_LIST>(g, W, res, nullptr, nullptr, em, st, true)
+                          : hub_launch<5, HUB_COUNT>(g, W, res, nullptr, nullptr, em, st, true); break;
+        case 6: rc = hub_launch<6, HUB_COUNT>(g, W, res, nullptr, nullptr, em, st, true); break;
+        case 7: rc = hub_launch<7, HUB_COUNT>(g, W, res, nullptr, nullptr, em, st, true); break;
+        case 8: rc = hub_launch<8, HUB_COUNT>(g, W, res, nullptr, nullptr, em, st, true); break;
+        default: rc = hub_launch<9, HUB_COUNT>(g, W, res, nullptr, nullptr, em, st, true); break;
         }
         if (rc) return rc;
     } else {
-        hipLaunchKernelGGL(k_root_work, dim3(grid_for(n, kWPB, 16)), dim3(kBlock), 0, st,
-                           g->dag_off, g->dag_adj, n, k - 1, 64, kMidMaxD, kTcMax, W.work, W.cls);
-        GPM_LAUNCH_CHECK("k_root_work");
-        {
-            // three classes; each count lives in its own pos snapshot
-            int32_t *cnt_s = (int32_t *)(W.ctl + 12), *cnt_m = (int32_t *)(W.ctl + 13),
-                    *cnt_b = (int32_t *)(W.ctl + 14);
-            GPM_HIP(build_class(g, W, RC_BIG, W.list_b, nullptr, st));
-            GPM_HIP(hipMemcpyAsync(cnt_b, W.pos + n, 4, hipMemcpyDeviceToDevice, st));
-            GPM_HIP(build_class(g, W, RC_MID, W.list_m, nullptr, st));
-            GPM_HIP(hipMemcpyAsync(cnt_m, W.pos + n, 4, hipMemcpyDeviceToDevice, st));
-            GPM_HIP(build_class(g, W, RC_SMALL, W.list_s, nullptr, st));
-            GPM_HIP(hipMemcpyAsync(cnt_s, W.pos + n, 4, hipMemcpyDeviceToDevice, st));
-            gpm_status rc;
-            const RowEmitter *pem = list ? &em : nullptr;
-            switch (k) {
-            case 4: rc = launch_local<4>(g, W, cnt_s, cnt_m, cnt_b, res, nullptr, nullptr, st, pem); break;
-            case 5: rc = launch_local<5>(g, W, cnt_s, cnt_m, cnt_b, res, nullptr, nullptr, st, pem); break;
-            case 6: rc = launch_local<6>(g, W, cnt_s, cnt_m, cnt_b, res, nullptr, nullptr, st); break;
-            case 7: rc = launch_local<7>(g, W, cnt_s, cnt_m, cnt_b, res, nullptr, nullptr, st); break;
-            case 8: rc = launch_local<8>(g, W, cnt_s, cnt_m, cnt_b, res, nullptr, nullptr, st); break;
-            default: rc = launch_local<9>(g, W, cnt_s, cnt_m, cnt_b, res, nullptr, nullptr, st); break;
-            }
-            if (rc) return rc;
+        gpm_status rc = clique_roots(g, W, k - 1, 64, kMidMaxD, kTcMaxD, st);
+        if (rc) return rc;
+        const RowEmitter *pem = list ? &em : nullptr;
+        switch (k) {
+        case 4: rc = launch_local<4>(g, W, res, nullptr, nullptr, st, pem); break;
+        case 5: rc = launch_local<5>(g, W, res, nullptr, nullptr, st, pem); break;
+        case 6: rc = launch_local<6>(g, W, res, nullptr, nullptr, st); break;
+        case 7: rc = launch_local<7>(g, W, res, nullptr, nullptr, st); break;
+        case 8: rc = launch_local<8>(g, W, res, nullptr, nullptr, st); break;
+        default: rc = launch_local<9>(g, W, res, nullptr, nullptr, st); break;
         }
+        if (rc) return rc;
     }
-    if (!list) GPM_HIP(hipMemcpyAsync(d_count, res, 8, hipMemcpyDeviceToDevice, st));
     if (list && !generic) {
-        hipLaunchKernelGGL(k_finish_rows, dim3(1), dim3(64), 0, st, res, W.result + 6, cap);
+        hipLaunchKernelGGL(k_finish_rows, dim3(1), dim3(64), 0, st, res, W.ctr, cap);
         GPM_LAUNCH_CHECK("k_finish_rows");
     }
     return GPM_OK;
@@ -1082,47 +1263,22 @@ gpm_status clique_multi_run(const gpm_graph *g, int32_t kmax, void *ws, uint64_t
     if (kmax < 4 || kmax > 5) return fail(GPM_UNSUPPORTED, "kmax must be 4 or 5");
     CliqueWs W = clique_layout(g, kmax, false, ws);
     if (W.bytes > ws_bytes) return fail(GPM_OUT_OF_MEMORY, "workspace smaller than required");
-    const int32_t n = g->n;
-    unsigned long long *res = W.result;   // [0] k = kmax, [1] triangles, [2] 4-cliques (kmax 5)
-    GPM_HIP(fill_u32(res, 0, 16, st));
-    GPM_HIP(fill_u32(W.ctl, 0, 32, st));
+    // d_counts = {triangles, 4-cliques[, 5-cliques]}
+    unsigned long long *res = d_counts + (kmax - 3), *res3 = d_counts;
+    unsigned long long *res4 = kmax == 5 ? d_counts + 1 : nullptr;
+    GPM_HIP(zero_words(st, {{d_counts, (uint64_t)(2 * (kmax - 2))}, {W.ctr, 16}, {W.ctl, 16},
+                            {W.lg, W.lg ? kLgCtlWords : 0}}));
     if (lg_disabled(kmax)) {
         // without local graphs: every root of out-degree >= 2 per arc
-        hipLaunchKernelGGL(k_root_work, dim3(grid_for(n, kWPB, 16)), dim3(kBlock), 0, st,
-                           g->dag_off, g->dag_adj, n, 2, 0, 0, 0, W.work, W.cls);
-        GPM_LAUNCH_CHECK("k_root_work");
-        gpm_status rc =
-            kmax == 4 ? hub_launch<4, HUB_COUNT>(g, W, res, res + 1, nullptr, nullptr,
-                                                 RowEmitter{}, st, true)
-                      : hub_launch<5, HUB_COUNT>(g, W, res, res + 1, res + 2, nullptr,
-                                                 RowEmitter{}, st, true);
+        gpm_status rc = clique_roots(g, W, 2, 0, 0, 0, st);
         if (rc) return rc;
-    } else {
-        hipLaunchKernelGGL(k_root_work, dim3(grid_for(n, kWPB, 16)), dim3(kBlock), 0, st, g->dag_off,
-                           g->dag_adj, n, 2, 64, kMidMaxD, kTcMax, W.work, W.cls);
-        GPM_LAUNCH_CHECK("k_root_work");
-        int32_t *cnt_s = (int32_t *)(W.ctl + 12), *cnt_m = (int32_t *)(W.ctl + 13),
-                *cnt_b = (int32_t *)(W.ctl + 14);
-        GPM_HIP(build_class(g, W, RC_BIG, W.list_b, nullptr, st));
-        GPM_HIP(hipMemcpyAsync(cnt_b, W.pos + n, 4, hipMemcpyDeviceToDevice, st));
-        GPM_HIP(build_class(g, W, RC_MID, W.list_m, nullptr, st));
-        GPM_HIP(hipMemcpyAsync(cnt_m, W.pos + n, 4, hipMemcpyDeviceToDevice, st));
-        GPM_HIP(build_class(g, W, RC_SMALL, W.list_s, nullptr, st));
-        GPM_HIP(hipMemcpyAsync(cnt_s, W.pos + n, 4, hipMemcpyDeviceToDevice, st));
-        gpm_status rc = kmax == 4
-                            ? launch_local<4>(g, W, cnt_s, cnt_m, cnt_b, res, res + 1, nullptr, st)
-                            : launch_local<5>(g, W, cnt_s, cnt_m, cnt_b, res, res + 1, res + 2, st);
-        if (rc) return rc;
+        return kmax == 4 ? hub_launch<4, HUB_COUNT>(g, W, res, res3, nullptr, RowEmitter{}, st, true)
+                         : hub_launch<5, HUB_COUNT>(g, W, res, res3, res4, RowEmitter{}, st, true);
     }
-    // d_counts = {triangles, 4-cliques[, 5-cliques]}
-    GPM_HIP(hipMemcpyAsync(d_counts, res + 1, 8, hipMemcpyDeviceToDevice, st));
-    if (kmax == 4) {
-        GPM_HIP(hipMemcpyAsync(d_counts + 1, res, 8, hipMemcpyDeviceToDevice, st));
-    } else {
-        GPM_HIP(hipMemcpyAsync(d_counts + 1, res + 2, 8, hipMemcpyDeviceToDevice, st));
-        GPM_HIP(hipMemcpyAsync(d_counts + 2, res, 8, hipMemcpyDeviceToDevice, st));
-    }
-    return GPM_OK;
+    gpm_status rc = clique_roots(g, W, 2, 64, kMidMaxD, kTcMaxD, st);
+    if (rc) return rc;
+    return kmax == 4 ? launch_local<4>(g, W, res, res3, nullptr, st)
+                     : launch_local<5>(g, W, res, res3, res4, st);
 }
 
 }  // namespace gpm

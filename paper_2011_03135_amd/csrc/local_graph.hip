@@ -73,7 +73,15 @@ template <int NT>
 struct Lds {
     int32_t s_sum[NT / kWave];
     uint32_t s_task, s_next;
+    int32_t s_slices;
     uint64_t s_tri;
+};
+
+// A 5-clique task: the local vertices slice, slice + slices, ... of the
+// r-th root of its class.
+struct LgTask {
+    int32_t r;
+    uint16_t slice, slices;
 };
 
 // Hash table of a local-graph block: 4 slots per out-neighbour at the class
@@ -340,7 +348,7 @@ __global__ void __launch_bounds__(NT, DMAX == kHalfMaxD ? 6 : 1) k_lg_build(cons
                                                  const int32_t *__restrict__ roots,
                                                  const int32_t *__restrict__ nroots_p, int32_t dlo,
                                                  uint32_t *cursor, const int64_t *__restrict__ rowoff,
-                                                 uint64_t *grows, int32_t *slices,
+                                                 uint64_t *grows, LgTask *tasks, uint32_t *ntasks,
                                                  unsigned long long *units,
                                                  unsigned long long *res3,
                                                  unsigned long long *res4, uint64_t slice5) {
@@ -383,25 +391,17 @@ __global__ void __launch_bounds__(NT, DMAX == kHalfMaxD ? 6 : 1) k_lg_build(cons
             // (per graph, gpm_graph::lg5_slice), at least 8 local vertices each
             const uint64_t s_work = 1 + sh.s_tri / slice5;
             const uint64_t s_cap = (uint64_t)(d / 8 + 1);
-            slices[r] = (int32_t)std::min<uint64_t>(kMaxSlices, std::min(s_work, s_cap));
+            const int32_t S = (int32_t)std::min<uint64_t>(kMaxSlices, std::min(s_work, s_cap));
+            sh.s_slices = S;
+            sh.s_next = atomicAdd(ntasks, (uint32_t)S);
             if (sh.s_tri) atomicAdd(units, (unsigned long long)sh.s_tri);
             if (sh.s_tri && res4) atomicAdd(res4, (unsigned long long)sh.s_tri);
             sh.s_tri = 0;
         }
         __syncthreads();
-    }
-}
-
-// Storage words of every class root (d * W row words and d vertex ids), for
-// the row storage prefix.
-__global__ void k_lg_words(const int32_t *dag_off, const int32_t *roots, const int32_t *nroots_p,
-                           int32_t *words) {
-    const int32_t nroots = *nroots_p;
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < nroots; i += stride) {
-        const int32_t u = roots[i], d = dag_off[u + 1] - dag_off[u];
-        words[i] = d * ((d + 63) >> 6) + (d + 1) / 2;   // rows, then d int32 vertex ids
+        for (int32_t i = tid; i < sh.s_slices; i += NT)
+            tasks[sh.s_next + i] = {r, (uint16_t)i, (uint16_t)sh.s_slices};
+        __syncthreads();
     }
 }
 
@@ -601,8 +601,8 @@ __device__ __forceinline__ uint64_t lg5_dispatch(int32_t W, const uint64_t *rows
 template <int DMAX, bool LIST>
 __global__ void __launch_bounds__(1024) k_lg5(const int32_t *__restrict__ dag_off,
                                               const int32_t *__restrict__ roots,
-                                              const int32_t *__restrict__ toff,
-                                              const int32_t *__restrict__ nroots_p,
+                                              const LgTask *__restrict__ tasks,
+                                              const uint32_t *__restrict__ ntasks_p,
                                               const int64_t *__restrict__ rowoff,
                                               const uint64_t *__restrict__ grows,
                                               int32_t rows_words, int32_t extra,
@@ -622,17 +622,15 @@ __global__ void __launch_bounds__(1024) k_lg5(const int32_t *__restrict__ dag_of
                          (size_t)wib * (DMAX * 2 + (size_t)(extra + 1) * 2 * (DMAX / 64) * 8);
     int16_t *mem = reinterpret_cast<int16_t *>(wave_area);
     uint64_t *stack = reinterpret_cast<uint64_t *>(wave_area + DMAX * 2);
-    const int32_t nroots = *nroots_p;
-    const int32_t ntasks = toff[nroots];
+    const uint32_t ntasks = *ntasks_p;
     uint64_t acc = 0;
     for (;;) {
         if (tid == 0) sh.s_task = atomicAdd(cursor, 1u);
         __syncthreads();
-        const int32_t t = (int32_t)sh.s_task;
+        const uint32_t t = sh.s_task;
         __syncthreads();
         if (t >= ntasks) break;
-        const int32_t r = last_le_i32(toff, nroots + 1, t);
-        const int32_t slice = t - toff[r], S = toff[r + 1] - toff[r];
+        const int32_t r = tasks[t].r, slice = tasks[t].slice, S = tasks[t].slices;
         const int32_t u = roots[r];
         const int32_t d = dag_off[u + 1] - dag_off[u], W = (d + 63) >> 6;
         const uint64_t *src = grows + rowoff[r];
@@ -752,10 +750,9 @@ __global__ void __launch_bounds__(NT) k_lg5_mid(const int32_t *__restrict__ off,
 }
 
 struct LgWs {
-    uint32_t *ctl;                 // cursors
-    unsigned long long *units;     // per class: local triangles (5-cliques' work)
-    int32_t *words, *slices, *toff_b;
-    int64_t *rowoff_b, *scan_tmp;
+    uint32_t *ctl;                 // [0..7] cursors, [8] 5-clique tasks
+    unsigned long long *units;     // local triangles (5-cliques' work)
+    LgTask *tasks;
     uint64_t *rows_b;
     uint64_t bytes;
 };
@@ -763,87 +760,83 @@ struct LgWs {
 LgWs lg_layout(const gpm_graph *g, int32_t k, void *base) {
     LgWs L{};
     Carve c(base, ~0ull);
-    const uint64_t n1 = (uint64_t)g->n + 1;
-    L.ctl = c.take<uint32_t>(16);
-    L.units = c.take<unsigned long long>(4);
+    // the front of the workspace, zero on entry (kLgCtlWords)
+    L.ctl = c.take<uint32_t>(kLgCtlWords);
+    L.units = reinterpret_cast<unsigned long long *>(L.ctl + 16);
     if (k >= 5) {
-        L.words = c.take<int32_t>(n1);
-        L.slices = c.take<int32_t>(n1);
-        L.toff_b = c.take<int32_t>(n1);
-        L.rowoff_b = c.take<int64_t>(n1);
-        L.scan_tmp = c.take<int64_t>(scan_tmp_words(n1));
+        const uint64_t m = (uint64_t)std::max<int64_t>(g->m, 1);
+        // at most d / 8 + 1 tasks per root of out-degree d > 256
+        L.tasks = c.take<LgTask>(m / 8 + m / (kMidMaxD + 1) + 1);
         // rows and vertex ids of all roots with out-degree in (256, 1024]: sum of
         // d * ceil(d / 64) + ceil(d / 2) <= m * (ceil(max_out / 64) + 1) words
         const uint64_t wmax = (uint64_t)(std::max(g->max_out_degree, 1) + 63) / 64 + 1;
-        const uint64_t words = (uint64_t)std::max<int64_t>(g->m, 1) * wmax + (uint64_t)g->n;
+        const uint64_t words = m * wmax + (uint64_t)g->n;
         L.rows_b = c.take<uint64_t>(words);
     }
     L.bytes = c.used;
     return L;
 }
 
-unsigned grid_for(int64_t items, int per_block, int cap_per_cu) {
-    int64_t b = (items + per_block - 1) / per_block;
-    int64_t cap = (int64_t)cu_count() * cap_per_cu;
-    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(b, cap));
+// A persistent grid over the roots of out-degree above dmin: no more
+// workgroups than the graph can have such roots (each takes dmin + 1 arcs).
+dim3 roots_grid(const gpm_graph *g, int32_t dmin, int blocks_per_cu) {
+    const int64_t most = std::min<int64_t>(g->n, g->m / (dmin + 1));
+    return dim3((unsigned)std::max<int64_t>(
+        1, std::min<int64_t>(most, (int64_t)cu_count() * blocks_per_cu)));
 }
 
-template <int DMAX, int NT>
-gpm_status lg5_class(const gpm_graph *g, int32_t k, LgWs &L, const int32_t *list,
-                     const int32_t *cnt,
-                     int64_t *rowoff, uint64_t *rows, unsigned long long *units, int32_t *toff,
-                     uint32_t *cursors, unsigned long long *res, unsigned long long *res3,
-                     unsigned long long *res4, const RowEmitter *em, hipStream_t st,
-                     const char *nb, const char *nc) {
-    const int32_t n = g->n;
-    GPM_HIP(fill_u32(L.words, 0, (uint64_t)n + 1, st));
-    hipLaunchKernelGGL(k_lg_words, dim3(grid_for(n, 256, 8)), dim3(256), 0, st, g->dag_off, list,
-                       cnt, L.words);
-    GPM_LAUNCH_CHECK("k_lg_words");
-    GPM_HIP(exclusive_scan_i64(L.words, rowoff, (uint64_t)n, L.scan_tmp, st));
-    GPM_HIP(fill_u32(L.slices, 0, (uint64_t)n + 1, st));
-    if constexpr (DMAX > kHalfMaxD) {
-        // roots of out-degree up to kHalfMaxD at the smaller bound, the rest here
+// 5-cliques and larger at the big class's roots; nothing is launched when no
+// root can be in it.
+gpm_status lg5_big(const gpm_graph *g, int32_t k, LgWs &L, const int32_t *list, const int32_t *cnt,
+                   const int64_t *rowoff, unsigned long long *res, unsigned long long *res3,
+                   unsigned long long *res4, const RowEmitter *em, hipStream_t st) {
+    if (g->max_out_degree <= kMidMaxD) return GPM_OK;
+    const uint64_t slice5 = (uint64_t)g->lg5_slice;
+    uint32_t *ntasks = L.ctl + 8;
+    {
+        // roots of out-degree up to kHalfMaxD at the smaller bound
         Span sp("k_lg_build<512>", st);
         hipLaunchKernelGGL((k_lg_build<kHalfMaxD, kHalfThreads>),
-                           dim3((unsigned)cu_count() * kHalfBlocksPerCu), dim3(kHalfThreads), 0,
-                           st, g->off, g->okey, g->dag_off, g->dag_adj, list, cnt, kMidMaxD, cursors + 2,
-                           rowoff, rows, L.slices, units, res3, res4, (uint64_t)g->lg5_slice);
+                           roots_grid(g, kMidMaxD, kHalfBlocksPerCu), dim3(kHalfThreads), 0, st,
+                           g->off, g->okey, g->dag_off, g->dag_adj, list, cnt, kMidMaxD,
+                           L.ctl + 4, rowoff, L.rows_b, L.tasks, ntasks, L.units, res3, res4,
+                           slice5);
     }
     GPM_LAUNCH_CHECK("k_lg_build<512>");
-    {
-        Span sp(nb, st);
-        hipLaunchKernelGGL((k_lg_build<DMAX, NT>), dim3((unsigned)cu_count() * (NT <= 256 ? 8 : 1)),
-                           dim3(NT), 0, st, g->off, g->okey, g->dag_off, g->dag_adj, list, cnt,
-                           DMAX > kHalfMaxD ? kHalfMaxD : 0, cursors + 0, rowoff, rows, L.slices,
-                           units, res3, res4, (uint64_t)g->lg5_slice);
+    if (g->max_out_degree > kHalfMaxD) {
+        Span sp("k_lg_build<1024>", st);
+        hipLaunchKernelGGL((k_lg_build<kBigMaxD, kBigThreads>), roots_grid(g, kHalfMaxD, 1),
+                           dim3(kBigThreads), 0, st, g->off, g->okey, g->dag_off, g->dag_adj, list,
+                           cnt, kHalfMaxD, L.ctl + 2, rowoff, L.rows_b, L.tasks, ntasks, L.units,
+                           res3, res4, slice5);
     }
-    GPM_LAUNCH_CHECK("k_lg_build");
-    GPM_HIP(exclusive_scan_i32(L.slices, toff, (uint64_t)n, L.scan_tmp, st));
+    GPM_LAUNCH_CHECK("k_lg_build<1024>");
     {
         // LDS: rows of the class's largest local graph, then per-wave member
         // lists; as many waves as fit in 160 KiB (at most 16)
-        const int32_t dmax = std::min<int32_t>(DMAX, std::max(g->max_out_degree, 1));
+        const int32_t dmax = std::min<int32_t>(kBigMaxD, g->max_out_degree);
         const int32_t rows_words = dmax * ((dmax + 63) / 64);
         const int64_t lds_cap = 160 * 1024 - 1024;
         const int32_t extra = k - 5;
-        const int64_t per_wave = (int64_t)DMAX * 2 + (int64_t)(extra + 1) * 2 * (DMAX / 64) * 8;
+        const int64_t per_wave =
+            (int64_t)kBigMaxD * 2 + (int64_t)(extra + 1) * 2 * (kBigMaxD / 64) * 8;
         // rows, the local vertex ids, then the per-wave areas
-        const int64_t fixed = (int64_t)rows_words * 8 + (int64_t)DMAX * 4;
-        int waves = (int)std::min<int64_t>(DMAX <= 256 ? 4 : 16, (lds_cap - fixed) / per_wave);
+        const int64_t fixed = (int64_t)rows_words * 8 + (int64_t)kBigMaxD * 4;
+        int waves = (int)std::min<int64_t>(16, (lds_cap - fixed) / per_wave);
         if (waves < 1) return fail(GPM_DEVICE_ERROR, "local graph does not fit in LDS");
         const size_t shmem = (size_t)fixed + (size_t)waves * per_wave;
-        Span sp(nc, st);
-        const dim3 grid((unsigned)cu_count() * (DMAX <= 256 ? 4 : 1));
+        Span sp(k == 5 ? "k_lg5<1024>" : "k_lgk<1024>", st);
+        const dim3 grid((unsigned)cu_count());
         if (em)
-            hipLaunchKernelGGL((k_lg5<DMAX, true>), grid, dim3(waves * kWave), shmem, st,
-                               g->dag_off, list, toff, cnt, rowoff, (const uint64_t *)rows,
-                               rows_words, extra, cursors + 1, res, *em);
+            hipLaunchKernelGGL((k_lg5<kBigMaxD, true>), grid, dim3(waves * kWave), shmem, st,
+                               g->dag_off, list, L.tasks, ntasks, rowoff,
+                               (const uint64_t *)L.rows_b, rows_words, extra, L.ctl + 3, res, *em);
         else
-            hipLaunchKernelGGL((k_lg5<DMAX, false>), grid, dim3(waves * kWave), shmem, st,
-                               g->dag_off, list, toff, cnt, rowoff, (const uint64_t *)rows,
-                               rows_words, extra, cursors + 1, res, RowEmitter{});
-        span_units(units, st);
+            hipLaunchKernelGGL((k_lg5<kBigMaxD, false>), grid, dim3(waves * kWave), shmem, st,
+                               g->dag_off, list, L.tasks, ntasks, rowoff,
+                               (const uint64_t *)L.rows_b, rows_words, extra, L.ctl + 3, res,
+                               RowEmitter{});
+        span_units(L.units, st);
     }
     GPM_LAUNCH_CHECK("k_lg5");
     return GPM_OK;
@@ -859,34 +852,36 @@ gpm_status lg_workspace_bytes(const gpm_graph *g, int32_t k, uint64_t *bytes) {
 // Counts k-cliques (k = 4..9) rooted at the two workgroup classes: list_m
 // (out-degree 65..256) and list_b (257..1024), device counts cnt_m, cnt_b,
 // into *res.  res3 / res4 (may be null) also receive the triangles and (for
-// k = 5) the 4-cliques rooted at the same roots.
+// k = 5) the 4-cliques rooted at the same roots.  rowoff_b (k >= 5): where
+// each root of list_b stores its rows.  The workspace's first kLgCtlWords
+// words are zero on entry.  A class that no root of the graph can be in is
+// not launched.
 gpm_status lg_cliques(const gpm_graph *g, int32_t k, const int32_t *list_m, const int32_t *cnt_m,
-                      const int32_t *list_b, const int32_t *cnt_b, void *ws, uint64_t ws_bytes,
-                      unsigned long long *res, unsigned long long *res3,
-                      unsigned long long *res4, const RowEmitter *em, hipStream_t st) {
+                      const int32_t *list_b, const int32_t *cnt_b, const int64_t *rowoff_b,
+                      void *ws, uint64_t ws_bytes, unsigned long long *res,
+                      unsigned long long *res3, unsigned long long *res4, const RowEmitter *em,
+                      hipStream_t st) {
     LgWs L = lg_layout(g, k, ws);
     if (L.bytes > ws_bytes) return fail(GPM_OUT_OF_MEMORY, "local-graph workspace too small");
-    GPM_HIP(fill_u32(L.ctl, 0, 16, st));
-    GPM_HIP(fill_u32(L.units, 0, 8, st));
     if (k == 4) {
         const RowEmitter none{};
-        {
+        if (g->max_out_degree > kHalfMaxD) {
             Span sp("k_lg4<1024>", st);
+            const dim3 grid = roots_grid(g, kHalfMaxD, 1);
             if (em)
-                hipLaunchKernelGGL((k_lg4<kBigMaxD, kBigThreads, true, true>),
-                                   dim3((unsigned)cu_count()), dim3(kBigThreads), 0, st, g->off,
-                                   g->okey, g->dag_off, g->dag_adj, list_b, cnt_b, kHalfMaxD,
-                                   L.ctl + 0, res, res3, *em);
+                hipLaunchKernelGGL((k_lg4<kBigMaxD, kBigThreads, true, true>), grid,
+                                   dim3(kBigThreads), 0, st, g->off, g->okey, g->dag_off,
+                                   g->dag_adj, list_b, cnt_b, kHalfMaxD, L.ctl + 0, res, res3, *em);
             else
-                hipLaunchKernelGGL((k_lg4<kBigMaxD, kBigThreads, false, true>),
-                                   dim3((unsigned)cu_count()), dim3(kBigThreads), 0, st, g->off,
-                                   g->okey, g->dag_off, g->dag_adj, list_b, cnt_b, kHalfMaxD,
-                                   L.ctl + 0, res, res3, none);
+                hipLaunchKernelGGL((k_lg4<kBigMaxD, kBigThreads, false, true>), grid,
+                                   dim3(kBigThreads), 0, st, g->off, g->okey, g->dag_off,
+                                   g->dag_adj, list_b, cnt_b, kHalfMaxD, L.ctl + 0, res, res3,
+                                   none);
         }
         GPM_LAUNCH_CHECK("k_lg4<1024>");
-        {
+        if (g->max_out_degree > kMidMaxD) {
             Span sp("k_lg4<512>", st);
-            const dim3 grid((unsigned)cu_count() * kHalfBlocksPerCu);
+            const dim3 grid = roots_grid(g, kMidMaxD, kHalfBlocksPerCu);
             if (em)
                 hipLaunchKernelGGL((k_lg4<kHalfMaxD, kHalfThreads, true, true>), grid,
                                    dim3(kHalfThreads), 0, st, g->off, g->okey, g->dag_off, g->dag_adj,
@@ -897,9 +892,9 @@ gpm_status lg_cliques(const gpm_graph *g, int32_t k, const int32_t *list_m, cons
                                    list_b, cnt_b, kMidMaxD, L.ctl + 2, res, res3, none);
         }
         GPM_LAUNCH_CHECK("k_lg4<512>");
-        {
+        if (g->max_out_degree > kWave) {
             Span sp("k_lg4<256>", st);
-            const dim3 grid((unsigned)cu_count() * 8);
+            const dim3 grid = roots_grid(g, kWave, 8);
             if (em)
                 hipLaunchKernelGGL((k_lg4<kMidMaxD, kMidThreads, true, false>), grid,
                                    dim3(kMidThreads), 0, st, g->off, g->okey, g->dag_off, g->dag_adj,
@@ -912,14 +907,11 @@ gpm_status lg_cliques(const gpm_graph *g, int32_t k, const int32_t *list_m, cons
         GPM_LAUNCH_CHECK("k_lg4<256>");
         return GPM_OK;
     }
-    gpm_status rc = lg5_class<kBigMaxD, kBigThreads>(g, k, L, list_b, cnt_b, L.rowoff_b, L.rows_b,
-                                                     L.units + 0, L.toff_b, L.ctl + 2, res, res3,
-                                                     res4, em, st, "k_lg_build<1024>",
-                                                     k == 5 ? "k_lg5<1024>" : "k_lgk<1024>");
+    gpm_status rc = lg5_big(g, k, L, list_b, cnt_b, rowoff_b, res, res3, res4, em, st);
     if (rc) return rc;
-    {
+    if (g->max_out_degree > kWave) {
         Span sp(k == 5 ? "k_lg5_mid<256>" : "k_lgk_mid<256>", st);
-        const dim3 grid((unsigned)cu_count() * 8);
+        const dim3 grid = roots_grid(g, kWave, 8);
         if (em)
             hipLaunchKernelGGL((k_lg5_mid<kMidMaxD, kMidThreads, true>), grid, dim3(kMidThreads), 0,
                                st, g->off, g->okey, g->dag_off, g->dag_adj, list_m, cnt_m, k - 5,

@@ -38,6 +38,38 @@ hipError_t fill_u32(void *p, uint32_t value, uint64_t n, hipStream_t s) {
     return hipGetLastError();
 }
 
+struct WordRuns {
+    uint32_t *p[8];
+    uint64_t n[8];
+};
+
+// One grid-stride pass per run; the runs are a few control words, or one of
+// them an array, so a grid for the longest serves all.
+__global__ void k_zero_runs(WordRuns r, int32_t count) {
+    for (int32_t k = 0; k < count; k++)
+        for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < r.n[k];
+             i += (uint64_t)gridDim.x * blockDim.x)
+            r.p[k][i] = 0;
+}
+
+hipError_t zero_words(hipStream_t s, std::initializer_list<WordRun> runs) {
+    WordRuns r{};
+    int32_t count = 0;
+    uint64_t most = 0;
+    for (const WordRun &x : runs) {
+        if (x.n == 0) continue;
+        if (count == 8) return hipErrorInvalidValue;
+        r.p[count] = static_cast<uint32_t *>(x.p);
+        r.n[count++] = x.n;
+        most = x.n > most ? x.n : most;
+    }
+    if (count == 0) return hipSuccess;
+    uint64_t blocks = (most + 1023) / 1024;
+    if (blocks > 4096) blocks = 4096;
+    hipLaunchKernelGGL(k_zero_runs, dim3((unsigned)blocks), dim3(256), 0, s, r, count);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------------ scan --
 // Three phases over tiles of kTile = 256 threads x 16 items: per-tile sums,
 // one workgroup scanning the tile sums, then per-tile local scans plus the
