@@ -1075,23 +1075,34 @@ uint64_t row_sort_bytes(int32_t n) {
     return b;
 }
 
-gpm_status sort_rows(const int32_t *off, int32_t *adj, int32_t n, void *area, hipStream_t st) {
+// The run of words that must be zero before sort_rows.
+WordRun sort_rows_zero(int32_t n, void *area) {
+    return {row_sort_layout(n, area, nullptr).flags, F_WORDS};
+}
+
+// No row is longer than max_len: sorters of longer rows are not launched.
+gpm_status sort_rows(const int32_t *off, int32_t *adj, int32_t n, int32_t max_len, void *area,
+                     hipStream_t st) {
     RowSortArea A = row_sort_layout(n, area, nullptr);
-    GPM_HIP(fill_u32(A.flags, 0, F_WORDS, st));
     hipLaunchKernelGGL(k_sort_small_rows, dim3(wave_grid(((int64_t)n + 3) / 4)), dim3(kBlock), 0,
                        st, off, adj, n, A.ucnt, A.med_list, A.big_list, A.flags);
-    const int32_t span = sort_span(n);
-    hipLaunchKernelGGL(k_sort_rows<false>, dim3(wave_grid(((int64_t)n + span - 1) / span)),
-                       dim3(kBlock), 0, st, off, adj, n, span, A.ucnt, nullptr, A.flags);
-    hipLaunchKernelGGL(k_sort_rows<true>, dim3(wave_grid(n)), dim3(kBlock), 0, st, off, adj, n, 1,
-                       A.ucnt, A.med_list, A.flags);
-    if (n <= kLdsBitmapIds)
-        hipLaunchKernelGGL(k_sort_big_rows_lds, dim3((unsigned)cu_count()), dim3(kBigNT),
-                           (size_t)A.words * 4, st, off, adj, A.ucnt, A.big_list, A.flags,
-                           (int32_t)A.words);
-    else
-        hipLaunchKernelGGL(k_sort_big_rows, dim3(A.nbig_blocks), dim3(kBlock), 0, st, off, adj,
-                           A.ucnt, A.big_list, A.flags, A.bitmaps, A.words);
+    if (max_len > kSmallRow) {
+        const int32_t span = sort_span(n);
+        hipLaunchKernelGGL(k_sort_rows<false>, dim3(wave_grid(((int64_t)n + span - 1) / span)),
+                           dim3(kBlock), 0, st, off, adj, n, span, A.ucnt, nullptr, A.flags);
+    }
+    if (max_len > kScanRow)
+        hipLaunchKernelGGL(k_sort_rows<true>, dim3(wave_grid(n)), dim3(kBlock), 0, st, off, adj, n,
+                           1, A.ucnt, A.med_list, A.flags);
+    if (max_len > kRegRow) {
+        if (n <= kLdsBitmapIds)
+            hipLaunchKernelGGL(k_sort_big_rows_lds, dim3((unsigned)cu_count()), dim3(kBigNT),
+                               (size_t)A.words * 4, st, off, adj, A.ucnt, A.big_list, A.flags,
+                               (int32_t)A.words);
+        else
+            hipLaunchKernelGGL(k_sort_big_rows, dim3(A.nbig_blocks), dim3(kBlock), 0, st, off, adj,
+                               A.ucnt, A.big_list, A.flags, A.bitmaps, A.words);
+    }
     GPM_LAUNCH_CHECK("sort_rows");
     return GPM_OK;
 }

@@ -28,7 +28,9 @@
 namespace gpm {
 
 uint64_t row_sort_bytes(int32_t n);
-gpm_status sort_rows(const int32_t *off, int32_t *adj, int32_t n, void *area, hipStream_t st);
+WordRun sort_rows_zero(int32_t n, void *area);
+gpm_status sort_rows(const int32_t *off, int32_t *adj, int32_t n, int32_t max_len, void *area,
+                     hipStream_t st);
 
 namespace {
 
@@ -113,18 +115,96 @@ __global__ void __launch_bounds__(kBlock) k_c4_work(const int32_t *__restrict__ 
     }
 }
 
-__global__ void k_flag_eq(const int32_t *cls, int32_t n, int32_t want, int32_t *flag) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) flag[i] = cls[i] == want ? 1 : 0;
+// The apexes of every class, ascending, in two passes over tiles of `tile`
+// ids (a multiple of kListTile): the classes' sizes per tile, 21 bits each,
+// then every workgroup adds up the tiles before its own and places its ids.
+// Ascending order matters: the counting kernel starts with the top ranks,
+// and with the tiles in the order of their arrival instead (one pass) it took
+// 2.27 ms, not 2.12, on RMAT-18.
+constexpr int kListPer = 4;
+constexpr int kListTile = kBlock * kListPer;
+constexpr int kListTiles = 1024;   // at most
+
+int32_t list_tile(int32_t n) {
+    const int64_t t = ((int64_t)n + kListTiles - 1) / kListTiles;
+    return (int32_t)((t + kListTile - 1) / kListTile * kListTile);
 }
 
-__global__ void k_compact_eq(const int32_t *cls, const int32_t *pos, int32_t n, int32_t want,
-                             int32_t *list) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride)
-        if (cls[i] == want) list[pos[i]] = (int32_t)i;
+template <bool PLACE>
+__global__ void __launch_bounds__(kBlock) k_c4_lists(const int32_t *__restrict__ cls, int32_t n,
+                                                     int32_t tile, unsigned long long *sums,
+                                                     int32_t *light, int32_t *heavy, int32_t *med,
+                                                     int32_t *count) {
+    __shared__ uint64_t s_sum[kWPB];
+    const int tid = threadIdx.x, lane = lane_id(), wid = tid / kWave;
+    auto block_scan = [&](uint64_t x, uint64_t &total) -> uint64_t {
+        const uint64_t inc = wave_incl_scan(x);
+        __syncthreads();
+        if (lane == 63) s_sum[wid] = inc;
+        __syncthreads();
+        uint64_t before = inc - x;
+        total = 0;
+#pragma unroll
+        for (int q = 0; q < kWPB; q++) {
+            before += q < wid ? s_sum[q] : 0;
+            total += s_sum[q];
+        }
+        return before;
+    };
+    uint64_t total;
+    int32_t base[3] = {0, 0, 0};   // of light, heavy, medium
+    if (PLACE) {
+        uint64_t two = 0, third = 0;   // light | heavy << 32, medium
+        for (uint32_t t = tid; t < blockIdx.x; t += kBlock) {
+            const uint64_t v = sums[t];
+            two += (v & 0x1fffffu) | ((v >> 21) & 0x1fffffu) << 32;
+            third += v >> 42;
+        }
+        block_scan(two, total);
+        base[0] = (int32_t)total;
+        base[1] = (int32_t)(total >> 32);
+        block_scan(third, total);
+        base[2] = (int32_t)total;
+    }
+    const int64_t z = min<int64_t>(n, ((int64_t)blockIdx.x + 1) * tile);
+    uint64_t all = 0;
+    for (int64_t r0 = (int64_t)blockIdx.x * tile; r0 < z; r0 += kListTile) {
+        int32_t c[kListPer];
+        uint64_t num = 0;   // 21 bits per class
+#pragma unroll
+        for (int q = 0; q < kListPer; q++) {
+            const int64_t r = r0 + tid * kListPer + q;
+            c[q] = r < z ? cls[r] : C4_NONE;
+            if (c[q] != C4_NONE) num += 1ull << (21 * (c[q] - 1));
+        }
+        if (!PLACE) {
+            all += num;
+            continue;
+        }
+        uint64_t at = block_scan(num, total);
+#pragma unroll
+        for (int q = 0; q < kListPer; q++) {
+            if (c[q] == C4_NONE) continue;
+            const int k = c[q] - 1;
+            int32_t *list = k == 0 ? light : (k == 1 ? heavy : med);
+            const int32_t b = k == 0 ? base[0] : (k == 1 ? base[1] : base[2]);
+            list[b + (int32_t)((at >> (21 * k)) & 0x1fffffu)] =
+                (int32_t)(r0 + tid * kListPer + q);
+            at += 1ull << (21 * k);
+        }
+#pragma unroll
+        for (int k = 0; k < 3; k++) base[k] += (int32_t)((total >> (21 * k)) & 0x1fffffu);
+    }
+    if (PLACE) {
+        if (blockIdx.x == gridDim.x - 1 && tid == 0) {
+            count[C4_LIGHT] = base[0];
+            count[C4_HEAVY] = base[1];
+            count[C4_MED] = base[2];
+        }
+    } else {
+        block_scan(all, total);
+        if (tid == 0) sums[blockIdx.x] = total;
+    }
 }
 
 // ------------------------------------------------------------- emission ---
@@ -497,12 +577,13 @@ __global__ void __launch_bounds__(kHeavyNT) k_c4r_heavy(const int32_t *__restric
                                                         const int32_t *__restrict__ med,
                                                         const int32_t *__restrict__ count_med,
                                                         int32_t n, int32_t nparts, int32_t narrow,
+                                                        int32_t words,
                                                         const int2 *__restrict__ seg,
                                                         uint32_t *cursor, unsigned long long *out,
                                                         const uint32_t *__restrict__ rtsym,
                                                         unsigned long long *cs) {
     constexpr int NW = kHeavyNT / kWave;
-    __shared__ __align__(16) uint32_t cnt[kCountWords];
+    extern __shared__ __align__(16) uint32_t cnt[];   // `words` of them, at most kCountWords
     __shared__ int32_t s_pre[kHeavyNT + 1];
     __shared__ int32_t s_off[kHeavyNT];    // segment start minus its pair prefix
     __shared__ int32_t s_sum[NW];
@@ -516,7 +597,7 @@ __global__ void __launch_bounds__(kHeavyNT) k_c4r_heavy(const int32_t *__restric
     uint64_t acc = 0;
     CycleSums sums;
     const int32_t zpart = narrow ? 2 * kCountWords : kCountWords;
-    for (int i = tid; i < kCountWords; i += kHeavyNT) cnt[i] = 0;
+    for (int i = tid; i < words; i += kHeavyNT) cnt[i] = 0;
     for (;;) {
         if (tid == 0) s_task = atomicAdd(cursor, 1u);
         __syncthreads();
@@ -528,9 +609,12 @@ __global__ void __launch_bounds__(kHeavyNT) k_c4r_heavy(const int32_t *__restric
         // part holds most of the hubs' ends, so the largest tasks start
         // first, and a part's tail is apexes below it, which have no work
         // there
-        const bool hashed = t >= nparted;
-        int32_t row = 0, x, z0 = 0, z1 = 0;   // row: the part (of the part table)
-        if (hashed) {
+        // (a medium apex is counted densely, too, where one part holds every
+        // rank: its words, half as many as the ranks below it, are never
+        // more than the hash's)
+        const bool medium = t >= nparted, hashed = medium && nparts > 1;
+        int32_t row = 0, x, z0 = 0, z1 = n;   // row: the part (of the part table)
+        if (medium) {
             x = med[nmed - 1 - (int32_t)(t - nparted)];
         } else {
             row = nparts - 1 - (int32_t)(t / (uint64_t)nheavy);
@@ -646,12 +730,15 @@ __global__ void __launch_bounds__(kHeavyNT) k_c4r_heavy(const int32_t *__restric
         {
             uint4 *c4 = reinterpret_cast<uint4 *>(cnt);
             const int i0 = hashed ? kMedSlots / 4 : 0;
-            for (int i = i0 + tid; i < kCountWords / 4; i += kHeavyNT) {
+            // the words of the ranks counted here (z1 is cut at x), four at a time
+            const int iz = min(words / 4, hashed ? words : (((z1 - z0) >> narrow) + 4) / 4);
+            for (int i = i0 + tid; i < iz; i += kHeavyNT) {
                 const uint4 v = c4[i];
                 acc += pairs_of(v.x, narrow && !hashed) + pairs_of(v.y, narrow && !hashed) +
                        pairs_of(v.z, narrow && !hashed) + pairs_of(v.w, narrow && !hashed);
+                c4[i] = make_uint4(0, 0, 0, 0);
             }
-            for (int i = tid; i < kCountWords / 4; i += kHeavyNT) c4[i] = make_uint4(0, 0, 0, 0);
+            for (int i = tid; i < i0; i += kHeavyNT) c4[i] = make_uint4(0, 0, 0, 0);
         }
         __syncthreads();
     }
@@ -1324,8 +1411,8 @@ struct C4Ws {
     uint32_t *ctl;                 // [0] heavy cursor; counts [1] light, [2] heavy, [3] medium;
                                    // [4..5] cursor of the large listing tasks' units
     unsigned long long *slot;      // listing slot counter
-    unsigned long long *sum;       // counting: 128-bit total
-    int32_t *deg, *cls, *flag, *pos, *light, *heavy, *med;
+    unsigned long long *tiles;     // the classes' sizes per tile
+    int32_t *deg, *cls, *light, *heavy, *med;
     int64_t *scan_tmp;
     int32_t *wedges;               // listing: per-workgroup wedge buffers
     int32_t *arena;                // listing: groups of the large tasks
@@ -1362,11 +1449,9 @@ C4Ws c4_layout(const gpm_graph *g, bool list, void *base) {
     const uint64_t n1 = (uint64_t)g->n + 1;
     W.ctl = c.take<uint32_t>(16);
     W.slot = c.take<unsigned long long>(2);
-    W.sum = c.take<unsigned long long>(2);
+    W.tiles = c.take<unsigned long long>(kListTiles);
     W.deg = c.take<int32_t>(n1);
     W.cls = c.take<int32_t>(n1);
-    W.flag = c.take<int32_t>(n1);
-    W.pos = c.take<int32_t>(n1);
     W.light = c.take<int32_t>(n1);
     W.heavy = c.take<int32_t>(n1);
     W.scan_tmp = c.take<int64_t>(scan_tmp_words(n1));
@@ -1430,24 +1515,17 @@ gpm_status c4_run(const gpm_graph *g, bool list, void *ws, uint64_t ws_bytes,
     if (list && g->max_degree > kWedgeCap)
         return fail(GPM_UNSUPPORTED, "4-cycle listing needs every degree <= 2^18");
     const int32_t n = g->n;
-    GPM_HIP(fill_u32(W.ctl, 0, 16, st));
-    GPM_HIP(fill_u32(W.slot, 0, 4, st));
-    if (list) GPM_HIP(fill_u32(d_result, 0, 6, st));
-    int32_t *cnt_light = (int32_t *)(W.ctl + 1), *cnt_heavy = (int32_t *)(W.ctl + 2);
-    int32_t *cnt_med = (int32_t *)(W.ctl + 3);
+    int32_t *cnt = (int32_t *)W.ctl;   // [class]: its apexes
+    int32_t *cnt_light = cnt + C4_LIGHT, *cnt_heavy = cnt + C4_HEAVY, *cnt_med = cnt + C4_MED;
     // the apex lists of each class (medium only when counting)
     auto split_classes = [&]() -> gpm_status {
-        for (int cls = C4_LIGHT; cls <= (list ? C4_HEAVY : C4_MED); cls++) {
-            int32_t *lst = cls == C4_LIGHT ? W.light : cls == C4_HEAVY ? W.heavy : W.med;
-            int32_t *lcnt = (int32_t *)(W.ctl + cls);
-            hipLaunchKernelGGL(k_flag_eq, dim3(grid_for(n, 256, 8)), dim3(256), 0, st, W.cls, n,
-                               cls, W.flag);
-            GPM_HIP(exclusive_scan_i32(W.flag, W.pos, (uint64_t)n, W.scan_tmp, st));
-            hipLaunchKernelGGL(k_compact_eq, dim3(grid_for(n, 256, 8)), dim3(256), 0, st, W.cls,
-                               W.pos, n, cls, lst);
-            GPM_HIP(hipMemcpyAsync(lcnt, W.pos + n, 4, hipMemcpyDeviceToDevice, st));
-        }
-        GPM_LAUNCH_CHECK("c4 classes");
+        const int32_t tile = list_tile(n);
+        const dim3 grid((unsigned)(((int64_t)n + tile - 1) / tile));
+        hipLaunchKernelGGL(k_c4_lists<false>, grid, dim3(kBlock), 0, st, W.cls, n, tile, W.tiles,
+                           nullptr, nullptr, nullptr, nullptr);
+        hipLaunchKernelGGL(k_c4_lists<true>, grid, dim3(kBlock), 0, st, W.cls, n, tile, W.tiles,
+                           W.light, W.heavy, W.med, cnt);
+        GPM_LAUNCH_CHECK("k_c4_lists");
         return GPM_OK;
     };
     if (!list) {
@@ -1455,8 +1533,8 @@ gpm_status c4_run(const gpm_graph *g, bool list, void *ws, uint64_t ws_bytes,
         {
             Span sp("c4_rank", st);
             const uint64_t dn = (uint64_t)g->max_degree + 1;
-            GPM_HIP(fill_u32(reinterpret_cast<uint32_t *>(W.dcnt), 0, dn, st));
-            GPM_HIP(fill_u32(reinterpret_cast<uint32_t *>(W.dcur), 0, dn, st));
+            GPM_HIP(zero_words(st, {{W.ctl, 16}, {W.dcnt, dn}, {W.dcur, dn},
+                                    sort_rows_zero(n, W.sort_area)}));
             const unsigned gb = (unsigned)std::max<int64_t>(1, ((int64_t)n + kGroupV - 1) / kGroupV);
             if (n > 0) {
                 hipLaunchKernelGGL(k_rank_group<false>, dim3(gb), dim3(kBlock), 0, st, g->off, n,
@@ -1471,7 +1549,7 @@ gpm_status c4_run(const gpm_graph *g, bool list, void *ws, uint64_t ws_bytes,
                                dim3(kBlock), 0, st,
                                g->off, g->adj, n, W.rank, W.roff, W.radj);
             GPM_LAUNCH_CHECK("k_rank_rows");
-            gpm_status src = sort_rows(W.roff, W.radj, n, W.sort_area, st);
+            gpm_status src = sort_rows(W.roff, W.radj, n, g->max_degree, W.sort_area, st);
             if (src) return src;
             if (cs) {
                 hipLaunchKernelGGL(k_rank_tsym, dim3(grid_for(n, kWPB, 16)), dim3(kBlock), 0, st,
@@ -1490,16 +1568,23 @@ gpm_status c4_run(const gpm_graph *g, bool list, void *ws, uint64_t ws_bytes,
                                W.radj, n, cparts, count_zpart(g), W.seg);
         GPM_LAUNCH_CHECK("k_c4_seg");
         const int narrow = narrow_counts(g) ? 1 : 0;
+        // the counter words of a task: all of them with several parts (and the
+        // medium apexes' hash), else one per counter of the graph's ranks.  (Held
+        // to 64 registers so that two workgroups share a CU, small graphs' time
+        // rose from 49 to 65 us on RMAT-12, the wedges in flight then stalling.)
+        const int32_t words = cparts > 1 ? kCountWords : std::min(kCountWords, (n >> narrow) + 8);
+        const size_t shmem = (size_t)words * 4;
+        const dim3 hgrid((unsigned)cu_count());
         if (cs) {
             Span sp("k_c4_heavy<sums>", st);
-            hipLaunchKernelGGL(k_c4r_heavy<true>, dim3((unsigned)cu_count()), dim3(kHeavyNT), 0,
+            hipLaunchKernelGGL(k_c4r_heavy<true>, hgrid, dim3(kHeavyNT), shmem,
                                st, W.roff, W.radj, W.nin, W.heavy, cnt_heavy, W.med, cnt_med, n,
-                               cparts, narrow, W.seg, W.ctl + 0, out128, W.rtsym, cs);
+                               cparts, narrow, words, W.seg, W.ctl + 0, out128, W.rtsym, cs);
         } else {
             Span sp("k_c4_heavy", st);
-            hipLaunchKernelGGL(k_c4r_heavy<false>, dim3((unsigned)cu_count()), dim3(kHeavyNT), 0,
+            hipLaunchKernelGGL(k_c4r_heavy<false>, hgrid, dim3(kHeavyNT), shmem,
                                st, W.roff, W.radj, W.nin, W.heavy, cnt_heavy, W.med, cnt_med, n,
-                               cparts, narrow, W.seg, W.ctl + 0, out128, nullptr, nullptr);
+                               cparts, narrow, words, W.seg, W.ctl + 0, out128, nullptr, nullptr);
         }
         GPM_LAUNCH_CHECK("k_c4_heavy");
         if (cs) {
@@ -1516,6 +1601,7 @@ gpm_status c4_run(const gpm_graph *g, bool list, void *ws, uint64_t ws_bytes,
         GPM_LAUNCH_CHECK("k_c4_light");
         return GPM_OK;
     }
+    GPM_HIP(zero_words(st, {{W.ctl, 16}, {W.slot, 4}, {W.big_ctr, 4}, {d_result, 6}}));
     hipLaunchKernelGGL(k_degrees, dim3(grid_for(n, 256, 8)), dim3(256), 0, st, g->off, n, W.deg);
     hipLaunchKernelGGL(k_c4_work, dim3(grid_for(n, kWPB, 16)), dim3(kBlock), 0, st, g->off,
                        g->adj, W.deg, n, W.cls);
@@ -1525,7 +1611,6 @@ gpm_status c4_run(const gpm_graph *g, bool list, void *ws, uint64_t ws_bytes,
     const bool fine = n <= kFineIds;
     const int32_t pz = fine ? kPartZFine : kPartZ, nparts = (n + pz - 1) / pz;
     Emitter em{W.slot, d_buf, d_buf ? cap : 0, 0, 0, 0};
-    GPM_HIP(fill_u32(W.big_ctr, 0, 4, st));
     {
         Span sp("k_c4_heavy_list", st);
         // tasks of at least this many pairs are shared out: 32,768 keep a

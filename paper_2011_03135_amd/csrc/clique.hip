@@ -1173,11 +1173,12 @@ static gpm_status tc_launch(const gpm_graph *g, CliqueWs &W, unsigned long long 
     return GPM_OK;
 }
 
+// Clears te (m words), *tri and the words of `also`, then counts.
 gpm_status triangle_arc_counts(const gpm_graph *g, void *ws, uint64_t ws_bytes, uint32_t *te,
-                               unsigned long long *tri, hipStream_t st) {
+                               unsigned long long *tri, hipStream_t st, WordRun also) {
     CliqueWs W = clique_layout(g, 3, false, ws);
     if (W.bytes > ws_bytes) return fail(GPM_OUT_OF_MEMORY, "workspace smaller than required");
-    GPM_HIP(zero_words(st, {{W.ctr, 16}, {W.ctl, 16}}));
+    GPM_HIP(zero_words(st, {{te, (uint64_t)g->m}, {tri, 2}, {W.ctr, 16}, {W.ctl, 16}, also}));
     return tc_launch<TC_ARCS>(g, W, tri, te, st);
 }
 

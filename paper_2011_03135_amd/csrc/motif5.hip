@@ -78,7 +78,7 @@ gpm_status clique_run(const gpm_graph *g, int32_t k, bool list, void *ws, uint64
                       unsigned long long *d_count, int32_t *d_buf, uint64_t cap,
                       unsigned long long *d_result, hipStream_t st);
 gpm_status triangle_arc_counts(const gpm_graph *g, void *ws, uint64_t ws_bytes, uint32_t *te,
-                               unsigned long long *tri, hipStream_t st);
+                               unsigned long long *tri, hipStream_t st, WordRun also);
 gpm_status c4_workspace_bytes(const gpm_graph *g, bool list, uint64_t *bytes);
 gpm_status c4_run(const gpm_graph *g, bool list, void *ws, uint64_t ws_bytes,
                   unsigned long long *out128, int32_t *d_buf, uint64_t cap,
@@ -911,11 +911,11 @@ gpm_status motif_formula_count(const gpm_graph *g, int32_t k, void *ws, uint64_t
         B.formula_of[kFormulaClass[F_K5E]] = -1;
         B.formula_of[kFormulaClass[F_WHEEL]] = -1;
     }
-    GPM_HIP(fill_u32(W.acc, 0, 2 * (uint64_t)A_WORDS, st));
-    GPM_HIP(fill_u32(W.t2, 0, 2 * ((uint64_t)n + 1), st));
-    if (m > 0) GPM_HIP(fill_u32(W.te, 0, (uint64_t)m, st));
-    // local counts: triangles per edge (and their total), per vertex
-    gpm_status rc = triangle_arc_counts(g, W.shared, W.shared_bytes, W.te, W.acc + A_TRI, st);
+    // local counts: triangles per edge (and their total), per vertex; the
+    // accumulators and t2 behind them are cleared with them
+    gpm_status rc = triangle_arc_counts(
+        g, W.shared, W.shared_bytes, W.te, W.acc + A_TRI, st,
+        {W.acc, 2 * ((uint64_t)(W.t2 - W.acc) + (uint64_t)n + 1)});
     if (rc) return rc;
     {
         Span sp("k_f5_local", st);

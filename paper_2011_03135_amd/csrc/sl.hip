@@ -21,7 +21,7 @@ namespace gpm {
 
 gpm_status clique_workspace_bytes(const gpm_graph *g, int32_t k, bool list, uint64_t *bytes);
 gpm_status triangle_arc_counts(const gpm_graph *g, void *ws, uint64_t ws_bytes, uint32_t *te,
-                               unsigned long long *tri, hipStream_t st);
+                               unsigned long long *tri, hipStream_t st, WordRun also);
 gpm_status c4_workspace_bytes(const gpm_graph *g, bool list, uint64_t *bytes);
 gpm_status c4_run(const gpm_graph *g, bool list, void *ws, uint64_t ws_bytes,
                   unsigned long long *out128, int32_t *d_buf, uint64_t cap,
@@ -263,10 +263,10 @@ DiamondWs diamond_layout(const gpm_graph *g, bool list, void *base) {
     DiamondWs W{};
     Carve c(base, ~0ull);
     const uint64_t m1 = (uint64_t)g->m + 1;
-    W.ctl = c.take<uint32_t>(16);
-    W.tri = c.take<unsigned long long>(2);
-    W.sum = c.take<unsigned long long>(2);
-    W.slot = c.take<unsigned long long>(2);
+    W.ctl = c.take<uint32_t>(32);   // then, in the same words, tri, sum and slot
+    W.tri = reinterpret_cast<unsigned long long *>(W.ctl + 16);
+    W.sum = W.tri + 2;
+    W.slot = W.tri + 4;
     W.te = c.take<uint32_t>(m1);
     if (list) {
         W.flag = c.take<int32_t>(m1);
@@ -296,12 +296,8 @@ gpm_status diamond_run(const gpm_graph *g, bool list, void *ws, uint64_t ws_byte
     DiamondWs W = diamond_layout(g, list, ws);
     if (W.bytes > ws_bytes) return fail(GPM_OUT_OF_MEMORY, "workspace smaller than required");
     const int64_t m = g->m;
-    GPM_HIP(fill_u32(W.ctl, 0, 16, st));
-    GPM_HIP(fill_u32(W.tri, 0, 4, st));
-    GPM_HIP(fill_u32(W.sum, 0, 4, st));
-    GPM_HIP(fill_u32(W.slot, 0, 4, st));
-    if (m > 0) GPM_HIP(fill_u32(W.te, 0, (uint64_t)m, st));
-    gpm_status rc = triangle_arc_counts(g, W.tc, W.tc_bytes, W.te, W.tri, st);
+    // with the cursor, the diamond sum and the slot counter
+    gpm_status rc = triangle_arc_counts(g, W.tc, W.tc_bytes, W.te, W.tri, st, {W.ctl, 32});
     if (rc) return rc;
     if (!list) {
         if (m > 0) {

@@ -71,12 +71,18 @@ hipError_t zero_words(hipStream_t s, std::initializer_list<WordRun> runs) {
 }
 
 // ------------------------------------------------------------------ scan --
-// Three phases over tiles of kTile = 256 threads x 16 items: per-tile sums,
-// one workgroup scanning the tile sums, then per-tile local scans plus the
-// tile's offset.
+// Up to kScanOne items: one workgroup, one launch (a launch costs 4.5 us in
+// a stream, as much as its pass over 16,384 items).  Above: tiles of kTile =
+// 256 threads x 16 items, per-tile sums, then per-tile local scans plus the
+// tile's offset, which every workgroup sums from the tiles before its own;
+// with more than kScanSelf tiles one workgroup scans the tile sums between
+// the two instead.
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kTile = kScanThreads * kScanItems;
+
+constexpr uint64_t kScanOne = 65536;
+constexpr uint64_t kScanSelf = 2048;
 
 uint64_t scan_tmp_words(uint64_t n) { return (n + kTile - 1) / kTile + 1; }
 
@@ -127,7 +133,9 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_tiles(int64_t *tile_sums,
     if (threadIdx.x == 0) tile_sums[ntiles] = carry;
 }
 
-template <class InT, class OutT>
+// SELF: tile_sums are the tiles' sums and the workgroup adds up those before
+// its own; else their exclusive scan, the total at [ntiles].
+template <class InT, class OutT, bool SELF>
 __global__ void __launch_bounds__(kScanThreads) k_scan_down(const InT *in, OutT *out,
                                                            uint64_t n, const int64_t *tile_sums,
                                                            uint64_t ntiles) {
@@ -138,6 +146,14 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_down(const InT *in, OutT 
         int j = i * kScanThreads + threadIdx.x;
         tile[j] = (base + j < n) ? in[base + j] : 0;
     }
+    int64_t before = 0;
+    if (SELF) {
+        int64_t mine = 0;
+        for (uint64_t t = threadIdx.x; t < blockIdx.x; t += kScanThreads) mine += tile_sums[t];
+        block_excl_scan(mine, sh, before);
+    } else {
+        before = tile_sums[blockIdx.x];
+    }
     __syncthreads();
     InT v[kScanItems];
     int64_t s = 0;
@@ -146,30 +162,70 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_down(const InT *in, OutT 
         s += v[i];
     }
     int64_t tot;
-    int64_t run = tile_sums[blockIdx.x] + block_excl_scan(s, sh, tot);
+    int64_t run = before + block_excl_scan(s, sh, tot);
     for (int i = 0; i < kScanItems; i++) {
         uint64_t idx = base + (uint64_t)threadIdx.x * kScanItems + i;
         if (idx < n) out[idx] = (OutT)run;
         run += v[i];
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = (OutT)tile_sums[ntiles];
+    if (blockIdx.x == ntiles - 1 && threadIdx.x == 0) out[n] = (OutT)(before + tot);
+}
+
+constexpr int kScanOneThreads = 1024;
+
+template <class InT, class OutT>
+__global__ void __launch_bounds__(kScanOneThreads) k_scan_one(const InT *in, OutT *out,
+                                                              uint64_t n) {
+    constexpr int PER = 16, NW = kScanOneThreads / 64;
+    __shared__ int64_t sh[NW];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    int64_t carry = 0;
+    for (uint64_t base = 0; base < n; base += (uint64_t)kScanOneThreads * PER) {
+        // PER consecutive items a thread: one lane scan per pass
+        const uint64_t i0 = base + (uint64_t)threadIdx.x * PER;
+        InT v[PER];
+#pragma unroll
+        for (int q = 0; q < PER; q++) v[q] = i0 + q < n ? in[i0 + q] : 0;
+        int64_t sum = 0;
+#pragma unroll
+        for (int q = 0; q < PER; q++) sum += v[q];
+        const int64_t inc = wave_incl_scan(sum);
+        __syncthreads();
+        if (lane == 63) sh[wid] = inc;
+        __syncthreads();
+        int64_t run = carry + inc - sum;
+#pragma unroll
+        for (int w = 0; w < NW; w++) {
+            run += w < wid ? sh[w] : 0;
+            carry += sh[w];
+        }
+#pragma unroll
+        for (int q = 0; q < PER; q++) {
+            if (i0 + q < n) out[i0 + q] = (OutT)run;
+            run += v[q];
+        }
+    }
+    if (threadIdx.x == 0) out[n] = (OutT)carry;
 }
 
 template <class InT, class OutT>
 static hipError_t scan_impl(const InT *in, OutT *out, uint64_t n, int64_t *tmp, hipStream_t s) {
-    uint64_t ntiles = (n + kTile - 1) / kTile;
-    if (ntiles == 0) {
-        // n == 0: out[0] = 0
-        hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kScanThreads), 0, s, tmp, (uint64_t)0);
-        hipLaunchKernelGGL((k_scan_down<InT, OutT>), dim3(1), dim3(kScanThreads), 0, s, in, out,
-                           (uint64_t)0, (const int64_t *)tmp, (uint64_t)0);
+    if (n <= kScanOne) {
+        hipLaunchKernelGGL((k_scan_one<InT, OutT>), dim3(1), dim3(kScanOneThreads), 0, s, in, out,
+                           n);
         return hipGetLastError();
     }
+    const uint64_t ntiles = (n + kTile - 1) / kTile;
     hipLaunchKernelGGL((k_scan_reduce<InT>), dim3((unsigned)ntiles), dim3(kScanThreads), 0, s, in,
                        n, tmp);
+    if (ntiles <= kScanSelf) {
+        hipLaunchKernelGGL((k_scan_down<InT, OutT, true>), dim3((unsigned)ntiles),
+                           dim3(kScanThreads), 0, s, in, out, n, (const int64_t *)tmp, ntiles);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kScanThreads), 0, s, tmp, ntiles);
-    hipLaunchKernelGGL((k_scan_down<InT, OutT>), dim3((unsigned)ntiles), dim3(kScanThreads), 0, s,
-                       in, out, n, (const int64_t *)tmp, ntiles);
+    hipLaunchKernelGGL((k_scan_down<InT, OutT, false>), dim3((unsigned)ntiles), dim3(kScanThreads),
+                       0, s, in, out, n, (const int64_t *)tmp, ntiles);
     return hipGetLastError();
 }
 
