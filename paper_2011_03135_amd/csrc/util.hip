@@ -81,7 +81,7 @@ constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kTile = kScanThreads * kScanItems;
 
-constexpr uint64_t kScanOne = 65536;
+constexpr uint64_t kScanOne = 16384;   // one pass of the one-launch scan
 constexpr uint64_t kScanSelf = 2048;
 
 uint64_t scan_tmp_words(uint64_t n) { return (n + kTile - 1) / kTile + 1; }
