@@ -10,9 +10,10 @@
 // Pipeline (one stream, no host round trip until the final size read-back):
 //   arcs into buckets of consecutive source ids (LDS histograms per tile)
 //   -> per bucket: row offsets and arcs into rows (LDS counters)
-//   -> per-row sort + unique (wave bitonic in registers for <= 64 entries,
-//      wave bitonic in LDS for <= 2048, workgroup bitmap for longer rows)
-//   -> scan unique counts -> compact rows -> count out-arcs -> scan -> fill.
+//   -> per-row sort + unique (16-lane groups up to 16 entries, a wave in
+//      registers up to 512 or 2048, a workgroup's bitmap for longer rows)
+//   -> scan unique counts -> rows and arcs cut into equal shares per wave
+//      -> compact rows and direct the arcs -> scan -> fill the DAG.
 #include "gpm_internal.h"
 
 #include <algorithm>
@@ -127,7 +128,7 @@ __global__ void __launch_bounds__(kScatterNT) k_bucket_scatter(const int32_t *__
                                                                const int32_t *__restrict__ v,
                                                                int64_t E, int32_t n, int32_t S,
                                                                int32_t nb, int32_t tile_edges,
-                                                               int32_t *bucket_cur, int32_t *bsrc,
+                                                               int32_t *bucket_cur, uint16_t *bsrc,
                                                                int32_t *bdst) {
     constexpr int PER = kMaxBuckets / kScatterNT;
     extern __shared__ int32_t sm[];
@@ -174,13 +175,9 @@ __global__ void __launch_bounds__(kScatterNT) k_bucket_scatter(const int32_t *__
         __syncthreads();
         const int32_t total = lpre[nb];
         for (int32_t i = tid; i < total; i += kScatterNT) {
-            int32_t lo = 0, hi = nb;   // last bucket with lpre <= i
-            while (hi - lo > 1) {
-                const int32_t mid = (lo + hi) >> 1;
-                if (lpre[mid] <= i) lo = mid; else hi = mid;
-            }
-            const int32_t g = gbase[lo] + (i - lpre[lo]);
-            bsrc[g] = ssrc[i];
+            const int32_t a = ssrc[i], b = a >> S;
+            const int32_t g = gbase[b] + (i - lpre[b]);
+            bsrc[g] = (uint16_t)(a - (b << S));
             bdst[g] = sdst[i];
         }
         __syncthreads();
@@ -192,14 +189,19 @@ size_t scatter_lds_bytes(int32_t nb, int32_t te) {
     return ((size_t)3 * nb + 1 + kScatterNT / kWave + 4 * (size_t)te) * 4;
 }
 
-// One block per bucket: row offsets of its 2^S sources and their arcs.
+// One block per bucket: row offsets of its 2^S sources and their arcs (bsrc
+// holds a source's place in its bucket).  kRowsUnroll arcs in flight per
+// thread in both passes: each is a load, an LDS counter and, in the second, a
+// store that depends on the counter's value.
+constexpr int kRowsUnroll = 8;
+
 __global__ void __launch_bounds__(kBucketNT) k_bucket_rows(const int32_t *__restrict__ bucket_off,
-                                                           const int32_t *__restrict__ bsrc,
+                                                           const uint16_t *__restrict__ bsrc,
                                                            const int32_t *__restrict__ bdst,
                                                            int32_t n, int32_t S, int32_t nb,
                                                            int32_t *raw_off, int32_t *raw_adj) {
     constexpr int PER = kMaxBucketIds / kBucketNT;
-    __shared__ int32_t cnt[kMaxBucketIds + 1];
+    extern __shared__ int32_t cnt[];   // 2^S + 1
     __shared__ int32_t s_sum[kBucketNT / kWave];
     const int32_t ids = 1 << S;
     for (int32_t b = blockIdx.x; b < nb; b += gridDim.x) {
@@ -207,7 +209,17 @@ __global__ void __launch_bounds__(kBucketNT) k_bucket_rows(const int32_t *__rest
         const int32_t a0 = bucket_off[b], a1 = bucket_off[b + 1];
         for (int32_t i = threadIdx.x; i < ids; i += kBucketNT) cnt[i] = 0;
         __syncthreads();
-        for (int32_t i = a0 + threadIdx.x; i < a1; i += kBucketNT) atomicAdd(&cnt[bsrc[i] - base], 1);
+        for (int32_t i0 = a0 + threadIdx.x; i0 < a1; i0 += kBucketNT * kRowsUnroll) {
+            int32_t r[kRowsUnroll];
+#pragma unroll
+            for (int q = 0; q < kRowsUnroll; q++) {
+                const int32_t i = i0 + q * kBucketNT;
+                r[q] = i < a1 ? (int32_t)bsrc[i] : -1;
+            }
+#pragma unroll
+            for (int q = 0; q < kRowsUnroll; q++)
+                if (r[q] >= 0) atomicAdd(&cnt[r[q]], 1);
+        }
         __syncthreads();
         int32_t val[PER];
 #pragma unroll
@@ -223,9 +235,17 @@ __global__ void __launch_bounds__(kBucketNT) k_bucket_rows(const int32_t *__rest
             if (vtx < n) raw_off[vtx] = a0 + cnt[i];
         }
         __syncthreads();
-        for (int32_t i = a0 + threadIdx.x; i < a1; i += kBucketNT) {
-            const int32_t p = atomicAdd(&cnt[bsrc[i] - base], 1);
-            raw_adj[a0 + p] = bdst[i];
+        for (int32_t i0 = a0 + threadIdx.x; i0 < a1; i0 += kBucketNT * kRowsUnroll) {
+            int32_t r[kRowsUnroll], w[kRowsUnroll];
+#pragma unroll
+            for (int q = 0; q < kRowsUnroll; q++) {
+                const int32_t i = i0 + q * kBucketNT;
+                r[q] = i < a1 ? (int32_t)bsrc[i] : -1;
+                w[q] = i < a1 ? bdst[i] : 0;
+            }
+#pragma unroll
+            for (int q = 0; q < kRowsUnroll; q++)
+                if (r[q] >= 0) raw_adj[a0 + atomicAdd(&cnt[r[q]], 1)] = w[q];
         }
         __syncthreads();
     }
@@ -253,7 +273,12 @@ __device__ __forceinline__ int32_t group_bitonic_sort(int32_t x) {
 
 constexpr int kSmallRow = 16;   // rows sorted by a 16-lane group, 4 per wave
 constexpr int kScanRow = 512;   // rows up to this length sort in registers within a row scan
-constexpr int kRegRow = 2048;   // rows up to this length sort in registers, a wave each
+constexpr int kRegRow = 2048;   // rows up to this length sort in registers, a wave each,
+constexpr int32_t kBitmapIds = 1 << 17;   // on graphs of more ids than this: below, a bitmap
+                                          // over the ids beats them from kScanRow on (16 or
+                                          // 32 registers a lane: 36 us for RMAT-12's few rows)
+
+int32_t reg_row(int32_t n) { return n > kBitmapIds ? kRegRow : kScanRow; }
 
 // Sorts + uniques one row of L <= 64 R entries in place with one wave, all in
 // registers: entry i sits in lane i % 64 of x[i / 64], so bitonic partners
@@ -311,13 +336,14 @@ __device__ int32_t wave_sort_row_regs(int32_t *r, int32_t L) {
 
 // Short rows: each 16-lane group sorts + uniques one row of at most 16
 // entries in place (4 consecutive rows per wave).  Rows beyond kScanRow go
-// to lists (up to kRegRow the list of the wave-per-row register sort, the
+// to lists (up to reg_max the list of the wave-per-row register sort, the
 // bitmap sorter's beyond); the rest are left to k_sort_rows' row scan.  Most
 // rows of power-law graphs are short.
 __global__ void __launch_bounds__(kBlock) k_sort_small_rows(const int32_t *__restrict__ raw_off,
                                                             int32_t *raw_adj, int32_t n,
-                                                            int32_t *ucnt, int32_t *med_list,
-                                                            int32_t *big_list, uint32_t *flags) {
+                                                            int32_t reg_max, int32_t *ucnt,
+                                                            int32_t *med_list, int32_t *big_list,
+                                                            uint32_t *flags) {
     const int lane = lane_id(), gl = lane & (kSmallRow - 1), grp = lane / kSmallRow;
     const int64_t wave0 = (int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave;
     const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
@@ -338,7 +364,7 @@ __global__ void __launch_bounds__(kBlock) k_sort_small_rows(const int32_t *__res
         if (keep) r[__popc(gmask & ((1u << gl) - 1u))] = x;
         if (live && gl == 0) {
             if (small) ucnt[row] = __popc(gmask);
-            else if (L > kRegRow) big_list[atomicAdd(&flags[F_BIG_COUNT], 1u)] = (int32_t)row;
+            else if (L > reg_max) big_list[atomicAdd(&flags[F_BIG_COUNT], 1u)] = (int32_t)row;
             else if (L > kScanRow) med_list[atomicAdd(&flags[F_MED_COUNT], 1u)] = (int32_t)row;
         }
     }
@@ -449,8 +475,10 @@ __global__ void __launch_bounds__(kBlock) k_sort_big_rows(const int32_t *__restr
     }
 }
 
-// The same with the bitmap in LDS (n <= kLdsBitmapIds): one workgroup of
-// kBigNT threads per CU; clearing and scanning the bitmap stay on chip.
+// The same with the bitmap in LDS (n <= kLdsBitmapIds), kBigNT threads.  Each
+// wave owns a run of the bitmap's words: it counts its bits, the waves' counts
+// are added up behind one barrier, and it writes its entries from there,
+// clearing the words for the next row on the way.
 constexpr int kBigNT = 1024;
 constexpr int64_t kLdsBitmapIds = 150 * 1024 * 8;   // 150 KiB of bits
 
@@ -460,203 +488,284 @@ __global__ void __launch_bounds__(kBigNT) k_sort_big_rows_lds(const int32_t *__r
                                                               const uint32_t *flags,
                                                               int32_t words) {
     extern __shared__ uint32_t bm[];
-    __shared__ int32_t sh[kBigNT / kWave];
     constexpr int NW = kBigNT / kWave;
+    __shared__ int32_t sh[NW];
     const int tid = threadIdx.x, lanew = tid & 63, wid = tid >> 6;
     const uint32_t nbig = flags[F_BIG_COUNT];
+    const int32_t per = ((words + NW - 1) / NW + kWave - 1) / kWave * kWave;
+    const int32_t w0 = min(words, wid * per), w1 = min(words, w0 + per);
+    for (int32_t w = tid; w < words; w += kBigNT) bm[w] = 0u;
     for (uint32_t b = blockIdx.x; b < nbig; b += gridDim.x) {
         const int32_t row = big_list[b];
         const int32_t s = raw_off[row];
         const int32_t L = raw_off[row + 1] - s;
         int32_t *r = raw_adj + s;
-        for (int32_t w = tid; w < words; w += kBigNT) bm[w] = 0u;
         __syncthreads();
         for (int32_t i = tid; i < L; i += kBigNT) {
             const uint32_t x = (uint32_t)r[i];
             atomicOr(&bm[x >> 5], 1u << (x & 31));
         }
         __syncthreads();
-        int32_t running = 0;
-        for (int32_t w0 = 0; w0 < words; w0 += kBigNT) {
-            const int32_t w = w0 + tid;
-            uint32_t word = w < words ? bm[w] : 0u;
+        int32_t mine = 0;
+        for (int32_t w = w0 + lanew; w < w1; w += kWave) mine += __popc(bm[w]);
+        mine = wave_sum(mine);
+        if (lanew == 0) sh[wid] = mine;
+        __syncthreads();
+        int32_t pos = 0, total = 0;
+#pragma unroll
+        for (int q = 0; q < NW; q++) {
+            pos += q < wid ? sh[q] : 0;
+            total += sh[q];
+        }
+        for (int32_t wb = w0; wb < w1; wb += kWave) {
+            const int32_t w = wb + lanew;
+            uint32_t word = w < w1 ? bm[w] : 0u;
+            if (!__any(word != 0u)) continue;
+            if (word) bm[w] = 0u;
             const int32_t c = __popc(word);
             const int32_t inc = wave_incl_scan(c);
-            if (lanew == 63) sh[wid] = inc;
-            __syncthreads();
-            int32_t before = 0, total = 0;
-#pragma unroll
-            for (int q = 0; q < NW; q++) {
-                before += q < wid ? sh[q] : 0;
-                total += sh[q];
-            }
-            int32_t pos = running + before + inc - c;
+            int32_t p = pos + inc - c;
             while (word) {
                 const int bit = __builtin_ctz(word);
                 word &= word - 1;
-                r[pos++] = w * 32 + bit;
+                r[p++] = w * 32 + bit;
             }
-            running += total;
-            __syncthreads();
+            pos += __shfl(inc, 63, 64);
         }
-        if (tid == 0) ucnt[row] = running;
-        __syncthreads();
+        if (tid == 0) ucnt[row] = total;
     }
 }
 
-// Copies the unique rows into the final CSR and counts each vertex's arcs
-// in the degree order (degrees are the unique counts); keep[i] records
-// whether arc i points up in that order, so the fill does not look the
-// degrees up again.
+// ------------------------------------------- equal shares of rows and arcs --
+// The final rows are walked in shares of kShare items, an item being a row's
+// start or one of its arcs: row r's start is item off[r] + r, its arcs follow
+// it, and row n's start is the last item.  A wave takes a share, so neither a
+// hub's row (67,751 arcs on RMAT-20: a chain of 1,059 dependent steps when one
+// wave took it, 0.8 of the 0.82 ms of the compaction) nor a run of empty rows
+// makes a wave the last to finish.
+constexpr int kShare = 1024;
+
+// start[c]: the first row whose start lies in or after share c.
+__global__ void __launch_bounds__(kBlock) k_shares(const int32_t *__restrict__ off, int32_t n,
+                                                   int32_t nshares, int32_t *start) {
+    const int32_t c = blockIdx.x * kBlock + threadIdx.x;
+    if (c > nshares) return;
+    const int64_t d = (int64_t)c * kShare;
+    int32_t lo = 0, hi = n + 1;
+    while (lo < hi) {
+        const int32_t mid = lo + (hi - lo) / 2;
+        if ((int64_t)off[mid] + mid < d) lo = mid + 1; else hi = mid;
+    }
+    start[c] = lo;
+}
+
+// A share's rows [r0, r1) and arcs [a0, a1), and the row of each arc: at most
+// kShare marks in the wave's LDS, row - r0 + 1 at the first arc of each
+// non-empty row.
+struct Share {
+    int32_t r0, r1, a0, a1;
+};
+
+__device__ __forceinline__ Share open_share(const int32_t *__restrict__ off, int32_t n, int32_t c,
+                                            const int32_t *__restrict__ start, int32_t *mark) {
+    const int lane = lane_id();
+    Share s;
+    s.r0 = __builtin_amdgcn_readfirstlane(start[c]);
+    s.r1 = __builtin_amdgcn_readfirstlane(start[c + 1]);
+    const int64_t d0 = (int64_t)c * kShare, last = (int64_t)off[n] + n + 1;
+    s.a0 = (int32_t)(min<int64_t>(d0, last) - s.r0);
+    s.a1 = (int32_t)(min<int64_t>(d0 + kShare, last) - s.r1);
+    for (int32_t i = lane; i < s.a1 - s.a0; i += kWave) mark[i] = 0;
+    wave_sync();
+    for (int32_t r = s.r0 + lane; r < min(s.r1, n); r += kWave) {
+        const int32_t o = off[r];
+        if (off[r + 1] > o && o < s.a1) mark[o - s.a0] = r - s.r0 + 1;
+    }
+    wave_sync();
+    return s;
+}
+
+// Row of the calling lane's arc in a tile of 64, from its mark; carry: the
+// row before the tile's first arc, then the tile's last row.
+__device__ __forceinline__ int32_t tile_row(int32_t m, int32_t r0, int32_t &carry) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int32_t y = __shfl_up(m, o, kWave);
+        if (lane >= o && y > m) m = y;
+    }
+    const int32_t row = m ? r0 + m - 1 : carry;
+    carry = __builtin_amdgcn_readlane(row, kWave - 1);
+    return row;
+}
+
+constexpr int kShareUnroll = 4;   // tiles in flight
+
+// Copies the unique rows into the final CSR (COPY; else adj already holds
+// them; deg: the degrees, null without COPY) and directs every arc in the
+// degree order: keep[i] says whether arc i points up, kept[c] counts them per
+// share.  Bound by the gather of each arc's other degree.
+template <bool COPY>
 __global__ void __launch_bounds__(kBlock) k_compact_rows(const int32_t *__restrict__ raw_off,
                                                          const int32_t *__restrict__ raw_adj,
                                                          const int32_t *__restrict__ off,
                                                          const int32_t *__restrict__ deg,
-                                                         int32_t *adj, int32_t n,
-                                                         int32_t *outcnt, uint8_t *keep,
-                                                         uint32_t *flags) {
-    const int lane = lane_id(), gl = lane & (kSmallRow - 1), grp = lane / kSmallRow;
-    const int64_t wave0 = (int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave;
-    const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
-    constexpr int kRows = kWave / kSmallRow;
-    int32_t maxd = 0, big16 = 0;
-    // 4 rows per wave: rows of <= 16 entries by a 16-lane group each, longer
-    // ones by the whole wave after them
-    for (int64_t r0 = wave0 * kRows; r0 < n; r0 += nwaves * kRows) {
-        const int64_t row = r0 + grp;
-        const bool live = row < n;
-        const int32_t u = (int32_t)row;
-        const int32_t src = live ? raw_off[row] : 0, dst = live ? off[row] : 0;
-        const int32_t L = live ? off[row + 1] - dst : 0;
-        maxd = L > maxd ? L : maxd;
-        big16 += (gl == 0 && L > 65535) ? 1 : 0;
-        const bool small = L <= kSmallRow;
-        int32_t c = 0;
-        if (small && gl < L) {
-            const int32_t v = raw_adj[src + gl];
-            adj[dst + gl] = v;
-            c = rank_less(L, u, deg[v], v) ? 1 : 0;
-            keep[dst + gl] = (uint8_t)c;
-        }
+                                                         int32_t *adj, int32_t n, int32_t nshares,
+                                                         const int32_t *__restrict__ start,
+                                                         uint8_t *keep, int32_t *kept) {
+    __shared__ int32_t s_mark[kWavesPerBlock][kShare];
+    const int lane = lane_id(), wid = threadIdx.x / kWave;
+    int32_t *mark = s_mark[wid];
+    for (int32_t c = blockIdx.x * kWavesPerBlock + wid; c < nshares;
+         c += gridDim.x * kWavesPerBlock) {
+        const Share s = open_share(off, n, c, start, mark);
+        int32_t carry = s.r0 - 1, sum = 0;
+        for (int32_t t0 = s.a0; t0 < s.a1; t0 += kWave * kShareUnroll) {
+            int32_t row[kShareUnroll], v[kShareUnroll], du[kShareUnroll], dv[kShareUnroll];
 #pragma unroll
-        for (int o = kSmallRow / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
-        if (live && small && gl == 0) outcnt[u] = c;
-        uint64_t longm = __ballot(live && !small && gl == 0);
-        while (longm) {
-            const int g = __builtin_ctzll(longm) / kSmallRow;
-            longm &= longm - 1ull;
-            const int32_t w = (int32_t)(r0 + g);
-            const int32_t ws = raw_off[w], wd = off[w], wl = off[w + 1] - wd;
-            int32_t cw = 0;
-            for (int32_t i = lane; i < wl; i += kWave) {
-                const int32_t v = raw_adj[ws + i];
-                adj[wd + i] = v;
-                const int32_t up = rank_less(wl, w, deg[v], v) ? 1 : 0;
-                keep[wd + i] = (uint8_t)up;
-                cw += up;
+            for (int q = 0; q < kShareUnroll; q++) {
+                const int32_t i = t0 + q * kWave + lane;
+                row[q] = tile_row(i < s.a1 ? mark[i - s.a0] : 0, s.r0, carry);
             }
-            cw = wave_sum(cw);
-            if (lane == 0) outcnt[w] = cw;
+#pragma unroll
+            for (int q = 0; q < kShareUnroll; q++) {
+                const int32_t i = t0 + q * kWave + lane;
+                v[q] = 0;
+                du[q] = 0;
+                if (i < s.a1) {
+                    const int32_t o = off[row[q]];
+                    du[q] = off[row[q] + 1] - o;
+                    v[q] = COPY ? raw_adj[raw_off[row[q]] + (i - o)] : adj[i];
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < kShareUnroll; q++)
+                dv[q] = COPY ? deg[v[q]] : off[v[q] + 1] - off[v[q]];
+#pragma unroll
+            for (int q = 0; q < kShareUnroll; q++) {
+                const int32_t i = t0 + q * kWave + lane;
+                const bool live = i < s.a1;
+                const bool up = live && rank_less(du[q], row[q], dv[q], v[q]);
+                if (live) {
+                    if (COPY) adj[i] = v[q];
+                    keep[i] = up ? 1 : 0;
+                }
+                sum += __popcll(__ballot(up));
+            }
         }
-    }
-    maxd = wave_max(maxd);
-    if (lane == 0 && maxd > 0) atomicMax(&flags[F_MAX_DEG], (uint32_t)maxd);
-    big16 = wave_sum(big16);
-    if (lane == 0 && big16 > 0) atomicAdd(&flags[F_DEG16], (uint32_t)big16);
-}
-
-__global__ void __launch_bounds__(kBlock) k_orient_count(const int32_t *__restrict__ off,
-                                                         const int32_t *__restrict__ adj,
-                                                         int32_t n, int32_t *outcnt,
-                                                         uint8_t *keep) {
-    const int lane = lane_id();
-    const int64_t wave0 = (int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave;
-    const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
-    for (int64_t row = wave0; row < n; row += nwaves) {
-        const int32_t u = (int32_t)row;
-        const int32_t s = off[u], du = off[u + 1] - s;
-        int32_t c = 0;
-        for (int32_t i = lane; i < du; i += kWave) {
-            int32_t v = adj[s + i];
-            int32_t dv = off[v + 1] - off[v];
-            const int32_t up = rank_less(du, u, dv, v) ? 1 : 0;
-            keep[s + i] = (uint8_t)up;
-            c += up;
-        }
-        c = wave_sum(c);
-        if (lane == 0) outcnt[u] = c;
+        if (lane == 0) kept[c] = sum;
+        wave_sync();
     }
 }
 
+// The DAG from the directed arcs: base[c] is the first of share c's out-arcs
+// (exclusive prefix of kept).
 __global__ void __launch_bounds__(kBlock) k_orient_fill(const int32_t *__restrict__ off,
                                                         const int32_t *__restrict__ adj,
-                                                        const uint8_t *__restrict__ up,
-                                                        const int32_t *__restrict__ dag_off,
-                                                        int32_t n, int64_t cap, int32_t *dag_adj,
-                                                        int32_t *dag_src, uint32_t *flags) {
-    const int lane = lane_id(), gl = lane & (kSmallRow - 1), grp = lane / kSmallRow;
-    const int64_t wave0 = (int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave;
-    const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
-    constexpr int kRows = kWave / kSmallRow;
-    int32_t maxo = 0;
-    // 4 rows per wave: rows of <= 16 entries by a 16-lane group each, longer
-    // ones by the whole wave after them
-    for (int64_t r0 = wave0 * kRows; r0 < n; r0 += nwaves * kRows) {
-        const int64_t row = r0 + grp;
-        const bool live = row < n;
-        const int32_t su = live ? off[row] : 0, dsu = live ? off[row + 1] - su : 0;
-        const bool small = dsu <= kSmallRow;
-        int32_t v = 0;
-        bool keep = false;
-        if (small && gl < dsu) {
-            v = adj[su + gl];
-            keep = up[su + gl] != 0;
-        }
-        const uint32_t gmask =
-            (uint32_t)(__ballot(keep) >> (grp * kSmallRow)) & ((1u << kSmallRow) - 1u);
-        if (keep) {
-            const int32_t p = dag_off[row] + __popc(gmask & ((1u << gl) - 1u));
-            if (p < cap) {
-                dag_adj[p] = v;
-                dag_src[p] = (int32_t)row;
-            } else {
-                atomicOr(&flags[F_ERR], 4u);   // more arcs than the storage holds
+                                                        const uint8_t *__restrict__ keep,
+                                                        const int32_t *__restrict__ base,
+                                                        int32_t n, int32_t nshares,
+                                                        const int32_t *__restrict__ start,
+                                                        int64_t cap, int32_t *dag_off,
+                                                        int32_t *dag_adj, int32_t *dag_src,
+                                                        uint32_t *flags) {
+    __shared__ int32_t s_mark[kWavesPerBlock][kShare];
+    __shared__ uint64_t s_mask[kWavesPerBlock][kShare / kWave + 1];
+    __shared__ int32_t s_run[kWavesPerBlock][kShare / kWave + 1];
+    const int lane = lane_id(), wid = threadIdx.x / kWave;
+    int32_t *mark = s_mark[wid], *run_at = s_run[wid];
+    uint64_t *mask_at = s_mask[wid];
+    for (int32_t c = blockIdx.x * kWavesPerBlock + wid; c < nshares;
+         c += gridDim.x * kWavesPerBlock) {
+        const Share s = open_share(off, n, c, start, mark);
+        int32_t carry = s.r0 - 1, run = base[c];
+        for (int32_t t0 = s.a0; t0 < s.a1; t0 += kWave * kShareUnroll) {
+            int32_t row[kShareUnroll], v[kShareUnroll];
+            bool up[kShareUnroll];
+#pragma unroll
+            for (int q = 0; q < kShareUnroll; q++) {
+                const int32_t i = t0 + q * kWave + lane;
+                up[q] = i < s.a1 && keep[i] != 0;
+                v[q] = i < s.a1 ? adj[i] : 0;
             }
-        }
-        maxo = max(maxo, __popc(gmask));
-        uint64_t longm = __ballot(live && !small && gl == 0);
-        while (longm) {
-            const int32_t u = (int32_t)(r0 + __builtin_ctzll(longm) / kSmallRow);
-            longm &= longm - 1ull;
-            const int32_t s = off[u], du = off[u + 1] - s;
-            int32_t base = dag_off[u];
-            for (int32_t i0 = 0; i0 < du; i0 += kWave) {
-                int32_t i = i0 + lane;
-                int32_t v = i < du ? adj[s + i] : 0;
-                bool keep = false;
-                if (i < du) keep = up[s + i] != 0;
-                uint64_t mask = __ballot(keep);
-                if (keep) {
-                    int32_t p = base + lanes_below(mask);
+#pragma unroll
+            for (int q = 0; q < kShareUnroll; q++) {
+                const int32_t i = t0 + q * kWave + lane;
+                row[q] = tile_row(i < s.a1 ? mark[i - s.a0] : 0, s.r0, carry);
+            }
+#pragma unroll
+            for (int q = 0; q < kShareUnroll; q++) {
+                const uint64_t m = __ballot(up[q]);
+                const int32_t tile = (t0 - s.a0) / kWave + q;
+                if (lane == 0 && tile <= kShare / kWave) {
+                    mask_at[tile] = m;
+                    run_at[tile] = run;
+                }
+                if (up[q]) {
+                    const int32_t p = run + lanes_below(m);
                     if (p < cap) {
-                        dag_adj[p] = v;
-                        dag_src[p] = u;
+                        dag_adj[p] = v[q];
+                        dag_src[p] = row[q];
                     } else {
                         atomicOr(&flags[F_ERR], 4u);   // more arcs than the storage holds
                     }
                 }
-                base += __popcll(mask);
+                run += __popcll(m);
             }
-            int32_t d = base - dag_off[u];
-            maxo = d > maxo ? d : maxo;
         }
+        wave_sync();
+        // the share's rows: the out-arcs before their first arc
+        for (int32_t r = s.r0 + lane; r < min(s.r1, n + 1); r += kWave) {
+            const int32_t i = off[r] - s.a0;   // in [0, a1 - a0]
+            dag_off[r] = i < s.a1 - s.a0
+                             ? run_at[i / kWave] +
+                                   __popcll(mask_at[i / kWave] & ((1ull << (i % kWave)) - 1ull))
+                             : run;
+        }
+        wave_sync();
     }
-    maxo = wave_max(maxo);
-    if (lane == 0 && maxo > 0) atomicMax(&flags[F_MAX_OUT], (uint32_t)maxo);
 }
 
-// Orientation key of the degree order, key[v] = deg(v): the local-graph
-// kernels rank each root's out-neighbours by (key, id), as the DAG does.
+// The degree order's key (key[v] = deg(v): the local-graph kernels rank each
+// root's out-neighbours by (key, id), as the DAG does) and the graph's
+// largest degree, largest out-degree and number of degrees above 65535.
+__global__ void __launch_bounds__(kBlock) k_vertex_meta(const int32_t *__restrict__ off,
+                                                        const int32_t *__restrict__ dag_off,
+                                                        int32_t n, int32_t *key,
+                                                        uint32_t *flags) {
+    __shared__ int32_t sh[kWavesPerBlock][3];
+    int32_t maxd = 0, maxo = 0, big16 = 0;
+    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
+         v += (int64_t)gridDim.x * kBlock) {
+        const int32_t d = off[v + 1] - off[v];
+        key[v] = d;
+        maxd = max(maxd, d);
+        maxo = max(maxo, dag_off[v + 1] - dag_off[v]);
+        big16 += d > 65535;
+    }
+    maxd = wave_max(maxd);
+    maxo = wave_max(maxo);
+    big16 = wave_sum(big16);
+    if (lane_id() == 0) {
+        int32_t *o = sh[threadIdx.x / kWave];
+        o[0] = maxd;
+        o[1] = maxo;
+        o[2] = big16;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < kWavesPerBlock; q++) {
+            maxd = max(maxd, sh[q][0]);
+            maxo = max(maxo, sh[q][1]);
+            big16 += sh[q][2];
+        }
+        if (maxd > 0) atomicMax(&flags[F_MAX_DEG], (uint32_t)maxd);
+        if (maxo > 0) atomicMax(&flags[F_MAX_OUT], (uint32_t)maxo);
+        if (big16 > 0) atomicAdd(&flags[F_DEG16], (uint32_t)big16);
+    }
+}
+
+// The degree order's key alone.
 __global__ void k_degree_key(const int32_t *__restrict__ off, int32_t n, int32_t *key) {
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n;
          v += (int64_t)gridDim.x * blockDim.x)
@@ -679,7 +788,7 @@ __global__ void k_meta(const int32_t *off, const int32_t *dag_off, int32_t n,
 // Checks of a caller's CSR (one wave per row).  Always: offsets ascending
 // and within [0, nnz], ids in [0, n); with FULL also strictly ascending rows,
 // no self-loop, and every arc (u, w) matched by (w, u).  Any failure sets
-// F_ERR; the largest degree goes to F_MAX_DEG.
+// F_ERR.
 template <bool FULL>
 __global__ void __launch_bounds__(kBlock) k_check_csr(const int32_t *__restrict__ off,
                                                       const int32_t *__restrict__ adj, int32_t n,
@@ -689,7 +798,6 @@ __global__ void __launch_bounds__(kBlock) k_check_csr(const int32_t *__restrict_
     const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
     if (blockIdx.x == 0 && threadIdx.x == 0 && (off[0] != 0 || (int64_t)off[n] != nnz))
         atomicOr(&flags[F_ERR], 2u);
-    int32_t maxd = 0, big16 = 0;
     for (int64_t row = wave0; row < n; row += nwaves) {
         const int32_t u = (int32_t)row;
         const int32_t s = off[u], e = off[u + 1];
@@ -697,8 +805,6 @@ __global__ void __launch_bounds__(kBlock) k_check_csr(const int32_t *__restrict_
             if (lane == 0) atomicOr(&flags[F_ERR], 2u);
             continue;
         }
-        maxd = max(maxd, e - s);
-        big16 += (lane == 0 && e - s > 65535) ? 1 : 0;
         bool bad = false;
         for (int32_t i = s + lane; i < e; i += kWave) {
             const int32_t w = adj[i];
@@ -725,10 +831,6 @@ __global__ void __launch_bounds__(kBlock) k_check_csr(const int32_t *__restrict_
         }
         if (__any(bad) && lane == 0) atomicOr(&flags[F_ERR], 2u);
     }
-    maxd = wave_max(maxd);
-    if (lane == 0 && maxd > 0) atomicMax(&flags[F_MAX_DEG], (uint32_t)maxd);
-    big16 = wave_sum(big16);
-    if (lane == 0 && big16 > 0) atomicAdd(&flags[F_DEG16], (uint32_t)big16);
 }
 
 struct BuildLayout {
@@ -737,10 +839,12 @@ struct BuildLayout {
     int64_t *meta;
     int32_t *okey;
     // scratch
-    int32_t *cnt, *raw_off, *raw_adj, *ucnt, *outcnt, *big_list, *med_list;
+    int32_t *cnt, *raw_off, *raw_adj, *ucnt, *big_list, *med_list;
     uint8_t *keep;                                  // per final arc: points up in the order
+    int32_t *share, *kept;                          // per share: first row, arcs pointing up
     int32_t S, nb;                                  // buckets of 2^S source ids (S = 0: none)
-    int32_t *bucket_cnt, *bucket_off, *bucket_cur, *bsrc, *bdst;
+    int32_t *bucket_cnt, *bucket_off, *bucket_cur, *bdst;
+    uint16_t *bsrc;                                 // a source's place in its bucket
     int64_t *scan_tmp;
     uint32_t *flags, *bitmaps;
     int64_t words;
@@ -748,13 +852,18 @@ struct BuildLayout {
     uint64_t graph_bytes, scratch_bytes;
 };
 
-// Bucket shift for n vertices: the smallest S >= 10 with at most
+// Shares of a graph of n vertices and at most `arcs` arcs.
+int64_t share_count(int32_t n, int64_t arcs) { return ((int64_t)n + 1 + arcs + kShare - 1) / kShare; }
+
+// Bucket shift for n vertices: the smallest S >= 6 with at most
 // kTargetBuckets buckets of 2^S ids, or 0 when 2^S would exceed
 // kMaxBucketIds.  About 1024 buckets (4 per CU at 256 CUs) keep a bucket
-// that holds a hub's arcs from dominating the per-bucket pass.
+// that holds a hub's arcs from dominating the per-bucket pass; from 64 ids on,
+// a small graph's buckets still spread over the chip (with 1,024 ids, 4,096
+// vertices were four workgroups' work).
 constexpr int kTargetBuckets = 1024;
 int32_t bucket_shift(int32_t n) {
-    int32_t S = 10;
+    int32_t S = 6;
     while (((int64_t)n + (1ll << S) - 1) >> S > kTargetBuckets) S++;
     return (1 << S) <= kMaxBucketIds ? S : 0;
 }
@@ -775,11 +884,13 @@ BuildLayout layout(int32_t n, int64_t E, void *gmem, void *smem) {
     L.raw_off = s.take<int32_t>((uint64_t)n + 1);
     L.raw_adj = s.take<int32_t>((uint64_t)(2 * E));
     L.ucnt = s.take<int32_t>((uint64_t)n + 1);
-    L.outcnt = s.take<int32_t>((uint64_t)n + 1);
     L.big_list = s.take<int32_t>((uint64_t)n + 1);
     L.med_list = s.take<int32_t>((uint64_t)n + 1);
     L.keep = s.take<uint8_t>((uint64_t)(2 * E));
-    L.scan_tmp = s.take<int64_t>(scan_tmp_words((uint64_t)n + 1));
+    L.share = s.take<int32_t>((uint64_t)share_count(n, 2 * E) + 1);
+    L.kept = s.take<int32_t>((uint64_t)share_count(n, 2 * E) + 1);
+    L.scan_tmp = s.take<int64_t>(scan_tmp_words(
+        std::max<uint64_t>((uint64_t)n, (uint64_t)share_count(n, 2 * E)) + 1));
     L.flags = s.take<uint32_t>(F_WORDS);
     L.S = bucket_shift(n);
     if (L.S > 0) {
@@ -787,7 +898,7 @@ BuildLayout layout(int32_t n, int64_t E, void *gmem, void *smem) {
         L.bucket_cnt = s.take<int32_t>((uint64_t)L.nb + 1);
         L.bucket_off = s.take<int32_t>((uint64_t)L.nb + 1);
         L.bucket_cur = s.take<int32_t>((uint64_t)L.nb + 1);
-        L.bsrc = s.take<int32_t>((uint64_t)(2 * E));
+        L.bsrc = s.take<uint16_t>((uint64_t)(2 * E));
         L.bdst = s.take<int32_t>((uint64_t)(2 * E));
     }
     L.words = ((int64_t)n + 31) / 32;
@@ -823,6 +934,32 @@ hipError_t degree_key(const int32_t *off, int32_t n, int32_t *key, hipStream_t s
 
 static gpm_status enqueue_build(int32_t n, const int32_t *d_u, const int32_t *d_v, int64_t E,
                                 const BuildLayout &L, hipStream_t st);
+
+static dim3 share_grid(int32_t nshares) {
+    return dim3((unsigned)std::min<int64_t>(((int64_t)nshares + kWavesPerBlock - 1) / kWavesPerBlock,
+                                            (int64_t)cu_count() * 64));
+}
+
+// The DAG, the orientation key and the graph's extremes from the directed
+// arcs of k_compact_rows (storage for `cap` out-arcs).
+static gpm_status fill_dag(const BuildLayout &L, int32_t n, int32_t nshares, const int32_t *share,
+                           const uint8_t *keep, int32_t *kept, int64_t *scan_tmp, int64_t cap,
+                           uint32_t *flags, hipStream_t st) {
+    GPM_HIP(exclusive_scan_i32(kept, kept, (uint64_t)nshares, scan_tmp, st));
+    hipLaunchKernelGGL(k_orient_fill, share_grid(nshares), dim3(kBlock), 0, st, L.off, L.adj, keep,
+                       kept, n, nshares, share, cap, L.dag_off, L.dag_adj, L.dag_src, flags);
+    GPM_LAUNCH_CHECK("k_orient_fill");
+    hipLaunchKernelGGL(k_vertex_meta, dim3((unsigned)std::min<int64_t>(((int64_t)n + kBlock - 1) / kBlock,
+                                                                       (int64_t)cu_count() * 4)),
+                       dim3(kBlock), 0, st, L.off, L.dag_off, n, L.okey, flags);
+    GPM_LAUNCH_CHECK("k_vertex_meta");
+    return GPM_OK;
+}
+
+static dim3 big_grid(int64_t words) {
+    // one workgroup per CU, two where two bitmaps fit
+    return dim3((unsigned)cu_count() * (words * 4 <= 64 * 1024 ? 2u : 1u));
+}
 
 gpm_status graph_build_bytes(int32_t n, int64_t E, uint64_t *gb, uint64_t *sb) {
     if (n < 1 || n > INT32_MAX - 1) return fail(GPM_INVALID_ARGUMENT, "n must be in [1, 2^31-2]");
@@ -882,8 +1019,10 @@ gpm_status graph_from_csr_bytes(int32_t n, int64_t nnz, uint64_t *gb, uint64_t *
     BuildLayout L = layout(n, nnz / 2, nullptr, nullptr);
     *gb = L.graph_bytes;
     Carve s(nullptr, ~0ull);
-    s.take<int32_t>((uint64_t)n + 1);                              // out-degrees
-    s.take<int64_t>(scan_tmp_words((uint64_t)n + 1));
+    const uint64_t shares = (uint64_t)share_count(n, nnz);
+    s.take<int32_t>(shares + 1);                                   // first row per share
+    s.take<int32_t>(shares + 1);                                   // out-arcs per share
+    s.take<int64_t>(scan_tmp_words(shares + 1));
     s.take<uint32_t>(F_WORDS);
     s.take<uint8_t>((uint64_t)nnz);                                // arc points up
     *sb = s.used;
@@ -905,8 +1044,10 @@ gpm_status graph_from_csr(int32_t n, const int32_t *d_off, const int32_t *d_adj,
         return fail(GPM_OUT_OF_MEMORY, "graph or scratch buffer smaller than required");
     BuildLayout L = layout(n, nnz / 2, gmem, nullptr);
     Carve sc(smem, ~0ull);
-    int32_t *outcnt = sc.take<int32_t>((uint64_t)n + 1);
-    int64_t *scan_tmp = sc.take<int64_t>(scan_tmp_words((uint64_t)n + 1));
+    const int32_t nshares = (int32_t)share_count(n, nnz);
+    int32_t *share = sc.take<int32_t>((uint64_t)nshares + 1);
+    int32_t *kept = sc.take<int32_t>((uint64_t)nshares + 1);
+    int64_t *scan_tmp = sc.take<int64_t>(scan_tmp_words((uint64_t)nshares + 1));
     uint32_t *flags = sc.take<uint32_t>(F_WORDS);
     uint8_t *up = sc.take<uint8_t>((uint64_t)nnz);
     {
@@ -930,14 +1071,13 @@ gpm_status graph_from_csr(int32_t n, const int32_t *d_off, const int32_t *d_adj,
         GPM_HIP(hipMemcpyAsync(meta, L.meta, sizeof(int64_t) * 7, hipMemcpyDeviceToHost, st));
         GPM_HIP(hipStreamSynchronize(st));
         if (meta[4] != 0) return fail(GPM_NOT_CANONICAL, "the CSR is not in canonical form");
-        hipLaunchKernelGGL(k_orient_count, dim3(wave_grid(n)), dim3(kBlock), 0, st, L.off, L.adj,
-                           n, outcnt, up);
-        GPM_LAUNCH_CHECK("k_orient_count");
-        GPM_HIP(exclusive_scan_i32(outcnt, L.dag_off, (uint64_t)n, scan_tmp, st));
-        hipLaunchKernelGGL(k_orient_fill, dim3(wave_grid(n)), dim3(kBlock), 0, st, L.off, L.adj,
-                           up, L.dag_off, n, nnz / 2, L.dag_adj, L.dag_src, flags);
-        GPM_LAUNCH_CHECK("k_orient_fill");
-        GPM_HIP(degree_key(L.off, n, L.okey, st));
+        hipLaunchKernelGGL(k_shares, dim3((unsigned)(nshares / kBlock + 1)), dim3(kBlock), 0, st,
+                           L.off, n, nshares, share);
+        hipLaunchKernelGGL(k_compact_rows<false>, share_grid(nshares), dim3(kBlock), 0, st, nullptr,
+                           nullptr, L.off, nullptr, L.adj, n, nshares, share, up, kept);
+        GPM_LAUNCH_CHECK("k_compact_rows");
+        gpm_status frc = fill_dag(L, n, nshares, share, up, kept, scan_tmp, nnz / 2, flags, st);
+        if (frc) return frc;
         hipLaunchKernelGGL(k_meta, dim3(1), dim3(64), 0, st, L.off, L.dag_off, n, flags, L.meta);
         GPM_LAUNCH_CHECK("k_meta");
     }
@@ -990,7 +1130,7 @@ static gpm_status enqueue_build(int32_t n, const int32_t *d_u, const int32_t *d_
         GPM_LAUNCH_CHECK("k_bucket_scatter");
         hipLaunchKernelGGL(k_bucket_rows,
                            dim3((unsigned)std::min<int64_t>(L.nb, (int64_t)cu_count() * 2)),
-                           dim3(kBucketNT), 0, st, L.bucket_off, L.bsrc, L.bdst, n, L.S, L.nb,
+                           dim3(kBucketNT), ((size_t)(1 << L.S) + 1) * 4, st, L.bucket_off, L.bsrc, L.bdst, n, L.S, L.nb,
                            L.raw_off, L.raw_adj);
         GPM_LAUNCH_CHECK("k_bucket_rows");
     } else {
@@ -1009,19 +1149,21 @@ static gpm_status enqueue_build(int32_t n, const int32_t *d_u, const int32_t *d_
         }
     }
     hipLaunchKernelGGL(k_sort_small_rows, dim3(wave_grid(((int64_t)n + 3) / 4)), dim3(kBlock), 0,
-                       st, L.raw_off, L.raw_adj, n, L.ucnt, L.med_list, L.big_list, L.flags);
+                       st, L.raw_off, L.raw_adj, n, reg_row(n), L.ucnt, L.med_list, L.big_list,
+                       L.flags);
     GPM_LAUNCH_CHECK("k_sort_small_rows");
     {
         const int32_t span = sort_span(n);
         hipLaunchKernelGGL(k_sort_rows<false>, dim3(wave_grid(((int64_t)n + span - 1) / span)),
                            dim3(kBlock), 0, st, L.raw_off, L.raw_adj, n, span, L.ucnt, nullptr,
                            L.flags);
-        hipLaunchKernelGGL(k_sort_rows<true>, dim3(wave_grid(n)), dim3(kBlock), 0, st, L.raw_off,
-                           L.raw_adj, n, 1, L.ucnt, L.med_list, L.flags);
+        if (reg_row(n) > kScanRow)
+            hipLaunchKernelGGL(k_sort_rows<true>, dim3(wave_grid(n)), dim3(kBlock), 0, st,
+                               L.raw_off, L.raw_adj, n, 1, L.ucnt, L.med_list, L.flags);
     }
     GPM_LAUNCH_CHECK("k_sort_rows");
     if (n <= kLdsBitmapIds)
-        hipLaunchKernelGGL(k_sort_big_rows_lds, dim3((unsigned)cu_count()), dim3(kBigNT),
+        hipLaunchKernelGGL(k_sort_big_rows_lds, big_grid(L.words), dim3(kBigNT),
                            (size_t)L.words * 4, st, L.raw_off, L.raw_adj, L.ucnt, L.big_list,
                            L.flags, (int32_t)L.words);
     else
@@ -1029,14 +1171,14 @@ static gpm_status enqueue_build(int32_t n, const int32_t *d_u, const int32_t *d_
                            L.raw_adj, L.ucnt, L.big_list, L.flags, L.bitmaps, L.words);
     GPM_LAUNCH_CHECK("k_sort_big_rows");
     GPM_HIP(exclusive_scan_i32(L.ucnt, L.off, (uint64_t)n, L.scan_tmp, st));
-    hipLaunchKernelGGL(k_compact_rows, dim3(wave_grid(n)), dim3(kBlock), 0, st, L.raw_off,
-                       L.raw_adj, L.off, L.ucnt, L.adj, n, L.outcnt, L.keep, L.flags);
+    const int32_t nshares = (int32_t)share_count(n, 2 * E);
+    hipLaunchKernelGGL(k_shares, dim3((unsigned)(nshares / kBlock + 1)), dim3(kBlock), 0, st, L.off,
+                       n, nshares, L.share);
+    hipLaunchKernelGGL(k_compact_rows<true>, share_grid(nshares), dim3(kBlock), 0, st, L.raw_off,
+                       L.raw_adj, L.off, L.ucnt, L.adj, n, nshares, L.share, L.keep, L.kept);
     GPM_LAUNCH_CHECK("k_compact_rows");
-    GPM_HIP(exclusive_scan_i32(L.outcnt, L.dag_off, (uint64_t)n, L.scan_tmp, st));
-    hipLaunchKernelGGL(k_orient_fill, dim3(wave_grid(n)), dim3(kBlock), 0, st, L.off, L.adj,
-                       L.keep, L.dag_off, n, E, L.dag_adj, L.dag_src, L.flags);
-    GPM_LAUNCH_CHECK("k_orient_fill");
-    GPM_HIP(degree_key(L.off, n, L.okey, st));
+    gpm_status rc = fill_dag(L, n, nshares, L.share, L.keep, L.kept, L.scan_tmp, E, L.flags, st);
+    if (rc) return rc;
     hipLaunchKernelGGL(k_meta, dim3(1), dim3(64), 0, st, L.off, L.dag_off, n, L.flags, L.meta);
     GPM_LAUNCH_CHECK("k_meta");
     return GPM_OK;
@@ -1085,18 +1227,18 @@ gpm_status sort_rows(const int32_t *off, int32_t *adj, int32_t n, int32_t max_le
                      hipStream_t st) {
     RowSortArea A = row_sort_layout(n, area, nullptr);
     hipLaunchKernelGGL(k_sort_small_rows, dim3(wave_grid(((int64_t)n + 3) / 4)), dim3(kBlock), 0,
-                       st, off, adj, n, A.ucnt, A.med_list, A.big_list, A.flags);
+                       st, off, adj, n, reg_row(n), A.ucnt, A.med_list, A.big_list, A.flags);
     if (max_len > kSmallRow) {
         const int32_t span = sort_span(n);
         hipLaunchKernelGGL(k_sort_rows<false>, dim3(wave_grid(((int64_t)n + span - 1) / span)),
                            dim3(kBlock), 0, st, off, adj, n, span, A.ucnt, nullptr, A.flags);
     }
-    if (max_len > kScanRow)
+    if (max_len > kScanRow && reg_row(n) > kScanRow)
         hipLaunchKernelGGL(k_sort_rows<true>, dim3(wave_grid(n)), dim3(kBlock), 0, st, off, adj, n,
                            1, A.ucnt, A.med_list, A.flags);
-    if (max_len > kRegRow) {
+    if (max_len > reg_row(n)) {
         if (n <= kLdsBitmapIds)
-            hipLaunchKernelGGL(k_sort_big_rows_lds, dim3((unsigned)cu_count()), dim3(kBigNT),
+            hipLaunchKernelGGL(k_sort_big_rows_lds, big_grid(A.words), dim3(kBigNT),
                                (size_t)A.words * 4, st, off, adj, A.ucnt, A.big_list, A.flags,
                                (int32_t)A.words);
         else
