@@ -402,6 +402,48 @@ __device__ __forceinline__ void walk_lookup(const int32_t *pre, const int32_t *o
     }
 }
 
+// The entries of 64 segments (one per lane: first entry st, len entries),
+// shared out over the wave: segments are cut into units of 16 entries, a unit
+// a 16-lane group, so short and long segments keep the lanes equally busy.
+// Calls f(e, live, seg) for U tiles of 64 entries at a time, with the entry,
+// whether there is one, and its segment's lane; the loads f issues for the U
+// tiles are in flight together.  e is st of some segment where live is false
+// (or 0).  The whole wave must call it.
+template <int U, class F>
+__device__ __forceinline__ void wave_segments(int32_t st, int32_t len, F &&f) {
+    const int lane = lane_id(), grp = lane / 16, gl = lane % 16;
+    const int32_t nu = (len + 15) / 16;
+    const int32_t inc = wave_incl_scan(nu);
+    const int32_t units = __builtin_amdgcn_readlane(inc, kWave - 1);
+    for (int32_t ub = 0; ub < units; ub += kWave) {
+        // this lane's unit of the next 64: its segment is the first whose
+        // inclusive count exceeds the unit's number
+        const int32_t u = ub + lane;
+        int32_t j = 0;
+#pragma unroll
+        for (int h = kWave / 2; h > 0; h >>= 1)
+            if (__shfl(inc, j + h - 1, kWave) <= u) j += h;
+        const int32_t o = (u - __shfl(inc - nu, j, kWave)) * 16;
+        const int32_t us = __shfl(st, j, kWave) + o;
+        const int32_t left = __shfl(len, j, kWave) - o;
+        const int32_t ul = (u < units ? min(16, left) : 0) | (j << 5);
+        const int32_t ntile = min(16, (units - ub + 3) / 4);
+        for (int32_t t0 = 0; t0 < ntile; t0 += U) {
+            int32_t e[U], seg[U];
+            bool live[U];
+#pragma unroll
+            for (int q = 0; q < U; q++) {
+                const int src = min((t0 + q) * 4 + grp, kWave - 1);
+                const int32_t x = __shfl(ul, src, kWave), first = __shfl(us, src, kWave);
+                live[q] = t0 + q < ntile && gl < (x & 31);
+                seg[q] = x >> 5;
+                e[q] = live[q] ? first + gl : 0;
+            }
+            f(e, live, seg);
+        }
+    }
+}
+
 // splitmix64 finaliser, for the listing checksum.
 __device__ __forceinline__ uint64_t fmix64(uint64_t z) {
     z ^= z >> 30; z *= 0xBF58476D1CE4E5B9ull;

@@ -121,11 +121,17 @@ enum Acc : int {
     A_TRI = A_MINUS + 2 * F_COUNT,    // u64: triangles (from the arc counts)
     A_C4 = A_TRI + 2,                 // u128: 4-cycles (edge sets)
     A_CYC = A_C4 + 2,                 // 2 u128: 4-cycle sums (degrees, doubled; edge triangles)
-    A_K4 = A_CYC + 4,                 // u64: 4-cliques
+    A_K4 = A_CYC + 4,                 // u128: 4-cliques (without lists)
     A_DIR = A_K4 + 2,                 // kClasses u64: induced counts of the direct classes
     A_CURSOR = A_DIR + kClasses,      // u64: the wheel kernel's work cursor
     A_TCURSOR = A_CURSOR + 1,         // u64: the A^2-row kernel's task cursor
-    A_WORDS = A_TCURSOR + 1,
+    A_BCURSOR = A_TCURSOR + 1,        // u64: the wheel kernel's cursor over the big arcs
+    A_NBIG = A_BCURSOR + 1,           // u64: the big arcs
+    A_RTASKS = A_NBIG + 1,            // u64: tasks of the split vertices
+    A_QUAD = A_RTASKS + 1,            // u128: 12 times the 4-cliques (lists)
+    A_PEND = A_QUAD + 2,              // u128: 3 times their vertices' degrees
+    A_TWO = A_PEND + 2,               // u128: twice their edges' triangles
+    A_WORDS = A_TWO + 2,
 };
 
 __device__ __forceinline__ u128 binom2(uint64_t n) { return n < 2 ? 0 : (u128)n * (n - 1) / 2; }
@@ -139,6 +145,47 @@ __device__ __forceinline__ void wave_sync() {
 __device__ __forceinline__ u128 binom4(uint64_t n) {
     return n < 4 ? 0 : (u128)n * (n - 1) / 2 * (n - 2) / 3 * (n - 3) / 4;
 }
+
+// Adds up the workgroup's per-thread values and adds each total to its
+// accumulator pair: one atomic per workgroup and sum (one per wave queued
+// 65,000 atomics on a few words).
+template <int NT, int N>
+__device__ void add_sums(const u128 (&s)[N], const int (&slot)[N], unsigned long long *acc) {
+    __shared__ u128 sh[NT / kWave][N];
+#pragma unroll
+    for (int q = 0; q < N; q++) {
+        const u128 t = wave_sum_u128(s[q]);
+        if (lane_id() == 0) sh[threadIdx.x / kWave][q] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x < N) {
+        u128 t = 0;
+        for (int w = 0; w < NT / kWave; w++) t += sh[w][threadIdx.x];
+        int at = slot[0];
+#pragma unroll
+        for (int q = 1; q < N; q++) at = (int)threadIdx.x == q ? slot[q] : at;
+        if (t) atomic_add_u128(acc + at, t);
+    }
+}
+
+// ------------------------------------------- common-neighbour lists ---
+//
+// Where they fit their arena, every edge's common neighbours are written out
+// once (3 T entries in all), ascending by id: lid[] the vertices, lpos[] and
+// lpos[cap + .] their positions in the rows of the edge's two ends (source
+// and end of its DAG arc).  The two kernels below then read T_e entries of
+// two bytes where they walked whole rows and tested each entry (RMAT-13:
+// 757M entries instead of 1,546M, none of them a miss), the neighbourhood of
+// a vertex becomes a graph over positions in its row, and the sums over the
+// triangles and the 4-cliques come with them.  n <= 65536 throughout.
+struct Lists {
+    const uint32_t *esym;    // per arc of the symmetric CSR: edge << 1 | (its source is the DAG arc's end)
+    const int64_t *loff;     // per edge: first entry; [m] = all entries
+    const uint16_t *lid, *lpos;
+    const uint32_t *te;
+    int64_t cap, m;
+    __device__ __forceinline__ bool fit() const { return loff[m] <= cap; }
+};
 
 // Per vertex: t_v from the arc triangle counts (each arc adds its count to
 // both ends; every triangle at v lies on two of v's arcs).
@@ -164,7 +211,7 @@ __global__ void __launch_bounds__(kBlock) k_f5_vertex(const int32_t *__restrict_
     const int lane = lane_id();
     const int64_t wave0 = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
     const int64_t nwaves = (int64_t)gridDim.x * (kBlock / kWave);
-    u128 plus[F_COUNT] = {}, minus[F_COUNT] = {};
+    u128 star = 0, path = 0, cricket = 0, tad = 0, td = 0, bowtie = 0, c5 = 0;
     for (int64_t v = wave0; v < n; v += nwaves) {
         const int32_t s0 = off[v], dv = off[v + 1] - s0;
         uint64_t s = 0, q = 0;
@@ -178,26 +225,22 @@ __global__ void __launch_bounds__(kBlock) k_f5_vertex(const int32_t *__restrict_
         q = wave_sum(q);
         if (lane != 0) continue;
         const uint64_t d = (uint64_t)dv, t = t2[v] / 2;
-        plus[F_STAR] += binom4(d);
+        star += binom4(d);
         // 5-path: pairs of neighbours b < b' of the middle, (d_b - 1)(d_b' - 1)
         const u128 sd = (u128)(s - d);
-        plus[F_PATH] += (sd * sd - (u128)q) / 2;
-        minus[F_PATH] += (u128)2 * t * d;
-        if (d >= 2) plus[F_CRICKET] += (u128)t * binom2(d - 2);
-        plus[F_TADPOLE] += (u128)t * (s - d);
-        minus[F_TADPOLE] += (u128)2 * t * d;
-        plus[F_BOWTIE] += binom2(t);
+        path += (sd * sd - (u128)q) / 2;
+        td += (u128)2 * t * d;
+        if (d >= 2) cricket += (u128)t * binom2(d - 2);
+        tad += (u128)t * (s - d);
+        bowtie += binom2(t);
         // 5-cycles: 10 sum_v (d_v - 2) t_v, with t2 = 2 t_v
-        if (d >= 2) minus[F_C5] += (u128)5 * (d - 2) * t2[v];
+        if (d >= 2) c5 += (u128)5 * (d - 2) * t2[v];
     }
-#pragma unroll
-    for (int f = 0; f < F_COUNT; f++) {
-        const u128 p = wave_sum_u128(plus[f]), mm = wave_sum_u128(minus[f]);
-        if (lane == 0) {
-            if (p) atomic_add_u128(acc + A_PLUS + 2 * f, p);
-            if (mm) atomic_add_u128(acc + A_MINUS + 2 * f, mm);
-        }
-    }
+    const u128 sums[8] = {star, path, td, cricket, tad, td, bowtie, c5};
+    const int slot[8] = {A_PLUS + 2 * F_STAR,    A_PLUS + 2 * F_PATH,    A_MINUS + 2 * F_PATH,
+                         A_PLUS + 2 * F_CRICKET, A_PLUS + 2 * F_TADPOLE, A_MINUS + 2 * F_TADPOLE,
+                         A_PLUS + 2 * F_BOWTIE,  A_MINUS + 2 * F_C5};
+    add_sums<kBlock, 8>(sums, slot, acc);
 }
 
 // tr(A^5) = sum over vertices i of the closed 5-walks at i,
@@ -229,8 +272,10 @@ constexpr int kTriGroups = kWave / kTriLanes;   // triangles per wave at a time
 template <int NT, bool SHARED>
 __global__ void __launch_bounds__(NT) k_f5_trace5(const int32_t *__restrict__ off,
                                                   const int32_t *__restrict__ adj, int32_t n,
-                                                  int32_t nparts, unsigned long long *acc) {
+                                                  int32_t nparts, Lists L,
+                                                  unsigned long long *acc) {
     extern __shared__ uint4 s_trace[];
+    if (L.loff && L.fit()) return;
     // P2(i, j) < n <= 65536: 16-bit counters packed two to a word (hw4
     // words, a multiple of 4), then the bitmaps; the reached j are the
     // nonzero counters, found by scanning the words
@@ -432,9 +477,10 @@ __device__ __forceinline__ bool marked(const uint32_t *bm, int32_t v) {
 
 __global__ void __launch_bounds__(kBlock) k_f5_wheel(const int32_t *__restrict__ off,
                                                      const int32_t *__restrict__ adj, int32_t n,
-                                                     int32_t maxdeg, int64_t arcs,
+                                                     int32_t maxdeg, int64_t arcs, Lists L,
                                                      unsigned long long *acc) {
     extern __shared__ uint4 s_wheel[];
+    if (L.loff && L.fit()) return;
     const int lane = lane_id(), wid = threadIdx.x / kWave;
     const int32_t cw = wheel_count_words(maxdeg), ww = wheel_words_per_wave(n, maxdeg);
     const int32_t nbw = (n + 31) / 32;
@@ -530,59 +576,18 @@ __global__ void __launch_bounds__(kBlock) k_f5_wheel(const int32_t *__restrict__
     if (lane == 0 && sum) atomic_add_u128(acc + A_PLUS + 2 * F_WHEEL, sum);
 }
 
-// One thread per undirected edge (an arc of the DAG): the edge terms.
-__global__ void __launch_bounds__(kBlock) k_f5_edge(const int32_t *__restrict__ off,
+constexpr uint32_t kBigT = 256;   // arcs of this many triangles: the wheel kernel's workgroup tasks
+
+// esym and tsym of every arc (one thread per DAG arc, a binary search in
+// each end's row), and the arcs of kBigT triangles or more.
+__global__ void __launch_bounds__(kBlock) k_f5_arcs(const int32_t *__restrict__ off,
+                                                    const int32_t *__restrict__ adj,
                                                     const int32_t *__restrict__ dag_src,
                                                     const int32_t *__restrict__ dag_adj,
                                                     const uint32_t *__restrict__ te, int64_t m,
-                                                    unsigned long long *acc) {
-    const int lane = lane_id();
-    u128 plus[F_COUNT] = {}, minus[F_COUNT] = {};
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e0 = (int64_t)blockIdx.x * blockDim.x; e0 < m; e0 += stride) {
-        const int64_t e = e0 + threadIdx.x;
-        if (e >= m) continue;
-        const int32_t x = dag_src[e], y = dag_adj[e];
-        const uint64_t dx = (uint64_t)(off[x + 1] - off[x]), dy = (uint64_t)(off[y + 1] - off[y]);
-        const uint64_t T = te[e];
-        // chair, both orientations: centre c, its neighbour x on the long arm
-        plus[F_CHAIR] += binom2(dx - 1) * (dy - 1) + binom2(dy - 1) * (dx - 1);
-        if (T) {
-            // a triangle on the edge puts both ends at degree >= 2
-            minus[F_CHAIR] += (u128)T * ((dx - 2) + (dy - 2));
-            plus[F_BULL] += (u128)T * ((dx - 2) * (dy - 2));
-            minus[F_BULL] += (u128)T * (T - 1);
-            minus[F_TADPOLE] += (u128)2 * T * (T - 1);
-            const u128 diamonds = binom2(T);
-            minus[F_BOWTIE] += 2 * diamonds;
-            minus[F_BANNER] += 2 * diamonds;
-            minus[F_HOUSE] += 4 * diamonds;
-            minus[F_KITE] += 4 * diamonds;
-            minus[F_TWIN] += 4 * diamonds;
-            // two triangles on the edge put both ends at degree >= 3
-            if (T >= 2) plus[F_DART] += diamonds * (dx + dy - 6);
-            if (T >= 3) plus[F_BOOK] += diamonds * (T - 2) / 3;
-        }
-    }
-#pragma unroll
-    for (int f = 0; f < F_COUNT; f++) {
-        const u128 p = wave_sum_u128(plus[f]), mm = wave_sum_u128(minus[f]);
-        if (lane == 0) {
-            if (p) atomic_add_u128(acc + A_PLUS + 2 * f, p);
-            if (mm) atomic_add_u128(acc + A_MINUS + 2 * f, mm);
-        }
-    }
-}
-
-// tsym[a] = triangles on the edge of arc a of the symmetric CSR, from the
-// counts per arc of the DAG (one thread per DAG arc, a binary search in
-// each end's row).
-__global__ void __launch_bounds__(kBlock) k_tsym(const int32_t *__restrict__ off,
-                                                 const int32_t *__restrict__ adj,
-                                                 const int32_t *__restrict__ dag_src,
-                                                 const int32_t *__restrict__ dag_adj,
-                                                 const uint32_t *__restrict__ te, int64_t m,
-                                                 uint32_t *__restrict__ tsym) {
+                                                    uint32_t *__restrict__ tsym,
+                                                    uint32_t *__restrict__ esym, int32_t *big,
+                                                    unsigned long long *nbig) {
     auto find = [&](int32_t u, int32_t v) {
         int32_t lo = off[u], hi = off[u + 1];
         while (lo < hi) {
@@ -595,9 +600,408 @@ __global__ void __launch_bounds__(kBlock) k_tsym(const int32_t *__restrict__ off
          e += (int64_t)gridDim.x * blockDim.x) {
         const int32_t u = dag_src[e], v = dag_adj[e];
         const uint32_t c = te[e];
-        tsym[find(u, v)] = c;
-        tsym[find(v, u)] = c;
+        const int32_t a = find(u, v), b = find(v, u);
+        tsym[a] = c;
+        tsym[b] = c;
+        if (!esym) continue;
+        esym[a] = (uint32_t)e << 1;
+        esym[b] = (uint32_t)e << 1 | 1u;
+        if (c >= kBigT) {
+            const unsigned long long at = atomicAdd(nbig, 2ull);
+            big[at] = a;
+            big[at + 1] = b;
+        }
     }
+}
+
+// The lists: a wave per edge walks the shorter row and looks its entries up
+// in the longer one.
+__global__ void __launch_bounds__(kBlock) k_f5_lists(const int32_t *__restrict__ off,
+                                                     const int32_t *__restrict__ adj,
+                                                     const int32_t *__restrict__ dag_src,
+                                                     const int32_t *__restrict__ dag_adj,
+                                                     Lists L, uint16_t *lid, uint16_t *lpos) {
+    if (!L.fit()) return;
+    const int lane = lane_id();
+    const int64_t wave0 = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
+    const int64_t nwaves = (int64_t)gridDim.x * (kBlock / kWave);
+    for (int64_t e = wave0; e < L.m; e += nwaves) {
+        const uint32_t t = L.te[e];
+        if (t == 0) continue;
+        const int32_t u = dag_src[e], v = dag_adj[e];
+        const int32_t su = off[u], du = off[u + 1] - su, sv = off[v], dv = off[v + 1] - sv;
+        const bool first = du <= dv;   // walk u's row
+        const int32_t sa = first ? su : sv, da = first ? du : dv;
+        const int32_t sb = first ? sv : su, db = first ? dv : du;
+        int64_t at = L.loff[e];
+        const int64_t end = at + t;
+        for (int32_t k0 = 0; k0 < da && at < end; k0 += kWave) {
+            const int32_t k = k0 + lane;
+            int32_t x = 0, lo = 0;
+            bool hit = false;
+            if (k < da) {
+                x = adj[sa + k];
+                int32_t hi = db;
+                while (lo < hi) {
+                    const int32_t mid = (lo + hi) >> 1;
+                    if (adj[sb + mid] < x) lo = mid + 1; else hi = mid;
+                }
+                hit = lo < db && adj[sb + lo] == x;
+            }
+            const uint64_t mask = __ballot(hit);
+            if (hit) {
+                const int64_t p = at + lanes_below(mask);
+                lid[p] = (uint16_t)x;
+                lpos[p] = (uint16_t)(first ? k : lo);
+                lpos[L.cap + p] = (uint16_t)(first ? lo : k);
+            }
+            at += __popcll(mask);
+        }
+    }
+}
+
+// Tasks of k_f5_rows beyond one per vertex: a vertex of more than kRowCorners
+// triangles is split into parts that share its neighbours a out in turn
+// (each part builds the row of A^2 again, so parts are large).
+constexpr int32_t kRowCorners = 8192;
+constexpr size_t kRowsFixedLds = 8 * 1024;   // at most, beside the row and the bitmap
+constexpr int32_t kMaxRowParts = 64;
+
+__device__ __forceinline__ int32_t row_parts(unsigned long long t2) {
+    const unsigned long long p = t2 / 2 / kRowCorners + 1;
+    return (int32_t)(p > kMaxRowParts ? kMaxRowParts : p);
+}
+
+struct RowTask {
+    int32_t i;
+    int16_t part, parts;
+};
+
+__global__ void k_f5_row_tasks(const unsigned long long *__restrict__ t2, int32_t n, Lists L,
+                               RowTask *tasks, unsigned long long *ntasks) {
+    if (!L.fit()) return;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t parts = row_parts(t2[i]);
+        if (parts == 1) continue;
+        const unsigned long long at = atomicAdd(ntasks, (unsigned long long)parts);
+        for (int32_t q = 0; q < parts; q++) tasks[at + q] = {(int32_t)i, (int16_t)q, (int16_t)parts};
+    }
+}
+
+// Vertex i's row of A^2, P2(i, .), in LDS (n 16-bit counters, two to a
+// word), and N(i) as a bitmap; then, over the triangles {i, a, b} with b
+// after a in N(i) (each triangle at each of its three vertices), e the edge
+// {a, b}, C_e its common neighbours and q = |C_e & N(i)|:
+//   twin   P2(i, d) over d in C_e, d != i     (class 16, see k_f5_trace5)
+//   k5e    C(q, 2)                            (three times K5 minus an edge)
+//   quad   q, three times the 4-cliques at i: 12 times all of them
+//   pend   d(i) q: three times the degrees over the 4-cliques
+//   two    q T_e: twice the edge triangles over the 4-cliques
+//   kite   (T_e - 1) d(i);  gem  (T_ia - 1)(T_ib - 1)
+// Part 0 of a vertex also takes K_{2,3} and tr(A^5) as k_f5_trace5 does.
+// Tasks: the parts of the vertices of many triangles first (tasks[]), then
+// every other vertex, from a cursor.  The neighbours a are dealt to the
+// waves in runs; each wave flattens its arcs' lists, 64 triangles at a time,
+// then those triangles' lists C_e (wave_segments).  Bound by the two random
+// LDS reads and the addressing of each entry of C_e.  P2, T and d are below
+// 2^16, so a lane's 64-bit sums hold 2^32 terms.
+template <int NT>
+__global__ void __launch_bounds__(NT) k_f5_rows(const int32_t *__restrict__ off,
+                                                const int32_t *__restrict__ adj, int32_t n,
+                                                const unsigned long long *__restrict__ t2, Lists L,
+                                                const RowTask *__restrict__ tasks,
+                                                unsigned long long *acc) {
+    constexpr int NW = NT / kWave, U = 4;
+    extern __shared__ uint4 s_rows[];
+    if (!L.fit()) return;
+    const int32_t hw = (n + 1) / 2, hw4 = (hw + 3) / 4 * 4, nbw = (n + 31) / 32;
+    uint32_t *p2w = reinterpret_cast<uint32_t *>(s_rows);
+    uint32_t *nbm = p2w + hw4;                           // bitmap of N(i)
+    __shared__ uint32_t s_q[NW][kWave];
+    __shared__ int64_t s_task;
+    auto p2 = [&](int32_t j) -> uint32_t { return (p2w[j >> 1] >> ((j & 1) * 16)) & 0xFFFFu; };
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wid = __builtin_amdgcn_readfirstlane(tid / kWave);
+    uint32_t *sq = s_q[wid];
+    for (int32_t k = tid; k < hw4 + nbw; k += NT) p2w[k] = 0;
+    sq[lane] = 0;
+    __syncthreads();
+    const int64_t nsplit = (int64_t)acc[A_RTASKS], ntasks = nsplit + n;
+    uint64_t tr = 0, twin = 0, k5e = 0, quad = 0, pend = 0, two = 0, kite = 0, gem = 0;
+    u128 k23 = 0;
+    for (;;) {
+        if (tid == 0) s_task = (int64_t)atomicAdd(acc + A_TCURSOR, 1ull);
+        __syncthreads();
+        const int64_t t = s_task;
+        __syncthreads();
+        if (t >= ntasks) break;
+        int32_t i, part = 0, parts = 1;
+        if (t < nsplit) {
+            i = tasks[t].i;
+            part = tasks[t].part;
+            parts = tasks[t].parts;
+        } else {
+            i = (int32_t)(t - nsplit);
+            if (row_parts(t2[i]) > 1) continue;
+        }
+        const int32_t si = off[i], di = off[i + 1] - si;
+        if (di == 0) continue;
+        // 2-walks i - x - j, and N(i)
+        const int32_t per = min(kWave, (di + NW - 1) / NW);
+        for (int32_t a0 = wid * per; a0 < di; a0 += NW * per) {
+            int32_t sx = 0, dx = 0;
+            if (lane < per && a0 + lane < di) {
+                const int32_t x = adj[si + a0 + lane];
+                sx = off[x];
+                dx = off[x + 1] - sx;
+                atomicOr(&nbm[x >> 5], 1u << (x & 31));
+            }
+            wave_segments<U>(sx, dx, [&](const int32_t (&e)[U], const bool (&live)[U],
+                                         const int32_t (&)[U]) {
+                int32_t j[U];
+#pragma unroll
+                for (int q = 0; q < U; q++) j[q] = adj[e[q]];
+#pragma unroll
+                for (int q = 0; q < U; q++)
+                    if (live[q]) atomicAdd(&p2w[j[q] >> 1], 1u << ((uint32_t)(j[q] & 1) * 16u));
+            });
+        }
+        __syncthreads();
+        if (part == 0) {
+            for (int32_t w0 = wid * kWave; w0 < hw; w0 += NW * kWave) {
+                const uint32_t v = w0 + lane < hw ? p2w[w0 + lane] : 0u;
+                if (!__any(v != 0u)) continue;
+#pragma unroll
+                for (int h = 0; h < 2; h++) {
+                    const uint64_t c = (v >> (16 * h)) & 0xFFFFu;
+                    const int32_t j = 2 * (w0 + lane) + h;
+                    if (j > i && c >= 3) k23 += (u128)(c * (c - 1) * (c - 2) / 6);
+                    // the row of j, unless the pair is j's to take (its end of
+                    // larger (degree, id)); doubled for j != i
+                    int32_t sj = 0, dj = 0;
+                    if (c) {
+                        sj = off[j];
+                        dj = off[j + 1] - sj;
+                        if (j != i && (dj > di || (dj == di && j > i))) dj = 0;
+                    }
+                    const uint32_t pj = (uint32_t)c << (j != i);
+                    wave_segments<U>(sj, dj, [&](const int32_t (&e)[U], const bool (&live)[U],
+                                                 const int32_t (&seg)[U]) {
+                        int32_t k[U];
+                        uint32_t f[U];
+#pragma unroll
+                        for (int q = 0; q < U; q++) k[q] = adj[e[q]];
+#pragma unroll
+                        for (int q = 0; q < U; q++) f[q] = __shfl(pj, seg[q], kWave);
+#pragma unroll
+                        for (int q = 0; q < U; q++)
+                            if (live[q]) tr += (uint64_t)f[q] * p2(k[q]);
+                    });
+                }
+            }
+        }
+        // triangles {i, a, b}: this part's neighbours a = part, part + parts, ...
+        const int32_t na = (di - part + parts - 1) / parts;
+        const int32_t pa = max(1, min(kWave, (na + NW - 1) / NW));
+        for (int32_t k0 = wid * pa; k0 < na; k0 += NW * pa) {
+            int32_t la = 0, ta = 0, ka = 0;      // arc i -> a: its list, its position
+            uint32_t from = 0, sa = 0;           // the end of the edge that i is; a's row
+            if (lane < pa && k0 + lane < na) {
+                ka = part + (k0 + lane) * parts;
+                const int32_t a = adj[si + ka];
+                const uint32_t es = L.esym[si + ka];
+                la = (int32_t)L.loff[es >> 1];
+                ta = (int32_t)L.te[es >> 1];
+                from = es & 1u;
+                sa = (uint32_t)off[a];
+            }
+            wave_segments<1>(la, ta, [&](const int32_t (&e1)[1], const bool (&live1)[1],
+                                         const int32_t (&seg1)[1]) {
+                const uint32_t fr = __shfl(from, seg1[0], kWave);
+                const int32_t kas = __shfl(ka, seg1[0], kWave);
+                const uint32_t sas = __shfl(sa, seg1[0], kWave);
+                const uint64_t t_ia = (uint64_t)__shfl(ta, seg1[0], kWave);
+                int32_t st = 0, len = 0;
+                if (live1[0]) {
+                    const int32_t kb = L.lpos[(fr ? L.cap : 0) + e1[0]];
+                    if (kb > kas) {
+                        const uint32_t eb = L.esym[sas + L.lpos[(fr ? 0 : L.cap) + e1[0]]] >> 1;
+                        st = (int32_t)L.loff[eb];
+                        len = (int32_t)L.te[eb];
+                        const uint64_t t_ib = L.te[L.esym[si + kb] >> 1];
+                        kite += (uint64_t)(len - 1) * (uint64_t)di;
+                        gem += (t_ia - 1) * (t_ib - 1);
+                        twin -= (uint64_t)di;   // d = i is in C_e: P2(i, i) = d(i)
+                    }
+                }
+                wave_segments<U>(st, len, [&](const int32_t (&e)[U], const bool (&live)[U],
+                                              const int32_t (&seg)[U]) {
+                    int32_t d[U];
+#pragma unroll
+                    for (int q = 0; q < U; q++) d[q] = L.lid[e[q]];
+#pragma unroll
+                    for (int q = 0; q < U; q++) {
+                        const bool in = live[q] && ((nbm[d[q] >> 5] >> (d[q] & 31)) & 1u);
+                        const uint64_t hit = __ballot(in);
+                        if (live[q]) twin += p2(d[q]);
+                        const uint32_t g = (uint32_t)(hit >> (lane & 48)) & 0xFFFFu;
+                        if ((lane & 15) == 0 && g) atomicAdd(&sq[seg[q]], (uint32_t)__popc(g));
+                    }
+                });
+                wave_sync();
+                const uint64_t q = sq[lane];
+                if (q) {
+                    sq[lane] = 0;
+                    k5e += q * (q - 1) / 2;
+                    quad += q;
+                    pend += q * (uint64_t)di;
+                    two += q * (uint64_t)len;
+                }
+                wave_sync();
+            });
+        }
+        __syncthreads();
+        uint4 *p2w4 = reinterpret_cast<uint4 *>(p2w);
+        for (int32_t k = tid; k < hw4 / 4; k += NT) p2w4[k] = make_uint4(0u, 0u, 0u, 0u);
+        for (int32_t k = tid; k < nbw; k += NT) nbm[k] = 0u;
+        __syncthreads();
+    }
+    // twin's subtractions wrap the lane's 64-bit sum, not the total's: the
+    // sum over the lanes is taken modulo 2^64 of a signed value
+    const u128 tw = (u128)(__int128)(int64_t)twin;
+    const u128 s[9] = {(u128)tr, k23, tw, (u128)k5e, (u128)quad, (u128)pend, (u128)two,
+                       (u128)kite, (u128)gem};
+    const int slot[9] = {A_PLUS + 2 * F_C5, A_PLUS + 2 * F_K23, A_PLUS + 2 * F_TWIN,
+                         A_PLUS + 2 * F_K5E, A_QUAD, A_PEND, A_TWO, A_PLUS + 2 * F_KITE,
+                         A_PLUS + 2 * F_GEM};
+    add_sums<NT, 9>(s, slot, acc);
+}
+
+// The wheels from the lists: see k_f5_wheel.  With positions in row i for
+// vertices, arc i -> x at position kx has the list of its common neighbours'
+// positions kp, and arc i -> p the list of ky; the task (i, x) counts the
+// walks x - p - y with kp, ky < kx per ky (16-bit counters, below d(i)), each
+// increment adding the count before it.  A team of NW waves takes an arc: one
+// wave (arcs of fewer than kBigT triangles), or a workgroup (the others: the
+// largest has a million entries).
+template <int NT, bool BIG>
+__global__ void __launch_bounds__(NT) k_f5_wheel_lists(const int32_t *__restrict__ off,
+                                                       const int32_t *__restrict__ dag_src,
+                                                       const int32_t *__restrict__ dag_adj,
+                                                       int32_t maxdeg, Lists L,
+                                                       const int32_t *__restrict__ big,
+                                                       unsigned long long *acc) {
+    constexpr int NW = BIG ? NT / kWave : 1, U = 4;
+    extern __shared__ uint4 s_wl[];
+    if (!L.fit()) return;
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wid = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int32_t cw = wheel_count_words(maxdeg);
+    uint32_t *cnt = reinterpret_cast<uint32_t *>(s_wl) + (BIG ? 0 : (int64_t)wid * cw);
+    const int32_t t_lane = BIG ? tid : lane, t_size = BIG ? NT : kWave;
+    auto team_sync = [&]() {
+        if (BIG) __syncthreads();
+        else wave_sync();
+    };
+    __shared__ unsigned long long s_next;
+    for (int32_t k = t_lane; k < cw; k += t_size) cnt[k] = 0u;
+    team_sync();
+    const unsigned long long narcs = BIG ? acc[A_NBIG] : 2ull * (unsigned long long)L.m;
+    constexpr unsigned long long kGrab = BIG ? 1 : kWheelArcs;
+    uint64_t sum = 0;
+    for (;;) {
+        unsigned long long r = 0;
+        if (BIG) {
+            if (tid == 0) s_next = atomicAdd(acc + A_BCURSOR, kGrab);
+            __syncthreads();
+            r = s_next;
+            __syncthreads();
+        } else {
+            if (lane == 0) r = atomicAdd(acc + A_CURSOR, kGrab);
+            r = __shfl(r, 0, kWave);
+        }
+        if (r >= narcs) break;
+        for (unsigned long long q = r; q < r + kGrab && q < narcs; q++) {
+            const int32_t arc = BIG ? big[q] : (int32_t)q;
+            const uint32_t es = L.esym[arc];
+            const uint32_t t = L.te[es >> 1];
+            if (t < 2 || (!BIG && t >= kBigT)) continue;
+            const int32_t i = (es & 1u) ? dag_adj[es >> 1] : dag_src[es >> 1];
+            const int32_t si = off[i], kx = arc - si;
+            if (kx < 3) continue;   // two p and a y before x
+            const uint16_t *px = L.lpos + ((es & 1u) ? L.cap : 0) + L.loff[es >> 1];
+            for (int32_t b0 = (BIG ? wid : 0) * kWave; b0 < (int32_t)t; b0 += NW * kWave) {
+                int32_t st = 0, len = 0;
+                uint32_t side = 0;
+                if (b0 + lane < (int32_t)t) {
+                    const int32_t kp = px[b0 + lane];
+                    if (kp < kx) {
+                        const uint32_t ep = L.esym[si + kp];
+                        side = ep & 1u;
+                        st = (int32_t)L.loff[ep >> 1];
+                        len = (int32_t)L.te[ep >> 1];
+                    }
+                }
+                wave_segments<U>(st, len, [&](const int32_t (&e)[U], const bool (&live)[U],
+                                              const int32_t (&seg)[U]) {
+                    int32_t ky[U];
+#pragma unroll
+                    for (int u = 0; u < U; u++)
+                        ky[u] = L.lpos[(__shfl(side, seg[u], kWave) ? L.cap : 0) + e[u]];
+#pragma unroll
+                    for (int u = 0; u < U; u++)
+                        if (live[u] && ky[u] < kx) {
+                            const uint32_t sh = (uint32_t)(ky[u] & 1) * 16u;
+                            const uint32_t old = atomicAdd(&cnt[ky[u] >> 1], 1u << sh);
+                            sum += (old >> sh) & 0xFFFFu;
+                        }
+                });
+            }
+            team_sync();
+            uint4 *c4 = reinterpret_cast<uint4 *>(cnt);
+            for (int32_t k = t_lane; k < (kx + 7) / 8; k += t_size) c4[k] = make_uint4(0u, 0u, 0u, 0u);
+            team_sync();
+        }
+    }
+    const u128 s[1] = {(u128)sum};
+    const int slot[1] = {A_PLUS + 2 * F_WHEEL};
+    add_sums<NT, 1>(s, slot, acc);
+}
+
+// One thread per undirected edge (an arc of the DAG): the edge terms.
+__global__ void __launch_bounds__(kBlock) k_f5_edge(const int32_t *__restrict__ off,
+                                                    const int32_t *__restrict__ dag_src,
+                                                    const int32_t *__restrict__ dag_adj,
+                                                    const uint32_t *__restrict__ te, int64_t m,
+                                                    unsigned long long *acc) {
+    u128 chair = 0, chair_t = 0, bull = 0, tt = 0, dia = 0, dart = 0, book = 0;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += stride) {
+        const int32_t x = dag_src[e], y = dag_adj[e];
+        const uint64_t dx = (uint64_t)(off[x + 1] - off[x]), dy = (uint64_t)(off[y + 1] - off[y]);
+        const uint64_t T = te[e];
+        // chair, both orientations: centre c, its neighbour x on the long arm
+        chair += binom2(dx - 1) * (dy - 1) + binom2(dy - 1) * (dx - 1);
+        if (T) {
+            // a triangle on the edge puts both ends at degree >= 2
+            chair_t += (u128)T * ((dx - 2) + (dy - 2));
+            bull += (u128)T * ((dx - 2) * (dy - 2));
+            tt += (u128)T * (T - 1);
+            const u128 diamonds = binom2(T);
+            dia += diamonds;
+            // two triangles on the edge put both ends at degree >= 3
+            if (T >= 2) dart += diamonds * (dx + dy - 6);
+            if (T >= 3) book += diamonds * (T - 2) / 3;
+        }
+    }
+    const u128 sums[12] = {chair,   chair_t, bull,    tt,      2 * tt, 2 * dia,
+                           2 * dia, 4 * dia, 4 * dia, 4 * dia, dart,   book};
+    const int slot[12] = {A_PLUS + 2 * F_CHAIR,    A_MINUS + 2 * F_CHAIR,  A_PLUS + 2 * F_BULL,
+                          A_MINUS + 2 * F_BULL,    A_MINUS + 2 * F_TADPOLE, A_MINUS + 2 * F_BOWTIE,
+                          A_MINUS + 2 * F_BANNER,  A_MINUS + 2 * F_HOUSE,  A_MINUS + 2 * F_KITE,
+                          A_MINUS + 2 * F_TWIN,    A_PLUS + 2 * F_DART,    A_PLUS + 2 * F_BOOK};
+    add_sums<kBlock, 12>(sums, slot, acc);
 }
 
 // The triangle terms of the kite and the gem.  One wave per DAG arc
@@ -608,7 +1012,8 @@ __global__ void __launch_bounds__(kBlock) k_f5_tri(const int32_t *__restrict__ o
                                                    const int32_t *__restrict__ dag_src,
                                                    const int32_t *__restrict__ dag_adj,
                                                    const uint32_t *__restrict__ te, int64_t m,
-                                                   unsigned long long *acc) {
+                                                   Lists L, unsigned long long *acc) {
+    if (L.loff && L.fit()) return;
     const int lane = lane_id();
     const int64_t wave0 = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
     const int64_t nwaves = (int64_t)gridDim.x * (kBlock / kWave);
@@ -638,23 +1043,22 @@ __global__ void __launch_bounds__(kBlock) k_f5_tri(const int32_t *__restrict__ o
             }
         }
     }
-    const u128 k = wave_sum_u128((u128)kite), g = wave_sum_u128((u128)gem);
-    if (lane == 0) {
-        if (k) atomic_add_u128(acc + A_PLUS + 2 * F_KITE, k);
-        if (g) atomic_add_u128(acc + A_PLUS + 2 * F_GEM, g);
-    }
+    const u128 s[2] = {(u128)kite, (u128)gem};
+    const int slot[2] = {A_PLUS + 2 * F_KITE, A_PLUS + 2 * F_GEM};
+    add_sums<kBlock, 2>(s, slot, acc);
 }
 
 // The 4-clique terms.  One wave per DAG arc u -> v: lanes find the w of
 // N+(v) in N+(u) (the triangles u, v, w); for each such w in turn, lanes
 // take x in N+(w) and look it up in N+(u) and N+(v).  Each 4-clique
-// u -> v -> w -> x is met once, with its six arcs.
+// u -> v -> w -> x is met once, with its six arcs, and counted.
 __global__ void __launch_bounds__(kBlock) k_f5_k4(const int32_t *__restrict__ off,
                                                   const int32_t *__restrict__ dag_off,
                                                   const int32_t *__restrict__ dag_src,
                                                   const int32_t *__restrict__ dag_adj,
                                                   const uint32_t *__restrict__ te, int64_t m,
-                                                  unsigned long long *acc) {
+                                                  Lists L, unsigned long long *acc) {
+    if (L.loff && L.fit()) return;
     const int lane = lane_id();
     const int64_t wave0 = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
     const int64_t nwaves = (int64_t)gridDim.x * (kBlock / kWave);
@@ -666,7 +1070,7 @@ __global__ void __launch_bounds__(kBlock) k_f5_k4(const int32_t *__restrict__ of
         }
         return lo < len && dag_adj[s0 + lo] == x ? lo : -1;
     };
-    uint64_t pend = 0, two = 0;
+    uint64_t pend = 0, two = 0, num = 0;
     for (int64_t e = wave0; e < m; e += nwaves) {
         const int32_t u = dag_src[e], v = dag_adj[e];
         if (te[e] < 2) continue;   // wave-uniform: an edge of a 4-clique has two triangles
@@ -696,17 +1100,16 @@ __global__ void __launch_bounds__(kBlock) k_f5_k4(const int32_t *__restrict__ of
                     const int32_t ixv = find(sv, dv, x);
                     if (ixv < 0) continue;
                     const uint64_t deg_x = (uint64_t)(off[x + 1] - off[x]);
+                    num++;
                     pend += deg_uv + deg_w + deg_x - 12u;
                     two += t3 + te[su + ixu] + te[sv + ixv] + te[sw + j] - 12u;
                 }
             }
         }
     }
-    const u128 a = wave_sum_u128((u128)pend), b = wave_sum_u128((u128)two);
-    if (lane == 0) {
-        if (a) atomic_add_u128(acc + A_PLUS + 2 * F_K4PEND, a);
-        if (b) atomic_add_u128(acc + A_PLUS + 2 * F_K4TWO, b);
-    }
+    const u128 s[3] = {(u128)pend, (u128)two, (u128)num};
+    const int slot[3] = {A_PLUS + 2 * F_K4PEND, A_PLUS + 2 * F_K4TWO, A_K4};
+    add_sums<kBlock, 3>(s, slot, acc);
 }
 
 __device__ __forceinline__ u128 load128(const unsigned long long *p) {
@@ -722,7 +1125,12 @@ __global__ void k_f5_combine(const unsigned long long *acc, Back B, unsigned lon
     const u128 T = (u128)acc[A_TRI];
     const u128 nc4 = load128(acc + A_C4);
     const u128 cyc_deg2 = load128(acc + A_CYC), cyc_tri = load128(acc + A_CYC + 2);
-    const u128 k4 = (u128)acc[A_K4];
+    // with lists: each 4-clique 12 times, its degrees 3 times, its edges'
+    // triangles twice
+    const u128 quad = load128(acc + A_QUAD), pend3 = load128(acc + A_PEND);
+    const u128 two2 = load128(acc + A_TWO), k4l = quad / 12;
+    if (quad % 12 || pend3 % 3 || (two2 & 1)) bad |= 1;
+    const u128 k4 = load128(acc + A_K4) + k4l;
     if (cyc_deg2 & 1) bad |= 1;   // twice a sum
     u128 N[kClasses];
     for (int h = 0; h < kClasses; h++) {
@@ -744,6 +1152,9 @@ __global__ void k_f5_combine(const unsigned long long *acc, Back B, unsigned lon
         }
         if (f == F_HOUSE) p += cyc_tri;
         if (f == F_KITE || f == F_GEM) mm += 12 * k4;
+        if (f == F_K4PEND) p += pend3 / 3;
+        if (f == F_K4TWO) p += two2 / 2;
+        if (f == F_K4PEND || f == F_K4TWO) mm += 12 * k4l;
         if (f == F_C5) mm += 30 * T;   // 5 tr(A^3) = 30 T
         if (p < mm) bad |= 1;
         N[h] = p - mm;
@@ -853,9 +1264,27 @@ const Back &back_matrix() {
     return B;
 }
 
+// Entries of the lists' arena: never more than 3 triangles an arc times the
+// largest out-degree, and at most 192 an edge (1.2 KB; RMAT-10 to RMAT-16 have
+// 34 to 60).  A graph that needs more is counted without lists.
+constexpr int64_t kListsPerEdge = 192;
+
+int64_t lists_bound(const gpm_graph *g) { return 3 * g->m * std::max<int64_t>(g->max_out_degree, 1); }
+
+int64_t lists_cap(const gpm_graph *g) {
+    return std::max<int64_t>(
+        1, std::min({lists_bound(g), kListsPerEdge * g->m, (int64_t)INT32_MAX - 64}));
+}
+
 struct F5Ws {
     unsigned long long *acc, *t2;
     uint32_t *te, *tsym;
+    // the lists (null above kTrace5MaxN vertices)
+    uint32_t *esym;
+    int32_t *big;
+    int64_t *loff, *scan_tmp;
+    uint16_t *lid, *lpos;
+    RowTask *tasks;
     void *shared;
     uint64_t shared_bytes, bytes;
 };
@@ -867,13 +1296,22 @@ F5Ws f5_layout(const gpm_graph *g, void *base) {
     W.t2 = c.take<unsigned long long>((uint64_t)g->n + 1);
     W.te = c.take<uint32_t>((uint64_t)g->m + 1);
     W.tsym = c.take<uint32_t>(2 * (uint64_t)g->m + 1);
+    if (g->n <= kTrace5MaxN) {
+        const uint64_t cap = (uint64_t)lists_cap(g);
+        W.esym = c.take<uint32_t>(2 * (uint64_t)g->m + 1);
+        W.big = c.take<int32_t>(2 * (uint64_t)g->m + 1);
+        W.loff = c.take<int64_t>((uint64_t)g->m + 1);
+        W.scan_tmp = c.take<int64_t>(scan_tmp_words((uint64_t)g->m + 1));
+        W.lid = c.take<uint16_t>(cap);
+        W.lpos = c.take<uint16_t>(2 * cap);
+        // a vertex of t > kRowCorners triangles has at most 2 t / kRowCorners parts
+        W.tasks = c.take<RowTask>(2 * cap / kRowCorners + 1);
+    }
     uint64_t b3 = 0, b5 = 0, bc4 = 0;
-    uint64_t b4 = 0;
     clique_workspace_bytes(g, 3, false, &b3);
-    clique_workspace_bytes(g, 4, false, &b4);
     clique_workspace_bytes(g, 5, false, &b5);
     c4_workspace_bytes(g, false, &bc4);
-    W.shared_bytes = std::max({b3, b4, b5, bc4, generic_workspace_bytes(g)});
+    W.shared_bytes = std::max({b3, b5, bc4, generic_workspace_bytes(g)});
     W.shared = c.take<char>(W.shared_bytes);
     W.bytes = c.used;
     return W;
@@ -917,25 +1355,74 @@ gpm_status motif_formula_count(const gpm_graph *g, int32_t k, void *ws, uint64_t
         g, W.shared, W.shared_bytes, W.te, W.acc + A_TRI, st,
         {W.acc, 2 * ((uint64_t)(W.t2 - W.acc) + (uint64_t)n + 1)});
     if (rc) return rc;
+    // the lists, and whether the graph's may exceed them
+    const int64_t cap = lists_cap(g);
+    const Lists L{W.esym, W.loff, W.lid, W.lpos, W.te, cap, m};
+    const bool lists = trace5 && m > 0, plain = !lists || lists_bound(g) > cap;
     {
         Span sp("k_f5_local", st);
+        const unsigned sum_grid = (unsigned)cu_count() * 2;
         if (m > 0) {
             hipLaunchKernelGGL(k_vertex_tri, dim3(grid_for(m, kBlock, 8)), dim3(kBlock), 0, st,
                                g->dag_src, g->dag_adj, W.te, m, W.t2);
-            hipLaunchKernelGGL(k_f5_edge, dim3(grid_for(m, kBlock, 8)), dim3(kBlock), 0, st,
-                               g->off, g->dag_src, g->dag_adj, W.te, m, W.acc);
-            hipLaunchKernelGGL(k_tsym, dim3(grid_for(m, kBlock, 8)), dim3(kBlock), 0, st, g->off,
-                               g->adj, g->dag_src, g->dag_adj, W.te, m, W.tsym);
-            hipLaunchKernelGGL(k_f5_tri, dim3(grid_for(m, kBlock / kWave, 16)), dim3(kBlock), 0,
-                               st, g->off, g->dag_off, g->dag_src, g->dag_adj, W.te, m, W.acc);
-            hipLaunchKernelGGL(k_f5_k4, dim3(grid_for(m, kBlock / kWave, 16)), dim3(kBlock), 0,
-                               st, g->off, g->dag_off, g->dag_src, g->dag_adj, W.te, m, W.acc);
+            hipLaunchKernelGGL(k_f5_edge, dim3(std::min(sum_grid, grid_for(m, kBlock, 8))),
+                               dim3(kBlock), 0, st, g->off, g->dag_src, g->dag_adj, W.te, m, W.acc);
+            hipLaunchKernelGGL(k_f5_arcs, dim3(grid_for(m, kBlock, 8)), dim3(kBlock), 0, st, g->off,
+                               g->adj, g->dag_src, g->dag_adj, W.te, m, W.tsym, W.esym, W.big,
+                               W.acc + A_NBIG);
         }
-        hipLaunchKernelGGL(k_f5_vertex, dim3(grid_for(n, kBlock / kWave, 8)), dim3(kBlock), 0,
-                           st, g->off, g->adj, n, W.t2, W.acc);
+        hipLaunchKernelGGL(k_f5_vertex,
+                           dim3(std::min(4 * sum_grid, grid_for(n, kBlock / kWave, 8))),
+                           dim3(kBlock), 0, st, g->off, g->adj, n, W.t2, W.acc);
+        GPM_LAUNCH_CHECK("k_f5_local");
+        if (lists) {
+            GPM_HIP(exclusive_scan_i64((const int32_t *)W.te, W.loff, (uint64_t)m, W.scan_tmp, st));
+            hipLaunchKernelGGL(k_f5_lists, dim3(grid_for(m, kBlock / kWave, 16)), dim3(kBlock), 0,
+                               st, g->off, g->adj, g->dag_src, g->dag_adj, L, W.lid, W.lpos);
+            hipLaunchKernelGGL(k_f5_row_tasks, dim3(grid_for(n, kBlock, 4)), dim3(kBlock), 0, st,
+                               W.t2, n, L, W.tasks, W.acc + A_RTASKS);
+        }
+        if (plain && m > 0) {
+            hipLaunchKernelGGL(k_f5_tri, dim3(grid_for(m, kBlock / kWave, 16)), dim3(kBlock), 0,
+                               st, g->off, g->dag_off, g->dag_src, g->dag_adj, W.te, m, L, W.acc);
+            hipLaunchKernelGGL(k_f5_k4, dim3(grid_for(m, kBlock / kWave, 16)), dim3(kBlock), 0,
+                               st, g->off, g->dag_off, g->dag_src, g->dag_adj, W.te, m, L, W.acc);
+        }
     }
     GPM_LAUNCH_CHECK("k_f5_local");
-    if (trace5 && m > 0) {
+    if (lists) {
+        Span sp("k_f5_rows", st);
+        const size_t shmem = (size_t)((((n + 1) / 2 + 3) / 4 * 4) + (n + 31) / 32) * 4;
+        // three 8-wave workgroups per CU where their rows fit, else one of 16 waves
+        if (3 * (shmem + kRowsFixedLds) <= 160 * 1024)
+            hipLaunchKernelGGL(k_f5_rows<512>, dim3((unsigned)cu_count() * 3), dim3(512), shmem, st,
+                               g->off, g->adj, n, W.t2, L, W.tasks, W.acc);
+        else
+            hipLaunchKernelGGL(k_f5_rows<1024>, dim3((unsigned)cu_count()), dim3(1024), shmem, st,
+                               g->off, g->adj, n, W.t2, L, W.tasks, W.acc);
+    }
+    GPM_LAUNCH_CHECK("k_f5_rows");
+    if (lists) {
+        Span sp("k_f5_wheel_lists", st);
+        const size_t per_wave = (size_t)wheel_count_words(g->max_degree) * 4;
+        hipLaunchKernelGGL((k_f5_wheel_lists<1024, true>), dim3((unsigned)cu_count()), dim3(1024),
+                           per_wave, st, g->off, g->dag_src, g->dag_adj, g->max_degree, L, W.big,
+                           W.acc);
+        // a wave per arc: workgroups of as many waves, up to 4, as the LDS allows
+        const int waves = (int)std::max<size_t>(1, std::min<size_t>(4, (150 * 1024) / per_wave));
+        const int per_cu = (int)std::max<size_t>(
+            1, std::min<size_t>(32 / waves, (150 * 1024) / (per_wave * waves + 1024)));
+        const dim3 grid(grid_for((2 * m + kWheelArcs - 1) / kWheelArcs, waves, per_cu));
+        if (waves == 4)
+            hipLaunchKernelGGL((k_f5_wheel_lists<256, false>), grid, dim3(256), per_wave * 4, st,
+                               g->off, g->dag_src, g->dag_adj, g->max_degree, L, W.big, W.acc);
+        else
+            hipLaunchKernelGGL((k_f5_wheel_lists<64, false>), dim3((unsigned)cu_count()), dim3(64),
+                               per_wave, st, g->off, g->dag_src, g->dag_adj, g->max_degree, L,
+                               W.big, W.acc);
+    }
+    GPM_LAUNCH_CHECK("k_f5_wheel_lists");
+    if (trace5 && m > 0 && plain) {
         Span sp("k_f5_trace5", st);
         // 16-bit P2 counters, the bitmaps of N(i) and of each wave's N(a)
         // in 16-wave workgroups; where those bitmaps do not fit (above
@@ -953,13 +1440,13 @@ gpm_status motif_formula_count(const gpm_graph *g, int32_t k, void *ws, uint64_t
         const dim3 grid(grid_for((int64_t)n * nparts, 1, per_cu));
         if (shared)
             hipLaunchKernelGGL((k_f5_trace5<1024, true>), grid, dim3(1024), shmem, st, g->off,
-                               g->adj, n, nparts, W.acc);
+                               g->adj, n, nparts, L, W.acc);
         else
             hipLaunchKernelGGL((k_f5_trace5<1024, false>), grid, dim3(1024), shmem, st, g->off,
-                               g->adj, n, nparts, W.acc);
+                               g->adj, n, nparts, L, W.acc);
     }
     GPM_LAUNCH_CHECK("k_f5_trace5");
-    if (trace5 && m > 0) {
+    if (trace5 && m > 0 && plain) {
         Span sp("k_f5_wheel", st);
         // per wave: the counters c(x, .) and the bitmap of N(i); up to 4
         // waves per workgroup, as many as their LDS allows
@@ -972,14 +1459,12 @@ gpm_status motif_formula_count(const gpm_graph *g, int32_t k, void *ws, uint64_t
         hipLaunchKernelGGL(k_f5_wheel,
                            dim3(grid_for((arcs + kWheelArcs - 1) / kWheelArcs, waves, per_cu)),
                            dim3(waves * kWave), shmem, st, g->off, g->adj, n, g->max_degree,
-                           arcs, W.acc);
+                           arcs, L, W.acc);
     }
     GPM_LAUNCH_CHECK("k_f5_wheel");
     // 4-cycles (edge sets) and the sums over them
     rc = c4_run(g, false, W.shared, W.shared_bytes, W.acc + A_C4, nullptr, 0, nullptr, st,
                 W.tsym, W.acc + A_CYC);
-    if (rc) return rc;
-    rc = clique_run(g, 4, false, W.shared, W.shared_bytes, W.acc + A_K4, nullptr, 0, nullptr, st);
     if (rc) return rc;
     // the direct classes: K5 by the clique kernels, the rest by the general
     // plan as vertex-induced patterns
