@@ -576,7 +576,9 @@ __global__ void __launch_bounds__(kBlock) k_f5_wheel(const int32_t *__restrict__
     if (lane == 0 && sum) atomic_add_u128(acc + A_PLUS + 2 * F_WHEEL, sum);
 }
 
-constexpr uint32_t kBigT = 256;   // arcs of this many triangles: the wheel kernel's workgroup tasks
+// arcs of this many triangles are the wheel kernel's workgroup tasks (RMAT-13,
+// both kernels: 1.57, 1.37, 1.48 ms from 256, 512, 1,024 on)
+constexpr uint32_t kBigT = 512;
 
 // esym and tsym of every arc (one thread per DAG arc, a binary search in
 // each end's row), and the arcs of kBigT triangles or more.
@@ -661,9 +663,11 @@ __global__ void __launch_bounds__(kBlock) k_f5_lists(const int32_t *__restrict__
 }
 
 // Tasks of k_f5_rows beyond one per vertex: a vertex of more than kRowCorners
-// triangles is split into parts that share its neighbours a out in turn
-// (each part builds the row of A^2 again, so parts are large).
-constexpr int32_t kRowCorners = 8192;
+// triangles is split into parts that share its neighbours a out in turn.
+// Each part builds the row of A^2 again; larger parts leave the last ones
+// running alone (RMAT-13, kernel: 2.36, 2.14, 1.97, 2.54 ms for parts of
+// 1,024, 2,048, 4,096 and 8,192).
+constexpr int32_t kRowCorners = 4096;
 constexpr size_t kRowsFixedLds = 8 * 1024;   // at most, beside the row and the bitmap
 constexpr int32_t kMaxRowParts = 64;
 
@@ -707,7 +711,7 @@ __global__ void k_f5_row_tasks(const unsigned long long *__restrict__ t2, int32_
 // LDS reads and the addressing of each entry of C_e.  P2, T and d are below
 // 2^16, so a lane's 64-bit sums hold 2^32 terms.
 template <int NT>
-__global__ void __launch_bounds__(NT) k_f5_rows(const int32_t *__restrict__ off,
+__global__ void __launch_bounds__(NT, NT == 512 ? 8 : 4) k_f5_rows(const int32_t *__restrict__ off,
                                                 const int32_t *__restrict__ adj, int32_t n,
                                                 const unsigned long long *__restrict__ t2, Lists L,
                                                 const RowTask *__restrict__ tasks,
@@ -1118,9 +1122,13 @@ __device__ __forceinline__ u128 load128(const unsigned long long *p) {
 
 // Totals of the formulas, then back-substitution from the densest class.
 // out[0..20] = induced counts, out[21] = status (1: a formula or a
-// subtraction went negative, 2: a count does not fit 64 bits).
-__global__ void k_f5_combine(const unsigned long long *acc, Back B, unsigned long long *out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// subtraction went negative, 2: a count does not fit 64 bits).  One wave, a
+// lane per class: each forms its class's N, then the counts are settled from
+// the densest class down, every lane subtracting its copies inside the class
+// just settled (in one lane the same took 56 us).
+__global__ void __launch_bounds__(kWave) k_f5_combine(const unsigned long long *acc, Back B,
+                                                      unsigned long long *out) {
+    const int h = lane_id();
     unsigned long long bad = 0;
     const u128 T = (u128)acc[A_TRI];
     const u128 nc4 = load128(acc + A_C4);
@@ -1132,13 +1140,9 @@ __global__ void k_f5_combine(const unsigned long long *acc, Back B, unsigned lon
     if (quad % 12 || pend3 % 3 || (two2 & 1)) bad |= 1;
     const u128 k4 = load128(acc + A_K4) + k4l;
     if (cyc_deg2 & 1) bad |= 1;   // twice a sum
-    u128 N[kClasses];
-    for (int h = 0; h < kClasses; h++) {
-        const int f = B.formula_of[h];
-        if (f < 0) {
-            N[h] = 0;
-            continue;
-        }
+    const int f = h < kClasses ? B.formula_of[h] : -1;
+    u128 v = h < kClasses ? (u128)acc[A_DIR + h] : 0;   // N (formula) or the count itself
+    if (f >= 0) {
         u128 p = load128(acc + A_PLUS + 2 * f), mm = load128(acc + A_MINUS + 2 * f);
         // the global terms
         if (f == F_PATH) {
@@ -1157,36 +1161,31 @@ __global__ void k_f5_combine(const unsigned long long *acc, Back B, unsigned lon
         if (f == F_K4PEND || f == F_K4TWO) mm += 12 * k4l;
         if (f == F_C5) mm += 30 * T;   // 5 tr(A^3) = 30 T
         if (p < mm) bad |= 1;
-        N[h] = p - mm;
-        if (f == F_C5) {   // ten closed 5-walks per 5-cycle
-            if (N[h] % 10) bad |= 1;
-            N[h] /= 10;
-        }
-        if (f == F_TWIN) {   // both orders of each pair {c, d}
-            if (N[h] & 1) bad |= 1;
-            N[h] /= 2;
-        }
-        if (f == F_K5E) {   // each triangle at each of its vertices
-            if (N[h] % 3) bad |= 1;
-            N[h] /= 3;
-        }
+        v = p - mm;
+        // ten closed 5-walks per 5-cycle, both orders of each pair {c, d},
+        // each triangle at each of its vertices
+        const uint32_t div = f == F_C5 ? 10u : (f == F_TWIN ? 2u : (f == F_K5E ? 3u : 1u));
+        if (v % div) bad |= 1;
+        v /= div;
     }
     // densest first: a direct class is its count, a formula class its N
     // minus the copies inside denser induced subgraphs
-    u128 I[kClasses];
-    for (int h = kClasses - 1; h >= 0; h--) {
-        if (B.formula_of[h] < 0) {
-            I[h] = (u128)acc[A_DIR + h];
-        } else {
-            u128 sub = 0;
-            for (int k = h + 1; k < kClasses; k++) sub += (u128)B.c[h][k] * I[k];
-            if (N[h] < sub) bad |= 1;
-            I[h] = N[h] - sub;
+    for (int k = kClasses - 1; k > 0; k--) {
+        const u128 Ik = ((u128)(uint64_t)__shfl((uint64_t)(v >> 64), k, kWave) << 64) |
+                        (uint64_t)__shfl((uint64_t)v, k, kWave);
+        if (h < k && f >= 0) {
+            const u128 sub = (u128)B.c[h][k] * Ik;
+            if (v < sub) bad |= 1;
+            v -= sub;
         }
-        if (I[h] >> 64) bad |= 2;
-        out[h] = (unsigned long long)I[h];
     }
-    out[kClasses] = bad;
+    if (h < kClasses) {
+        if (v >> 64) bad |= 2;
+        out[h] = (unsigned long long)v;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) bad |= __shfl_xor(bad, o, kWave);
+    if (h == 0) out[kClasses] = bad;
 }
 
 __global__ void k_copy_u64(const unsigned long long *src, unsigned long long *dst) {
@@ -1393,9 +1392,10 @@ gpm_status motif_formula_count(const gpm_graph *g, int32_t k, void *ws, uint64_t
     if (lists) {
         Span sp("k_f5_rows", st);
         const size_t shmem = (size_t)((((n + 1) / 2 + 3) / 4 * 4) + (n + 31) / 32) * 4;
-        // three 8-wave workgroups per CU where their rows fit, else one of 16 waves
-        if (3 * (shmem + kRowsFixedLds) <= 160 * 1024)
-            hipLaunchKernelGGL(k_f5_rows<512>, dim3((unsigned)cu_count() * 3), dim3(512), shmem, st,
+        // four 8-wave workgroups per CU where their rows fit, else one of 16
+        // waves (RMAT-13: 2.5 ms with four, 2.9 with three, 3.7 with the one)
+        if (4 * (shmem + kRowsFixedLds) <= 160 * 1024)
+            hipLaunchKernelGGL(k_f5_rows<512>, dim3((unsigned)cu_count() * 4), dim3(512), shmem, st,
                                g->off, g->adj, n, W.t2, L, W.tasks, W.acc);
         else
             hipLaunchKernelGGL(k_f5_rows<1024>, dim3((unsigned)cu_count()), dim3(1024), shmem, st,

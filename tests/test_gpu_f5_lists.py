@@ -1,5 +1,5 @@
 """The 5-motif formulas with and without the common-neighbour lists: dense
-graphs whose lists exceed their arena (counted without them), edges of 256
+graphs whose lists exceed their arena (counted without them), edges of 512
 triangles and more, vertices split into several tasks; closed forms and the
 enumeration route."""
 from math import comb
@@ -29,11 +29,15 @@ def test_complete_graphs(gpm, n):
 
 
 def test_big_arcs_and_split_vertices(gpm):
-    """K_260 beside a cycle of 60,000: 258 triangles on an edge (a workgroup
-    per arc), 33,411 at a vertex (five tasks), and room for the lists."""
-    e = graphgen.disjoint_union([graphgen.complete_graph(260), graphgen.cycle_graph(60000)])
+    """K_514 beside K_{300,800}: 512 triangles on an edge (a workgroup per
+    arc), 131,328 at a vertex (many tasks), and room for the lists.  K_{a,b}
+    alone has 4-stars and K_{2,3} copies, two classes."""
+    a, b = 300, 800
+    e = graphgen.disjoint_union([graphgen.complete_graph(514), graphgen.complete_bipartite(a, b)])
     want = [0] * 21
-    want[20], want[2] = comb(260, 5), 60000
+    want[20] = comb(514, 5)
+    want[0] = a * comb(b, 4) + b * comb(a, 4)
+    want[10] = comb(a, 2) * comb(b, 3) + comb(a, 3) * comb(b, 2)
     assert gpm.motif_count_formula(build(gpm, graphgen.relabel(e, 5)), 5) == want
 
 
