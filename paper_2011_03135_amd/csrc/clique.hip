@@ -375,8 +375,8 @@ __global__ void __launch_bounds__(kBlock, MODE == TC_COUNT ? 8 : 4)
     k_tc_seg(const int32_t *__restrict__ off, const int32_t *__restrict__ adj,
              const int32_t *__restrict__ okey, const int32_t *__restrict__ dag_off,
              const int32_t *__restrict__ dag_adj, const TcTask *__restrict__ tasks,
-             const uint32_t *__restrict__ ntasks_p, Tau tau, uint32_t *cursor,
-             unsigned long long *result, uint32_t *te, RowEmitter em) {
+             const uint32_t *__restrict__ ntasks_p, Tau tau,
+             unsigned long long *cursor, unsigned long long *result, uint32_t *te, RowEmitter em) {
     constexpr int TU = 4;                        // tiles in flight
     constexpr int H = HUB ? 4 : 4096;
     constexpr bool ARCS = MODE == TC_ARCS, VALS = ARCS && !HUB;
@@ -387,19 +387,22 @@ __global__ void __launch_bounds__(kBlock, MODE == TC_COUNT ? 8 : 4)
     __shared__ uint32_t scnt[ARCS ? kBlock : 1];
     __shared__ int32_t sy[MODE == TC_LIST ? kBlock : 1];   // y, or ~y for y -> x
     __shared__ int32_t s_sum[kWPB];
-    __shared__ uint32_t s_task;
+    __shared__ int32_t s_task;
     const int tid = threadIdx.x, lane = lane_id();
     const int wid = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int grp = lane / kTcUnit, gl = lane % kTcUnit;
-    const uint32_t ntasks = *ntasks_p;
+    TaskQueue queue(cursor, *ntasks_p, blockIdx.x, gridDim.x);
     uint64_t acc = 0;   // wave-uniform
     if (VALS)
         for (int i = tid; i < kTcMaxD; i += kBlock) cnt[i] = 0;
     for (;;) {
-        if (tid == 0) s_task = atomicAdd(cursor, 1u);
+        if (wid == 0) {
+            const int32_t got = (int32_t)queue.next();
+            if (lane == 0) s_task = got;
+        }
         __syncthreads();
-        const uint32_t t = s_task;
-        if (t >= ntasks) break;
+        const int32_t t = s_task;
+        if (t < 0) break;
         const int32_t x = tasks[t].x, c0 = tasks[t].c0;
         const int32_t s = dag_off[x], d = dag_off[x + 1] - s;
         const int32_t r0 = off[x], cz = min(off[x + 1] - r0, c0 + tc_task_nbrs(d, tau));
@@ -970,10 +973,12 @@ __global__ void __launch_bounds__(kBlock) k_clique_hub(const int32_t *__restrict
 
 // ------------------------------------------------------------ host side --
 
+constexpr uint64_t kCtlCur = 32, kCtlWords = kCtlCur + 2 * kCursorWords;
+
 struct CliqueWs {
     unsigned long long *ctr;      // [8]: [0] listing slots, [1] row words, [2] hubs, [3..7] unused
-    uint32_t *ctl;                // [16]: [0..1] triangle cursors, [2..3] triangle tasks,
-                                  // [4..7] class counts
+    uint32_t *ctl;                // [2..3] triangle tasks, [4..7] class counts, from
+                                  // kCtlCur two sets of cursors (triangles)
     int32_t *list_s, *list_m, *list_b, *list_h;
     int64_t *rowoff_b, *hpre;
     TcTask *tasks, *hub_tasks;
@@ -1024,7 +1029,7 @@ CliqueWs clique_layout(const gpm_graph *g, int32_t k, bool list, void *base) {
     Carve c(base, ~0ull);
     const uint64_t n1 = (uint64_t)g->n + 1;
     W.ctr = c.take<unsigned long long>(8);
-    W.ctl = c.take<uint32_t>(16);
+    W.ctl = c.take<uint32_t>(kCtlWords);
     const bool generic = uses_generic(g, k, list);
     if (!generic && k == 3) {
         if (g->max_out_degree > kTcArcMax) W.tasks = c.take<TcTask>(tc_task_bound(g));
@@ -1151,7 +1156,8 @@ static gpm_status tc_launch(const gpm_graph *g, CliqueWs &W, unsigned long long 
         {
             Span sp(MODE == TC_LIST ? "k_tc_seg<list>" : (MODE == TC_ARCS ? "k_tc_seg<arcs>" : "k_tc_seg"), st);
             hipLaunchKernelGGL((k_tc_seg<MODE, false>), grid, dim3(kBlock), 0, st, g->off, g->adj,
-                               g->okey, g->dag_off, g->dag_adj, W.tasks, W.ctl + 2, tau, W.ctl + 0,
+                               g->okey, g->dag_off, g->dag_adj, W.tasks, W.ctl + 2, tau,
+                               (unsigned long long *)(W.ctl + kCtlCur),
                                res, te, em);
         }
         GPM_LAUNCH_CHECK("k_tc_seg");
@@ -1159,7 +1165,7 @@ static gpm_status tc_launch(const gpm_graph *g, CliqueWs &W, unsigned long long 
             Span sp("k_tc_seg<hub>", st);
             hipLaunchKernelGGL((k_tc_seg<MODE, true>), grid, dim3(kBlock), 0, st, g->off, g->adj,
                                g->okey, g->dag_off, g->dag_adj, W.hub_tasks, W.ctl + 3, tau,
-                               W.ctl + 1, res, te, em);
+                               (unsigned long long *)(W.ctl + kCtlCur + kCursorWords), res, te, em);
         }
         GPM_LAUNCH_CHECK("k_tc_seg<hub>");
     }
@@ -1178,7 +1184,7 @@ gpm_status triangle_arc_counts(const gpm_graph *g, void *ws, uint64_t ws_bytes, 
                                unsigned long long *tri, hipStream_t st, WordRun also) {
     CliqueWs W = clique_layout(g, 3, false, ws);
     if (W.bytes > ws_bytes) return fail(GPM_OUT_OF_MEMORY, "workspace smaller than required");
-    GPM_HIP(zero_words(st, {{te, (uint64_t)g->m}, {tri, 2}, {W.ctr, 16}, {W.ctl, 16}, also}));
+    GPM_HIP(zero_words(st, {{te, (uint64_t)g->m}, {tri, 2}, {W.ctr, 16}, {W.ctl, kCtlWords}, also}));
     return tc_launch<TC_ARCS>(g, W, tri, te, st);
 }
 
@@ -1191,7 +1197,7 @@ gpm_status clique_run(const gpm_graph *g, int32_t k, bool list, void *ws, uint64
     // counts go straight to the caller's word, listing totals and checksums
     // to its three; the slot counter is in the workspace
     unsigned long long *res = list ? d_result : d_count;
-    GPM_HIP(zero_words(st, {{res, list ? 6u : 2u}, {W.ctr, 16}, {W.ctl, 16},
+    GPM_HIP(zero_words(st, {{res, list ? 6u : 2u}, {W.ctr, 16}, {W.ctl, kCtlWords},
                             {W.lg, W.lg ? kLgCtlWords : 0}}));
     const bool generic = uses_generic(g, k, list);
     RowEmitter em{W.ctr, d_buf, list ? cap : 0, 0, 0, 0};
@@ -1267,7 +1273,7 @@ gpm_status clique_multi_run(const gpm_graph *g, int32_t kmax, void *ws, uint64_t
     // d_counts = {triangles, 4-cliques[, 5-cliques]}
     unsigned long long *res = d_counts + (kmax - 3), *res3 = d_counts;
     unsigned long long *res4 = kmax == 5 ? d_counts + 1 : nullptr;
-    GPM_HIP(zero_words(st, {{d_counts, (uint64_t)(2 * (kmax - 2))}, {W.ctr, 16}, {W.ctl, 16},
+    GPM_HIP(zero_words(st, {{d_counts, (uint64_t)(2 * (kmax - 2))}, {W.ctr, 16}, {W.ctl, kCtlWords},
                             {W.lg, W.lg ? kLgCtlWords : 0}}));
     if (lg_disabled(kmax)) {
         // without local graphs: every root of out-degree >= 2 per arc

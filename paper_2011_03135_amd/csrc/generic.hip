@@ -15,7 +15,7 @@
 // Kernels.  Steps 0 and 1 are the arcs of the symmetric CSR.  A first pass
 // counts, per arc the partial orders accept, the 64-candidate chunks of
 // step 2; their exclusive scan numbers the work units (arc, chunk), which
-// waves take from an atomic cursor, running the depth-first search below
+// waves take as they become free, running the depth-first search below
 // the chunk with a per-wave stack in LDS.  At step s >= 2 the candidates
 // are a row of the symmetric CSR: that of the already matched backward
 // neighbour with the fewest entries, cut by binary search to the range the
@@ -272,13 +272,13 @@ __global__ void __launch_bounds__(kGenNT) k_generic(const int32_t *__restrict__ 
         wave_sync();
     };
     // a work unit is one 64-candidate chunk of step 2 below one arc (steps
-    // 0 and 1), with the whole search below it; units come from an atomic
-    // cursor, so a hub's arcs and chunks spread over the grid
+    // 0 and 1), with the whole search below it; units come from
+    // work cursors, so a hub's arcs and chunks spread over the grid
+    TaskQueue queue(cursor, nchunks, wib * gridDim.x + blockIdx.x,
+                    gridDim.x * (kGenNT / kWave));
     for (;;) {
-        unsigned long long got = 0;
-        if (lane == 0) got = atomicAdd(cursor, 1ull);
-        const int64_t c = (int64_t)__shfl(got, 0);
-        if (c >= nchunks) break;   // wave-uniform
+        const int64_t c = queue.next();
+        if (c < 0) break;   // wave-uniform
         int64_t lo = 0, hi = narcs;   // the arc of unit c: last a with chunk_off[a] <= c
         while (hi - lo > 1) {
             const int64_t mid = (lo + hi) >> 1;
@@ -583,7 +583,7 @@ static void gen_layout(Carve &cv, int64_t narcs, int32_t **chunks, int64_t **chu
     *chunks = cv.take<int32_t>((uint64_t)std::max<int64_t>(narcs, 1));
     *chunk_off = cv.take<int64_t>((uint64_t)narcs + 1);
     *tmp = cv.take<int64_t>(scan_tmp_words((uint64_t)narcs));
-    *cursor = cv.take<unsigned long long>(2);   // work cursor, listing slot counter
+    *cursor = cv.take<unsigned long long>(kCursorWords / 2 + 1);   // work cursors, listing slot counter
 }
 
 uint64_t generic_workspace_bytes(const gpm_graph *g) {
@@ -613,8 +613,8 @@ static gpm_status generic_run(const gpm_graph *g, const gpm_pattern *p, bool lis
     GPM_HIP(fill_u32(reinterpret_cast<uint32_t *>(out), 0, list ? 6 : 2, st));
     if (g->m == 0) return GPM_OK;
     Span sp(list ? "k_generic_list" : "k_generic", st);
-    GPM_HIP(fill_u32(cursor, 0, 4, st));
-    RowEmitter em{cursor + 1, buf, list ? cap : 0, 0, 0, 0};
+    GPM_HIP(fill_u32(cursor, 0, kCursorWords + 2, st));
+    RowEmitter em{cursor + kCursorWords / 2, buf, list ? cap : 0, 0, 0, 0};
     const unsigned cblocks = (unsigned)std::min<int64_t>((narcs + 255) / 256, 4096);
     if (list && P.k == 2) {
         hipLaunchKernelGGL(k_gen_list2, dim3(cblocks), dim3(256), 0, st, g->off, g->adj, g->n, P,

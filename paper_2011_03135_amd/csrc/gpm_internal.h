@@ -85,9 +85,17 @@ struct WordRun {
     uint64_t n;
 };
 hipError_t zero_words(hipStream_t s, std::initializer_list<WordRun> runs);
+// Work cursors.  A kernel whose workers (a workgroup, or a wave) take their
+// tasks as they become free does so from kCursors counters, each in a cache
+// line of its own.  One counter serves a task about every 12 ns whatever the
+// grid (24 ns in kernels that also load), so that it bounds a kernel of many
+// small tasks: 65,536 of them take 750 us at one counter, 120 us at 8, and 18
+// us at 64 (8 counters in one line are no better than one).
+constexpr int kCursors = 16, kCursorStride = 16;          // u64 words
+constexpr uint64_t kCursorWords = 2ull * kCursors * kCursorStride;   // 32-bit words, zero on entry
 // The words at the front of the local-graph workspace that must be zero when
-// the clique kernels start.
-constexpr uint64_t kLgCtlWords = 32;
+// the clique kernels start: counts, then 7 sets of cursors.
+constexpr uint64_t kLgCtlWords = 64 + 7 * kCursorWords;
 // key[v] = off[v + 1] - off[v] for v < n (the degree order's key).
 hipError_t degree_key(const int32_t *off, int32_t n, int32_t *key, hipStream_t s);
 // Exclusive scan of n int32 counts into out[0..n] (out[n] = total), using
@@ -401,6 +409,53 @@ __device__ __forceinline__ void walk_lookup(const int32_t *pre, const int32_t *o
         j = __builtin_amdgcn_readlane(jj[U - 1], 63);
     }
 }
+
+// The tasks 0 .. n - 1 as a worker (worker < workers) takes them; one whole
+// wave of the worker calls next(), which gives -1 when none is left.  Counter
+// w gives out tasks w, w + kCursors, ..., so the order is about that of one
+// counter; a worker starts at counter worker % kCursors (with one worker per
+// workgroup, the workgroups of one XCD) and goes on to another when it is used
+// up, found by one look at all of them (a lane each, so that the kernel needs
+// no registers for it) and not by adding to each.  With no more tasks than
+// workers, each takes the one of its own number.
+struct TaskQueue {
+    unsigned long long *cur;
+    int64_t n;
+    int32_t w;
+    uint32_t open;   // bit i: counter i is not known to be used up; 0: a task per worker
+    __device__ TaskQueue(unsigned long long *c, int64_t n_tasks, int32_t worker, int32_t workers)
+        : cur(c), n(n_tasks) {
+        const bool one = n_tasks <= workers;
+        w = one ? worker : worker % kCursors;
+        open = one ? 0u : (2u << kCursors) - 1u;   // (bit kCursors keeps it from 0)
+        w = __builtin_amdgcn_readfirstlane(w);
+    }
+    __device__ __forceinline__ int64_t next() {
+        if (!open) {
+            const int64_t t = w;
+            w = INT32_MAX;
+            return t < n ? t : -1;
+        }
+        while (w >= 0) {
+            unsigned long long got = 0;
+            if (lane_id() == 0) got = atomicAdd(cur + w * kCursorStride, 1ull);
+            const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)got);
+            const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(got >> 32));
+            const int64_t t = (int64_t)(((uint64_t)hi << 32) | lo) * kCursors + w;
+            if (t < n) return t;
+            open &= ~(1u << w);
+            // the next counter after w, cyclically, that has tasks left
+            const int i = lane_id() % kCursors;
+            const unsigned long long c = __hip_atomic_load(
+                cur + i * kCursorStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t left = (uint32_t)__ballot((int64_t)c * kCursors + i < n) & open &
+                                  ((1u << kCursors) - 1u);
+            const uint32_t after = left & ~((2u << w) - 1u);
+            w = left ? __builtin_ctz(after ? after : left) : -1;
+        }
+        return -1;
+    }
+};
 
 // The entries of 64 segments (one per lane: first entry st, len entries),
 // shared out over the wave: segments are cut into units of 16 entries, a unit

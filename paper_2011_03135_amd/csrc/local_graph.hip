@@ -72,7 +72,8 @@ __device__ __forceinline__ int select_bit64(uint64_t x, int r) {
 template <int NT>
 struct Lds {
     int32_t s_sum[NT / kWave];
-    uint32_t s_task, s_next;
+    int32_t s_task;
+    uint32_t s_next;
     int32_t s_slices;
     uint64_t s_tri;
 };
@@ -281,7 +282,7 @@ __global__ void __launch_bounds__(NT, DMAX == kHalfMaxD ? 6 : 1) k_lg4(const int
                                             const int32_t *__restrict__ dag_adj,
                                             const int32_t *__restrict__ roots,
                                             const int32_t *__restrict__ nroots_p, int32_t dlo,
-                                            uint32_t *cursor, unsigned long long *result,
+                                            unsigned long long *cursor, unsigned long long *result,
                                             unsigned long long *res3, RowEmitter em) {
     __shared__ uint64_t rows[DMAX * (DMAX / 64)];
     __shared__ __align__(16) int32_t keys[LgHash<DMAX>::kSlots];
@@ -291,14 +292,18 @@ __global__ void __launch_bounds__(NT, DMAX == kHalfMaxD ? 6 : 1) k_lg4(const int
     __shared__ int16_t lidx[RANK ? DMAX : 1];
     __shared__ Lds<NT> sh;
     const int tid = threadIdx.x;
-    const int32_t nroots = *nroots_p;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    TaskQueue queue(cursor, *nroots_p, blockIdx.x, gridDim.x);
     uint64_t acc = 0;
     for (;;) {
-        if (tid == 0) sh.s_task = atomicAdd(cursor, 1u);
+        if (wave == 0) {
+            const int32_t got = (int32_t)queue.next();
+            if (tid == 0) sh.s_task = got;
+        }
         __syncthreads();
-        const int32_t r = (int32_t)sh.s_task;
+        const int32_t r = sh.s_task;
         __syncthreads();
-        if (r >= nroots) break;
+        if (r < 0) break;
         const int32_t u = roots[r];
         const int32_t d = dag_off[u + 1] - dag_off[u], W = (d + 63) >> 6;
         if (d <= dlo || d > DMAX) continue;
@@ -347,7 +352,7 @@ __global__ void __launch_bounds__(NT, DMAX == kHalfMaxD ? 6 : 1) k_lg_build(cons
                                                  const int32_t *__restrict__ dag_adj,
                                                  const int32_t *__restrict__ roots,
                                                  const int32_t *__restrict__ nroots_p, int32_t dlo,
-                                                 uint32_t *cursor, const int64_t *__restrict__ rowoff,
+                                                 unsigned long long *cursor, const int64_t *__restrict__ rowoff,
                                                  uint64_t *grows, LgTask *tasks, uint32_t *ntasks,
                                                  unsigned long long *units,
                                                  unsigned long long *res3,
@@ -360,14 +365,18 @@ __global__ void __launch_bounds__(NT, DMAX == kHalfMaxD ? 6 : 1) k_lg_build(cons
     __shared__ int32_t verts[DMAX];
     __shared__ Lds<NT> sh;
     const int tid = threadIdx.x;
-    const int32_t nroots = *nroots_p;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    TaskQueue queue(cursor, *nroots_p, blockIdx.x, gridDim.x);
     if (tid == 0) sh.s_tri = 0;
     for (;;) {
-        if (tid == 0) sh.s_task = atomicAdd(cursor, 1u);
+        if (wave == 0) {
+            const int32_t got = (int32_t)queue.next();
+            if (tid == 0) sh.s_task = got;
+        }
         __syncthreads();
-        const int32_t r = (int32_t)sh.s_task;
+        const int32_t r = sh.s_task;
         __syncthreads();
-        if (r >= nroots) break;
+        if (r < 0) break;
         const int32_t u = roots[r];
         const int32_t d = dag_off[u + 1] - dag_off[u], W = (d + 63) >> 6;
         if (d <= dlo || d > DMAX) continue;
@@ -606,7 +615,7 @@ __global__ void __launch_bounds__(1024) k_lg5(const int32_t *__restrict__ dag_of
                                               const int64_t *__restrict__ rowoff,
                                               const uint64_t *__restrict__ grows,
                                               int32_t rows_words, int32_t extra,
-                                              uint32_t *cursor, unsigned long long *result,
+                                              unsigned long long *cursor, unsigned long long *result,
                                               RowEmitter em) {
     // row widths of the class: out-degrees (DMAX/4, DMAX]
     constexpr int WLO = DMAX / 256 + 1, WHI = DMAX / 64;
@@ -622,14 +631,18 @@ __global__ void __launch_bounds__(1024) k_lg5(const int32_t *__restrict__ dag_of
                          (size_t)wib * (DMAX * 2 + (size_t)(extra + 1) * 2 * (DMAX / 64) * 8);
     int16_t *mem = reinterpret_cast<int16_t *>(wave_area);
     uint64_t *stack = reinterpret_cast<uint64_t *>(wave_area + DMAX * 2);
-    const uint32_t ntasks = *ntasks_p;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    TaskQueue queue(cursor, *ntasks_p, blockIdx.x, gridDim.x);
     uint64_t acc = 0;
     for (;;) {
-        if (tid == 0) sh.s_task = atomicAdd(cursor, 1u);
+        if (wave == 0) {
+            const int32_t got = (int32_t)queue.next();
+            if (tid == 0) sh.s_task = got;
+        }
         __syncthreads();
-        const uint32_t t = sh.s_task;
+        const int32_t t = sh.s_task;
         __syncthreads();
-        if (t >= ntasks) break;
+        if (t < 0) break;
         const int32_t r = tasks[t].r, slice = tasks[t].slice, S = tasks[t].slices;
         const int32_t u = roots[r];
         const int32_t d = dag_off[u + 1] - dag_off[u], W = (d + 63) >> 6;
@@ -680,7 +693,7 @@ __global__ void __launch_bounds__(NT) k_lg5_mid(const int32_t *__restrict__ off,
                                                 const int32_t *__restrict__ dag_adj,
                                                 const int32_t *__restrict__ roots,
                                                 const int32_t *__restrict__ nroots_p,
-                                                int32_t extra, uint32_t *cursor,
+                                                int32_t extra, unsigned long long *cursor,
                                                 unsigned long long *result,
                                                 unsigned long long *res3,
                                                 unsigned long long *res4, RowEmitter em) {
@@ -701,9 +714,11 @@ __global__ void __launch_bounds__(NT) k_lg5_mid(const int32_t *__restrict__ off,
     const int32_t nroots = *nroots_p;
     uint64_t acc = 0, acc3 = 0, acc4 = 0;
     for (;;) {
-        if (tid == 0) sh.s_task = atomicAdd(cursor, 1u);
+        // (one counter: a root takes about 2 us of a workgroup, and with
+        // spread cursors the kernel took 6.2 ms instead of 5.8 on RMAT-20)
+        if (tid == 0) sh.s_task = (int32_t)atomicAdd(cursor, 1ull);
         __syncthreads();
-        const int32_t r = (int32_t)sh.s_task;
+        const int32_t r = sh.s_task;
         __syncthreads();
         if (r >= nroots) break;
         const int32_t u = roots[r];
@@ -750,7 +765,10 @@ __global__ void __launch_bounds__(NT) k_lg5_mid(const int32_t *__restrict__ off,
 }
 
 struct LgWs {
-    uint32_t *ctl;                 // [0..7] cursors, [8] 5-clique tasks
+    unsigned long long *cursor(int i) const {
+        return reinterpret_cast<unsigned long long *>(ctl + 64 + i * kCursorWords);
+    }
+    uint32_t *ctl;                 // [8] 5-clique tasks, from 64 the sets of cursors
     unsigned long long *units;     // local triangles (5-cliques' work)
     LgTask *tasks;
     uint64_t *rows_b;
@@ -799,7 +817,7 @@ gpm_status lg5_big(const gpm_graph *g, int32_t k, LgWs &L, const int32_t *list, 
         hipLaunchKernelGGL((k_lg_build<kHalfMaxD, kHalfThreads>),
                            roots_grid(g, kMidMaxD, kHalfBlocksPerCu), dim3(kHalfThreads), 0, st,
                            g->off, g->okey, g->dag_off, g->dag_adj, list, cnt, kMidMaxD,
-                           L.ctl + 4, rowoff, L.rows_b, L.tasks, ntasks, L.units, res3, res4,
+                           L.cursor(4), rowoff, L.rows_b, L.tasks, ntasks, L.units, res3, res4,
                            slice5);
     }
     GPM_LAUNCH_CHECK("k_lg_build<512>");
@@ -807,7 +825,7 @@ gpm_status lg5_big(const gpm_graph *g, int32_t k, LgWs &L, const int32_t *list, 
         Span sp("k_lg_build<1024>", st);
         hipLaunchKernelGGL((k_lg_build<kBigMaxD, kBigThreads>), roots_grid(g, kHalfMaxD, 1),
                            dim3(kBigThreads), 0, st, g->off, g->okey, g->dag_off, g->dag_adj, list,
-                           cnt, kHalfMaxD, L.ctl + 2, rowoff, L.rows_b, L.tasks, ntasks, L.units,
+                           cnt, kHalfMaxD, L.cursor(2), rowoff, L.rows_b, L.tasks, ntasks, L.units,
                            res3, res4, slice5);
     }
     GPM_LAUNCH_CHECK("k_lg_build<1024>");
@@ -830,11 +848,11 @@ gpm_status lg5_big(const gpm_graph *g, int32_t k, LgWs &L, const int32_t *list, 
         if (em)
             hipLaunchKernelGGL((k_lg5<kBigMaxD, true>), grid, dim3(waves * kWave), shmem, st,
                                g->dag_off, list, L.tasks, ntasks, rowoff,
-                               (const uint64_t *)L.rows_b, rows_words, extra, L.ctl + 3, res, *em);
+                               (const uint64_t *)L.rows_b, rows_words, extra, L.cursor(3), res, *em);
         else
             hipLaunchKernelGGL((k_lg5<kBigMaxD, false>), grid, dim3(waves * kWave), shmem, st,
                                g->dag_off, list, L.tasks, ntasks, rowoff,
-                               (const uint64_t *)L.rows_b, rows_words, extra, L.ctl + 3, res,
+                               (const uint64_t *)L.rows_b, rows_words, extra, L.cursor(3), res,
                                RowEmitter{});
         span_units(L.units, st);
     }
@@ -871,11 +889,11 @@ gpm_status lg_cliques(const gpm_graph *g, int32_t k, const int32_t *list_m, cons
             if (em)
                 hipLaunchKernelGGL((k_lg4<kBigMaxD, kBigThreads, true, true>), grid,
                                    dim3(kBigThreads), 0, st, g->off, g->okey, g->dag_off,
-                                   g->dag_adj, list_b, cnt_b, kHalfMaxD, L.ctl + 0, res, res3, *em);
+                                   g->dag_adj, list_b, cnt_b, kHalfMaxD, L.cursor(0), res, res3, *em);
             else
                 hipLaunchKernelGGL((k_lg4<kBigMaxD, kBigThreads, false, true>), grid,
                                    dim3(kBigThreads), 0, st, g->off, g->okey, g->dag_off,
-                                   g->dag_adj, list_b, cnt_b, kHalfMaxD, L.ctl + 0, res, res3,
+                                   g->dag_adj, list_b, cnt_b, kHalfMaxD, L.cursor(0), res, res3,
                                    none);
         }
         GPM_LAUNCH_CHECK("k_lg4<1024>");
@@ -885,11 +903,11 @@ gpm_status lg_cliques(const gpm_graph *g, int32_t k, const int32_t *list_m, cons
             if (em)
                 hipLaunchKernelGGL((k_lg4<kHalfMaxD, kHalfThreads, true, true>), grid,
                                    dim3(kHalfThreads), 0, st, g->off, g->okey, g->dag_off, g->dag_adj,
-                                   list_b, cnt_b, kMidMaxD, L.ctl + 2, res, res3, *em);
+                                   list_b, cnt_b, kMidMaxD, L.cursor(2), res, res3, *em);
             else
                 hipLaunchKernelGGL((k_lg4<kHalfMaxD, kHalfThreads, false, true>), grid,
                                    dim3(kHalfThreads), 0, st, g->off, g->okey, g->dag_off, g->dag_adj,
-                                   list_b, cnt_b, kMidMaxD, L.ctl + 2, res, res3, none);
+                                   list_b, cnt_b, kMidMaxD, L.cursor(2), res, res3, none);
         }
         GPM_LAUNCH_CHECK("k_lg4<512>");
         if (g->max_out_degree > kWave) {
@@ -898,11 +916,11 @@ gpm_status lg_cliques(const gpm_graph *g, int32_t k, const int32_t *list_m, cons
             if (em)
                 hipLaunchKernelGGL((k_lg4<kMidMaxD, kMidThreads, true, false>), grid,
                                    dim3(kMidThreads), 0, st, g->off, g->okey, g->dag_off, g->dag_adj,
-                                   list_m, cnt_m, 0, L.ctl + 1, res, res3, *em);
+                                   list_m, cnt_m, 0, L.cursor(1), res, res3, *em);
             else
                 hipLaunchKernelGGL((k_lg4<kMidMaxD, kMidThreads, false, false>), grid,
                                    dim3(kMidThreads), 0, st, g->off, g->okey, g->dag_off, g->dag_adj,
-                                   list_m, cnt_m, 0, L.ctl + 1, res, res3, none);
+                                   list_m, cnt_m, 0, L.cursor(1), res, res3, none);
         }
         GPM_LAUNCH_CHECK("k_lg4<256>");
         return GPM_OK;
@@ -915,11 +933,11 @@ gpm_status lg_cliques(const gpm_graph *g, int32_t k, const int32_t *list_m, cons
         if (em)
             hipLaunchKernelGGL((k_lg5_mid<kMidMaxD, kMidThreads, true>), grid, dim3(kMidThreads), 0,
                                st, g->off, g->okey, g->dag_off, g->dag_adj, list_m, cnt_m, k - 5,
-                               L.ctl + 6, res, res3, res4, *em);
+                               L.cursor(6), res, res3, res4, *em);
         else
             hipLaunchKernelGGL((k_lg5_mid<kMidMaxD, kMidThreads, false>), grid, dim3(kMidThreads),
                                0, st, g->off, g->okey, g->dag_off, g->dag_adj, list_m, cnt_m, k - 5,
-                               L.ctl + 6, res, res3, res4, RowEmitter{});
+                               L.cursor(6), res, res3, res4, RowEmitter{});
     }
     GPM_LAUNCH_CHECK("k_lg5_mid");
     return GPM_OK;

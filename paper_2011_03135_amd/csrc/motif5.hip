@@ -123,15 +123,16 @@ enum Acc : int {
     A_CYC = A_C4 + 2,                 // 2 u128: 4-cycle sums (degrees, doubled; edge triangles)
     A_K4 = A_CYC + 4,                 // u128: 4-cliques (without lists)
     A_DIR = A_K4 + 2,                 // kClasses u64: induced counts of the direct classes
-    A_CURSOR = A_DIR + kClasses,      // u64: the wheel kernel's work cursor
-    A_TCURSOR = A_CURSOR + 1,         // u64: the A^2-row kernel's task cursor
-    A_BCURSOR = A_TCURSOR + 1,        // u64: the wheel kernel's cursor over the big arcs
-    A_NBIG = A_BCURSOR + 1,           // u64: the big arcs
+    A_NBIG = A_DIR + kClasses,        // u64: the big arcs
     A_RTASKS = A_NBIG + 1,            // u64: tasks of the split vertices
     A_QUAD = A_RTASKS + 1,            // u128: 12 times the 4-cliques (lists)
     A_PEND = A_QUAD + 2,              // u128: 3 times their vertices' degrees
     A_TWO = A_PEND + 2,               // u128: twice their edges' triangles
-    A_WORDS = A_TWO + 2,
+    A_SETS = (A_TWO + 2 + 15) / 16 * 16,   // cursors:
+    A_CURSOR = A_SETS,                     // of the wheel kernel,
+    A_TCURSOR = A_CURSOR + (int)kCursorWords / 2,    // of the A^2-row kernel,
+    A_BCURSOR = A_TCURSOR + (int)kCursorWords / 2,   // of the wheel kernel over the big arcs
+    A_WORDS = A_BCURSOR + (int)kCursorWords / 2,
 };
 
 __device__ __forceinline__ u128 binom2(uint64_t n) { return n < 2 ? 0 : (u128)n * (n - 1) / 2; }
@@ -296,13 +297,16 @@ __global__ void __launch_bounds__(NT) k_f5_trace5(const int32_t *__restrict__ of
     u128 tr = 0, k23 = 0, twin = 0, k5e = 0;
     // tasks (i, part) from a cursor, the parts from the last down, so that
     // the vertices of highest degree start first
-    const int64_t ntasks = (int64_t)n * nparts;
+    TaskQueue queue(acc + A_TCURSOR, (int64_t)n * nparts, blockIdx.x, gridDim.x);
     for (;;) {
-        if (tid == 0) s_task = (int64_t)atomicAdd(acc + A_TCURSOR, 1ull);
+        if (wid == 0) {
+            const int64_t got = queue.next();
+            if (lane == 0) s_task = got;
+        }
         __syncthreads();
         const int64_t t = s_task;
         __syncthreads();
-        if (t >= ntasks) break;
+        if (t < 0) break;
         const int32_t part = nparts - 1 - (int32_t)(t / n), i = (int32_t)(t % n);
         const int32_t si = off[i], di = off[i + 1] - si;
         const int32_t a_lo = part * kTracePart;
@@ -493,11 +497,11 @@ __global__ void __launch_bounds__(kBlock) k_f5_wheel(const int32_t *__restrict__
     u128 sum = 0;
     int32_t cur = -1;   // the vertex whose neighbours are marked
     const int64_t nblocks = (arcs + kWheelArcs - 1) / kWheelArcs;
+    TaskQueue queue(acc + A_CURSOR, nblocks, wid * gridDim.x + blockIdx.x,
+                    gridDim.x * (kBlock / kWave));
     for (;;) {
-        unsigned long long r = 0;
-        if (lane == 0) r = atomicAdd(acc + A_CURSOR, 1ull);
-        const int64_t b = __shfl((int64_t)r, 0, kWave);
-        if (b >= nblocks) break;
+        const int64_t b = queue.next();
+        if (b < 0) break;
         const int64_t t0 = b * kWheelArcs, t1 = t0 + kWheelArcs < arcs ? t0 + kWheelArcs : arcs;
         // the row holding arc t0: off[i] <= t0 < off[i + 1]
         int32_t lo = 0, hi = n;
@@ -731,15 +735,19 @@ __global__ void __launch_bounds__(NT, NT == 512 ? 8 : 4) k_f5_rows(const int32_t
     for (int32_t k = tid; k < hw4 + nbw; k += NT) p2w[k] = 0;
     sq[lane] = 0;
     __syncthreads();
-    const int64_t nsplit = (int64_t)acc[A_RTASKS], ntasks = nsplit + n;
+    const int64_t nsplit = (int64_t)acc[A_RTASKS];
+    TaskQueue queue(acc + A_TCURSOR, nsplit + n, blockIdx.x, gridDim.x);
     uint64_t tr = 0, twin = 0, k5e = 0, quad = 0, pend = 0, two = 0, kite = 0, gem = 0;
     u128 k23 = 0;
     for (;;) {
-        if (tid == 0) s_task = (int64_t)atomicAdd(acc + A_TCURSOR, 1ull);
+        if (wid == 0) {
+            const int64_t got = queue.next();
+            if (lane == 0) s_task = got;
+        }
         __syncthreads();
         const int64_t t = s_task;
         __syncthreads();
-        if (t >= ntasks) break;
+        if (t < 0) break;
         int32_t i, part = 0, parts = 1;
         if (t < nsplit) {
             i = tasks[t].i;
@@ -908,25 +916,29 @@ __global__ void __launch_bounds__(NT) k_f5_wheel_lists(const int32_t *__restrict
         if (BIG) __syncthreads();
         else wave_sync();
     };
-    __shared__ unsigned long long s_next;
+    __shared__ int64_t s_next;
     for (int32_t k = t_lane; k < cw; k += t_size) cnt[k] = 0u;
     team_sync();
-    const unsigned long long narcs = BIG ? acc[A_NBIG] : 2ull * (unsigned long long)L.m;
-    constexpr unsigned long long kGrab = BIG ? 1 : kWheelArcs;
+    const int64_t narcs = BIG ? (int64_t)acc[A_NBIG] : 2 * L.m;
+    constexpr int64_t kGrab = BIG ? 1 : kWheelArcs;
+    TaskQueue queue(acc + (BIG ? A_BCURSOR : A_CURSOR), (narcs + kGrab - 1) / kGrab,
+                    BIG ? blockIdx.x : wid * gridDim.x + blockIdx.x, gridDim.x * (BIG ? 1 : NW));
     uint64_t sum = 0;
     for (;;) {
-        unsigned long long r = 0;
+        int64_t r;
         if (BIG) {
-            if (tid == 0) s_next = atomicAdd(acc + A_BCURSOR, kGrab);
+            if (wid == 0) {
+                const int64_t got = queue.next();
+                if (lane == 0) s_next = got;
+            }
             __syncthreads();
             r = s_next;
             __syncthreads();
         } else {
-            if (lane == 0) r = atomicAdd(acc + A_CURSOR, kGrab);
-            r = __shfl(r, 0, kWave);
+            r = queue.next();
         }
-        if (r >= narcs) break;
-        for (unsigned long long q = r; q < r + kGrab && q < narcs; q++) {
+        if (r < 0) break;
+        for (int64_t q = r * kGrab; q < (r + 1) * kGrab && q < narcs; q++) {
             const int32_t arc = BIG ? big[q] : (int32_t)q;
             const uint32_t es = L.esym[arc];
             const uint32_t t = L.te[es >> 1];

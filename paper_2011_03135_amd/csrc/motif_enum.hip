@@ -198,20 +198,19 @@ __global__ void __launch_bounds__(kMeNT) k_motif_enum(const int32_t *__restrict_
     // A work unit is a run of G consecutive chunks (64 candidates of
     // position 2 below one arc, with everything below them).  Units are
     // taken in a fixed interleave for k = 3, whose chunks are single steps,
-    // and one chunk at a time from an atomic cursor otherwise (subtrees
+    // and one chunk at a time from work cursors otherwise (subtrees
     // differ widely).
     constexpr int64_t G = K == 3 ? 32 : 1;
+    TaskQueue queue(cursor, nchunks, wib * gridDim.x + blockIdx.x, (int32_t)nwaves);   // k > 3
     for (int64_t t = 0;; t++) {
         int64_t unit;
         if (K == 3) {
             unit = t * nwaves + wave0;
         } else {
-            unsigned long long got = 0;
-            if (lane == 0) got = atomicAdd(cursor, 1ull);
-            unit = (int64_t)__shfl(got, 0);
+            unit = queue.next();
         }
         int64_t c = unit * G;
-        if (c >= nchunks) break;   // wave-uniform
+        if (c < 0 || c >= nchunks) break;   // wave-uniform
         const int64_t c_end = min(c + G, nchunks);
         // the arc of chunk c: the last a with chunk_off[a] <= c
         int64_t a;
@@ -437,7 +436,7 @@ static void me_layout(Carve &cv, int64_t narcs, int32_t **chunks, int64_t **chun
     *chunks = cv.take<int32_t>((uint64_t)std::max<int64_t>(narcs, 1));
     *chunk_off = cv.take<int64_t>((uint64_t)narcs + 1);
     *tmp = cv.take<int64_t>(scan_tmp_words((uint64_t)narcs));
-    *cursor = cv.take<unsigned long long>(1);
+    *cursor = cv.take<unsigned long long>(kCursorWords / 2);
 }
 
 gpm_status motif_enum_workspace_bytes(const gpm_graph *g, uint64_t *bytes) {
@@ -473,7 +472,7 @@ gpm_status motif_enum_count(const gpm_graph *g, int k, void *ws, uint64_t ws_byt
     GPM_HIP(fill_u32(reinterpret_cast<uint32_t *>(out), 0, 2 * (uint64_t)nclass, st));
     if (g->m == 0) return GPM_OK;
     Span sp("k_motif_enum", st);
-    GPM_HIP(fill_u32(cursor, 0, 2, st));
+    GPM_HIP(fill_u32(cursor, 0, kCursorWords, st));
     const unsigned cblocks = (unsigned)std::min<int64_t>((narcs + 255) / 256, 4096);
     hipLaunchKernelGGL(k_me_chunks, dim3(cblocks), dim3(256), 0, st, g->off, g->adj, g->n, chunks);
     GPM_LAUNCH_CHECK("k_me_chunks");
