@@ -37,6 +37,19 @@ constexpr int kBigThreads = 1024;
 constexpr int kHalfMaxD = 512;
 constexpr int kHalfThreads = 512;
 constexpr int kHalfBlocksPerCu = 3;
+// Threads and workgroups per CU of the 5-clique kernel: by registers, 4 waves a
+// SIMD for local graphs of up to 8 words a row and 3 up to 16 (RMAT-20: 8.4 ms;
+// 9.2 with 2 waves).  The descents of larger cliques and the listing, whose
+// tasks differ more, take one workgroup of 16 waves (6-cliques of RMAT-16: 6.4
+// ms in this class; 11.3 with two of 8).
+template <int DMAX, bool TILES> struct Lg5Block {
+    static constexpr int kThreads = !TILES ? 1024 : (DMAX == 512 ? 512 : 768);
+    static constexpr int kWaves = !TILES ? 4 : (DMAX == 512 ? 4 : 3);
+    static constexpr int kPerCu = TILES && DMAX == 512 ? 2 : 1;
+};
+// waves per SIMD of the middle class's 5-clique kernel (RMAT-20: 5.6 ms; 5.8 at
+// 5 or 7, whose spills or lower occupancy cost more)
+constexpr int kMidWaves = 6;
 constexpr int32_t kMaxSlices = 1024;
 
 __device__ __forceinline__ void wave_sync() {
@@ -200,7 +213,7 @@ __device__ __forceinline__ uint64_t wave_or64(uint64_t x) {
 // the word are walked one after the other, so the lane's bit test is one
 // bit-field extract of a 32-bit register and its product with the count one
 // 24-bit multiply-add; row_b is a broadcast LDS read.
-template <int W>
+template <int W, int S>
 __device__ __forceinline__ uint32_t pair_sweep(const uint64_t *rows, const uint64_t (&X)[W], int q,
                                                uint64_t m, uint32_t part) {
 #pragma unroll
@@ -210,7 +223,7 @@ __device__ __forceinline__ uint32_t pair_sweep(const uint64_t *rows, const uint6
         while (mh) {
             const int bp = __builtin_ctz(mh);
             mh &= mh - 1u;
-            const uint64_t *yb = rows + (q * kWave + h * 32 + bp) * W;
+            const uint64_t *yb = rows + (q * kWave + h * 32 + bp) * S;
             uint32_t sc = 0;
 #pragma unroll
             for (int w = q; w < W; w++) sc += (uint32_t)__popcll(X[w] & yb[w]);
@@ -252,7 +265,7 @@ __device__ uint64_t local_tri(const uint64_t *rows, int32_t d, int wib, int nw) 
             uint64_t X[W];
 #pragma unroll
             for (int w = qq; w < W; w++) X[w] = a < d ? rows[a * W + w] : 0ull;
-            part = pair_sweep<W>(rows, X, qq, wave_or64(X[qq]), part);
+            part = pair_sweep<W, W>(rows, X, qq, wave_or64(X[qq]), part);
         }
         acc += part;
     }
@@ -409,26 +422,27 @@ __global__ void __launch_bounds__(NT, DMAX == kHalfMaxD ? 6 : 1) k_lg_build(cons
         }
         __syncthreads();
         for (int32_t i = tid; i < sh.s_slices; i += NT)
-            tasks[sh.s_next + i] = {r, (uint16_t)i, (uint16_t)sh.s_slices};
+            tasks[DMAX == kHalfMaxD ? sh.s_next + i : -1 - (int64_t)(sh.s_next + i)] = {r, (uint16_t)i, (uint16_t)sh.s_slices};
         __syncthreads();
     }
 }
 
-// 5-cliques, step 2: task (root, slice); rows come back from HBM into LDS.
-// For local vertex i with out-row R (members p_0 < ... < p_{c-1}), the
-// 5-cliques {u, v_i, ...} are the triangles a < b < x of the local DAG
+// 5-cliques and larger, step 2: task (root, slice); rows come back from HBM
+// into LDS.  For local vertex i with out-row R (members p_0 < ... < p_{c-1}),
+// the 5-cliques {u, v_i, ...} are the triangles a < b < x of the local DAG
 // inside R: the sum over members a < b of [a -> b] * |row_a & R & row_b|.
+// LDS is dynamic: rows (dmax x (ceil(dmax/64) | 1) words for the class's
+// largest out-degree), then per wave a member list of DMAX int16.
+
+// That sum by population counts, for the leaves of the descents below (k > 5).
 // Lanes own a (64 members at a time, row_a & R in registers); b runs over
 // R's members in a wave-uniform loop, so row_b is a broadcast LDS read, and
 // the AND + population count runs over the words from b's word up (a row
 // only holds bits above its own vertex).  Local graphs of hub roots are
 // dense, so testing every pair costs little more than following edges and
 // keeps all 64 lanes busy.
-// LDS is dynamic: rows (dmax x ceil(dmax/64) words for the class's largest
-// out-degree), then per wave a member list of DMAX int16.
-
-template <int W>
-__device__ uint64_t lg5_vertex(const uint64_t *rows, const uint64_t *ri, int32_t c, int16_t *mem) {
+template <int W, int S>
+__device__ uint64_t lg5_sweep(const uint64_t *rows, const uint64_t *ri, int32_t c, int16_t *mem) {
     const int lane = lane_id();
     uint64_t R[W];
 #pragma unroll
@@ -445,7 +459,7 @@ __device__ uint64_t lg5_vertex(const uint64_t *rows, const uint64_t *ri, int32_t
         const int32_t a = a0 + lane;
         uint64_t X[W];
         if (a < c) {
-            const uint64_t *ra = rows + (int32_t)mem[a] * W;
+            const uint64_t *ra = rows + (int32_t)mem[a] * S;
 #pragma unroll
             for (int q = 0; q < W; q++) X[q] = ra[q] & R[q];
         } else {
@@ -460,7 +474,7 @@ __device__ uint64_t lg5_vertex(const uint64_t *rows, const uint64_t *ri, int32_t
             if (q < q0) continue;
             uint64_t m = R[q];
             if (q == q0) m &= ~((2ull << (p0 & 63)) - 1ull);   // members above p0
-            part = pair_sweep<W>(rows, X, q, m, part);
+            part = pair_sweep<W, S>(rows, X, q, m, part);
         }
         acc += part;
     }
@@ -468,10 +482,134 @@ __device__ uint64_t lg5_vertex(const uint64_t *rows, const uint64_t *ri, int32_t
     return acc;
 }
 
-// Listing form of lg5_vertex: emits every 5-clique {u, v_i, a, b, x} with
+// 0/1 words as FP4 operands of the 32 x 32 x 64 matrix instruction: a lane's
+// word holds 32 entries of a row, one per bit, and bit b of every nibble goes to
+// register b with the nibble's own code (1, 2, 4: the values 0.5, 1 and 2; bit 3
+// is moved to 4) in the left operand and the inverse value in the right one, so
+// that every product is 1.  The order of the 64 entries does not matter, as
+// both operands use the same.
+typedef int fp4x64 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ fp4x64 fp4_left(uint32_t w) {
+    fp4x64 r = {};
+    r[0] = (int)(w & 0x11111111u);
+    r[1] = (int)(w & 0x22222222u);
+    r[2] = (int)(w & 0x44444444u);
+    r[3] = (int)((w >> 1) & 0x44444444u);
+    return r;
+}
+__device__ __forceinline__ fp4x64 fp4_right(uint32_t w) {
+    fp4x64 r = {};
+    r[0] = (int)((w << 2) & 0x44444444u);
+    r[1] = (int)(w & 0x22222222u);
+    r[2] = (int)((w >> 2) & 0x11111111u);
+    r[3] = (int)((w >> 3) & 0x11111111u);
+    return r;
+}
+
+// The same sum (5-cliques) on the matrix cores.  A tile is 32 members a by 32
+// members b, taken by their indices from the list, so the 0/1 product needs
+// only c x c / 2 of its d x d entries; its 64-entry steps run over the row
+// words from b's up, with R cut out of b's rows.  b's operands stay in registers
+// over all a's tiles.  The step that holds b's own bits is taken twice, the
+// second time with that bit alone and the weight 2048 (more than any
+// count), which puts [a -> b] beside the count: an entry's share is what is
+// left above 2048, if anything is.  The unit is 2^-16, so that two entries
+// become 16-bit counts by one conversion to fractions of 1 (n - n / 65536 rounds
+// to n below 32768) and the rest is a saturating subtraction and a dot product.
+// Sums stay whole: an entry is below 2^24 units and a lane adds at most
+// 528 tiles x 16 entries x 1021.  The last tile repeats the last member, whose
+// row has nothing inside R: it adds nothing on either side.
+// Bound by the vector units (about 95 operations a wave and tile of 2.7 steps, two
+// thirds of its time) and the latency of the gathered rows; the matrix cores take a
+// fifth.  RMAT-20, 3.7e7 tiles: 8.4 ms; by population counts, as lg5_sweep, 15.1.
+template <int W, int S>
+__device__ uint64_t lg5_tiles(const uint64_t *rows, const uint64_t *ri, int32_t c, int16_t *mem) {
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    // the unit is 2^-16, so that a conversion to 16-bit fractions of 1 gives
+    // the counts; a quarter of a unit makes it exact under any rounding
+    constexpr int kOne = 0x6f6f6f6f, kAdj = 0x7a7a7a7a, kLeft = 0x7f7f7f7f;
+    const int lane = lane_id(), l32 = lane & 31, half = lane >> 5;
+    uint64_t R[W];
+#pragma unroll
+    for (int q = 0; q < W; q++) R[q] = uniform64(ri[q]);
+    int32_t base = 0;
+#pragma unroll
+    for (int q = 0; q < W; q++) {
+        if ((R[q] >> lane) & 1ull) mem[base + lanes_below(R[q])] = (int16_t)(q * 64 + lane);
+        base += __popcll(R[q]);
+    }
+    wave_sync();
+    const uint32_t *rows32 = reinterpret_cast<const uint32_t *>(rows) + half;
+    uint32_t sum = 0;
+    for (int32_t tb = 0; tb < c; tb += 32) {
+        const int32_t pb = mem[min(tb + l32, c - 1)];
+        const int32_t q0 = __builtin_amdgcn_readfirstlane((int32_t)mem[tb]) >> 6;
+        const int32_t q1 = __builtin_amdgcn_readfirstlane((int32_t)mem[min(tb + 31, c - 1)]) >> 6;
+        const int32_t wb = (pb >> 5) - half;   // 2 q of the word that holds b, in this half
+        const uint32_t ob = 1u << (pb & 31);
+        const fp4x64 O0 = fp4_right(wb == 2 * q0 ? ob : 0u);
+        const fp4x64 O1 = fp4_right(wb == 2 * q0 + 2 ? ob : 0u);
+        uint32_t bw[W];
+#pragma unroll
+        for (int q = 0; q < W; q++) bw[q] = rows32[pb * (2 * S) + 2 * q];
+        fp4x64 XB[W];
+#pragma unroll
+        for (int q = W - 1; q >= 0; q--) {
+            if (q < W - 1 && q < q0) break;
+            const uint32_t m = half ? (uint32_t)(R[q] >> 32) : (uint32_t)R[q];
+            XB[q] = fp4_right(bw[q] & m);
+        }
+        int32_t pa = mem[min(l32, c - 1)];
+        for (int32_t ta = 0; ta <= tb; ta += 32) {
+            uint32_t aw[W];
+            const uint32_t *ra = rows32 + pa * (2 * S);
+            // (opaque, or the compiler keeps a condition per word)
+            int32_t first = q0;
+            asm volatile("" : "+s"(first));
+#pragma unroll
+            for (int q = W - 1; q >= 0; q--) {
+                if (q < W - 1 && q < first) break;
+                aw[q] = ra[2 * q];
+            }
+            pa = mem[min(ta + 32 + l32, c - 1)];   // the next tile's
+            f32x16 C = {};
+            auto mfma = [&](const fp4x64 &A, const fp4x64 &B, int scale) {
+                C = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A, B, C, 4, 4, 0, kLeft, 0, scale);
+            };
+            fp4x64 A = fp4_left(aw[W - 1]), A1 = A;
+            mfma(A, XB[W - 1], kOne);
+#pragma unroll
+            for (int q = W - 2; q >= 0; q--) {
+                if (q < first) break;
+                A1 = A;
+                A = fp4_left(aw[q]);
+                mfma(A, XB[q], kOne);
+            }
+            // 2048 where a -> b: b's own bit, in words q0 .. q1
+            mfma(A, O0, kAdj);
+            if (q1 > first) {
+                mfma(A1, O1, kAdj);
+                for (int32_t q = first + 2; q <= q1; q++)
+                    mfma(fp4_left(ra[2 * q]), fp4_right(wb == 2 * q ? ob : 0u), kAdj);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; r += 2) {
+                u16x2 p = __builtin_bit_cast(u16x2, __builtin_amdgcn_cvt_pknorm_u16(C[r], C[r + 1]));
+                p = __builtin_elementwise_sub_sat(p, u16x2{2048, 2048});
+                sum = __builtin_amdgcn_udot2(p, u16x2{1, 1}, sum, false);
+            }
+        }
+    }
+    wave_sync();
+    return (uint64_t)sum;
+}
+
+// Listing form: emits every 5-clique {u, v_i, a, b, x} with
 // a < b < x a triangle inside R (vertex ids from verts, the out-neighbours
 // in local order).
-template <int W>
+template <int W, int S>
 __device__ void lg5_list(const uint64_t *rows, const uint64_t *ri, int32_t c, int16_t *mem,
                          const int32_t *verts, int32_t u, int32_t vi, RowEmitter &em) {
     const int lane = lane_id();
@@ -491,7 +629,7 @@ __device__ void lg5_list(const uint64_t *rows, const uint64_t *ri, int32_t c, in
         int32_t pa = 0;
         if (a < c) {
             pa = mem[a];
-            const uint64_t *ra = rows + pa * W;
+            const uint64_t *ra = rows + pa * S;
 #pragma unroll
             for (int q = 0; q < W; q++) X[q] = ra[q] & R[q];
         } else {
@@ -510,7 +648,7 @@ __device__ void lg5_list(const uint64_t *rows, const uint64_t *ri, int32_t c, in
                 m &= m - 1ull;
                 const int32_t pb = q * 64 + bp;
                 if ((X[q] >> bp) & 1ull) {
-                    const uint64_t *yb = rows + pb * W;
+                    const uint64_t *yb = rows + pb * S;
 #pragma unroll
                     for (int w = q; w < W; w++) {
                         uint64_t mm = X[w] & yb[w];
@@ -528,14 +666,14 @@ __device__ void lg5_list(const uint64_t *rows, const uint64_t *ri, int32_t c, in
     wave_sync();
 }
 
-template <int WLO, int WHI>
+template <int WLO, int WHI, bool PAD>
 __device__ __forceinline__ void lg5_list_dispatch(int32_t W, const uint64_t *rows,
                                                   const uint64_t *ri, int32_t c, int16_t *mem,
                                                   const int32_t *verts, int32_t u, int32_t vi,
                                                   RowEmitter &em) {
     if constexpr (WLO <= WHI) {
-        if (W == WLO) lg5_list<WLO>(rows, ri, c, mem, verts, u, vi, em);
-        else lg5_list_dispatch<WLO + 1, WHI>(W, rows, ri, c, mem, verts, u, vi, em);
+        if (W == WLO) lg5_list<WLO, PAD ? (WLO | 1) : WLO>(rows, ri, c, mem, verts, u, vi, em);
+        else lg5_list_dispatch<WLO + 1, WHI, PAD>(W, rows, ri, c, mem, verts, u, vi, em);
     }
 }
 
@@ -546,14 +684,13 @@ __device__ __forceinline__ void lg5_list_dispatch(int32_t W, const uint64_t *row
 // The descent is wave-uniform and iterative: level l keeps its set and the
 // members still to visit in the wave's stack area (2 W words per level,
 // e + 1 levels), the deepest child set in the last slot.
-template <int W>
-__device__ uint64_t lgk_set(const uint64_t *rows, const uint64_t *S, int32_t c, int32_t e,
+template <int W, int S>
+__device__ uint64_t lgk_set(const uint64_t *rows, const uint64_t *set0, int32_t c, int32_t e,
                             int16_t *mem, uint64_t *stack) {
-    if (e == 0) return lg5_vertex<W>(rows, S, c, mem);
     uint64_t acc = 0;
 #pragma unroll
     for (int q = 0; q < W; q++) {
-        const uint64_t x = uniform64(S[q]);
+        const uint64_t x = uniform64(set0[q]);
         stack[q] = x;
         stack[W + q] = x;
     }
@@ -575,7 +712,7 @@ __device__ uint64_t lgk_set(const uint64_t *rows, const uint64_t *S, int32_t c, 
             lvl--;
             continue;
         }
-        const uint64_t *rv = rows + v * W;
+        const uint64_t *rv = rows + v * S;
         uint64_t *child = stack + (lvl + 1) * 2 * W;
         int32_t cnt = 0;
 #pragma unroll
@@ -587,7 +724,7 @@ __device__ uint64_t lgk_set(const uint64_t *rows, const uint64_t *S, int32_t c, 
         }
         wave_sync();
         if (lvl + 1 == e) {
-            if (cnt >= 3) acc += lg5_vertex<W>(rows, child, cnt, mem);
+            if (cnt >= 3) acc += lg5_sweep<W, S>(rows, child, cnt, mem);
         } else if (cnt >= e - lvl + 2) {
             lvl++;
         }
@@ -595,30 +732,36 @@ __device__ uint64_t lgk_set(const uint64_t *rows, const uint64_t *S, int32_t c, 
     return acc;
 }
 
-template <int WLO, int WHI>
+template <int WLO, int WHI, bool PAD, bool DEEP>
 __device__ __forceinline__ uint64_t lg5_dispatch(int32_t W, const uint64_t *rows, const uint64_t *ri,
                                                  int32_t c, int32_t e, int16_t *mem,
                                                  uint64_t *stack) {
     if constexpr (WLO > WHI) {
         return 0;
     } else {
-        if (W == WLO) return lgk_set<WLO>(rows, ri, c, e, mem, stack);
-        return lg5_dispatch<WLO + 1, WHI>(W, rows, ri, c, e, mem, stack);
+        constexpr int S = PAD ? (WLO | 1) : WLO;
+        if (W == WLO) {
+            if constexpr (DEEP) return lgk_set<WLO, S>(rows, ri, c, e, mem, stack);
+            else return lg5_tiles<WLO, S>(rows, ri, c, mem);
+        }
+        return lg5_dispatch<WLO + 1, WHI, PAD, DEEP>(W, rows, ri, c, e, mem, stack);
     }
 }
 
-template <int DMAX, bool LIST>
-__global__ void __launch_bounds__(1024) k_lg5(const int32_t *__restrict__ dag_off,
-                                              const int32_t *__restrict__ roots,
-                                              const LgTask *__restrict__ tasks,
-                                              const uint32_t *__restrict__ ntasks_p,
-                                              const int64_t *__restrict__ rowoff,
-                                              const uint64_t *__restrict__ grows,
-                                              int32_t rows_words, int32_t extra,
-                                              unsigned long long *cursor, unsigned long long *result,
-                                              RowEmitter em) {
-    // row widths of the class: out-degrees (DMAX/4, DMAX]
-    constexpr int WLO = DMAX / 256 + 1, WHI = DMAX / 64;
+template <int DMAX, bool LIST, bool DEEP>
+__global__ void __launch_bounds__((Lg5Block<DMAX, !LIST && !DEEP>::kThreads),
+                                  (Lg5Block<DMAX, !LIST && !DEEP>::kWaves))
+    k_lg5(const int32_t *__restrict__ dag_off,
+          const int32_t *__restrict__ roots,
+          const LgTask *__restrict__ tasks,
+          const uint32_t *__restrict__ ntasks_p,
+          const int64_t *__restrict__ rowoff,
+          const uint64_t *__restrict__ grows,
+          int32_t rows_words, int32_t extra,
+          unsigned long long *cursor, unsigned long long *result,
+          RowEmitter em) {
+    // row widths of the class: out-degrees (DMAX/2, DMAX]
+    constexpr int WLO = DMAX / 128 + 1, WHI = DMAX / 64;
     extern __shared__ uint64_t dyn[];
     uint64_t *rows = dyn;
     __shared__ Lds<1024> sh;
@@ -643,11 +786,15 @@ __global__ void __launch_bounds__(1024) k_lg5(const int32_t *__restrict__ dag_of
         const int32_t t = sh.s_task;
         __syncthreads();
         if (t < 0) break;
-        const int32_t r = tasks[t].r, slice = tasks[t].slice, S = tasks[t].slices;
+        const LgTask T = tasks[DMAX == kHalfMaxD ? t : -1 - t];
+        const int32_t r = T.r, slice = T.slice, S = T.slices;
         const int32_t u = roots[r];
         const int32_t d = dag_off[u + 1] - dag_off[u], W = (d + 63) >> 6;
         const uint64_t *src = grows + rowoff[r];
-        for (int32_t i = tid; i < d * W; i += NT) rows[i] = src[i];
+        // rows at an odd stride, so that a column of them is spread over the banks
+        const int32_t S64 = W | 1;
+        for (int32_t i = wib; i < d; i += NT / kWave)
+            if (lane < W) rows[i * S64 + lane] = src[i * W + lane];
         if (LIST) {
             const int32_t *sv = reinterpret_cast<const int32_t *>(src + d * W);
             for (int32_t i = tid; i < d; i += NT) verts[i] = sv[i];
@@ -661,14 +808,14 @@ __global__ void __launch_bounds__(1024) k_lg5(const int32_t *__restrict__ dag_of
             c = __shfl(c, 0, 64);
             const int32_t i = slice + S * (int32_t)c;
             if (i >= d) break;
-            const uint64_t *ri = rows + i * W;
+            const uint64_t *ri = rows + i * S64;
             int32_t cnt = 0;
             for (int32_t w = 0; w < W; w++) cnt += __popcll(ri[w]);
             if (cnt < 3 + extra) continue;
             if constexpr (LIST)
-                lg5_list_dispatch<WLO, WHI>(W, rows, ri, cnt, mem, verts, u, verts[i], em);
+                lg5_list_dispatch<WLO, WHI, true>(W, rows, ri, cnt, mem, verts, u, verts[i], em);
             else
-                acc += lg5_dispatch<WLO, WHI>(W, rows, ri, cnt, extra, mem, stack);
+                acc += lg5_dispatch<WLO, WHI, true, DEEP>(W, rows, ri, cnt, extra, mem, stack);
         }
         __syncthreads();
     }
@@ -686,8 +833,8 @@ __global__ void __launch_bounds__(1024) k_lg5(const int32_t *__restrict__ dag_of
 // u) to res4 when asked, then its waves take the level-1 vertices and count
 // (or list) as k_lg5 does.  The local graphs are small, so no slicing and no
 // trip through HBM.
-template <int DMAX, int NT, bool LIST>
-__global__ void __launch_bounds__(NT) k_lg5_mid(const int32_t *__restrict__ off,
+template <int DMAX, int NT, bool LIST, bool DEEP>
+__global__ void __launch_bounds__(NT, DEEP ? 7 : kMidWaves) k_lg5_mid(const int32_t *__restrict__ off,
                                                 const int32_t *__restrict__ okey,
                                                 const int32_t *__restrict__ dag_off,
                                                 const int32_t *__restrict__ dag_adj,
@@ -742,9 +889,10 @@ __global__ void __launch_bounds__(NT) k_lg5_mid(const int32_t *__restrict__ off,
             for (int32_t w = 0; w < W; w++) cnt += __popcll(ri[w]);
             if (cnt < 3 + extra) continue;
             if constexpr (LIST)
-                lg5_list_dispatch<WLO, WHI>(W, rows, ri, cnt, s_mem[wib], verts, u, verts[i], em);
+                lg5_list_dispatch<WLO, WHI, false>(W, rows, ri, cnt, s_mem[wib], verts, u, verts[i], em);
             else
-                acc += lg5_dispatch<WLO, WHI>(W, rows, ri, cnt, extra, s_mem[wib], s_stack[wib]);
+                acc += lg5_dispatch<WLO, WHI, false, DEEP>(W, rows, ri, cnt, extra, s_mem[wib],
+                                                           s_stack[wib]);
         }
         __syncthreads();
     }
@@ -768,9 +916,9 @@ struct LgWs {
     unsigned long long *cursor(int i) const {
         return reinterpret_cast<unsigned long long *>(ctl + 64 + i * kCursorWords);
     }
-    uint32_t *ctl;                 // [8] 5-clique tasks, from 64 the sets of cursors
+    uint32_t *ctl;                 // [8..9] 5-clique tasks of the two classes, from 64 the sets of cursors
     unsigned long long *units;     // local triangles (5-cliques' work)
-    LgTask *tasks;
+    LgTask *tasks, *tasks_end;
     uint64_t *rows_b;
     uint64_t bytes;
 };
@@ -784,7 +932,10 @@ LgWs lg_layout(const gpm_graph *g, int32_t k, void *base) {
     if (k >= 5) {
         const uint64_t m = (uint64_t)std::max<int64_t>(g->m, 1);
         // at most d / 8 + 1 tasks per root of out-degree d > 256
-        L.tasks = c.take<LgTask>(m / 8 + m / (kMidMaxD + 1) + 1);
+        // (those of the smaller class from the front, the larger from the end)
+        const uint64_t most = m / 8 + m / (kMidMaxD + 1) + 1;
+        L.tasks = c.take<LgTask>(most);
+        L.tasks_end = L.tasks + most;
         // rows and vertex ids of all roots with out-degree in (256, 1024]: sum of
         // d * ceil(d / 64) + ceil(d / 2) <= m * (ceil(max_out / 64) + 1) words
         const uint64_t wmax = (uint64_t)(std::max(g->max_out_degree, 1) + 63) / 64 + 1;
@@ -825,37 +976,45 @@ gpm_status lg5_big(const gpm_graph *g, int32_t k, LgWs &L, const int32_t *list, 
         Span sp("k_lg_build<1024>", st);
         hipLaunchKernelGGL((k_lg_build<kBigMaxD, kBigThreads>), roots_grid(g, kHalfMaxD, 1),
                            dim3(kBigThreads), 0, st, g->off, g->okey, g->dag_off, g->dag_adj, list,
-                           cnt, kHalfMaxD, L.cursor(2), rowoff, L.rows_b, L.tasks, ntasks, L.units,
+                           cnt, kHalfMaxD, L.cursor(2), rowoff, L.rows_b, L.tasks_end, ntasks + 1, L.units,
                            res3, res4, slice5);
     }
     GPM_LAUNCH_CHECK("k_lg_build<1024>");
-    {
-        // LDS: rows of the class's largest local graph, then per-wave member
-        // lists; as many waves as fit in 160 KiB (at most 16)
-        const int32_t dmax = std::min<int32_t>(kBigMaxD, g->max_out_degree);
-        const int32_t rows_words = dmax * ((dmax + 63) / 64);
+    // step 2, a class at a time.  LDS: rows of the class's largest local graph,
+    // the local vertex ids, then per-wave areas, for as many waves as fit
+    auto count = [&](auto dmax_class, int cursor, const LgTask *tasks, const uint32_t *nt) -> gpm_status {
+        constexpr int DMAX = decltype(dmax_class)::value;
+        const int32_t dmax = std::min<int32_t>(DMAX, g->max_out_degree);
+        const int32_t rows_words = dmax * (((dmax + 63) / 64) | 1);
         const int64_t lds_cap = 160 * 1024 - 1024;
         const int32_t extra = k - 5;
-        const int64_t per_wave =
-            (int64_t)kBigMaxD * 2 + (int64_t)(extra + 1) * 2 * (kBigMaxD / 64) * 8;
-        // rows, the local vertex ids, then the per-wave areas
-        const int64_t fixed = (int64_t)rows_words * 8 + (int64_t)kBigMaxD * 4;
-        int waves = (int)std::min<int64_t>(16, (lds_cap - fixed) / per_wave);
+        const int64_t per_wave = (int64_t)DMAX * 2 + (int64_t)(extra + 1) * 2 * (DMAX / 64) * 8;
+        const int64_t fixed = (int64_t)rows_words * 8 + (int64_t)DMAX * 4;
+        const int threads = em || extra ? Lg5Block<DMAX, false>::kThreads : Lg5Block<DMAX, true>::kThreads;
+        int waves = (int)std::min<int64_t>(threads / kWave, (lds_cap - fixed) / per_wave);
         if (waves < 1) return fail(GPM_DEVICE_ERROR, "local graph does not fit in LDS");
         const size_t shmem = (size_t)fixed + (size_t)waves * per_wave;
-        Span sp(k == 5 ? "k_lg5<1024>" : "k_lgk<1024>", st);
-        const dim3 grid((unsigned)cu_count());
+        const dim3 grid((unsigned)cu_count() *
+                        (em || extra ? Lg5Block<DMAX, false>::kPerCu : Lg5Block<DMAX, true>::kPerCu));
         if (em)
-            hipLaunchKernelGGL((k_lg5<kBigMaxD, true>), grid, dim3(waves * kWave), shmem, st,
-                               g->dag_off, list, L.tasks, ntasks, rowoff,
-                               (const uint64_t *)L.rows_b, rows_words, extra, L.cursor(3), res, *em);
+            hipLaunchKernelGGL((k_lg5<DMAX, true, false>), grid, dim3(waves * kWave), shmem, st,
+                               g->dag_off, list, tasks, nt, rowoff, (const uint64_t *)L.rows_b,
+                               rows_words, extra, L.cursor(cursor), res, *em);
         else
-            hipLaunchKernelGGL((k_lg5<kBigMaxD, false>), grid, dim3(waves * kWave), shmem, st,
-                               g->dag_off, list, L.tasks, ntasks, rowoff,
-                               (const uint64_t *)L.rows_b, rows_words, extra, L.cursor(3), res,
+            hipLaunchKernelGGL(extra ? (k_lg5<DMAX, false, true>) : (k_lg5<DMAX, false, false>), grid,
+                               dim3(waves * kWave), shmem, st, g->dag_off, list, tasks, nt, rowoff,
+                               (const uint64_t *)L.rows_b, rows_words, extra, L.cursor(cursor), res,
                                RowEmitter{});
-        span_units(L.units, st);
+        return GPM_OK;
+    };
+    Span sp(k == 5 ? "k_lg5<1024>" : "k_lgk<1024>", st);
+    if (g->max_out_degree > kHalfMaxD) {
+        gpm_status rc = count(std::integral_constant<int, kBigMaxD>(), 3, L.tasks_end, ntasks + 1);
+        if (rc) return rc;
     }
+    gpm_status rc = count(std::integral_constant<int, kHalfMaxD>(), 5, L.tasks, ntasks);
+    if (rc) return rc;
+    span_units(L.units, st);
     GPM_LAUNCH_CHECK("k_lg5");
     return GPM_OK;
 }
@@ -931,13 +1090,15 @@ gpm_status lg_cliques(const gpm_graph *g, int32_t k, const int32_t *list_m, cons
         Span sp(k == 5 ? "k_lg5_mid<256>" : "k_lgk_mid<256>", st);
         const dim3 grid = roots_grid(g, kWave, 8);
         if (em)
-            hipLaunchKernelGGL((k_lg5_mid<kMidMaxD, kMidThreads, true>), grid, dim3(kMidThreads), 0,
+            hipLaunchKernelGGL((k_lg5_mid<kMidMaxD, kMidThreads, true, false>), grid, dim3(kMidThreads), 0,
                                st, g->off, g->okey, g->dag_off, g->dag_adj, list_m, cnt_m, k - 5,
                                L.cursor(6), res, res3, res4, *em);
         else
-            hipLaunchKernelGGL((k_lg5_mid<kMidMaxD, kMidThreads, false>), grid, dim3(kMidThreads),
-                               0, st, g->off, g->okey, g->dag_off, g->dag_adj, list_m, cnt_m, k - 5,
-                               L.cursor(6), res, res3, res4, RowEmitter{});
+            hipLaunchKernelGGL(k > 5 ? (k_lg5_mid<kMidMaxD, kMidThreads, false, true>)
+                                     : (k_lg5_mid<kMidMaxD, kMidThreads, false, false>),
+                               grid, dim3(kMidThreads), 0, st, g->off, g->okey, g->dag_off,
+                               g->dag_adj, list_m, cnt_m, k - 5, L.cursor(6), res, res3, res4,
+                               RowEmitter{});
     }
     GPM_LAUNCH_CHECK("k_lg5_mid");
     return GPM_OK;
