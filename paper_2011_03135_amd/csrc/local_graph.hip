@@ -47,8 +47,8 @@ template <int DMAX, bool TILES> struct Lg5Block {
     static constexpr int kWaves = !TILES ? 4 : (DMAX == 512 ? 4 : 3);
     static constexpr int kPerCu = TILES && DMAX == 512 ? 2 : 1;
 };
-// waves per SIMD of the middle class's 5-clique kernel (RMAT-20: 5.6 ms; 5.8 at
-// 5 or 7, whose spills or lower occupancy cost more)
+// waves per SIMD of the middle class's 5-clique kernel (RMAT-20: 5.0 ms; 5.4 at
+// 5 and 5.2 at 7, for want of waves and for spills)
 constexpr int kMidWaves = 6;
 constexpr int32_t kMaxSlices = 1024;
 
@@ -108,8 +108,17 @@ template <int DMAX> struct LgHash {
     static_assert((1 << kBits) == kSlots, "slots must be a power of two");
 };
 
-// Builds the local graph of root u (d out-neighbours, W words per row) in
-// LDS: row a gets bit b for every pair (v, w) of the root with v, w the
+// Row words of a class's LDS area, and the rows' stride: odd where it fits, so
+// that a column of words is spread over the banks.
+template <int DMAX> struct LgRows {
+    static constexpr int kWords = DMAX == 256 ? 256 * 5 : DMAX * (DMAX / 64);
+    static __device__ __forceinline__ int32_t stride(int32_t d, int32_t W) {
+        return d * (W | 1) <= kWords ? W | 1 : W;
+    }
+};
+
+// Builds the local graph of root u (d out-neighbours, W words per row at
+// stride S) in LDS: row a gets bit b for every pair (v, w) of the root with v, w the
 // out-neighbours of local indices a and b.  Local indices are positions in
 // the out-list, or with RANK positions in the DAG's order, by (okey, id)
 // (the graph's orientation key: degrees, or the core-value key); lidx, d
@@ -119,7 +128,7 @@ template <int DMAX> struct LgHash {
 template <int DMAX, int NT, bool RANK>
 __device__ void build_rows(const int32_t *__restrict__ off, const int32_t *__restrict__ okey,
                            const int32_t *__restrict__ dag_off,
-                           const int32_t *__restrict__ dag_adj, int32_t u, int32_t d, int32_t W,
+                           const int32_t *__restrict__ dag_adj, int32_t u, int32_t d, int32_t S,
                            uint64_t *rows, int32_t *keys, int16_t *vals, int32_t *pre,
                            int32_t *offj, int16_t *lidx, int32_t *s_sum,
                            int32_t *verts = nullptr) {
@@ -146,7 +155,7 @@ __device__ void build_rows(const int32_t *__restrict__ off, const int32_t *__res
     }
     const int32_t hb = min(lds_hash_bits(d), LgHash<DMAX>::kBits);
     for (int32_t i = threadIdx.x; i < (1 << hb); i += NT) keys[i] = -1;
-    for (int32_t i = threadIdx.x; i < d * W; i += NT) rows[i] = 0ull;
+    for (int32_t i = threadIdx.x; i < d * S; i += NT) rows[i] = 0ull;
     stage_root<NT, PER>(dag_off, dag_adj, s, d, keys, vals, hb, pre, offj, s_sum,
                         RANK ? lidx : nullptr, verts);
     const int32_t npairs = pre[d];
@@ -158,7 +167,7 @@ __device__ void build_rows(const int32_t *__restrict__ off, const int32_t *__res
         if (slot >= 0) {
             const int32_t a = RANK ? (int32_t)lidx[j] : j;
             const int32_t b = vals[slot];
-            atomicOr((unsigned long long *)&rows[a * W + (b >> 6)], 1ull << (b & 63));
+            atomicOr((unsigned long long *)&rows[a * S + (b >> 6)], 1ull << (b & 63));
         }
     });
     __syncthreads();
@@ -166,7 +175,7 @@ __device__ void build_rows(const int32_t *__restrict__ off, const int32_t *__res
 
 // pre[i] = number of local edges in rows 0..i-1; returns the total.
 template <int DMAX, int NT>
-__device__ int32_t row_prefix(const uint64_t *rows, int32_t d, int32_t W, int32_t *pre,
+__device__ int32_t row_prefix(const uint64_t *rows, int32_t d, int32_t W, int32_t S, int32_t *pre,
                               int32_t *s_sum) {
     constexpr int PER = (DMAX + NT - 1) / NT;
     int32_t pc[PER];
@@ -175,7 +184,7 @@ __device__ int32_t row_prefix(const uint64_t *rows, int32_t d, int32_t W, int32_
         const int32_t i = threadIdx.x * PER + q;
         pc[q] = 0;
         if (i < d)
-            for (int32_t w = 0; w < W; w++) pc[q] += __popcll(rows[i * W + w]);
+            for (int32_t w = 0; w < W; w++) pc[q] += __popcll(rows[i * S + w]);
     }
     block_prefix<NT, PER>(pc, d, pre, s_sum);
     return pre[d];
@@ -183,10 +192,10 @@ __device__ int32_t row_prefix(const uint64_t *rows, int32_t d, int32_t W, int32_
 
 // Local edge number e -> (row i, column j).
 __device__ __forceinline__ void edge_at(const uint64_t *rows, const int32_t *pre, int32_t d,
-                                        int32_t W, int32_t e, int32_t &i, int32_t &j) {
+                                        int32_t S, int32_t e, int32_t &i, int32_t &j) {
     i = last_le_i32(pre, d + 1, e);
     int32_t rr = e - pre[i];
-    const uint64_t *ri = rows + i * W;
+    const uint64_t *ri = rows + i * S;
     int32_t wj = 0;
     for (;; wj++) {
         const int pc = __popcll(ri[wj]);
@@ -238,58 +247,100 @@ __device__ __forceinline__ uint32_t pair_sweep(const uint64_t *rows, const uint6
     return part;
 }
 
-// Triangles of a local graph in degree order (d vertices, W words per row,
-// every row holding only bits above its own index): the sum over local
-// edges a -> b of |row_a & row_b|.  The work is cut into pieces (t, q): rows
-// 64t..64t+63 (one per lane, in registers) against the columns b of word q
-// (q >= t).  b runs over the union of the 64 rows' bits in word q in a
-// wave-uniform loop, so row_b is a broadcast LDS read, and the AND +
-// population count covers the words from q up.  Pieces go round robin to the
-// workgroup's waves in order of q, i.e. from the costliest (W - q words per
-// column) down.  Returns the calling lane's share.
-template <int W>
-__device__ uint64_t local_tri(const uint64_t *rows, int32_t d, int wib, int nw) {
-    const int lane = lane_id();
-    constexpr int kPieces = W * (W + 1) / 2;
-    uint64_t acc = 0;
-    for (int p = wib; p < kPieces; p += nw) {
-        int q = 0;
-        while ((q + 1) * (q + 2) / 2 <= p) q++;
-        const int t = p - q * (q + 1) / 2;
-        const int32_t a = t * kWave + lane;
-        if (t * kWave >= d) continue;
-        uint32_t part = 0;
+// 0/1 words as FP4 operands of the 32 x 32 x 64 matrix instruction: a lane's
+// word holds 32 entries of a row, one per bit, and bit b of every nibble goes to
+// register b with the nibble's own code (1, 2, 4: the values 0.5, 1 and 2; bit 3
+// is moved to 4) in the left operand and the inverse value in the right one, so
+// that every product is 1.  The order of the 64 entries does not matter, as
+// both operands use the same.
+typedef int fp4x64 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ fp4x64 fp4_left(uint32_t w) {
+    fp4x64 r = {};
+    r[0] = (int)(w & 0x11111111u);
+    r[1] = (int)(w & 0x22222222u);
+    r[2] = (int)(w & 0x44444444u);
+    r[3] = (int)((w >> 1) & 0x44444444u);
+    return r;
+}
+__device__ __forceinline__ fp4x64 fp4_right(uint32_t w) {
+    fp4x64 r = {};
+    r[0] = (int)((w << 2) & 0x44444444u);
+    r[1] = (int)(w & 0x22222222u);
+    r[2] = (int)((w >> 2) & 0x11111111u);
+    r[3] = (int)((w >> 3) & 0x11111111u);
+    return r;
+}
+
+// C + the 32 x 32 products of 64 entries of the rows in A and B, in units of
+// 2^-16 (kFp4Count) or of 2^-5 (kFp4Adj): 2048 of the first.
+constexpr int kFp4Count = 0x6f6f6f6f, kFp4Adj = 0x7a7a7a7a;
+__device__ __forceinline__ f32x16 fp4_step(const fp4x64 &A, const fp4x64 &B, const f32x16 &C,
+                                           int unit) {
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A, B, C, 4, 4, 0, 0x7f7f7f7f, 0, unit);
+}
+// sum + a tile's counts at entries whose adjacency bit (2048) is set.
+__device__ __forceinline__ uint32_t fp4_masked_sum(const f32x16 &C, uint32_t sum) {
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
-        for (int qq = 0; qq < W; qq++) {
-            if (qq != q) continue;
-            uint64_t X[W];
-#pragma unroll
-            for (int w = qq; w < W; w++) X[w] = a < d ? rows[a * W + w] : 0ull;
-            part = pair_sweep<W, W>(rows, X, qq, wave_or64(X[qq]), part);
+    for (int r = 0; r < 16; r += 2) {
+        u16x2 p = __builtin_bit_cast(u16x2, __builtin_amdgcn_cvt_pknorm_u16(C[r], C[r + 1]));
+        p = __builtin_elementwise_sub_sat(p, u16x2{2048, 2048});
+        sum = __builtin_amdgcn_udot2(p, u16x2{1, 1}, sum, false);
+    }
+    return sum;
+}
+
+// Triangles of a local graph in degree order (d vertices, W words per row at
+// stride S, every row holding only bits above its own index): the sum over
+// local edges a -> b of |row_a & row_b|, on the matrix cores as in lg5_tiles,
+// with consecutive vertices for members and every word for R.  Tiles (ta <=
+// tb) are dealt round robin to the nw waves; b's operands are expanded at each
+// tile, which keeps the registers of the building phase.  Rows from d on are
+// taken as row d - 1, which is empty, and their own bits are beyond every row.
+// Returns the calling lane's share.
+__device__ __forceinline__ uint64_t local_tri(const uint64_t *rows, int32_t d, int32_t W, int32_t S,
+                                              int wib, int nw) {
+    const int lane = lane_id(), l32 = lane & 31, half = lane >> 5;
+    const uint32_t *rows32 = reinterpret_cast<const uint32_t *>(rows) + half;
+    const int32_t T = (d + 31) / 32, tiles = T * (T + 1) / 2;
+    uint32_t sum = 0;
+    int32_t tb = 0, before = 0;   // the tiles of the columns before tb
+    for (int32_t p = __builtin_amdgcn_readfirstlane(wib); p < tiles; p += nw) {
+        while (before + tb + 1 <= p) before += ++tb;
+        const int32_t ta = p - before;
+        const uint32_t *ra = rows32 + min(ta * 32 + l32, d - 1) * (2 * S);
+        const uint32_t *rb = rows32 + min(tb * 32 + l32, d - 1) * (2 * S);
+        const int32_t q0 = tb >> 1;
+        uint32_t aw = ra[2 * (W - 1)], bw = rb[2 * (W - 1)];
+        fp4x64 A;
+        f32x16 C = {};
+        for (int32_t q = W - 1; q >= q0; q--) {
+            A = fp4_left(aw);
+            const fp4x64 B = fp4_right(bw);
+            const int32_t nq = max(q - 1, q0);
+            aw = ra[2 * nq];
+            bw = rb[2 * nq];
+            C = fp4_step(A, B, C, kFp4Count);
         }
-        acc += part;
+        C = fp4_step(A, fp4_right(half == (tb & 1) ? 1u << l32 : 0u), C, kFp4Adj);
+        sum = fp4_masked_sum(C, sum);
     }
-    return acc;
+    return sum;
 }
 
-template <int WLO, int WHI>
-__device__ __forceinline__ uint64_t local_tri_dispatch(int32_t W, const uint64_t *rows, int32_t d,
-                                                       int wib, int nw) {
-    if constexpr (WLO > WHI) {
-        return 0;
-    } else {
-        if (W == WLO) return local_tri<WLO>(rows, d, wib, nw);
-        return local_tri_dispatch<WLO + 1, WHI>(W, rows, d, wib, nw);
-    }
-}
-
-// 4-cliques: workgroup per root (atomic cursor over the class list; roots of
-// out-degree <= dlo are left to another launch); the root's 4-cliques are the
-// triangles of its local graph.  RANK puts the local graph in degree order
-// and counts its triangles with local_tri, else they are counted per local
-// edge.  With LIST every 4-clique (u, v_i, v_j, v_x) is emitted instead.
+// 4-cliques: workgroup per root (from the work cursors; roots of out-degree
+// <= dlo are left to another launch); the root's 4-cliques are the triangles of
+// its local graph.  RANK puts the local graph in degree order, in which they are
+// counted (local_tri); the listing needs no order.  With LIST every 4-clique
+// (u, v_i, v_j, v_x) is emitted instead.  Bound by the building of the rows,
+// i.e. the lookups; the sum over local edges that local_tri replaced took
+// another 30 to 60 % (RMAT, 100,003 vertices, roots of 65..256: 425 us, now
+// 307; out-degrees up to 1,024 at density 0.83: 657 us, now 400).
 template <int DMAX, int NT, bool LIST, bool RANK>
-__global__ void __launch_bounds__(NT, DMAX == kHalfMaxD ? 6 : 1) k_lg4(const int32_t *__restrict__ off,
+__global__ void __launch_bounds__(NT, DMAX == kHalfMaxD ? 6 : (DMAX == kMidMaxD ? 8 : 1))
+    k_lg4(const int32_t *__restrict__ off,
                                             const int32_t *__restrict__ okey,
                                             const int32_t *__restrict__ dag_off,
                                             const int32_t *__restrict__ dag_adj,
@@ -297,7 +348,7 @@ __global__ void __launch_bounds__(NT, DMAX == kHalfMaxD ? 6 : 1) k_lg4(const int
                                             const int32_t *__restrict__ nroots_p, int32_t dlo,
                                             unsigned long long *cursor, unsigned long long *result,
                                             unsigned long long *res3, RowEmitter em) {
-    __shared__ uint64_t rows[DMAX * (DMAX / 64)];
+    __shared__ uint64_t rows[LgRows<DMAX>::kWords];
     __shared__ __align__(16) int32_t keys[LgHash<DMAX>::kSlots];
     __shared__ int16_t vals[LgHash<DMAX>::kSlots];
     __shared__ int32_t offj[DMAX], pre[DMAX + 1];
@@ -320,31 +371,28 @@ __global__ void __launch_bounds__(NT, DMAX == kHalfMaxD ? 6 : 1) k_lg4(const int
         const int32_t u = roots[r];
         const int32_t d = dag_off[u + 1] - dag_off[u], W = (d + 63) >> 6;
         if (d <= dlo || d > DMAX) continue;
-        build_rows<DMAX, NT, RANK>(off, okey, dag_off, dag_adj, u, d, W, rows, keys, vals, pre, offj,
+        const int32_t S = LgRows<DMAX>::stride(d, W);
+        build_rows<DMAX, NT, RANK>(off, okey, dag_off, dag_adj, u, d, S, rows, keys, vals, pre, offj,
                                    RANK ? lidx : nullptr, sh.s_sum, LIST ? verts : nullptr);
-        const int32_t ne = row_prefix<DMAX, NT>(rows, d, W, pre, sh.s_sum);
+        const int32_t ne = row_prefix<DMAX, NT>(rows, d, W, S, pre, sh.s_sum);
         if (res3 && tid == 0 && ne) atomicAdd(res3, (unsigned long long)ne);   // triangles at u
-        if constexpr (LIST || !RANK) {
+        if constexpr (LIST) {
             for (int32_t e = tid; e < ne; e += NT) {
                 int32_t i, j;
-                edge_at(rows, pre, d, W, e, i, j);
-                const uint64_t *ri = rows + i * W, *rj = rows + j * W;
-                if constexpr (LIST) {
-                    for (int32_t w = 0; w < W; w++) {
-                        uint64_t m = ri[w] & rj[w];
-                        while (m) {
-                            const int32_t x = w * 64 + __builtin_ctzll(m);
-                            m &= m - 1ull;
-                            const int32_t q[4] = {u, verts[i], verts[j], verts[x]};
-                            emit_vertices<4>(em, q);
-                        }
+                edge_at(rows, pre, d, S, e, i, j);
+                const uint64_t *ri = rows + i * S, *rj = rows + j * S;
+                for (int32_t w = 0; w < W; w++) {
+                    uint64_t m = ri[w] & rj[w];
+                    while (m) {
+                        const int32_t x = w * 64 + __builtin_ctzll(m);
+                        m &= m - 1ull;
+                        const int32_t q[4] = {u, verts[i], verts[j], verts[x]};
+                        emit_vertices<4>(em, q);
                     }
-                } else {
-                    for (int32_t w = 0; w < W; w++) acc += __popcll(ri[w] & rj[w]);
                 }
             }
         } else if (ne) {
-            acc += local_tri_dispatch<1, DMAX / kWave>(W, rows, d, tid / kWave, NT / kWave);
+            acc += local_tri(rows, d, W, S, tid / kWave, NT / kWave);
         }
         __syncthreads();
     }
@@ -370,7 +418,7 @@ __global__ void __launch_bounds__(NT, DMAX == kHalfMaxD ? 6 : 1) k_lg_build(cons
                                                  unsigned long long *units,
                                                  unsigned long long *res3,
                                                  unsigned long long *res4, uint64_t slice5) {
-    __shared__ uint64_t rows[DMAX * (DMAX / 64)];
+    __shared__ uint64_t rows[LgRows<DMAX>::kWords];
     __shared__ __align__(16) int32_t keys[LgHash<DMAX>::kSlots];
     __shared__ int16_t vals[LgHash<DMAX>::kSlots];
     __shared__ int16_t lidx[DMAX];
@@ -393,18 +441,19 @@ __global__ void __launch_bounds__(NT, DMAX == kHalfMaxD ? 6 : 1) k_lg_build(cons
         const int32_t u = roots[r];
         const int32_t d = dag_off[u + 1] - dag_off[u], W = (d + 63) >> 6;
         if (d <= dlo || d > DMAX) continue;
-        build_rows<DMAX, NT, true>(off, okey, dag_off, dag_adj, u, d, W, rows, keys, vals, pre, offj,
+        const int32_t S = LgRows<DMAX>::stride(d, W);
+        build_rows<DMAX, NT, true>(off, okey, dag_off, dag_adj, u, d, S, rows, keys, vals, pre, offj,
                                    lidx, sh.s_sum, verts);
         uint64_t *dst = grows + rowoff[r];
-        for (int32_t i = tid; i < d * W; i += NT) dst[i] = rows[i];
+        for (int32_t i = tid / kWave; i < d; i += NT / kWave)
+            if (lane_id() < W) dst[i * W + lane_id()] = rows[i * S + lane_id()];
         // then the out-neighbours in local (degree) order, for listings
         int32_t *dverts = reinterpret_cast<int32_t *>(dst + d * W);
         for (int32_t i = tid; i < d; i += NT) dverts[i] = verts[i];
-        const int32_t ne = row_prefix<DMAX, NT>(rows, d, W, pre, sh.s_sum);
+        const int32_t ne = row_prefix<DMAX, NT>(rows, d, W, S, pre, sh.s_sum);
         if (res3 && tid == 0 && ne) atomicAdd(res3, (unsigned long long)ne);   // triangles at u
         // local triangles (the 4-cliques at u): the 5-clique work
-        uint64_t tri = ne ? local_tri_dispatch<1, DMAX / kWave>(W, rows, d, tid / kWave, NT / kWave)
-                          : 0;
+        uint64_t tri = ne ? local_tri(rows, d, W, S, tid / kWave, NT / kWave) : 0;
         tri = wave_sum(tri);
         if (lane_id() == 0 && tri) atomicAdd((unsigned long long *)&sh.s_tri, (unsigned long long)tri);
         __syncthreads();
@@ -482,32 +531,6 @@ __device__ uint64_t lg5_sweep(const uint64_t *rows, const uint64_t *ri, int32_t 
     return acc;
 }
 
-// 0/1 words as FP4 operands of the 32 x 32 x 64 matrix instruction: a lane's
-// word holds 32 entries of a row, one per bit, and bit b of every nibble goes to
-// register b with the nibble's own code (1, 2, 4: the values 0.5, 1 and 2; bit 3
-// is moved to 4) in the left operand and the inverse value in the right one, so
-// that every product is 1.  The order of the 64 entries does not matter, as
-// both operands use the same.
-typedef int fp4x64 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-__device__ __forceinline__ fp4x64 fp4_left(uint32_t w) {
-    fp4x64 r = {};
-    r[0] = (int)(w & 0x11111111u);
-    r[1] = (int)(w & 0x22222222u);
-    r[2] = (int)(w & 0x44444444u);
-    r[3] = (int)((w >> 1) & 0x44444444u);
-    return r;
-}
-__device__ __forceinline__ fp4x64 fp4_right(uint32_t w) {
-    fp4x64 r = {};
-    r[0] = (int)((w << 2) & 0x44444444u);
-    r[1] = (int)(w & 0x22222222u);
-    r[2] = (int)((w >> 2) & 0x11111111u);
-    r[3] = (int)((w >> 3) & 0x11111111u);
-    return r;
-}
-
 // The same sum (5-cliques) on the matrix cores.  A tile is 32 members a by 32
 // members b, taken by their indices from the list, so the 0/1 product needs
 // only c x c / 2 of its d x d entries; its 64-entry steps run over the row
@@ -526,10 +549,6 @@ __device__ __forceinline__ fp4x64 fp4_right(uint32_t w) {
 // fifth.  RMAT-20, 3.7e7 tiles: 8.4 ms; by population counts, as lg5_sweep, 15.1.
 template <int W, int S>
 __device__ uint64_t lg5_tiles(const uint64_t *rows, const uint64_t *ri, int32_t c, int16_t *mem) {
-    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-    // the unit is 2^-16, so that a conversion to 16-bit fractions of 1 gives
-    // the counts; a quarter of a unit makes it exact under any rounding
-    constexpr int kOne = 0x6f6f6f6f, kAdj = 0x7a7a7a7a, kLeft = 0x7f7f7f7f;
     const int lane = lane_id(), l32 = lane & 31, half = lane >> 5;
     uint64_t R[W];
 #pragma unroll
@@ -575,31 +594,23 @@ __device__ uint64_t lg5_tiles(const uint64_t *rows, const uint64_t *ri, int32_t 
             }
             pa = mem[min(ta + 32 + l32, c - 1)];   // the next tile's
             f32x16 C = {};
-            auto mfma = [&](const fp4x64 &A, const fp4x64 &B, int scale) {
-                C = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A, B, C, 4, 4, 0, kLeft, 0, scale);
-            };
             fp4x64 A = fp4_left(aw[W - 1]), A1 = A;
-            mfma(A, XB[W - 1], kOne);
+            C = fp4_step(A, XB[W - 1], C, kFp4Count);
 #pragma unroll
             for (int q = W - 2; q >= 0; q--) {
                 if (q < first) break;
                 A1 = A;
                 A = fp4_left(aw[q]);
-                mfma(A, XB[q], kOne);
+                C = fp4_step(A, XB[q], C, kFp4Count);
             }
             // 2048 where a -> b: b's own bit, in words q0 .. q1
-            mfma(A, O0, kAdj);
+            C = fp4_step(A, O0, C, kFp4Adj);
             if (q1 > first) {
-                mfma(A1, O1, kAdj);
+                C = fp4_step(A1, O1, C, kFp4Adj);
                 for (int32_t q = first + 2; q <= q1; q++)
-                    mfma(fp4_left(ra[2 * q]), fp4_right(wb == 2 * q ? ob : 0u), kAdj);
+                    C = fp4_step(fp4_left(ra[2 * q]), fp4_right(wb == 2 * q ? ob : 0u), C, kFp4Adj);
             }
-#pragma unroll
-            for (int r = 0; r < 16; r += 2) {
-                u16x2 p = __builtin_bit_cast(u16x2, __builtin_amdgcn_cvt_pknorm_u16(C[r], C[r + 1]));
-                p = __builtin_elementwise_sub_sat(p, u16x2{2048, 2048});
-                sum = __builtin_amdgcn_udot2(p, u16x2{1, 1}, sum, false);
-            }
+            sum = fp4_masked_sum(C, sum);
         }
     }
     wave_sync();
@@ -666,14 +677,14 @@ __device__ void lg5_list(const uint64_t *rows, const uint64_t *ri, int32_t c, in
     wave_sync();
 }
 
-template <int WLO, int WHI, bool PAD>
+template <int WLO, int WHI>
 __device__ __forceinline__ void lg5_list_dispatch(int32_t W, const uint64_t *rows,
                                                   const uint64_t *ri, int32_t c, int16_t *mem,
                                                   const int32_t *verts, int32_t u, int32_t vi,
                                                   RowEmitter &em) {
     if constexpr (WLO <= WHI) {
-        if (W == WLO) lg5_list<WLO, PAD ? (WLO | 1) : WLO>(rows, ri, c, mem, verts, u, vi, em);
-        else lg5_list_dispatch<WLO + 1, WHI, PAD>(W, rows, ri, c, mem, verts, u, vi, em);
+        if (W == WLO) lg5_list<WLO, (WLO | 1)>(rows, ri, c, mem, verts, u, vi, em);
+        else lg5_list_dispatch<WLO + 1, WHI>(W, rows, ri, c, mem, verts, u, vi, em);
     }
 }
 
@@ -732,19 +743,19 @@ __device__ uint64_t lgk_set(const uint64_t *rows, const uint64_t *set0, int32_t 
     return acc;
 }
 
-template <int WLO, int WHI, bool PAD, bool DEEP>
+template <int WLO, int WHI, bool DEEP>
 __device__ __forceinline__ uint64_t lg5_dispatch(int32_t W, const uint64_t *rows, const uint64_t *ri,
                                                  int32_t c, int32_t e, int16_t *mem,
                                                  uint64_t *stack) {
     if constexpr (WLO > WHI) {
         return 0;
     } else {
-        constexpr int S = PAD ? (WLO | 1) : WLO;
+        constexpr int S = WLO | 1;   // the rows' stride
         if (W == WLO) {
             if constexpr (DEEP) return lgk_set<WLO, S>(rows, ri, c, e, mem, stack);
             else return lg5_tiles<WLO, S>(rows, ri, c, mem);
         }
-        return lg5_dispatch<WLO + 1, WHI, PAD, DEEP>(W, rows, ri, c, e, mem, stack);
+        return lg5_dispatch<WLO + 1, WHI, DEEP>(W, rows, ri, c, e, mem, stack);
     }
 }
 
@@ -813,9 +824,9 @@ __global__ void __launch_bounds__((Lg5Block<DMAX, !LIST && !DEEP>::kThreads),
             for (int32_t w = 0; w < W; w++) cnt += __popcll(ri[w]);
             if (cnt < 3 + extra) continue;
             if constexpr (LIST)
-                lg5_list_dispatch<WLO, WHI, true>(W, rows, ri, cnt, mem, verts, u, verts[i], em);
+                lg5_list_dispatch<WLO, WHI>(W, rows, ri, cnt, mem, verts, u, verts[i], em);
             else
-                acc += lg5_dispatch<WLO, WHI, true, DEEP>(W, rows, ri, cnt, extra, mem, stack);
+                acc += lg5_dispatch<WLO, WHI, DEEP>(W, rows, ri, cnt, extra, mem, stack);
         }
         __syncthreads();
     }
@@ -848,7 +859,7 @@ __global__ void __launch_bounds__(NT, DEEP ? 7 : kMidWaves) k_lg5_mid(const int3
     constexpr int WMAX = DMAX / 64;
     constexpr int WLO = 2, WHI = WMAX;   // out-degrees 65..DMAX
     constexpr int kMaxExtra = 4;         // k <= 9
-    __shared__ uint64_t rows[DMAX * WMAX];
+    __shared__ uint64_t rows[LgRows<DMAX>::kWords];
     __shared__ __align__(16) int32_t keys[LgHash<DMAX>::kSlots];
     __shared__ int16_t vals[LgHash<DMAX>::kSlots];
     __shared__ int16_t lidx[DMAX];
@@ -869,29 +880,23 @@ __global__ void __launch_bounds__(NT, DEEP ? 7 : kMidWaves) k_lg5_mid(const int3
         __syncthreads();
         if (r >= nroots) break;
         const int32_t u = roots[r];
-        const int32_t d = dag_off[u + 1] - dag_off[u], W = (d + 63) >> 6;
-        build_rows<DMAX, NT, true>(off, okey, dag_off, dag_adj, u, d, W, rows, keys, vals, pre, offj,
+        const int32_t d = dag_off[u + 1] - dag_off[u], W = (d + 63) >> 6, S = W | 1;
+        build_rows<DMAX, NT, true>(off, okey, dag_off, dag_adj, u, d, S, rows, keys, vals, pre, offj,
                                    lidx, sh.s_sum, verts);
         if (res3 || res4) {
-            const int32_t ne = row_prefix<DMAX, NT>(rows, d, W, pre, sh.s_sum);
+            const int32_t ne = row_prefix<DMAX, NT>(rows, d, W, S, pre, sh.s_sum);
             if (tid == 0) acc3 += ne;
-            if (res4)
-                for (int32_t e = tid; e < ne; e += NT) {
-                    int32_t i, j;
-                    edge_at(rows, pre, d, W, e, i, j);
-                    const uint64_t *ri = rows + i * W, *rj = rows + j * W;
-                    for (int32_t w = 0; w < W; w++) acc4 += __popcll(ri[w] & rj[w]);
-                }
+            if (res4 && ne) acc4 += local_tri(rows, d, W, S, wib, NW);
         }
         for (int32_t i = wib; i < d; i += NW) {
-            const uint64_t *ri = rows + i * W;
+            const uint64_t *ri = rows + i * S;
             int32_t cnt = 0;
             for (int32_t w = 0; w < W; w++) cnt += __popcll(ri[w]);
             if (cnt < 3 + extra) continue;
             if constexpr (LIST)
-                lg5_list_dispatch<WLO, WHI, false>(W, rows, ri, cnt, s_mem[wib], verts, u, verts[i], em);
+                lg5_list_dispatch<WLO, WHI>(W, rows, ri, cnt, s_mem[wib], verts, u, verts[i], em);
             else
-                acc += lg5_dispatch<WLO, WHI, false, DEEP>(W, rows, ri, cnt, extra, s_mem[wib],
+                acc += lg5_dispatch<WLO, WHI, DEEP>(W, rows, ri, cnt, extra, s_mem[wib],
                                                            s_stack[wib]);
         }
         __syncthreads();
@@ -1077,7 +1082,7 @@ gpm_status lg_cliques(const gpm_graph *g, int32_t k, const int32_t *list_m, cons
                                    dim3(kMidThreads), 0, st, g->off, g->okey, g->dag_off, g->dag_adj,
                                    list_m, cnt_m, 0, L.cursor(1), res, res3, *em);
             else
-                hipLaunchKernelGGL((k_lg4<kMidMaxD, kMidThreads, false, false>), grid,
+                hipLaunchKernelGGL((k_lg4<kMidMaxD, kMidThreads, false, true>), grid,
                                    dim3(kMidThreads), 0, st, g->off, g->okey, g->dag_off, g->dag_adj,
                                    list_m, cnt_m, 0, L.cursor(1), res, res3, none);
         }
