@@ -23,7 +23,8 @@
 // neighbours (binary search in their sorted rows), the non-neighbours when
 // vertex-induced, and distinctness; the survivors are a lane mask.  At the
 // last step the mask's population count is the count; otherwise the wave
-// descends into its candidates one by one.
+// descends into its candidates one by one, but where the connectivity map is
+// kept a count takes the last two steps at once (leaf_pairs).
 #include <algorithm>
 #include <cstdlib>
 #include <vector>
@@ -36,6 +37,7 @@ namespace {
 
 constexpr int kGenMaxK = 6;
 constexpr int kGenMaxE = kGenMaxK * (kGenMaxK - 1) / 2;
+constexpr int kGenMncMaxK = 5;           // largest pattern with a connectivity map
 constexpr int kGenNT = 256;             // 4 waves per workgroup
 constexpr int32_t kGenMncMaxN = 8192;    // graphs up to this size keep a connectivity map per wave
 
@@ -244,7 +246,7 @@ __global__ void __launch_bounds__(kGenNT) k_generic(const int32_t *__restrict__ 
     const int32_t last = P.k - 1;
     const int64_t narcs = off[n];
     const int64_t nchunks = chunk_off[narcs];
-    uint64_t count = 0;   // wave-uniform
+    uint64_t count = 0;   // the lane's share (mod 2^64)
     // candidates of step s: the allowed range of the smallest backward row
     auto open_step = [&](int32_t s) {
         int32_t best = -1, best_len = 0;
@@ -270,6 +272,99 @@ __global__ void __launch_bounds__(kGenNT) k_generic(const int32_t *__restrict__ 
             S.mask[s] = 0ull;
         }
         wave_sync();
+    };
+    // The matches of the last step below up to 64 candidates v of the step s
+    // before it, one a lane (ok), all at once; the lanes' sum is the result.
+    // X holds the vertices x that the last step accepts by the steps before s:
+    // x is adjacent to none or all of them as the pattern has it, by the map,
+    // within their bounds and not one of them.  With v it is |X & N(v)| where
+    // the last step is adjacent to s, |X - v| where the pattern does not care,
+    // and the difference where it must not be; a bound between x and v cuts
+    // both to one side of v.  |X| takes one pass over a backward row for the 64
+    // candidates; the rows N(v) are walked end to end, 256 entries at a time.
+    // (The degree filter follows from the adjacency at the last step.)
+    // Bound by the walk's instructions, about 25 per 64 entries; candidates
+    // one by one took a marking and a clearing of each N(v) in the map and a
+    // chain of LDS and row latencies besides (induced 4-paths of RMAT-12: 8.1
+    // ms, now 1.7; induced 4-cycles 2.7 ms, now 0.7).
+    auto leaf_pairs = [&](int32_t s, int32_t v, bool ok) -> uint64_t {
+        const int32_t last = s + 1;
+        const uint32_t before = (1u << s) - 1u;
+        const uint32_t need = P.back_adj[last] & before;
+        const uint32_t non = P.induced ? P.back_non[last] & before : 0u;
+        const bool adj_v = (P.back_adj[last] >> s) & 1u;
+        const bool non_v = P.induced && ((P.back_non[last] >> s) & 1u);
+        const bool above_v = (P.above[last] >> s) & 1u, below_v = (P.below[last] >> s) & 1u;
+        int32_t m[kGenMncMaxK - 2], lo = 0, hi = n;   // x in [lo, hi) by the earlier steps
+#pragma unroll
+        for (int t = 0; t < kGenMncMaxK - 2; t++) {
+            m[t] = -1;
+            if (t >= s) continue;
+            m[t] = __builtin_amdgcn_readfirstlane(S.m[t]);
+            if ((P.above[last] >> t) & 1u) lo = max(lo, m[t] + 1);
+            if ((P.below[last] >> t) & 1u) hi = min(hi, m[t]);
+        }
+        auto in_x = [&](int32_t x) {   // (the bounds apart)
+            const uint32_t bits = map[x >> 3] >> ((x & 7) * 4);
+            bool r = (bits & (need | non)) == need;
+#pragma unroll
+            for (int t = 0; t < kGenMncMaxK - 2; t++) r = r && x != m[t];
+            return r;
+        };
+        const int32_t xlo = above_v ? max(lo, v + 1) : lo, xhi = below_v ? min(hi, v) : hi;
+        int64_t total = 0;
+        if (adj_v || non_v) {
+            int32_t st = 0, en = 0;
+            if (ok) {
+                st = off[v];
+                en = off[v + 1];
+                if (above_v || lo > 0) st = lower_idx(adj, st, en, xlo);
+                if (below_v || hi < n) en = lower_idx(adj, st, en, xhi);
+            }
+            int32_t hits = 0;
+            wave_segments<4>(st, max(0, en - st), [&](const int32_t (&e)[4], const bool (&live)[4],
+                                                      const int32_t (&)[4]) {
+                int32_t x[4];
+#pragma unroll
+                for (int q = 0; q < 4; q++) x[q] = adj[e[q]];
+#pragma unroll
+                for (int q = 0; q < 4; q++) hits += live[q] && in_x(x[q]);
+            });
+            total = adj_v ? (int64_t)hits : -(int64_t)hits;
+        }
+        if (!adj_v) {
+            // X, by the shortest of the backward rows before s
+            int32_t rs = 0, rz = 0;
+            bool first = true;
+#pragma unroll
+            for (int t = 0; t < kGenMncMaxK - 2; t++) {
+                if (!((need >> t) & 1u)) continue;
+                const int32_t a = off[m[t]], z = off[m[t] + 1];
+                if (first || z - a < rz - rs) {
+                    rs = a;
+                    rz = z;
+                    first = false;
+                }
+            }
+            if (lo > 0) rs = lower_idx(adj, rs, rz, lo);
+            if (hi < n) rz = lower_idx(adj, rs, rz, hi);
+            int32_t is = rs, iz = rz;   // the lane's part of it
+            if (ok && above_v) is = lower_idx(adj, rs, rz, xlo);
+            if (ok && below_v) iz = lower_idx(adj, rs, rz, xhi);
+            int32_t found = 0;
+            for (int32_t p = rs; p < rz; p += kWave) {
+                const int32_t i = p + lane;
+                const uint64_t mask = __ballot(i < rz && in_x(adj[min(i, rz - 1)]));
+                const int32_t n0 = min(max(is - p, 0), 64), n1 = min(max(iz - p, 0), 64);
+                const uint64_t from = n0 < 64 ? mask >> n0 << n0 : 0ull;
+                found += __popcll(n1 < 64 ? from & ((1ull << n1) - 1ull) : from);
+            }
+            if (ok) {
+                total += found;
+                if (!above_v && !below_v && v >= lo && v < hi && in_x(v)) total--;
+            }
+        }
+        return (uint64_t)total;
     };
     // a work unit is one 64-candidate chunk of step 2 below one arc (steps
     // 0 and 1), with the whole search below it; units come from
@@ -337,6 +432,13 @@ __global__ void __launch_bounds__(kGenNT) k_generic(const int32_t *__restrict__ 
                 msk = __ballot(ok);
                 wave_sync();
                 if (lane == 0) S.pos[s] = p + kWave;
+                if constexpr (MNC && !LIST) {
+                    if (s + 1 == last) {
+                        if (msk) count += leaf_pairs(s, v, ok);
+                        wave_sync();
+                        continue;
+                    }
+                }
                 if (s == last) {
                     if (LIST) {
                         if (ok) {
@@ -346,7 +448,7 @@ __global__ void __launch_bounds__(kGenNT) k_generic(const int32_t *__restrict__ 
                             gen_emit(em, P, mm);
                         }
                     } else {
-                        count += (uint64_t)__popcll(msk);
+                        if (lane == 0) count += (uint64_t)__popcll(msk);
                     }
                     wave_sync();
                     continue;
@@ -374,7 +476,10 @@ __global__ void __launch_bounds__(kGenNT) k_generic(const int32_t *__restrict__ 
         }
     }
     if (LIST) row_emitter_flush(em, result);
-    else if (lane == 0 && count) atomicAdd(result, (unsigned long long)count);
+    else {
+        count = wave_sum(count);
+        if (lane == 0 && count) atomicAdd(result, (unsigned long long)count);
+    }
 }
 
 // Listing of two-vertex patterns: every arc the partial orders accept.
@@ -641,7 +746,7 @@ static gpm_status generic_run(const gpm_graph *g, const gpm_pattern *p, bool lis
     // of at most 5 vertices on graphs of at most 8192 vertices (larger maps
     // cost more occupancy than the searches they save)
     const char *env = getenv("GPM_MNC");
-    const bool mnc = P.k <= 5 && g->n <= kGenMncMaxN && !(env && env[0] == '0');
+    const bool mnc = P.k <= kGenMncMaxK && g->n <= kGenMncMaxN && !(env && env[0] == '0');
     const int32_t stride = mnc ? (g->n + 7) / 8 : 0;
     const size_t dyn = mnc ? (size_t)(kGenNT / kWave) * stride * sizeof(uint32_t) : 0;
 #define GEN_LAUNCH(M, L)                                                                       \
