@@ -418,16 +418,17 @@ __device__ __forceinline__ void walk_lookup(const int32_t *pre, const int32_t *o
 // up, found by one look at all of them (a lane each, so that the kernel needs
 // no registers for it) and not by adding to each.  With no more tasks than
 // workers, each takes the one of its own number.
-struct TaskQueue {
-    unsigned long long *cur;
+template <class T, int N> struct TaskQueueOf {
+    static constexpr int kStride = 128 / sizeof(T);
+    T *cur;
     int64_t n;
     int32_t w;
     uint32_t open;   // bit i: counter i is not known to be used up; 0: a task per worker
-    __device__ TaskQueue(unsigned long long *c, int64_t n_tasks, int32_t worker, int32_t workers)
+    __device__ TaskQueueOf(T *c, int64_t n_tasks, int32_t worker, int32_t workers)
         : cur(c), n(n_tasks) {
         const bool one = n_tasks <= workers;
-        w = one ? worker : worker % kCursors;
-        open = one ? 0u : (2u << kCursors) - 1u;   // (bit kCursors keeps it from 0)
+        w = one ? worker : worker % N;
+        open = one ? 0u : (2u << N) - 1u;   // (bit N keeps it from 0)
         w = __builtin_amdgcn_readfirstlane(w);
     }
     __device__ __forceinline__ int64_t next() {
@@ -437,25 +438,26 @@ struct TaskQueue {
             return t < n ? t : -1;
         }
         while (w >= 0) {
-            unsigned long long got = 0;
-            if (lane_id() == 0) got = atomicAdd(cur + w * kCursorStride, 1ull);
+            T got = 0;
+            if (lane_id() == 0) got = atomicAdd(cur + w * kStride, (T)1);
             const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)got);
-            const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(got >> 32));
-            const int64_t t = (int64_t)(((uint64_t)hi << 32) | lo) * kCursors + w;
+            const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)got >> 32));
+            const int64_t t = (int64_t)(((uint64_t)hi << 32) | lo) * N + w;
             if (t < n) return t;
             open &= ~(1u << w);
             // the next counter after w, cyclically, that has tasks left
-            const int i = lane_id() % kCursors;
-            const unsigned long long c = __hip_atomic_load(
-                cur + i * kCursorStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint32_t left = (uint32_t)__ballot((int64_t)c * kCursors + i < n) & open &
-                                  ((1u << kCursors) - 1u);
+            const int i = lane_id() % N;
+            const T c = __hip_atomic_load(
+                cur + i * kStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t left = (uint32_t)__ballot((int64_t)c * N + i < n) & open &
+                                  ((1u << N) - 1u);
             const uint32_t after = left & ~((2u << w) - 1u);
             w = left ? __builtin_ctz(after ? after : left) : -1;
         }
         return -1;
     }
 };
+using TaskQueue = TaskQueueOf<unsigned long long, kCursors>;
 
 // The entries of 64 segments (one per lane: first entry st, len entries),
 // shared out over the wave: segments are cut into units of 16 entries, a unit
@@ -497,6 +499,40 @@ __device__ __forceinline__ void wave_segments(int32_t st, int32_t len, F &&f) {
             f(e, live, seg);
         }
     }
+}
+
+// 0/1 words as FP4 operands of the 32 x 32 x 64 matrix instruction: a lane's
+// word holds 32 entries of a row, one per bit, and bit b of every nibble goes to
+// register b with the nibble's own code (1, 2, 4: the values 0.5, 1 and 2; bit 3
+// is moved to 4) in the left operand and the inverse value in the right one, so
+// that every product is 1.  The order of the 64 entries does not matter, as
+// both operands use the same.
+typedef int fp4x64 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ fp4x64 fp4_left(uint32_t w) {
+    fp4x64 r = {};
+    r[0] = (int)(w & 0x11111111u);
+    r[1] = (int)(w & 0x22222222u);
+    r[2] = (int)(w & 0x44444444u);
+    r[3] = (int)((w >> 1) & 0x44444444u);
+    return r;
+}
+__device__ __forceinline__ fp4x64 fp4_right(uint32_t w) {
+    fp4x64 r = {};
+    r[0] = (int)((w << 2) & 0x44444444u);
+    r[1] = (int)(w & 0x22222222u);
+    r[2] = (int)((w >> 2) & 0x11111111u);
+    r[3] = (int)((w >> 3) & 0x11111111u);
+    return r;
+}
+
+// C + the 32 x 32 products of 64 entries of the rows in A and B, in the unit
+// given as four scale bytes (0x7f: 1, one less halves it).
+constexpr int kFp4One = 0x7f7f7f7f;
+__device__ __forceinline__ f32x16 fp4_step(const fp4x64 &A, const fp4x64 &B, const f32x16 &C,
+                                           int unit) {
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A, B, C, 4, 4, 0, kFp4One, 0, unit);
 }
 
 // splitmix64 finaliser, for the listing checksum.

@@ -247,39 +247,8 @@ __device__ __forceinline__ uint32_t pair_sweep(const uint64_t *rows, const uint6
     return part;
 }
 
-// 0/1 words as FP4 operands of the 32 x 32 x 64 matrix instruction: a lane's
-// word holds 32 entries of a row, one per bit, and bit b of every nibble goes to
-// register b with the nibble's own code (1, 2, 4: the values 0.5, 1 and 2; bit 3
-// is moved to 4) in the left operand and the inverse value in the right one, so
-// that every product is 1.  The order of the 64 entries does not matter, as
-// both operands use the same.
-typedef int fp4x64 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-__device__ __forceinline__ fp4x64 fp4_left(uint32_t w) {
-    fp4x64 r = {};
-    r[0] = (int)(w & 0x11111111u);
-    r[1] = (int)(w & 0x22222222u);
-    r[2] = (int)(w & 0x44444444u);
-    r[3] = (int)((w >> 1) & 0x44444444u);
-    return r;
-}
-__device__ __forceinline__ fp4x64 fp4_right(uint32_t w) {
-    fp4x64 r = {};
-    r[0] = (int)((w << 2) & 0x44444444u);
-    r[1] = (int)(w & 0x22222222u);
-    r[2] = (int)((w >> 2) & 0x11111111u);
-    r[3] = (int)((w >> 3) & 0x11111111u);
-    return r;
-}
-
-// C + the 32 x 32 products of 64 entries of the rows in A and B, in units of
-// 2^-16 (kFp4Count) or of 2^-5 (kFp4Adj): 2048 of the first.
+// Units of the products: 2^-16 for counts, and 2^-5, i.e. 2048 of the first.
 constexpr int kFp4Count = 0x6f6f6f6f, kFp4Adj = 0x7a7a7a7a;
-__device__ __forceinline__ f32x16 fp4_step(const fp4x64 &A, const fp4x64 &B, const f32x16 &C,
-                                           int unit) {
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A, B, C, 4, 4, 0, 0x7f7f7f7f, 0, unit);
-}
 // sum + a tile's counts at entries whose adjacency bit (2048) is set.
 __device__ __forceinline__ uint32_t fp4_masked_sum(const f32x16 &C, uint32_t sum) {
     typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
