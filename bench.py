@@ -47,7 +47,8 @@ HBM_PEAK_GBS = 8000.0
 # per clock (a wave64 instruction occupies a 16-lane SIMD for 4 clocks)
 INT32_VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 # algorithmic int32 ops per local triangle of the 5-clique kernel: the AND and
-# the population count of one 64-bit candidate word (2 + 2 32-bit ops)
+# the population count of one 64-bit candidate word (2 + 2 32-bit ops), whatever
+# the kernel does instead (it takes dense tiles of them on the matrix cores)
 OPS_PER_LOCAL_TRIANGLE = 4
 
 
@@ -81,7 +82,8 @@ def dag_class_bytes(off, adj, dmin, dmax, kmin):
     """Algorithmic bytes of one triangle/local-graph-build launch over the
     roots u with dmin < d+(u) <= dmax and d+(u) >= kmin: per root, its
     out-list (4 B per arc); per out-neighbour v, v's two offsets (8 B) and
-    v's out-list (4 B per entry, the (v, w) pairs)."""
+    v's out-list (4 B per entry, the (v, w) pairs), or the shorter of its and
+    u's for triangles (kmin 2)."""
     n = off.shape[0] - 1
     deg = np.diff(off).astype(np.int64)
     rows = np.repeat(np.arange(n, dtype=np.int64), deg)
@@ -89,7 +91,12 @@ def dag_class_bytes(off, adj, dmin, dmax, kmin):
     fwd = (deg[rows] < deg[cols]) | ((deg[rows] == deg[cols]) & (rows < cols))
     src, dst = rows[fwd], cols[fwd]
     dout = np.bincount(src, minlength=n)
-    pairs_root = np.bincount(src, weights=dout[dst], minlength=n).astype(np.int64)
+    if kmin == 2:
+        # triangles: an arc's shorter out-list, looked up in the longer
+        walked = np.minimum(dout[src], dout[dst])
+    else:
+        walked = dout[dst]
+    pairs_root = np.bincount(src, weights=walked, minlength=n).astype(np.int64)
     sel = (dout > dmin) & (dout <= dmax) & (dout >= kmin) & (pairs_root > 0)
     arcs = int(dout[sel].sum())
     pairs = int(pairs_root[sel].sum())

@@ -236,7 +236,7 @@ gpm_status gpm_graph_orient(gpm_graph *g, int32_t order, void *d_scratch, uint64
  * split into tasks of about 8 tc_tau / d of its neighbours (at least 256;
  * tc_tau[0], [1], [2] for d up to 64, up to 256 and above), roughly tc_tau
  * candidate pairs, that cu_count * max(tc_blocks_per_cu[1], [2]) persistent
- * workgroups take from an atomic cursor, and the arcs between shorter lists
+ * workgroups take from work cursors, and the arcs between shorter lists
  * are merged, a lane per arc, by at most cu_count * tc_blocks_per_cu[0]
  * workgroups; 5-clique counting splits each root of out-degree above 256
  * into tasks of about lg5_slice local triangles; k-cliques (k >= 4) at roots of

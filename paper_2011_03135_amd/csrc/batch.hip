@@ -2,7 +2,7 @@
 //
 // The G graphs are one union graph g whose graph i owns vertices
 // voff[i] .. voff[i+1]-1.  Teams of threads (one workgroup per graph at a
-// time, graphs popped from an atomic cursor) compute every step of the motif
+// time, taken from the work cursors) compute every step of the motif
 // path for their graph entirely on chip: the graph's offsets are staged in
 // LDS, its adjacency becomes bit rows in LDS (row v = neighbours of v,
 // ceil(n/64) words), and
@@ -10,9 +10,9 @@
 //   per-edge triangles  T_uv = |A_u & A_v|               (Section 5)
 //   local-count sums    the four per-edge sums of the motif path
 //   4-cliques           sum over triangles u < v < w of |A_u & A_v & A_w & above(w)|
-//   4-cycles            sum over x, z < x of C(|A_x & A_z & below(x)|, 2)
-//                       (each cycle once, from its largest vertex x and the
-//                       opposite vertex z; the middles lie below x)
+//   4-cycles            an eighth of the sum over x != z of |A_x & A_z|^2, less
+//                       what its wedges and degrees add to it (each cycle has
+//                       two diagonals, each in both orders)
 // are combined into the induced counts with the same exact identities as the
 // single-graph path, and written to the graph's row of the output.
 //
@@ -304,10 +304,11 @@ __global__ void __launch_bounds__(NT) k_batch(const int32_t *__restrict__ off,
             // 4-cycles by their diagonals: the squares of the codegrees of all
             // ordered pairs, on the matrix cores, 32 x 32 pairs a tile (an
             // entry is at most 1,023 and a lane's 16 squares below 2^24).
-            // Sum over x != z of C(c, 2) = 4 times the 4-cycles, where the sum
-            // of c is twice the wedges and c of (x, x) the degree of x.
-            // Replaces the population counts over all pairs, which took most of
-            // a graph's operations (20,000 graphs of 10 to 200 vertices: 886 us).
+            // The sum over x != z of C(c, 2) is 4 times the 4-cycles, that of c
+            // twice the wedges, and c of (x, x) the degree of x.  The population
+            // counts over all pairs that this replaced took most of a graph's
+            // operations (20,000 graphs of 10 to 200 vertices: 886 us, now 463,
+            // bound by the latency of a graph's own chain of loads and sums).
             const uint32_t *rows32 = reinterpret_cast<const uint32_t *>(sh.rows) + (lane >> 5);
             const int32_t tiles = T * (T + 1) / 2;
             int32_t tb = 0, before = 0;   // the tiles of the columns before tb

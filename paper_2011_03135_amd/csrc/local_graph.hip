@@ -11,15 +11,17 @@
 // Rows are 64-bit words in LDS (at most 1024 x 16 words = 128 KiB of the
 // 160 KiB a gfx950 workgroup may use).
 //
-// 4-cliques: one workgroup per root builds the rows and counts (counting
-// costs about as much as building).
-// 5-cliques: counting can cost far more than building on hub roots, so one
-// kernel builds every root's rows once and stores them in HBM, and a second
-// kernel splits each root into slices of its local edges (e = s mod S, S
-// proportional to the root's local edge count times its row width); a slice
-// copies the rows back into LDS and runs a per-lane work loop (fetch an
-// edge, then step through its candidates one at a time) so skewed candidate
-// sets do not stall a wave.
+// Both sums run as 32 x 32 tiles of pairs on the matrix cores, the rows' bits
+// expanded to FP4 in registers (local_tri, lg5_tiles); larger cliques descend
+// with AND + population count.
+//
+// 4-cliques: one workgroup per root builds the rows and counts.
+// 5-cliques and larger: counting can cost far more than building on hub roots,
+// so above 256 out-neighbours one kernel builds every root's rows once and
+// stores them in HBM, and a second splits each root into slices of its local
+// vertices (i = s mod S, S proportional to the root's local triangles); a slice
+// copies the rows back into LDS and its waves take the vertices as they become
+// free.  Roots of 65..256 do both in one kernel.
 #include "gpm_internal.h"
 
 #include <algorithm>

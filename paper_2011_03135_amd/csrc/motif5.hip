@@ -64,7 +64,10 @@
 //   wheel       sum over vertices i of N(C4) in G[N(i)]
 // (graphs of up to kTrace5MaxN vertices; above, these five are counted
 // directly as induced patterns by the general plan).  K5 is counted by the
-// clique kernels.
+// clique kernels.  Up to kTrace5MaxN vertices the sums over triangles and
+// 4-cliques and these five read the edges' common neighbours from lists made
+// once (k_f5_lists); a graph whose lists exceed kListsPerEdge entries an edge
+// walks the rows for them.
 #include "gpm_internal.h"
 
 #include <algorithm>
