@@ -307,8 +307,9 @@ __global__ void __launch_bounds__(NT) k_batch(const int32_t *__restrict__ off,
             // The sum over x != z of C(c, 2) is 4 times the 4-cycles, that of c
             // twice the wedges, and c of (x, x) the degree of x.  The population
             // counts over all pairs that this replaced took most of a graph's
-            // operations (20,000 graphs of 10 to 200 vertices: 886 us, now 463,
-            // bound by the latency of a graph's own chain of loads and sums).
+            // operations (20,000 graphs of 10 to 200 vertices: 886 us; with
+            // this and the spread cursors 342, bound by the latency of a graph's
+            // own chain of loads and sums).
             const uint32_t *rows32 = reinterpret_cast<const uint32_t *>(sh.rows) + (lane >> 5);
             const int32_t tiles = T * (T + 1) / 2;
             int32_t tb = 0, before = 0;   // the tiles of the columns before tb

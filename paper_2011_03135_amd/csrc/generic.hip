@@ -286,7 +286,7 @@ __global__ void __launch_bounds__(kGenNT) k_generic(const int32_t *__restrict__ 
     // Bound by the walk's instructions, about 25 per 64 entries; candidates
     // one by one took a marking and a clearing of each N(v) in the map and a
     // chain of LDS and row latencies besides (induced 4-paths of RMAT-12: 8.1
-    // ms, now 1.7; induced 4-cycles 2.7 ms, now 0.7).
+    // ms, now 1.6; induced 4-cycles 2.7 ms, now 0.7).
     auto leaf_pairs = [&](int32_t s, int32_t v, bool ok) -> uint64_t {
         const int32_t last = s + 1;
         const uint32_t before = (1u << s) - 1u;
