@@ -22,6 +22,7 @@
 // Listing (in vertex ids) groups each apex's wedges by z and emits every
 // pair of middles: light apexes per wave, heavy ones per (apex, id part).
 #include "gpm_internal.h"
+#include "list_tiles.h"
 
 #include <algorithm>
 
@@ -116,19 +117,13 @@ __global__ void __launch_bounds__(kBlock) k_c4_work(const int32_t *__restrict__ 
 }
 
 // The apexes of every class, ascending, in two passes over tiles of `tile`
-// ids (a multiple of kListTile): the classes' sizes per tile, 21 bits each,
-// then every workgroup adds up the tiles before its own and places its ids.
+// ids (list_tiles.h): the classes' sizes per tile, packed in one word, then
+// every workgroup adds up the tiles before its own and places its ids.
 // Ascending order matters: the counting kernel starts with the top ranks,
 // and with the tiles in the order of their arrival instead (one pass) it took
 // 2.27 ms, not 2.12, on RMAT-18.
 constexpr int kListPer = 4;
-constexpr int kListTile = kBlock * kListPer;
-constexpr int kListTiles = 1024;   // at most
-
-int32_t list_tile(int32_t n) {
-    const int64_t t = ((int64_t)n + kListTiles - 1) / kListTiles;
-    return (int32_t)((t + kListTile - 1) / kListTile * kListTile);
-}
+static_assert(kListTile == kBlock * kListPer, "a workgroup takes a step of its tile");
 
 template <bool PLACE>
 __global__ void __launch_bounds__(kBlock) k_c4_lists(const int32_t *__restrict__ cls, int32_t n,
@@ -157,8 +152,8 @@ __global__ void __launch_bounds__(kBlock) k_c4_lists(const int32_t *__restrict__
         uint64_t two = 0, third = 0;   // light | heavy << 32, medium
         for (uint32_t t = tid; t < blockIdx.x; t += kBlock) {
             const uint64_t v = sums[t];
-            two += (v & 0x1fffffu) | ((v >> 21) & 0x1fffffu) << 32;
-            third += v >> 42;
+            two += ids_of_class(v, 0) | (uint64_t)ids_of_class(v, 1) << 32;
+            third += ids_of_class(v, 2);
         }
         block_scan(two, total);
         base[0] = (int32_t)total;
@@ -170,12 +165,12 @@ __global__ void __launch_bounds__(kBlock) k_c4_lists(const int32_t *__restrict__
     uint64_t all = 0;
     for (int64_t r0 = (int64_t)blockIdx.x * tile; r0 < z; r0 += kListTile) {
         int32_t c[kListPer];
-        uint64_t num = 0;   // 21 bits per class
+        uint64_t num = 0;   // kClassBits per class
 #pragma unroll
         for (int q = 0; q < kListPer; q++) {
             const int64_t r = r0 + tid * kListPer + q;
             c[q] = r < z ? cls[r] : C4_NONE;
-            if (c[q] != C4_NONE) num += 1ull << (21 * (c[q] - 1));
+            if (c[q] != C4_NONE) num += one_of_class(c[q] - 1);
         }
         if (!PLACE) {
             all += num;
@@ -188,12 +183,11 @@ __global__ void __launch_bounds__(kBlock) k_c4_lists(const int32_t *__restrict__
             const int k = c[q] - 1;
             int32_t *list = k == 0 ? light : (k == 1 ? heavy : med);
             const int32_t b = k == 0 ? base[0] : (k == 1 ? base[1] : base[2]);
-            list[b + (int32_t)((at >> (21 * k)) & 0x1fffffu)] =
-                (int32_t)(r0 + tid * kListPer + q);
-            at += 1ull << (21 * k);
+            list[b + (int32_t)ids_of_class(at, k)] = (int32_t)(r0 + tid * kListPer + q);
+            at += one_of_class(k);
         }
 #pragma unroll
-        for (int k = 0; k < 3; k++) base[k] += (int32_t)((total >> (21 * k)) & 0x1fffffu);
+        for (int k = 0; k < 3; k++) base[k] += (int32_t)ids_of_class(total, k);
     }
     if (PLACE) {
         if (blockIdx.x == gridDim.x - 1 && tid == 0) {
