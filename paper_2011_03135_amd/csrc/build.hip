@@ -192,7 +192,8 @@ size_t scatter_lds_bytes(int32_t nb, int32_t te) {
 // One block per bucket: row offsets of its 2^S sources and their arcs (bsrc
 // holds a source's place in its bucket).  kRowsUnroll arcs in flight per
 // thread in both passes: each is a load, an LDS counter and, in the second, a
-// store that depends on the counter's value.
+// store that depends on the counter's value.  Arcs may number 2^31 - 2, so a
+// step past the last one leaves 32 signed bits: the indices are unsigned.
 constexpr int kRowsUnroll = 8;
 
 __global__ void __launch_bounds__(kBucketNT) k_bucket_rows(const int32_t *__restrict__ bucket_off,
@@ -206,14 +207,14 @@ __global__ void __launch_bounds__(kBucketNT) k_bucket_rows(const int32_t *__rest
     const int32_t ids = 1 << S;
     for (int32_t b = blockIdx.x; b < nb; b += gridDim.x) {
         const int32_t base = b << S;
-        const int32_t a0 = bucket_off[b], a1 = bucket_off[b + 1];
+        const uint32_t a0 = bucket_off[b], a1 = bucket_off[b + 1];
         for (int32_t i = threadIdx.x; i < ids; i += kBucketNT) cnt[i] = 0;
         __syncthreads();
-        for (int32_t i0 = a0 + threadIdx.x; i0 < a1; i0 += kBucketNT * kRowsUnroll) {
+        for (uint32_t i0 = a0 + threadIdx.x; i0 < a1; i0 += kBucketNT * kRowsUnroll) {
             int32_t r[kRowsUnroll];
 #pragma unroll
             for (int q = 0; q < kRowsUnroll; q++) {
-                const int32_t i = i0 + q * kBucketNT;
+                const uint32_t i = i0 + q * kBucketNT;
                 r[q] = i < a1 ? (int32_t)bsrc[i] : -1;
             }
 #pragma unroll
@@ -232,14 +233,14 @@ __global__ void __launch_bounds__(kBucketNT) k_bucket_rows(const int32_t *__rest
         block_prefix<kBucketNT, PER>(val, ids, cnt, s_sum);
         for (int32_t i = threadIdx.x; i < ids; i += kBucketNT) {
             const int32_t vtx = base + i;
-            if (vtx < n) raw_off[vtx] = a0 + cnt[i];
+            if (vtx < n) raw_off[vtx] = (int32_t)a0 + cnt[i];
         }
         __syncthreads();
-        for (int32_t i0 = a0 + threadIdx.x; i0 < a1; i0 += kBucketNT * kRowsUnroll) {
+        for (uint32_t i0 = a0 + threadIdx.x; i0 < a1; i0 += kBucketNT * kRowsUnroll) {
             int32_t r[kRowsUnroll], w[kRowsUnroll];
 #pragma unroll
             for (int q = 0; q < kRowsUnroll; q++) {
-                const int32_t i = i0 + q * kBucketNT;
+                const uint32_t i = i0 + q * kBucketNT;
                 r[q] = i < a1 ? (int32_t)bsrc[i] : -1;
                 w[q] = i < a1 ? bdst[i] : 0;
             }
@@ -577,9 +578,9 @@ __device__ __forceinline__ Share open_share(const int32_t *__restrict__ off, int
     s.a1 = (int32_t)(min<int64_t>(d0 + kShare, last) - s.r1);
     for (int32_t i = lane; i < s.a1 - s.a0; i += kWave) mark[i] = 0;
     wave_sync();
-    for (int32_t r = s.r0 + lane; r < min(s.r1, n); r += kWave) {
-        const int32_t o = off[r];
-        if (off[r + 1] > o && o < s.a1) mark[o - s.a0] = r - s.r0 + 1;
+    for (int32_t q = lane; q < min(s.r1, n) - s.r0; q += kWave) {   // (r0 + q may be past 2^31)
+        const int32_t o = off[s.r0 + q];
+        if (off[s.r0 + q + 1] > o && o < s.a1) mark[o - s.a0] = q + 1;
     }
     wave_sync();
     return s;
@@ -620,20 +621,21 @@ __global__ void __launch_bounds__(kBlock) k_compact_rows(const int32_t *__restri
          c += gridDim.x * kWavesPerBlock) {
         const Share s = open_share(off, n, c, start, mark);
         int32_t carry = s.r0 - 1, sum = 0;
-        for (int32_t t0 = s.a0; t0 < s.a1; t0 += kWave * kShareUnroll) {
+        const int32_t na = s.a1 - s.a0;   // at most kShare; arc j of them is arc a0 + j
+        for (int32_t t0 = 0; t0 < na; t0 += kWave * kShareUnroll) {
             int32_t row[kShareUnroll], v[kShareUnroll], du[kShareUnroll], dv[kShareUnroll];
 #pragma unroll
             for (int q = 0; q < kShareUnroll; q++) {
-                const int32_t i = t0 + q * kWave + lane;
-                row[q] = tile_row(i < s.a1 ? mark[i - s.a0] : 0, s.r0, carry);
+                const int32_t j = t0 + q * kWave + lane;
+                row[q] = tile_row(j < na ? mark[j] : 0, s.r0, carry);
             }
 #pragma unroll
             for (int q = 0; q < kShareUnroll; q++) {
-                const int32_t i = t0 + q * kWave + lane;
+                const int32_t j = t0 + q * kWave + lane;
                 v[q] = 0;
                 du[q] = 0;
-                if (i < s.a1) {
-                    const int32_t o = off[row[q]];
+                if (j < na) {
+                    const int32_t i = s.a0 + j, o = off[row[q]];
                     du[q] = off[row[q] + 1] - o;
                     v[q] = COPY ? raw_adj[raw_off[row[q]] + (i - o)] : adj[i];
                 }
@@ -643,12 +645,12 @@ __global__ void __launch_bounds__(kBlock) k_compact_rows(const int32_t *__restri
                 dv[q] = COPY ? deg[v[q]] : off[v[q] + 1] - off[v[q]];
 #pragma unroll
             for (int q = 0; q < kShareUnroll; q++) {
-                const int32_t i = t0 + q * kWave + lane;
-                const bool live = i < s.a1;
+                const int32_t j = t0 + q * kWave + lane;
+                const bool live = j < na;
                 const bool up = live && rank_less(du[q], row[q], dv[q], v[q]);
                 if (live) {
-                    if (COPY) adj[i] = v[q];
-                    keep[i] = up ? 1 : 0;
+                    if (COPY) adj[s.a0 + j] = v[q];
+                    keep[s.a0 + j] = up ? 1 : 0;
                 }
                 sum += __popcll(__ballot(up));
             }
@@ -679,24 +681,25 @@ __global__ void __launch_bounds__(kBlock) k_orient_fill(const int32_t *__restric
          c += gridDim.x * kWavesPerBlock) {
         const Share s = open_share(off, n, c, start, mark);
         int32_t carry = s.r0 - 1, run = base[c];
-        for (int32_t t0 = s.a0; t0 < s.a1; t0 += kWave * kShareUnroll) {
+        const int32_t na = s.a1 - s.a0;
+        for (int32_t t0 = 0; t0 < na; t0 += kWave * kShareUnroll) {
             int32_t row[kShareUnroll], v[kShareUnroll];
             bool up[kShareUnroll];
 #pragma unroll
             for (int q = 0; q < kShareUnroll; q++) {
-                const int32_t i = t0 + q * kWave + lane;
-                up[q] = i < s.a1 && keep[i] != 0;
-                v[q] = i < s.a1 ? adj[i] : 0;
+                const int32_t j = t0 + q * kWave + lane;
+                up[q] = j < na && keep[s.a0 + j] != 0;
+                v[q] = j < na ? adj[s.a0 + j] : 0;
             }
 #pragma unroll
             for (int q = 0; q < kShareUnroll; q++) {
-                const int32_t i = t0 + q * kWave + lane;
-                row[q] = tile_row(i < s.a1 ? mark[i - s.a0] : 0, s.r0, carry);
+                const int32_t j = t0 + q * kWave + lane;
+                row[q] = tile_row(j < na ? mark[j] : 0, s.r0, carry);
             }
 #pragma unroll
             for (int q = 0; q < kShareUnroll; q++) {
                 const uint64_t m = __ballot(up[q]);
-                const int32_t tile = (t0 - s.a0) / kWave + q;
+                const int32_t tile = t0 / kWave + q;
                 if (lane == 0 && tile <= kShare / kWave) {
                     mask_at[tile] = m;
                     run_at[tile] = run;
@@ -715,9 +718,9 @@ __global__ void __launch_bounds__(kBlock) k_orient_fill(const int32_t *__restric
         }
         wave_sync();
         // the share's rows: the out-arcs before their first arc
-        for (int32_t r = s.r0 + lane; r < min(s.r1, n + 1); r += kWave) {
-            const int32_t i = off[r] - s.a0;   // in [0, a1 - a0]
-            dag_off[r] = i < s.a1 - s.a0
+        for (int32_t q = lane; q < min(s.r1, n + 1) - s.r0; q += kWave) {
+            const int32_t i = off[s.r0 + q] - s.a0;   // in [0, na]
+            dag_off[s.r0 + q] = i < na
                              ? run_at[i / kWave] +
                                    __popcll(mask_at[i / kWave] & ((1ull << (i % kWave)) - 1ull))
                              : run;
