@@ -648,6 +648,45 @@ __device__ void lg5_list(const uint64_t *rows, const uint64_t *ri, int32_t c, in
     wave_sync();
 }
 
+// The same for the widest rows (the class above 512), read from LDS where they
+// are used.  With the words in registers as above, each of the W (W + 1) / 2
+// pairs of words holds a copy of the emission: 63 to 187 KB of code from 9 to
+// 16 words, more than an instruction cache, and above 128 KB more than a branch
+// reaches.  (The compiler then jumped through the register pair of the return
+// address, and 14 words never came back.)
+__device__ __forceinline__ void lg5_list_wide(const uint64_t *rows, int32_t S, int32_t W,
+                                              const uint64_t *ri, int32_t c, int16_t *mem,
+                                              const int32_t *verts, int32_t u, int32_t vi,
+                                              RowEmitter &em) {
+    const int lane = lane_id();
+    int32_t base = 0;
+    for (int32_t q = 0; q < W; q++) {
+        const uint64_t R = uniform64(ri[q]);
+        if ((R >> lane) & 1ull) mem[base + lanes_below(R)] = (int16_t)(q * 64 + lane);
+        base += __popcll(R);
+    }
+    wave_sync();
+    for (int32_t a0 = 0; a0 < c; a0 += kWave) {
+        const int32_t a = a0 + lane, pa = mem[min(a, c - 1)];
+        const uint64_t *ra = rows + pa * S;
+        for (int32_t b = a0 + 1; b < c; b++) {
+            const int32_t pb = __builtin_amdgcn_readfirstlane((int32_t)mem[b]), q = pb >> 6;
+            if (a >= c || !((ra[q] >> (pb & 63)) & 1ull)) continue;   // a -> b: b is above a
+            const uint64_t *yb = rows + pb * S;
+            for (int32_t w = q; w < W; w++) {
+                uint64_t mm = ra[w] & yb[w] & ri[w];
+                while (mm) {
+                    const int32_t x = w * 64 + __builtin_ctzll(mm);
+                    mm &= mm - 1ull;
+                    const int32_t clq[5] = {u, vi, verts[pa], verts[pb], verts[x]};
+                    emit_vertices<5>(em, clq);
+                }
+            }
+        }
+    }
+    wave_sync();
+}
+
 template <int WLO, int WHI>
 __device__ __forceinline__ void lg5_list_dispatch(int32_t W, const uint64_t *rows,
                                                   const uint64_t *ri, int32_t c, int16_t *mem,
@@ -794,7 +833,9 @@ __global__ void __launch_bounds__((Lg5Block<DMAX, !LIST && !DEEP>::kThreads),
             int32_t cnt = 0;
             for (int32_t w = 0; w < W; w++) cnt += __popcll(ri[w]);
             if (cnt < 3 + extra) continue;
-            if constexpr (LIST)
+            if constexpr (LIST && DMAX > kHalfMaxD)
+                lg5_list_wide(rows, S64, W, ri, cnt, mem, verts, u, verts[i], em);
+            else if constexpr (LIST)
                 lg5_list_dispatch<WLO, WHI>(W, rows, ri, cnt, mem, verts, u, verts[i], em);
             else
                 acc += lg5_dispatch<WLO, WHI, DEEP>(W, rows, ri, cnt, extra, mem, stack);
