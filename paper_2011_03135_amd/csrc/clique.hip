@@ -301,7 +301,8 @@ __global__ void __launch_bounds__(kBlock) k_tc_arcs(const int32_t *__restrict__ 
         int32_t b = dag_off[v];
         const int32_t bz = dag_off[v + 1];
         if (bz - b > kTcArcMax) continue;
-        uint32_t mine = 0;
+        uint32_t mine = 0, found = 0;   // found (TC_LIST): the hits' positions in u's list
+        const int32_t a0 = a;
         auto load = [&](int32_t at, int32_t end, int32_t pad) {
             Int4u x = *reinterpret_cast<const Int4u *>(dag_adj + at);
             x.y = at + 1 < end ? x.y : pad;
@@ -325,10 +326,7 @@ __global__ void __launch_bounds__(kBlock) k_tc_arcs(const int32_t *__restrict__ 
                     atomicAdd(&te[a + i], 1u);
                     atomicAdd(&te[b + j], 1u);
                 }
-                if (MODE == TC_LIST && hit) {
-                    const int32_t tri[3] = {u, v, x[i]};
-                    emit_vertices<3>(em, tri);
-                }
+                if (MODE == TC_LIST && hit) found |= 1u << (a - a0 + i);
             }
             const int32_t la = a + 4 < az ? A.w : INT_MAX, lb = b + 4 < bz ? B.w : INT_MAX;
             if (la <= lb) {
@@ -341,6 +339,15 @@ __global__ void __launch_bounds__(kBlock) k_tc_arcs(const int32_t *__restrict__ 
             }
         }
         if (MODE == TC_ARCS && mine) atomicAdd(&te[e0], mine);
+        // (emitted after the merge, every lane's next one together: an emission
+        // takes as long for one lane as for 64, and at each of the merge's
+        // steps it was one for few.  1,000,000 vertices of 8 neighbours among
+        // 100: 8.8 ms, now 1.4)
+        if (MODE == TC_LIST)
+            for (; found; found &= found - 1u) {
+                const int32_t tri[3] = {u, v, dag_adj[a0 + __builtin_ctz(found)]};
+                emit_vertices<3>(em, tri);
+            }
         acc += mine;
     }
     total = wave_sum((uint64_t)acc);
