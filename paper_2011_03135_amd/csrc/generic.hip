@@ -367,13 +367,25 @@ __global__ void __launch_bounds__(kGenNT) k_generic(const int32_t *__restrict__ 
         return (uint64_t)total;
     };
     // a work unit is one 64-candidate chunk of step 2 below one arc (steps
-    // 0 and 1), with the whole search below it; units come from
-    // work cursors, so a hub's arcs and chunks spread over the grid
+    // 0 and 1), with the whole search below it; units come from work cursors,
+    // so a hub's arcs and chunks spread over the grid.  (Counts by leaf_pairs,
+    // whose units are short.  The others keep one counter: the cursors'
+    // registers cost the listing one of five waves a SIMD, 4-paths of 10,000
+    // vertices 99 ms, not 89, and induced 6-cycles of 1,024 took 181, not 177.)
+    constexpr bool kSpread = MNC && !LIST;
     TaskQueue queue(cursor, nchunks, wib * gridDim.x + blockIdx.x,
                     gridDim.x * (kGenNT / kWave));
     for (;;) {
-        const int64_t c = queue.next();
-        if (c < 0) break;   // wave-uniform
+        int64_t c;   // wave-uniform
+        if constexpr (kSpread) {
+            c = queue.next();
+            if (c < 0) break;
+        } else {
+            unsigned long long got = 0;
+            if (lane == 0) got = atomicAdd(cursor, 1ull);
+            c = (int64_t)__shfl(got, 0);
+            if (c >= nchunks) break;
+        }
         int64_t lo = 0, hi = narcs;   // the arc of unit c: last a with chunk_off[a] <= c
         while (hi - lo > 1) {
             const int64_t mid = (lo + hi) >> 1;
