@@ -451,8 +451,8 @@ __global__ void __launch_bounds__(NT, DMAX == kHalfMaxD ? 6 : 1) k_lg_build(cons
 // into LDS.  For local vertex i with out-row R (members p_0 < ... < p_{c-1}),
 // the 5-cliques {u, v_i, ...} are the triangles a < b < x of the local DAG
 // inside R: the sum over members a < b of [a -> b] * |row_a & R & row_b|.
-// LDS is dynamic: rows (dmax x (ceil(dmax/64) | 1) words for the class's
-// largest out-degree), then per wave a member list of DMAX int16.
+// LDS is dynamic: rows (dmax x row_stride words for the class's largest
+// out-degree), then per wave a member list of DMAX int16.
 
 // That sum by population counts, for the leaves of the descents below (k > 5).
 // Lanes own a (64 members at a time, row_a & R in registers); b runs over
@@ -753,6 +753,14 @@ __device__ uint64_t lgk_set(const uint64_t *rows, const uint64_t *set0, int32_t 
     return acc;
 }
 
+// Stride of a class's rows in LDS for W words: odd, so that a column of them is
+// spread over the banks; but not for the descents above 512, where the room for
+// more waves is worth more (6-cliques of 7,000 vertices, out-degrees up to 986:
+// 260 ms with 8 waves, 213 with 10).
+template <int DMAX> __host__ __device__ constexpr int32_t row_stride(int32_t W, bool deep) {
+    return deep && DMAX > kHalfMaxD ? W : W | 1;
+}
+
 template <int WLO, int WHI, bool DEEP>
 __device__ __forceinline__ uint64_t lg5_dispatch(int32_t W, const uint64_t *rows, const uint64_t *ri,
                                                  int32_t c, int32_t e, int16_t *mem,
@@ -760,7 +768,7 @@ __device__ __forceinline__ uint64_t lg5_dispatch(int32_t W, const uint64_t *rows
     if constexpr (WLO > WHI) {
         return 0;
     } else {
-        constexpr int S = WLO | 1;   // the rows' stride
+        constexpr int S = row_stride<WHI * kWave>(WLO, DEEP);
         if (W == WLO) {
             if constexpr (DEEP) return lgk_set<WLO, S>(rows, ri, c, e, mem, stack);
             else return lg5_tiles<WLO, S>(rows, ri, c, mem);
@@ -812,8 +820,7 @@ __global__ void __launch_bounds__((Lg5Block<DMAX, !LIST && !DEEP>::kThreads),
         const int32_t u = roots[r];
         const int32_t d = dag_off[u + 1] - dag_off[u], W = (d + 63) >> 6;
         const uint64_t *src = grows + rowoff[r];
-        // rows at an odd stride, so that a column of them is spread over the banks
-        const int32_t S64 = W | 1;
+        const int32_t S64 = row_stride<DMAX>(W, DEEP);
         // the words tid, tid + NT, ..., four in flight (a row per wave at a time
         // waited for memory once a row: 5-cliques of 20,000 vertices, out-degrees
         // up to 893, took 20.1 ms, now 16.3)
@@ -1023,9 +1030,9 @@ gpm_status lg5_big(const gpm_graph *g, int32_t k, LgWs &L, const int32_t *list, 
     auto count = [&](auto dmax_class, int cursor, const LgTask *tasks, const uint32_t *nt) -> gpm_status {
         constexpr int DMAX = decltype(dmax_class)::value;
         const int32_t dmax = std::min<int32_t>(DMAX, g->max_out_degree);
-        const int32_t rows_words = dmax * (((dmax + 63) / 64) | 1);
-        const int64_t lds_cap = 160 * 1024 - 1024;
         const int32_t extra = k - 5;
+        const int32_t rows_words = dmax * row_stride<DMAX>((dmax + 63) / 64, extra > 0);
+        const int64_t lds_cap = 160 * 1024 - 1024;
         const int64_t per_wave = (int64_t)DMAX * 2 + (int64_t)(extra + 1) * 2 * (DMAX / 64) * 8;
         const int64_t fixed = (int64_t)rows_words * 8 + (int64_t)DMAX * 4;
         const int threads = em || extra ? Lg5Block<DMAX, false>::kThreads : Lg5Block<DMAX, true>::kThreads;
