@@ -35,7 +35,7 @@ namespace gpm {
 
 namespace {
 
-typedef unsigned long long u64;
+typedef unsigned __int128 u128;
 
 constexpr int kMaxN = GPM_BATCH_MAX_VERTICES;
 constexpr int kLargeNT = 256;
@@ -87,10 +87,9 @@ __device__ __forceinline__ uint64_t below_mask(int32_t x, int32_t w) {
     return (1ull << (x - lo)) - 1ull;
 }
 
-// Exact combination (one thread; of 1,024 vertices at most, every sum is below
-// 2^50); flags |= B_DIVISION on a failed check.
-__device__ void combine(int32_t k, u64 wedge, u64 tri, u64 k4, u64 s1, u64 s2, u64 s3,
-                        u64 s4, u64 nc4, unsigned long long flags, unsigned long long *out) {
+// Exact combination (one thread); flags |= B_DIVISION on a failed check.
+__device__ void combine(int32_t k, u128 wedge, u128 tri, u128 k4, u128 s1, u128 s2, u128 s3,
+                        u128 s4, u128 nc4, unsigned long long flags, unsigned long long *out) {
     if (k == 3) {
         unsigned long long bad = flags;
         if (wedge < 3 * tri) bad |= B_DIVISION;
@@ -100,7 +99,7 @@ __device__ void combine(int32_t k, u64 wedge, u64 tri, u64 k4, u64 s1, u64 s2, u
         return;
     }
     unsigned long long bad = flags;
-    u64 dia = 0, paw = 0, c4 = 0, p4 = 0, claw = 0;
+    u128 dia = 0, paw = 0, c4 = 0, p4 = 0, claw = 0;
     if (s1 < 6 * k4) bad |= B_DIVISION; else dia = s1 - 6 * k4;
     if (s2 < 4 * dia || ((s2 - 4 * dia) & 1)) bad |= B_DIVISION; else paw = (s2 - 4 * dia) / 2;
     if (nc4 < dia + 3 * k4) bad |= B_DIVISION; else c4 = nc4 - dia - 3 * k4;
