@@ -714,8 +714,13 @@ __global__ void k_f5_row_tasks(const unsigned long long *__restrict__ t2, int32_
 // every other vertex, from a cursor.  The neighbours a are dealt to the
 // waves in runs; each wave flattens its arcs' lists, 64 triangles at a time,
 // then those triangles' lists C_e (wave_segments).  Bound by the two random
-// LDS reads and the addressing of each entry of C_e.  P2, T and d are below
-// 2^16, so a lane's 64-bit sums hold 2^32 terms.
+// LDS reads and the addressing of each entry of C_e.
+//   Sums in 64 bits: the lists hold fewer than 2^31 entries, so there are as
+// many corners {i, a, b}, each adding less than 2^32 to k5e, quad, pend, two,
+// kite and gem; T_e < 2^16 entries each make it 2^47 of C_e, each adding less
+// than 2^16 to twin: every one of these stays below 2^63 over the whole graph.
+// tr does not: it is added up in 64 bits per vertex (a lane meets at most 2^27
+// entries of the rows, each adding less than 2^33), then in 128.
 template <int NT>
 __global__ void __launch_bounds__(NT, NT == 512 ? 8 : 4) k_f5_rows(const int32_t *__restrict__ off,
                                                 const int32_t *__restrict__ adj, int32_t n,
@@ -739,8 +744,8 @@ __global__ void __launch_bounds__(NT, NT == 512 ? 8 : 4) k_f5_rows(const int32_t
     __syncthreads();
     const int64_t nsplit = (int64_t)acc[A_RTASKS];
     TaskQueue queue(acc + A_TCURSOR, nsplit + n, blockIdx.x, gridDim.x);
-    uint64_t tr = 0, twin = 0, k5e = 0, quad = 0, pend = 0, two = 0, kite = 0, gem = 0;
-    u128 k23 = 0;
+    uint64_t twin = 0, k5e = 0, quad = 0, pend = 0, two = 0, kite = 0, gem = 0;
+    u128 tr = 0, k23 = 0;
     for (;;) {
         if (wid == 0) {
             const int64_t got = queue.next();
@@ -783,6 +788,7 @@ __global__ void __launch_bounds__(NT, NT == 512 ? 8 : 4) k_f5_rows(const int32_t
         }
         __syncthreads();
         if (part == 0) {
+            uint64_t tri = 0;
             for (int32_t w0 = wid * kWave; w0 < hw; w0 += NW * kWave) {
                 const uint32_t v = w0 + lane < hw ? p2w[w0 + lane] : 0u;
                 if (!__any(v != 0u)) continue;
@@ -810,10 +816,11 @@ __global__ void __launch_bounds__(NT, NT == 512 ? 8 : 4) k_f5_rows(const int32_t
                         for (int q = 0; q < U; q++) f[q] = __shfl(pj, seg[q], kWave);
 #pragma unroll
                         for (int q = 0; q < U; q++)
-                            if (live[q]) tr += (uint64_t)f[q] * p2(k[q]);
+                            if (live[q]) tri += (uint64_t)f[q] * p2(k[q]);
                     });
                 }
             }
+            tr += tri;
         }
         // triangles {i, a, b}: this part's neighbours a = part, part + parts, ...
         const int32_t na = (di - part + parts - 1) / parts;
@@ -884,7 +891,7 @@ __global__ void __launch_bounds__(NT, NT == 512 ? 8 : 4) k_f5_rows(const int32_t
     // twin's subtractions wrap the lane's 64-bit sum, not the total's: the
     // sum over the lanes is taken modulo 2^64 of a signed value
     const u128 tw = (u128)(__int128)(int64_t)twin;
-    const u128 s[9] = {(u128)tr, k23, tw, (u128)k5e, (u128)quad, (u128)pend, (u128)two,
+    const u128 s[9] = {tr, k23, tw, (u128)k5e, (u128)quad, (u128)pend, (u128)two,
                        (u128)kite, (u128)gem};
     const int slot[9] = {A_PLUS + 2 * F_C5, A_PLUS + 2 * F_K23, A_PLUS + 2 * F_TWIN,
                          A_PLUS + 2 * F_K5E, A_QUAD, A_PEND, A_TWO, A_PLUS + 2 * F_KITE,
@@ -898,7 +905,9 @@ __global__ void __launch_bounds__(NT, NT == 512 ? 8 : 4) k_f5_rows(const int32_t
 // walks x - p - y with kp, ky < kx per ky (16-bit counters, below d(i)), each
 // increment adding the count before it.  A team of NW waves takes an arc: one
 // wave (arcs of fewer than kBigT triangles), or a workgroup (the others: the
-// largest has a million entries).
+// largest has a million entries).  Sums in 64 bits: the arcs i -> p are met
+// T_ip^2 times, half of them with y before x, 2^47 in all (see k_f5_rows), and
+// each adds less than 2^16.
 template <int NT, bool BIG>
 __global__ void __launch_bounds__(NT) k_f5_wheel_lists(const int32_t *__restrict__ off,
                                                        const int32_t *__restrict__ dag_src,
