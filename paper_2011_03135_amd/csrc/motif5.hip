@@ -933,7 +933,8 @@ __global__ void __launch_bounds__(NT) k_f5_wheel_lists(const int32_t *__restrict
     const int64_t narcs = BIG ? (int64_t)acc[A_NBIG] : 2 * L.m;
     constexpr int64_t kGrab = BIG ? 1 : kWheelArcs;
     TaskQueue queue(acc + (BIG ? A_BCURSOR : A_CURSOR), (narcs + kGrab - 1) / kGrab,
-                    BIG ? blockIdx.x : wid * gridDim.x + blockIdx.x, gridDim.x * (BIG ? 1 : NW));
+                    BIG ? blockIdx.x : wid * gridDim.x + blockIdx.x,
+                    gridDim.x * (BIG ? 1 : NT / kWave));
     uint64_t sum = 0;
     for (;;) {
         int64_t r;
@@ -1431,18 +1432,15 @@ gpm_status motif_formula_count(const gpm_graph *g, int32_t k, void *ws, uint64_t
         hipLaunchKernelGGL((k_f5_wheel_lists<1024, true>), dim3((unsigned)cu_count()), dim3(1024),
                            per_wave, st, g->off, g->dag_src, g->dag_adj, g->max_degree, L, W.big,
                            W.acc);
-        // a wave per arc: workgroups of as many waves, up to 4, as the LDS allows
-        const int waves = (int)std::max<size_t>(1, std::min<size_t>(4, (150 * 1024) / per_wave));
+        // a wave per arc: workgroups of four where their counters fit, else of one
+        // (degrees above about 19,200), as many a CU as the LDS allows
+        const int waves = 4 * per_wave <= 150 * 1024 ? 4 : 1;
         const int per_cu = (int)std::max<size_t>(
             1, std::min<size_t>(32 / waves, (150 * 1024) / (per_wave * waves + 1024)));
         const dim3 grid(grid_for((2 * m + kWheelArcs - 1) / kWheelArcs, waves, per_cu));
-        if (waves == 4)
-            hipLaunchKernelGGL((k_f5_wheel_lists<256, false>), grid, dim3(256), per_wave * 4, st,
-                               g->off, g->dag_src, g->dag_adj, g->max_degree, L, W.big, W.acc);
-        else
-            hipLaunchKernelGGL((k_f5_wheel_lists<64, false>), dim3((unsigned)cu_count()), dim3(64),
-                               per_wave, st, g->off, g->dag_src, g->dag_adj, g->max_degree, L,
-                               W.big, W.acc);
+        hipLaunchKernelGGL(waves == 4 ? (k_f5_wheel_lists<256, false>) : (k_f5_wheel_lists<64, false>),
+                           grid, dim3(waves * kWave), per_wave * waves, st, g->off, g->dag_src,
+                           g->dag_adj, g->max_degree, L, W.big, W.acc);
     }
     GPM_LAUNCH_CHECK("k_f5_wheel_lists");
     if (trace5 && m > 0 && plain) {
