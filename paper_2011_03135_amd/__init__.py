@@ -33,6 +33,7 @@ from .binding import (  # noqa: F401
     motif_class_pattern,
     motif_count_enum,
     motif_count_formula,
+    motif_formula_compact_bytes,
     motif_formula_workspace_bytes,
     motif_enum_workspace_bytes,
     motif_workspace_bytes,

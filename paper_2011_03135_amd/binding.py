@@ -103,6 +103,8 @@ def load():
         "gpm_motif_count_enum": ([P, i32, P, u64, P, P], i32),
         "gpm_motif_formula_workspace_bytes": ([P, i32, P], i32),
         "gpm_motif_count_formula": ([P, i32, P, u64, P, P], i32),
+        "gpm_motif_formula_compact_bytes": ([P, i32, P], i32),
+        "gpm_motif_count_formula_compact": ([P, i32, P, u64, P, P], i32),
         "gpm_batch_workspace_bytes": ([i32, i32, P], i32),
         "gpm_batch_motif_count": ([P, P, i32, i32, P, u64, P, P], i32),
         "gpm_batch_default_config": ([P], i32),
@@ -146,6 +148,15 @@ def _buffer(nbytes, device):
     if t.data_ptr() % 256:
         raise GpmError(1, "allocator returned a buffer that is not 256-byte aligned")
     return t
+
+
+def _workspace(nbytes, least, device):
+    """A buffer of nbytes, or of least() where the device has no room for that;
+    and whether it is the smaller one."""
+    try:
+        return _buffer(nbytes, device), False
+    except torch.OutOfMemoryError:
+        return _buffer(least(), device), True
 
 
 def _u64(x):
@@ -476,16 +487,24 @@ def motif_formula_workspace_bytes(g, k=5):
     return b.value
 
 
+def motif_formula_compact_bytes(g, k=5):
+    b = ctypes.c_uint64()
+    _check(load().gpm_motif_formula_compact_bytes(g.handle, int(k), ctypes.byref(b)))
+    return b.value
+
+
 def motif_count_formula(g, k=5, stream=None, ws=None, out=None):
     """gpm_motif_count_formula -> the 21 induced 5-motif counts (exact ints),
     by local-count formulas and back-substitution.  With `out` (int64 device
-    tensor of 22 entries) the call only enqueues and returns `out`."""
+    tensor of 22 entries) the call only enqueues and returns `out`.  Where the
+    device has no room for the workspace, gpm_motif_count_formula_compact."""
     nbytes = motif_formula_workspace_bytes(g, k)
+    compact = False
     if ws is None or ws.numel() < nbytes:
-        ws = _buffer(nbytes, g.device)
+        ws, compact = _workspace(nbytes, lambda: motif_formula_compact_bytes(g, k), g.device)
     res = out if out is not None else torch.zeros(22, dtype=torch.int64, device=g.device)
-    _check(load().gpm_motif_count_formula(g.handle, int(k), _ptr(ws), ws.numel(), _ptr(res),
-                                          _stream(stream)))
+    call = load().gpm_motif_count_formula_compact if compact else load().gpm_motif_count_formula
+    _check(call(g.handle, int(k), _ptr(ws), ws.numel(), _ptr(res), _stream(stream)))
     if out is not None:
         return out
     vals = [_u64(x) for x in res.tolist()]

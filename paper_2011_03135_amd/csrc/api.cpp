@@ -55,8 +55,9 @@ gpm_status motif_enum_workspace_bytes(const gpm_graph *g, uint64_t *bytes);
 gpm_status motif_enum_count(const gpm_graph *g, int k, void *ws, uint64_t ws_bytes,
                             unsigned long long *out, hipStream_t st);
 gpm_status motif_formula_workspace_bytes(const gpm_graph *g, int32_t k, uint64_t *bytes);
+gpm_status motif_formula_compact_bytes(const gpm_graph *g, int32_t k, uint64_t *bytes);
 gpm_status motif_formula_count(const gpm_graph *g, int32_t k, void *ws, uint64_t ws_bytes,
-                               unsigned long long *d_counts, hipStream_t st);
+                               bool compact, unsigned long long *d_counts, hipStream_t st);
 gpm_status batch_workspace_bytes(int32_t G, int32_t k, uint64_t *bytes);
 gpm_status batch_default_config(gpm_batch_config *c);
 gpm_status batch_run(const gpm_graph *g, const int32_t *d_voff, int32_t G, int32_t k,
@@ -486,16 +487,33 @@ gpm_status gpm_motif_formula_workspace_bytes(const gpm_graph *g, int32_t k, uint
     return gpm::motif_formula_workspace_bytes(g, k, bytes);
 }
 
-gpm_status gpm_motif_count_formula(const gpm_graph *g, int32_t k, void *d_ws, uint64_t ws_bytes,
-                                   uint64_t *d_counts, void *stream) {
+gpm_status gpm_motif_formula_compact_bytes(const gpm_graph *g, int32_t k, uint64_t *bytes) {
+    gpm_status rc = check_graph(g);
+    if (rc) return rc;
+    if (!bytes) return fail(GPM_INVALID_ARGUMENT, "NULL argument");
+    return gpm::motif_formula_compact_bytes(g, k, bytes);
+}
+
+static gpm_status formula_count(const gpm_graph *g, int32_t k, void *d_ws, uint64_t ws_bytes,
+                                bool compact, uint64_t *d_counts, void *stream) {
     gpm_status rc = check_graph(g);
     if (rc) return rc;
     if (k != 5) return fail(GPM_UNSUPPORTED, "formula motif counting is for k = 5");
     if (!d_counts) return fail(GPM_INVALID_ARGUMENT, "NULL argument");
     if (!d_ws || !aligned256(d_ws)) return fail(GPM_INVALID_ARGUMENT, "workspace NULL or unaligned");
-    return gpm::motif_formula_count(g, k, d_ws, ws_bytes,
+    return gpm::motif_formula_count(g, k, d_ws, ws_bytes, compact,
                                     reinterpret_cast<unsigned long long *>(d_counts),
                                     static_cast<hipStream_t>(stream));
+}
+
+gpm_status gpm_motif_count_formula(const gpm_graph *g, int32_t k, void *d_ws, uint64_t ws_bytes,
+                                   uint64_t *d_counts, void *stream) {
+    return formula_count(g, k, d_ws, ws_bytes, false, d_counts, stream);
+}
+
+gpm_status gpm_motif_count_formula_compact(const gpm_graph *g, int32_t k, void *d_ws,
+                                           uint64_t ws_bytes, uint64_t *d_counts, void *stream) {
+    return formula_count(g, k, d_ws, ws_bytes, true, d_counts, stream);
 }
 
 gpm_status gpm_batch_workspace_bytes(int32_t G, int32_t k, uint64_t *bytes) {

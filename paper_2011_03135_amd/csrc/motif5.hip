@@ -1302,41 +1302,67 @@ int64_t lists_cap(const gpm_graph *g) {
 struct F5Ws {
     unsigned long long *acc, *t2;
     uint32_t *te, *tsym;
-    // the lists (null above kTrace5MaxN vertices)
+    // the lists (null above kTrace5MaxN vertices, or without room) and their
+    // entries
     uint32_t *esym;
     int32_t *big;
     int64_t *loff, *scan_tmp;
     uint16_t *lid, *lpos;
     RowTask *tasks;
-    void *shared;
-    uint64_t shared_bytes, bytes;
+    int64_t cap;
+    void *shared;   // the other calls' workspace, in the lists' place
+    uint64_t shared_bytes;
+    uint64_t bytes, least;   // with the lists at their largest, without them
 };
 
-F5Ws f5_layout(const gpm_graph *g, void *base) {
+// The lists for `cap` entries at c.
+void f5_lists(const gpm_graph *g, Carve &c, F5Ws &W, uint64_t cap) {
+    W.esym = c.take<uint32_t>(2 * (uint64_t)g->m + 1);
+    W.big = c.take<int32_t>(2 * (uint64_t)g->m + 1);
+    W.loff = c.take<int64_t>((uint64_t)g->m + 1);
+    W.scan_tmp = c.take<int64_t>(scan_tmp_words((uint64_t)g->m + 1));
+    W.lid = c.take<uint16_t>(cap);
+    W.lpos = c.take<uint16_t>(2 * cap);
+    // a vertex of t > kRowCorners triangles has at most 2 t / kRowCorners parts
+    W.tasks = c.take<RowTask>(2 * cap / kRowCorners + 1);
+    W.cap = (int64_t)cap;
+}
+
+// A workspace of `room` bytes: what lies beyond the fixed part holds the lists,
+// as many entries of them as fit, and, before they are made and after they are
+// read, the workspace of the other calls.
+F5Ws f5_layout(const gpm_graph *g, void *base, uint64_t room) {
     F5Ws W{};
     Carve c(base, ~0ull);
     W.acc = c.take<unsigned long long>(A_WORDS);
     W.t2 = c.take<unsigned long long>((uint64_t)g->n + 1);
     W.te = c.take<uint32_t>((uint64_t)g->m + 1);
     W.tsym = c.take<uint32_t>(2 * (uint64_t)g->m + 1);
-    if (g->n <= kTrace5MaxN) {
-        const uint64_t cap = (uint64_t)lists_cap(g);
-        W.esym = c.take<uint32_t>(2 * (uint64_t)g->m + 1);
-        W.big = c.take<int32_t>(2 * (uint64_t)g->m + 1);
-        W.loff = c.take<int64_t>((uint64_t)g->m + 1);
-        W.scan_tmp = c.take<int64_t>(scan_tmp_words((uint64_t)g->m + 1));
-        W.lid = c.take<uint16_t>(cap);
-        W.lpos = c.take<uint16_t>(2 * cap);
-        // a vertex of t > kRowCorners triangles has at most 2 t / kRowCorners parts
-        W.tasks = c.take<RowTask>(2 * cap / kRowCorners + 1);
-    }
     uint64_t b3 = 0, b5 = 0, bc4 = 0;
     clique_workspace_bytes(g, 3, false, &b3);
     clique_workspace_bytes(g, 5, false, &b5);
     c4_workspace_bytes(g, false, &bc4);
     W.shared_bytes = std::max({b3, b5, bc4, generic_workspace_bytes(g)});
+    const uint64_t at = c.used;
     W.shared = c.take<char>(W.shared_bytes);
-    W.bytes = c.used;
+    W.bytes = W.least = c.used;
+    if (g->n > kTrace5MaxN || g->m == 0) return W;
+    const uint64_t most = (uint64_t)lists_cap(g);
+    F5Ws full{}, none{};
+    Carve cf(nullptr, ~0ull), cn(nullptr, ~0ull);
+    f5_lists(g, cf, full, most);
+    f5_lists(g, cn, none, 0);
+    W.bytes = std::max(W.least, at + cf.used);
+    // an entry takes 6 bytes and its share of the tasks 1/256; three arrays
+    // are rounded up to 256 bytes
+    uint64_t cap = most;
+    if (room < at + cf.used)
+        cap = room < at + cn.used + 1024 ? 0 : (room - at - cn.used - 1024) * 256 / 1537;
+    cap = std::min(cap, most);
+    if (cap > 0) {
+        Carve cl(base ? static_cast<char *>(base) + at : nullptr, ~0ull);
+        f5_lists(g, cl, W, cap);
+    }
     return W;
 }
 
@@ -1350,15 +1376,21 @@ unsigned grid_for(int64_t items, int per_block, int cap_per_cu) {
 
 gpm_status motif_formula_workspace_bytes(const gpm_graph *g, int32_t k, uint64_t *bytes) {
     if (k != 5) return fail(GPM_UNSUPPORTED, "formula motif counting is for k = 5");
-    *bytes = f5_layout(g, nullptr).bytes;
+    *bytes = f5_layout(g, nullptr, ~0ull).bytes;
+    return GPM_OK;
+}
+
+gpm_status motif_formula_compact_bytes(const gpm_graph *g, int32_t k, uint64_t *bytes) {
+    if (k != 5) return fail(GPM_UNSUPPORTED, "formula motif counting is for k = 5");
+    *bytes = f5_layout(g, nullptr, 0).least;
     return GPM_OK;
 }
 
 gpm_status motif_formula_count(const gpm_graph *g, int32_t k, void *ws, uint64_t ws_bytes,
-                               unsigned long long *d_counts, hipStream_t st) {
+                               bool compact, unsigned long long *d_counts, hipStream_t st) {
     if (k != 5) return fail(GPM_UNSUPPORTED, "formula motif counting is for k = 5");
-    F5Ws W = f5_layout(g, ws);
-    if (W.bytes > ws_bytes) return fail(GPM_OUT_OF_MEMORY, "workspace smaller than required");
+    F5Ws W = f5_layout(g, ws, ws_bytes);
+    if ((compact ? W.least : W.bytes) > ws_bytes) return fail(GPM_OUT_OF_MEMORY, "workspace smaller than required");
     // the 5-cycle, K_{2,3}, class 16 and K5 minus an edge from the rows of
     // A^2 where they fit in LDS, else counted directly
     Back B = back_matrix();
@@ -1379,9 +1411,8 @@ gpm_status motif_formula_count(const gpm_graph *g, int32_t k, void *ws, uint64_t
         {W.acc, 2 * ((uint64_t)(W.t2 - W.acc) + (uint64_t)n + 1)});
     if (rc) return rc;
     // the lists, and whether the graph's may exceed them
-    const int64_t cap = lists_cap(g);
-    const Lists L{W.esym, W.loff, W.lid, W.lpos, W.te, cap, m};
-    const bool lists = trace5 && m > 0, plain = !lists || lists_bound(g) > cap;
+    const Lists L{W.esym, W.loff, W.lid, W.lpos, W.te, W.cap, m};
+    const bool lists = W.cap > 0, plain = !lists || lists_bound(g) > W.cap;
     {
         Span sp("k_f5_local", st);
         const unsigned sum_grid = (unsigned)cu_count() * 2;
