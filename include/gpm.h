@@ -311,6 +311,16 @@ gpm_status gpm_count(const gpm_graph *g, const gpm_pattern *p, void *d_ws, uint6
  * GPM_OUT_OF_MEMORY before anything is enqueued (outputs untouched). */
 gpm_status gpm_list(const gpm_graph *g, const gpm_pattern *p, void *d_ws, uint64_t ws_bytes,
                     int32_t *d_buf, uint64_t cap, uint64_t *d_result, void *stream);
+/* The same listing in less memory, for 4-cycles, whose workspace holds an
+ * arena of up to 512 MiB for the pairs of large tasks: _compact takes any
+ * workspace from gpm_list_compact_bytes on, the arena what lies beyond that.
+ * A task without room in it lists its pairs by itself, which takes longer
+ * where a few hubs hold most of them (RMAT-15: 100 ms, not 13).  Other
+ * patterns are listed as by gpm_list, in the same workspace. */
+gpm_status gpm_list_compact_bytes(const gpm_graph *g, const gpm_pattern *p, uint64_t *bytes);
+gpm_status gpm_list_compact(const gpm_graph *g, const gpm_pattern *p, void *d_ws,
+                            uint64_t ws_bytes, int32_t *d_buf, uint64_t cap, uint64_t *d_result,
+                            void *stream);
 
 /* Triangles, 4-cliques and (kmax = 5) 5-cliques of g in one pass: the
  * local graph on N+(u) (Section 5, search on a local graph) holds the

@@ -25,6 +25,7 @@ from .binding import (  # noqa: F401
     diamond,
     cycle4,
     library_path,
+    list_compact_bytes,
     list_embeddings,
     matching_order,
     load,

@@ -87,6 +87,8 @@ def load():
         "gpm_workspace_bytes": ([P, P, P], i32),
         "gpm_count": ([P, P, P, u64, P, P], i32),
         "gpm_list": ([P, P, P, u64, P, u64, P, P], i32),
+        "gpm_list_compact_bytes": ([P, P, P], i32),
+        "gpm_list_compact": ([P, P, P, u64, P, u64, P, P], i32),
         "gpm_clique_counts_workspace_bytes": ([P, i32, P], i32),
         "gpm_clique_counts": ([P, i32, P, u64, P, P], i32),
         "gpm_motif_workspace_bytes": ([P, i32, P], i32),
@@ -387,16 +389,25 @@ def count(g, p, stream=None, ws=None, out=None):
     return _u64(res.item())
 
 
+def list_compact_bytes(g, p):
+    b = ctypes.c_uint64()
+    _check(load().gpm_list_compact_bytes(g.handle, ctypes.byref(p), ctypes.byref(b)))
+    return b.value
+
+
 def list_embeddings(g, p, cap, stream=None, ws=None):
-    """gpm_list -> (total, written, checksum, rows[written, k] int32 tensor)."""
+    """gpm_list -> (total, written, checksum, rows[written, k] int32 tensor).
+    Where the device has no room for the workspace, gpm_list_compact."""
     nb = workspace_bytes(g, p)
+    compact = False
     if ws is None or ws.numel() < nb:
-        ws = _buffer(nb, g.device)
+        ws, compact = _workspace(nb, lambda: list_compact_bytes(g, p), g.device)
+    call = load().gpm_list_compact if compact else load().gpm_list
     k = p.k
     buf = torch.empty((max(int(cap), 1), k), dtype=torch.int32, device=g.device)
     res = torch.zeros(3, dtype=torch.int64, device=g.device)
-    _check(load().gpm_list(g.handle, ctypes.byref(p), _ptr(ws), ws.numel(), _ptr(buf), int(cap),
-                           _ptr(res), _stream(stream)))
+    _check(call(g.handle, ctypes.byref(p), _ptr(ws), ws.numel(), _ptr(buf), int(cap), _ptr(res),
+                _stream(stream)))
     total, written, chk = (_u64(x) for x in res.tolist())
     return total, written, chk, buf[:written]
 

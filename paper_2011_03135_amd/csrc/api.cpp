@@ -28,7 +28,8 @@ gpm_status clique_run(const gpm_graph *g, int32_t k, bool list, void *ws, uint64
 gpm_status motif_workspace_bytes(const gpm_graph *g, int32_t k, uint64_t *bytes);
 gpm_status motif_run(const gpm_graph *g, int32_t k, void *ws, uint64_t ws_bytes,
                      unsigned long long *d_counts, hipStream_t st);
-gpm_status sl_workspace_bytes(const gpm_graph *g, int32_t plan, bool list, uint64_t *bytes);
+gpm_status sl_workspace_bytes(const gpm_graph *g, int32_t plan, bool list, bool compact,
+                              uint64_t *bytes);
 bool generic_pattern_ok(const gpm_pattern *p);
 gpm_status generic_describe(const gpm_pattern *p, int32_t *order, uint32_t *less);
 uint64_t generic_workspace_bytes(const gpm_graph *g);
@@ -38,8 +39,8 @@ gpm_status generic_count(const gpm_graph *g, const gpm_pattern *p, void *ws, uin
                          unsigned long long *out, hipStream_t st);
 gpm_status permute_rows4(int32_t *buf, uint64_t cap, const unsigned long long *result,
                          const int32_t perm[4], hipStream_t st);
-gpm_status sl_run(const gpm_graph *g, int32_t plan, bool list, void *ws, uint64_t ws_bytes,
-                  unsigned long long *d_count, int32_t *d_buf, uint64_t cap,
+gpm_status sl_run(const gpm_graph *g, int32_t plan, bool list, bool compact, void *ws,
+                  uint64_t ws_bytes, unsigned long long *d_count, int32_t *d_buf, uint64_t cap,
                   unsigned long long *d_result, hipStream_t st);
 uint64_t orient_scratch_bytes(const gpm_graph *g);
 void tuning_get(const gpm_graph *g, gpm_tuning *t);
@@ -355,7 +356,8 @@ gpm_status gpm_graph_autotune(gpm_graph *g, void *d_ws, uint64_t ws_bytes, void 
     return gpm::graph_autotune(g, d_ws, ws_bytes, static_cast<hipStream_t>(stream), chosen);
 }
 
-gpm_status gpm_workspace_bytes(const gpm_graph *g, const gpm_pattern *p, uint64_t *bytes) {
+static gpm_status pattern_bytes(const gpm_graph *g, const gpm_pattern *p, bool compact,
+                                uint64_t *bytes) {
     gpm_status rc = check_graph(g);
     if (rc) return rc;
     if (!p || !bytes) return fail(GPM_INVALID_ARGUMENT, "NULL argument");
@@ -368,7 +370,16 @@ gpm_status gpm_workspace_bytes(const gpm_graph *g, const gpm_pattern *p, uint64_
         *bytes = gpm::generic_workspace_bytes(g);
         return GPM_OK;
     }
-    return gpm::sl_workspace_bytes(g, plan, list, bytes);
+    return gpm::sl_workspace_bytes(g, plan, list, compact, bytes);
+}
+
+gpm_status gpm_workspace_bytes(const gpm_graph *g, const gpm_pattern *p, uint64_t *bytes) {
+    return pattern_bytes(g, p, false, bytes);
+}
+
+gpm_status gpm_list_compact_bytes(const gpm_graph *g, const gpm_pattern *p, uint64_t *bytes) {
+    if (p && !(p->flags & GPM_LIST)) return fail(GPM_INVALID_ARGUMENT, "not a GPM_LIST pattern");
+    return pattern_bytes(g, p, true, bytes);
 }
 
 gpm_status gpm_count(const gpm_graph *g, const gpm_pattern *p, void *d_ws, uint64_t ws_bytes,
@@ -386,11 +397,12 @@ gpm_status gpm_count(const gpm_graph *g, const gpm_pattern *p, void *d_ws, uint6
     if (plan == GPM_PLAN_CLIQUE_DAG)
         return gpm::clique_run(g, p->k, false, d_ws, ws_bytes, out, nullptr, 0, nullptr, st);
     if (plan == GPM_PLAN_GENERIC) return gpm::generic_count(g, p, d_ws, ws_bytes, out, st);
-    return gpm::sl_run(g, plan, false, d_ws, ws_bytes, out, nullptr, 0, nullptr, st);
+    return gpm::sl_run(g, plan, false, false, d_ws, ws_bytes, out, nullptr, 0, nullptr, st);
 }
 
-gpm_status gpm_list(const gpm_graph *g, const gpm_pattern *p, void *d_ws, uint64_t ws_bytes,
-                    int32_t *d_buf, uint64_t cap, uint64_t *d_result, void *stream) {
+static gpm_status list_run(const gpm_graph *g, const gpm_pattern *p, bool compact, void *d_ws,
+                           uint64_t ws_bytes, int32_t *d_buf, uint64_t cap, uint64_t *d_result,
+                           void *stream) {
     gpm_status rc = check_graph(g);
     if (rc) return rc;
     if (!p || !d_result) return fail(GPM_INVALID_ARGUMENT, "NULL argument");
@@ -406,12 +418,23 @@ gpm_status gpm_list(const gpm_graph *g, const gpm_pattern *p, void *d_ws, uint64
         return gpm::clique_run(g, p->k, true, d_ws, ws_bytes, nullptr, d_buf, cap, res, st);
     if (plan == GPM_PLAN_GENERIC)
         return gpm::generic_list(g, p, d_ws, ws_bytes, d_buf, cap, res, st);
-    rc = gpm::sl_run(g, plan, true, d_ws, ws_bytes, nullptr, d_buf, cap, res, st);
+    rc = gpm::sl_run(g, plan, true, compact, d_ws, ws_bytes, nullptr, d_buf, cap, res, st);
     if (rc) return rc;
     int32_t perm[4];
     sl_column_perm(p, plan, perm);
     if (perm[0] == 0 && perm[1] == 1 && perm[2] == 2 && perm[3] == 3) return GPM_OK;
     return gpm::permute_rows4(d_buf, cap, res, perm, st);
+}
+
+gpm_status gpm_list(const gpm_graph *g, const gpm_pattern *p, void *d_ws, uint64_t ws_bytes,
+                    int32_t *d_buf, uint64_t cap, uint64_t *d_result, void *stream) {
+    return list_run(g, p, false, d_ws, ws_bytes, d_buf, cap, d_result, stream);
+}
+
+gpm_status gpm_list_compact(const gpm_graph *g, const gpm_pattern *p, void *d_ws,
+                            uint64_t ws_bytes, int32_t *d_buf, uint64_t cap, uint64_t *d_result,
+                            void *stream) {
+    return list_run(g, p, true, d_ws, ws_bytes, d_buf, cap, d_result, stream);
 }
 
 gpm_status gpm_clique_counts_workspace_bytes(const gpm_graph *g, int32_t kmax, uint64_t *bytes) {

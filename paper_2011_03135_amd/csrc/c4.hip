@@ -1422,7 +1422,7 @@ struct C4Ws {
     int32_t *rank, *perm, *rdeg, *roff, *radj, *nin, *dcnt, *dstart, *dcur;
     uint32_t *rtsym;               // with cycle sums: triangles per relabelled arc
     void *sort_area;
-    uint64_t bytes;
+    uint64_t bytes, least;         // with the arena at its largest, without it
 };
 
 // 16-bit counters when at most one vertex (the top-ranked one, never a
@@ -1441,7 +1441,9 @@ bool seg_table(const gpm_graph *g) {
     return np <= kSegMaxParts && (uint64_t)np * (uint64_t)g->n * sizeof(int2) <= kSegMaxBytes;
 }
 
-C4Ws c4_layout(const gpm_graph *g, bool list, void *base) {
+// A workspace of `room` bytes: the arena of a listing takes what lies beyond the
+// rest, up to its largest size (none below a task list and 4,096 words).
+C4Ws c4_layout(const gpm_graph *g, bool list, void *base, uint64_t room = ~0ull) {
     C4Ws W{};
     Carve c(base, ~0ull);
     const uint64_t n1 = (uint64_t)g->n + 1;
@@ -1455,15 +1457,25 @@ C4Ws c4_layout(const gpm_graph *g, bool list, void *base) {
     W.scan_tmp = c.take<int64_t>(scan_tmp_words(n1));
     if (list) {
         W.wedges = c.take<int32_t>((uint64_t)kListBlocks * kWedgeCap);
+        W.least = c.used;
         // a wedge is an arc y -> z with its arc x -> y: at most m * max_degree
         // of them, two words a kept one
-        W.arena_words = std::min<uint64_t>(
+        const uint64_t most = std::min<uint64_t>(
             kArenaWords, 4 * (uint64_t)g->m * (uint64_t)std::max(g->max_degree, 1) + 4096);
-        W.arena = c.take<int32_t>(W.arena_words);
+        Carve all = c;
+        all.take<BigTask>(kMaxBig);
+        all.take<unsigned long long>(2);
+        const uint64_t words = room > all.used ? std::min<uint64_t>(most, (room - all.used) / 256 * 64) : 0;
+        all.take<int32_t>(most);
+        W.bytes = all.used;
+        if (words < 4096) return W;
         W.big = c.take<BigTask>(kMaxBig);
         W.big_ctr = c.take<unsigned long long>(2);
+        W.arena = c.take<int32_t>(words);
+        W.arena_words = words;
+        return W;
     }
-    if (!list) {
+    {
         const uint64_t arcs = (uint64_t)std::max<int64_t>(2 * g->m, 1);
         W.med = c.take<int32_t>(n1);
         W.rank = c.take<int32_t>(n1);
@@ -1479,7 +1491,7 @@ C4Ws c4_layout(const gpm_graph *g, bool list, void *base) {
         W.sort_area = c.take<char>(row_sort_bytes(g->n));
         if (seg_table(g)) W.seg = c.take<int2>((uint64_t)count_parts(g) * (uint64_t)g->n);
     }
-    W.bytes = c.used;
+    W.bytes = W.least = c.used;
     return W;
 }
 
@@ -1491,11 +1503,21 @@ unsigned grid_for(int64_t items, int per_block, int cap_per_cu) {
 
 }  // namespace
 
-gpm_status c4_workspace_bytes(const gpm_graph *g, bool list, uint64_t *bytes) {
+static gpm_status c4_bytes(const gpm_graph *g, bool list, bool compact, uint64_t *bytes) {
     if (list && g->max_degree > kWedgeCap)
         return fail(GPM_UNSUPPORTED, "4-cycle listing needs every degree <= 2^18");
-    *bytes = c4_layout(g, list, nullptr).bytes;
+    const C4Ws W = c4_layout(g, list, nullptr);
+    *bytes = compact ? W.least : W.bytes;
     return GPM_OK;
+}
+
+gpm_status c4_workspace_bytes(const gpm_graph *g, bool list, uint64_t *bytes) {
+    return c4_bytes(g, list, false, bytes);
+}
+
+// Listing without the arena.
+gpm_status c4_compact_bytes(const gpm_graph *g, uint64_t *bytes) {
+    return c4_bytes(g, true, true, bytes);
 }
 
 // Counting (list == false): adds the number of 4-cycles to out128 (two
@@ -1508,8 +1530,8 @@ gpm_status c4_run(const gpm_graph *g, bool list, void *ws, uint64_t ws_bytes,
                   unsigned long long *d_result, hipStream_t st,
                   const uint32_t *tsym, unsigned long long *cs) {
     if (list && cs) return fail(GPM_INVALID_ARGUMENT, "cycle sums are a counting mode");
-    C4Ws W = c4_layout(g, list, ws);
-    if (W.bytes > ws_bytes) return fail(GPM_OUT_OF_MEMORY, "workspace smaller than required");
+    C4Ws W = c4_layout(g, list, ws, ws_bytes);
+    if (W.least > ws_bytes) return fail(GPM_OUT_OF_MEMORY, "workspace smaller than required");
     if (list && g->max_degree > kWedgeCap)
         return fail(GPM_UNSUPPORTED, "4-cycle listing needs every degree <= 2^18");
     const int32_t n = g->n;
@@ -1599,7 +1621,7 @@ gpm_status c4_run(const gpm_graph *g, bool list, void *ws, uint64_t ws_bytes,
         GPM_LAUNCH_CHECK("k_c4_light");
         return GPM_OK;
     }
-    GPM_HIP(zero_words(st, {{W.ctl, 16}, {W.slot, 4}, {W.big_ctr, 4}, {d_result, 6}}));
+    GPM_HIP(zero_words(st, {{W.ctl, 16}, {W.slot, 4}, {W.big_ctr, W.arena ? 4u : 0u}, {d_result, 6}}));
     hipLaunchKernelGGL(k_degrees, dim3(grid_for(n, 256, 8)), dim3(256), 0, st, g->off, n, W.deg);
     hipLaunchKernelGGL(k_c4_work, dim3(grid_for(n, kWPB, 16)), dim3(kBlock), 0, st, g->off,
                        g->adj, W.deg, n, W.cls);
@@ -1614,7 +1636,8 @@ gpm_status c4_run(const gpm_graph *g, bool list, void *ws, uint64_t ws_bytes,
         // tasks of at least this many pairs are shared out: 32,768 keep a
         // workgroup busy for 0.15 ms, and larger graphs have tasks enough
         // above it to fill the arena, so the line grows with them
-        const uint64_t big_pairs = (uint64_t)std::max<int64_t>(1 << 15, g->m / 16);
+        const uint64_t big_pairs =
+            W.arena ? (uint64_t)std::max<int64_t>(1 << 15, g->m / 16) : ~0ull;
         hipLaunchKernelGGL(fine ? k_c4_heavy_list<kPartZFine> : k_c4_heavy_list<kPartZ>,
                            dim3(fine ? kListBlocksFine : kListBlocks), dim3(kBlock), 0, st, g->off,
                            g->adj, W.deg, W.heavy, cnt_heavy, nparts, W.ctl + 0, W.wedges, W.arena,
@@ -1622,7 +1645,7 @@ gpm_status c4_run(const gpm_graph *g, bool list, void *ws, uint64_t ws_bytes,
                            d_result);
     }
     GPM_LAUNCH_CHECK("k_c4_heavy_list");
-    {
+    if (W.arena) {
         Span sp("k_c4_big_list", st);
         hipLaunchKernelGGL(k_c4_big_list, dim3((unsigned)persistent_blocks(kWPB, 8)), dim3(kBlock),
                            0, st, W.arena, W.big, W.big_ctr,

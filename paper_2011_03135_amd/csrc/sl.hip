@@ -23,6 +23,7 @@ gpm_status clique_workspace_bytes(const gpm_graph *g, int32_t k, bool list, uint
 gpm_status triangle_arc_counts(const gpm_graph *g, void *ws, uint64_t ws_bytes, uint32_t *te,
                                unsigned long long *tri, hipStream_t st, WordRun also);
 gpm_status c4_workspace_bytes(const gpm_graph *g, bool list, uint64_t *bytes);
+gpm_status c4_compact_bytes(const gpm_graph *g, uint64_t *bytes);
 gpm_status c4_run(const gpm_graph *g, bool list, void *ws, uint64_t ws_bytes,
                   unsigned long long *out128, int32_t *d_buf, uint64_t cap,
                   unsigned long long *d_result, hipStream_t st,
@@ -338,11 +339,13 @@ struct C4CountWs {
     uint64_t c4_bytes, bytes;
 };
 
-C4CountWs c4count_layout(const gpm_graph *g, bool list, void *base) {
+// compact (listing): the smallest workspace.
+C4CountWs c4count_layout(const gpm_graph *g, bool list, bool compact, void *base) {
     C4CountWs W{};
     Carve c(base, ~0ull);
     W.sum = c.take<unsigned long long>(2);
-    c4_workspace_bytes(g, list, &W.c4_bytes);
+    if (list && compact) c4_compact_bytes(g, &W.c4_bytes);
+    else c4_workspace_bytes(g, list, &W.c4_bytes);
     W.c4 = c.take<char>(W.c4_bytes);
     W.bytes = c.used;
     return W;
@@ -350,25 +353,28 @@ C4CountWs c4count_layout(const gpm_graph *g, bool list, void *base) {
 
 }  // namespace
 
-gpm_status sl_workspace_bytes(const gpm_graph *g, int32_t plan, bool list, uint64_t *bytes) {
+gpm_status sl_workspace_bytes(const gpm_graph *g, int32_t plan, bool list, bool compact,
+                              uint64_t *bytes) {
     if (plan == GPM_PLAN_SL_DIAMOND) {
         *bytes = diamond_layout(g, list, nullptr).bytes;
         return GPM_OK;
     }
     gpm_status rc = c4_workspace_bytes(g, list, bytes);
     if (rc) return rc;
-    *bytes = c4count_layout(g, list, nullptr).bytes;
+    *bytes = c4count_layout(g, list, compact, nullptr).bytes;
     return GPM_OK;
 }
 
-gpm_status sl_run(const gpm_graph *g, int32_t plan, bool list, void *ws, uint64_t ws_bytes,
-                  unsigned long long *d_count, int32_t *d_buf, uint64_t cap,
+gpm_status sl_run(const gpm_graph *g, int32_t plan, bool list, bool compact, void *ws,
+                  uint64_t ws_bytes, unsigned long long *d_count, int32_t *d_buf, uint64_t cap,
                   unsigned long long *d_result, hipStream_t st) {
     if (plan == GPM_PLAN_SL_DIAMOND)
         return diamond_run(g, list, ws, ws_bytes, d_count, d_buf, cap, d_result, st);
-    C4CountWs W = c4count_layout(g, list, ws);
+    C4CountWs W = c4count_layout(g, list, compact, ws);
     if (W.bytes > ws_bytes) return fail(GPM_OUT_OF_MEMORY, "workspace smaller than required");
-    if (list) return c4_run(g, true, W.c4, W.c4_bytes, nullptr, d_buf, cap, d_result, st);
+    if (list)
+        return c4_run(g, true, W.c4, W.c4_bytes + (ws_bytes - W.bytes), nullptr, d_buf, cap,
+                      d_result, st);
     GPM_HIP(fill_u32(W.sum, 0, 4, st));
     gpm_status rc = c4_run(g, false, W.c4, W.c4_bytes, W.sum, nullptr, 0, nullptr, st);
     if (rc) return rc;

@@ -79,3 +79,46 @@ def test_formulas_where_the_lists_have_no_room(gpm):
     assert most > least + (256 << 20)
     with limited_memory(least + (64 << 20)):
         assert gpm.motif_count_formula(g, 5) == want
+
+
+# K_{12,100}: the five largest tasks have 32,768 pairs and more, the line from
+# which a task's pairs are shared out through the arena; with 65,537 vertices
+# the ids of a task are cut otherwise.  RMAT-12 has hundreds of such tasks.
+@pytest.mark.parametrize("name", ["k12_100", "k12_100 wide", "rmat12"])
+def test_4_cycle_listing(gpm, name):
+    e = graphgen.rmat(12, seed=3) if name == "rmat12" else graphgen.complete_bipartite(12, 100)
+    if name[-4:] == "wide":
+        e = graphgen.EdgeList(65537, e.u, e.v, name)
+    g = build(gpm, e)
+    p = gpm.cycle4(gpm.EDGE_INDUCED | gpm.LIST)
+    want = list(gpm.list_embeddings(g, p, 1000)[:3])
+    if name != "rmat12":
+        assert want[:2] == [comb(12, 2) * comb(100, 2), 1000]
+    least, most = gpm.list_compact_bytes(g, p), gpm.workspace_bytes(g, p)
+    assert least < most
+    lib, ws = gpm.load(), torch.empty(most, dtype=torch.uint8, device="cuda")
+    buf = torch.empty((1000, 4), dtype=torch.int32, device="cuda")
+    arena = [least + (2 << 20) + x for x in (0, 20000, 300000, 3000000)]   # past the task list
+    for n in sizes(least, most) + [x for x in arena if x < most]:
+        print(f"4-cycles of {name} in {n} of {most} bytes", flush=True)
+        ws[least:] = 0xA5
+        out = torch.full((3,), -1, dtype=torch.int64, device="cuda")
+        assert lib.gpm_list_compact(g.handle, ctypes.byref(p), ptr(ws), n, ptr(buf), 1000,
+                                    ptr(out), None) == 0
+        torch.cuda.synchronize()
+        assert [x % (1 << 64) for x in out.tolist()] == want, n
+        assert bool((ws[n:] == 0xA5).all()), n
+    out = torch.full((3,), -1, dtype=torch.int64, device="cuda")
+    rc = lib.gpm_list_compact(g.handle, ctypes.byref(p), ptr(ws), least - 256, ptr(buf), 1000,
+                              ptr(out), None)
+    assert rc == 2 and bool((out == -1).all())
+
+
+def test_4_cycle_listing_where_the_arena_has_no_room(gpm):
+    g = build(gpm, graphgen.rmat(13, seed=6))
+    p = gpm.cycle4(gpm.EDGE_INDUCED | gpm.LIST)
+    want = gpm.list_embeddings(g, p, 100)[:3]
+    least, most = gpm.list_compact_bytes(g, p), gpm.workspace_bytes(g, p)
+    assert most > least + (400 << 20)
+    with limited_memory(least + (64 << 20)):
+        assert gpm.list_embeddings(g, p, 100)[:3] == want
