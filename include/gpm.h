@@ -575,7 +575,8 @@ gpm_status gpm_timing_enable(int32_t on);
  * units is 0 for kernels that report none, and any pointer may be NULL),
  * clears the record, and returns the number of spans recorded (may exceed
  * cap).  Work units, where reported, are counted on the device:
- * k_tc_flat* = (v, w) pairs tested, k_lg5* = local triangles expanded. */
+ * k_tc_arcs*, k_tc_seg* = list entries looked up (the shorter out-list of
+ * each arc's two), k_lg5* = local triangles expanded. */
 int32_t gpm_timing_read(const char **names, float *ms, uint64_t *units, int32_t cap);
 
 #ifdef __cplusplus

@@ -586,6 +586,29 @@ __global__ void __launch_bounds__(kBlock, MODE == TC_COUNT ? 8 : 4)
     block_add<kWPB>(acc, result);
 }
 
+// Entries that the triangle kernels look up, the shorter out-list of each arc's
+// two, by the kernel that takes the arc: units[0] k_tc_arcs, [1] k_tc_seg, [2]
+// its hub form (all zero on entry).  Launched while timing is on only.
+__global__ void __launch_bounds__(kBlock) k_tc_units(const int32_t *__restrict__ dag_off,
+                                                     const int32_t *__restrict__ dag_adj,
+                                                     const int32_t *__restrict__ dag_src,
+                                                     int64_t m, unsigned long long *units) {
+    uint64_t n[3] = {0, 0, 0};
+    for (int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x; e < m;
+         e += (int64_t)gridDim.x * kBlock) {
+        const int32_t u = dag_src[e], v = dag_adj[e];
+        const int32_t du = dag_off[u + 1] - dag_off[u], dv = dag_off[v + 1] - dag_off[v];
+        const int32_t most = max(du, dv), least = min(du, dv);
+        if (most <= kTcArcMax) n[0] += du >= 2 ? least : 0;
+        else n[most <= kTcMaxD ? 1 : 2] += least;
+    }
+#pragma unroll
+    for (int q = 0; q < 3; q++) {
+        const uint64_t t = wave_sum(n[q]);
+        if (lane_id() == 0 && t) atomicAdd(&units[q], (unsigned long long)t);
+    }
+}
+
 // ------------------------------------------- local-graph k-cliques ---
 
 // Number of D-vertex cliques of the local DAG (rows: 64-bit masks, local
@@ -983,7 +1006,8 @@ __global__ void __launch_bounds__(kBlock) k_clique_hub(const int32_t *__restrict
 constexpr uint64_t kCtlCur = 32, kCtlWords = kCtlCur + 2 * kCursorWords;
 
 struct CliqueWs {
-    unsigned long long *ctr;      // [8]: [0] listing slots, [1] row words, [2] hubs, [3..7] unused
+    unsigned long long *ctr;      // [8]: [0] listing slots, [1] row words, [2] hubs, [3..5]
+                                  // triangles' work units, [6..7] unused
     uint32_t *ctl;                // [2..3] triangle tasks, [4..7] class counts, from
                                   // kCtlCur two sets of cursors (triangles)
     int32_t *list_s, *list_m, *list_b, *list_h;
@@ -1153,6 +1177,11 @@ template <int MODE>
 static gpm_status tc_launch(const gpm_graph *g, CliqueWs &W, unsigned long long *res,
                             uint32_t *te, hipStream_t st, const RowEmitter &em = RowEmitter{}) {
     if (g->m == 0) return GPM_OK;
+    if (timing_on()) {
+        hipLaunchKernelGGL(k_tc_units, dim3(grid_for(g->m, kBlock, 8)), dim3(kBlock), 0, st,
+                           g->dag_off, g->dag_adj, g->dag_src, g->m, W.ctr + 3);
+        GPM_LAUNCH_CHECK("k_tc_units");
+    }
     if (g->max_out_degree > kTcArcMax) {
         const Tau tau = tau_of(g);
         hipLaunchKernelGGL(k_tc_tasks, dim3(grid_for(g->n, kRootsBlock, 8)), dim3(kBlock), 0, st,
@@ -1166,6 +1195,7 @@ static gpm_status tc_launch(const gpm_graph *g, CliqueWs &W, unsigned long long 
                                g->okey, g->dag_off, g->dag_adj, W.tasks, W.ctl + 2, tau,
                                (unsigned long long *)(W.ctl + kCtlCur),
                                res, te, em);
+            span_units(W.ctr + 4, st);
         }
         GPM_LAUNCH_CHECK("k_tc_seg");
         if (has_hubs(g)) {
@@ -1173,6 +1203,7 @@ static gpm_status tc_launch(const gpm_graph *g, CliqueWs &W, unsigned long long 
             hipLaunchKernelGGL((k_tc_seg<MODE, true>), grid, dim3(kBlock), 0, st, g->off, g->adj,
                                g->okey, g->dag_off, g->dag_adj, W.hub_tasks, W.ctl + 3, tau,
                                (unsigned long long *)(W.ctl + kCtlCur + kCursorWords), res, te, em);
+            span_units(W.ctr + 5, st);
         }
         GPM_LAUNCH_CHECK("k_tc_seg<hub>");
     }
@@ -1181,6 +1212,7 @@ static gpm_status tc_launch(const gpm_graph *g, CliqueWs &W, unsigned long long 
         hipLaunchKernelGGL(k_tc_arcs<MODE>, dim3(grid_for(g->m, kBlock, g->tc_bpc[0])),
                            dim3(kBlock), 0, st, g->dag_off, g->dag_adj, g->dag_src, g->m, res, te,
                            em);
+        span_units(W.ctr + 3, st);
     }
     GPM_LAUNCH_CHECK("k_tc_arcs");
     return GPM_OK;
