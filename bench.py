@@ -82,8 +82,9 @@ def dag_class_bytes(off, adj, dmin, dmax, kmin):
     """Algorithmic bytes of one triangle/local-graph-build launch over the
     roots u with dmin < d+(u) <= dmax and d+(u) >= kmin: per root, its
     out-list (4 B per arc); per out-neighbour v, v's two offsets (8 B) and
-    v's out-list (4 B per entry, the (v, w) pairs), or the shorter of its and
-    u's for triangles (kmin 2)."""
+    v's out-list (4 B per entry, the (v, w) pairs).  For triangles (kmin 2) an
+    arc belongs to its end of larger out-degree, and its entries are the
+    shorter out-list of the two."""
     n = off.shape[0] - 1
     deg = np.diff(off).astype(np.int64)
     rows = np.repeat(np.arange(n, dtype=np.int64), deg)
@@ -92,13 +93,14 @@ def dag_class_bytes(off, adj, dmin, dmax, kmin):
     src, dst = rows[fwd], cols[fwd]
     dout = np.bincount(src, minlength=n)
     if kmin == 2:
-        # triangles: an arc's shorter out-list, looked up in the longer
+        root = np.where(dout[src] >= dout[dst], src, dst)
         walked = np.minimum(dout[src], dout[dst])
     else:
-        walked = dout[dst]
-    pairs_root = np.bincount(src, weights=walked, minlength=n).astype(np.int64)
+        root, walked = src, dout[dst]
+    arcs_root = np.bincount(root, minlength=n)
+    pairs_root = np.bincount(root, weights=walked, minlength=n).astype(np.int64)
     sel = (dout > dmin) & (dout <= dmax) & (dout >= kmin) & (pairs_root > 0)
-    arcs = int(dout[sel].sum())
+    arcs = int(arcs_root[sel].sum())
     pairs = int(pairs_root[sel].sum())
     return 12 * arcs + 4 * pairs, arcs, pairs
 
@@ -112,8 +114,10 @@ def roofline(dom, ms, units, off, adj, lg5_slice):
                 "traffic": measured_traffic(dom, lg5_slice), "traffic_unit": "bytes per launch",
                 "units_per_launch": units, "unit_name": "local triangles",
                 "ops_per_unit": OPS_PER_LOCAL_TRIANGLE, "avg_launch_ms": ms}
-    if dom.startswith("k_tc_flat"):
-        dmin, dmax, kmin = (0, 256, 2) if "<256" in dom else (256, 1024, 2)
+    if dom.startswith("k_tc_arcs"):
+        dmin, dmax, kmin = 0, 32, 2
+    elif dom.startswith("k_tc_seg"):
+        dmin, dmax, kmin = (1024, 1 << 30, 2) if "hub" in dom else (32, 1024, 2)
     elif dom.startswith("k_clique_wave"):
         dmin, dmax, kmin = 0, 64, int(dom.split("<")[1][0]) - 1
     elif "<256>" in dom or "<256," in dom:
