@@ -262,8 +262,8 @@ gpm_status gpm_graph_set_tuning(gpm_graph *g, const gpm_tuning *t);
 /* Autotuner: times triangle counting, 4-clique counting and (when the graph
  * has roots of out-degree above 256) 5-clique counting on g under candidate
  * settings, walking the knobs one at a time (each tc_tau x4, x2, /2, /4,
- * each tc_blocks_per_cu x2, /2, two passes; clique_wave_blocks_per_cu x4,
- * x2, /2; lg5_slice x4, x2, /2, /4) and
+ * tc_blocks_per_cu[0] and the larger of [1] and [2] x2, /2, two passes;
+ * clique_wave_blocks_per_cu x4, x2, /2; lg5_slice x4, x2, /2, /4) and
  * keeping a change when it is at least 3% faster (median of three calls
  * after a warm-up, HIP events on the stream).  Stores the result in the
  * handle and, when chosen is not NULL, in *chosen; on failure the handle

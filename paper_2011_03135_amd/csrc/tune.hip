@@ -1,8 +1,8 @@
 // Per-graph tuning of the plain path's task granularity (Section 4.1 splits
-// the work into tasks and leaves their size open).  The knobs: pairs per
-// work chunk and workgroups per CU of the three triangle classes, the grid
-// of the wave-per-root clique kernel, and local triangles per 5-clique
-// task.  The tuner times the calls they govern on
+// the work into tasks and leaves their size open).  The knobs: pairs per task
+// of the staged triangle roots of three out-degree classes, workgroups per CU
+// of the arc merge and of the staged roots, the grid of the wave-per-root
+// clique kernel, and local triangles per 5-clique task.  The tuner times the calls they govern on
 // the graph itself (HIP events on the caller's stream, the median of three
 // runs after a warm-up) and walks the knobs one at a time (coordinate
 // descent), keeping a change only when it is at least 3% faster.  Counts
@@ -137,11 +137,16 @@ gpm_status graph_autotune(gpm_graph *g, void *ws, uint64_t ws_bytes, hipStream_t
                 t.tc_tau[c] = std::min(kTauHi, std::max(kTauLo, (int64_t)(cur.tc_tau[c] * f)));
                 if (t.tc_tau[c] != cur.tc_tau[c]) attempt(t, 3, best3);
             }
+            // [1] and [2] act through their maximum: one knob, tried once
             for (const double f : {2.0, 0.5}) {
+                if (c == 2) break;
                 gpm_tuning t = cur;
-                t.tc_blocks_per_cu[c] = std::min(
-                    kBpcHi, std::max(kBpcLo, (int32_t)(cur.tc_blocks_per_cu[c] * f)));
-                if (t.tc_blocks_per_cu[c] != cur.tc_blocks_per_cu[c]) attempt(t, 3, best3);
+                const int32_t now = c == 0 ? cur.tc_blocks_per_cu[0]
+                                           : std::max(cur.tc_blocks_per_cu[1], cur.tc_blocks_per_cu[2]);
+                const int32_t next = std::min(kBpcHi, std::max(kBpcLo, (int32_t)(now * f)));
+                t.tc_blocks_per_cu[c] = next;
+                if (c == 1) t.tc_blocks_per_cu[2] = std::min(cur.tc_blocks_per_cu[2], next);
+                if (next != now) attempt(t, 3, best3);
             }
         }
     if (!err) {
