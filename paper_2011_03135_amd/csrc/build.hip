@@ -809,14 +809,14 @@ __global__ void __launch_bounds__(kBlock) k_check_csr(const int32_t *__restrict_
             continue;
         }
         bool bad = false;
-        for (int32_t i = s + lane; i < e; i += kWave) {
+        for (uint32_t i = s + lane; i < (uint32_t)e; i += kWave) {   // (may step past 2^31)
             const int32_t w = adj[i];
             if (w < 0 || w >= n) {
                 bad = true;
                 continue;
             }
             if (FULL) {
-                if (w == u || (i > s && adj[i - 1] >= w)) bad = true;
+                if (w == u || (i > (uint32_t)s && adj[i - 1] >= w)) bad = true;
                 // (w, u) present: binary search u in N(w), whose bounds are
                 // checked first
                 const int32_t ws = off[w], we = off[w + 1];
@@ -826,7 +826,7 @@ __global__ void __launch_bounds__(kBlock) k_check_csr(const int32_t *__restrict_
                 }
                 int32_t lo = ws, hi = we;
                 while (lo < hi) {
-                    const int32_t mid = (lo + hi) >> 1;
+                    const int32_t mid = arc_mid(lo, hi);
                     if (adj[mid] < u) lo = mid + 1; else hi = mid;
                 }
                 if (lo >= we || adj[lo] != u) bad = true;

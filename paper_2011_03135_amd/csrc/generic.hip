@@ -136,7 +136,7 @@ __device__ __forceinline__ bool row_has(const int32_t *__restrict__ off,
                                         const int32_t *__restrict__ adj, int32_t u, int32_t v) {
     int32_t lo = off[u], hi = off[u + 1];
     while (lo < hi) {
-        const int32_t mid = (lo + hi) >> 1;
+        const int32_t mid = arc_mid(lo, hi);
         if (adj[mid] < v) lo = mid + 1; else hi = mid;
     }
     return lo < off[u + 1] && adj[lo] == v;
@@ -146,7 +146,7 @@ __device__ __forceinline__ bool row_has(const int32_t *__restrict__ off,
 __device__ __forceinline__ int32_t lower_idx(const int32_t *__restrict__ adj, int32_t lo,
                                              int32_t hi, int32_t x) {
     while (lo < hi) {
-        const int32_t mid = (lo + hi) >> 1;
+        const int32_t mid = arc_mid(lo, hi);
         if (adj[mid] < x) lo = mid + 1; else hi = mid;
     }
     return lo;
@@ -164,7 +164,7 @@ __device__ __forceinline__ int32_t gen_arc_row(const int32_t *__restrict__ off, 
                                                int64_t a) {
     int32_t lo = 0, hi = n;
     while (hi - lo > 1) {
-        const int32_t mid = (lo + hi) >> 1;
+        const int32_t mid = arc_mid(lo, hi);
         if (off[mid] <= a) lo = mid; else hi = mid;
     }
     return lo;

@@ -544,6 +544,11 @@ __device__ __forceinline__ f32x16 fp4_step(const fp4x64 &A, const fp4x64 &B, con
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A, B, C, 4, 4, 0, kFp4One, 0, unit);
 }
 
+// Middle of [lo, hi] for ranges of arcs, whose ends' sum may pass 2^31.
+__device__ __forceinline__ int32_t arc_mid(int32_t lo, int32_t hi) {
+    return (int32_t)(((uint32_t)lo + (uint32_t)hi) >> 1);
+}
+
 // splitmix64 finaliser, for the listing checksum.
 __device__ __forceinline__ uint64_t fmix64(uint64_t z) {
     z ^= z >> 30; z *= 0xBF58476D1CE4E5B9ull;

@@ -599,7 +599,7 @@ __global__ void __launch_bounds__(kBlock) k_f5_arcs(const int32_t *__restrict__ 
     auto find = [&](int32_t u, int32_t v) {
         int32_t lo = off[u], hi = off[u + 1];
         while (lo < hi) {
-            const int32_t mid = (lo + hi) >> 1;
+            const int32_t mid = arc_mid(lo, hi);
             if (adj[mid] < v) lo = mid + 1; else hi = mid;
         }
         return lo;

@@ -69,7 +69,7 @@ __device__ __forceinline__ bool me_row_has(const int32_t *__restrict__ off,
     const int32_t end = off[u + 1];
     int32_t hi = end;
     while (lo < hi) {
-        const int32_t mid = (lo + hi) >> 1;
+        const int32_t mid = arc_mid(lo, hi);
         if (adj[mid] < v) lo = mid + 1; else hi = mid;
     }
     return lo < end && adj[lo] == v;
@@ -78,7 +78,7 @@ __device__ __forceinline__ bool me_row_has(const int32_t *__restrict__ off,
 __device__ __forceinline__ int32_t me_lower(const int32_t *__restrict__ adj, int32_t lo,
                                             int32_t hi, int32_t x) {
     while (lo < hi) {
-        const int32_t mid = (lo + hi) >> 1;
+        const int32_t mid = arc_mid(lo, hi);
         if (adj[mid] < x) lo = mid + 1; else hi = mid;
     }
     return lo;
@@ -102,7 +102,7 @@ __device__ __forceinline__ int32_t me_arc_row(const int32_t *__restrict__ off, i
                                               int64_t a) {
     int32_t lo = 0, hi = n;
     while (hi - lo > 1) {
-        const int32_t mid = (lo + hi) >> 1;
+        const int32_t mid = arc_mid(lo, hi);
         if (off[mid] <= a) lo = mid; else hi = mid;
     }
     return lo;

@@ -79,3 +79,35 @@ def test_most_vertices(gpm):
             assert int(part.min()) == int(part.max()) == total
             at, total = r + 1, total + d
         assert int(offs[at:].min()) == int(offs[at:].max()) == total
+
+
+def test_most_arcs_from_csr(gpm, circulant):
+    """The checked adoption of the same CSR: its search in rows that begin
+    beyond 2^30."""
+    g = gpm.Graph.build(N, *circulant)
+    off, adj = (t.clone() for t in g.csr())
+    del g
+    print("adoption of 2^31 - 2 arcs", flush=True)
+    check_circulant(gpm.Graph.from_csr(N, off, adj))
+    last = adj[-1].clone()
+    adj[-1] = adj[-2]                    # not ascending
+    with pytest.raises(gpm.GpmError) as err:
+        gpm.Graph.from_csr(N, off, adj)
+    assert err.value.status == 6
+    adj[-1] = last
+
+
+def test_searches_beyond_half_the_arcs(gpm):
+    """A cycle of 600,000,000 vertices: the searches in its rows add up arc
+    numbers above 2^31.  It has as many induced 4-paths and wedges as vertices."""
+    torch.cuda.empty_cache()
+    n = 600_000_000
+    u = torch.arange(n, **I32)
+    v = torch.roll(u, -1)
+    g = gpm.Graph.build(n, u, v)
+    del u, v
+    torch.cuda.empty_cache()
+    print("patterns of a cycle of 600,000,000 vertices", flush=True)
+    assert gpm.count(g, gpm.pattern(4, [(0, 1), (1, 2), (2, 3)], gpm.VERTEX_INDUCED)) == n
+    torch.cuda.empty_cache()
+    assert gpm.motif_count_enum(g, 3) == [n, 0]
