@@ -368,11 +368,13 @@ __global__ void __launch_bounds__(kGenNT) k_generic(const int32_t *__restrict__ 
     };
     // a work unit is one 64-candidate chunk of step 2 below one arc (steps
     // 0 and 1), with the whole search below it; units come from work cursors,
-    // so a hub's arcs and chunks spread over the grid.  (Counts by leaf_pairs,
-    // whose units are short.  The others keep one counter: the cursors'
-    // registers cost the listing one of five waves a SIMD, 4-paths of 10,000
-    // vertices 99 ms, not 89, and induced 6-cycles of 1,024 took 181, not 177.)
-    constexpr bool kSpread = MNC && !LIST;
+    // so a hub's arcs and chunks spread over the grid.  Counts take spread
+    // cursors: with short units one counter is the bound (4-paths of a uniform
+    // graph of 1,000,000 vertices and 3,000,000 edges 36.1 ms, 21.6 with them;
+    // induced 6-cycles of 1,024 vertices 179 and 177).  Listings keep one: the
+    // cursors' registers cost them one of five waves a SIMD (the same 4-paths
+    // 43.8 ms, not 38.1; those of 10,000 vertices 99, not 89).
+    constexpr bool kSpread = !LIST;
     TaskQueue queue(cursor, nchunks, wib * gridDim.x + blockIdx.x,
                     gridDim.x * (kGenNT / kWave));
     for (;;) {
