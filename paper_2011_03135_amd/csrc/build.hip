@@ -275,9 +275,12 @@ __device__ __forceinline__ int32_t group_bitonic_sort(int32_t x) {
 constexpr int kSmallRow = 16;   // rows sorted by a 16-lane group, 4 per wave
 constexpr int kScanRow = 512;   // rows up to this length sort in registers within a row scan
 constexpr int kRegRow = 2048;   // rows up to this length sort in registers, a wave each,
-constexpr int32_t kBitmapIds = 1 << 17;   // on graphs of more ids than this: below, a bitmap
-                                          // over the ids beats them from kScanRow on (16 or
-                                          // 32 registers a lane: 36 us for RMAT-12's few rows)
+// on graphs of more ids than this: below, a bitmap over the ids beats them from
+// kScanRow on (16 or 32 registers a lane).  Builds, bitmap and registers: RMAT
+// of 4,096 ids 170 and 194 us, 65,536 303 and 350, 131,072 393 and 433,
+// 262,144 645 and 646, 1,048,576 1,826 and 1,655; uniform, 200,000 ids and 1e8
+// edges, 9.2 and 7.9 ms
+constexpr int32_t kBitmapIds = 1 << 17;
 
 int32_t reg_row(int32_t n) { return n > kBitmapIds ? kRegRow : kScanRow; }
 

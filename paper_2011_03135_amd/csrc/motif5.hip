@@ -583,7 +583,9 @@ __global__ void __launch_bounds__(kBlock) k_f5_wheel(const int32_t *__restrict__
 }
 
 // arcs of this many triangles are the wheel kernel's workgroup tasks (RMAT-13,
-// both kernels: 1.57, 1.37, 1.48 ms from 256, 512, 1,024 on)
+// both kernels: 1.57, 1.37, 1.48 ms from 256, 512, 1,024 on; whole calls on
+// RMAT graphs of 16,384 and 30,000 vertices: 8.71, 8.54, 8.59 and 13.9, 13.7,
+// 14.0 ms; of 4,096, and uniform, no difference)
 constexpr uint32_t kBigT = 512;
 
 // esym and tsym of every arc (one thread per DAG arc, a binary search in
@@ -672,7 +674,9 @@ __global__ void __launch_bounds__(kBlock) k_f5_lists(const int32_t *__restrict__
 // triangles is split into parts that share its neighbours a out in turn.
 // Each part builds the row of A^2 again; larger parts leave the last ones
 // running alone (RMAT-13, kernel: 2.36, 2.14, 1.97, 2.54 ms for parts of
-// 1,024, 2,048, 4,096 and 8,192).
+// 1,024, 2,048, 4,096 and 8,192).  The best size grows with the graph: whole
+// calls for 2,048, 4,096 and 8,192 on RMAT graphs of 4,096 vertices 2.32, 2.52
+// and 2.60 ms, of 16,384 9.41, 8.54 and 8.49, of 30,000 14.8, 13.7 and 13.5.
 constexpr int32_t kRowCorners = 4096;
 constexpr size_t kRowsFixedLds = 8 * 1024;   // at most, beside the row and the bitmap
 constexpr int32_t kMaxRowParts = 64;
