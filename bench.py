@@ -52,18 +52,18 @@ INT32_VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 OPS_PER_LOCAL_TRIANGLE = 4
 
 
-# Bytes beyond L2 per launch of the dominant kernel from two rocprofv3 counter
-# runs: TCC EA read requests x 128 B (32 B for TCC_EA0_RDREQ_32B) and write
+# Bytes beyond L2 per call of the dominant kernel (k_lg5: both its launches, one
+# span) from two rocprofv3 counter runs: TCC EA read requests x 128 B (32 B for TCC_EA0_RDREQ_32B) and write
 # requests x 64 B (TCC_EA0_WRREQ_64B) or 32 B
 # (profiles/rmat20_cliques_hbm_traffic.md); valid only while the kernel's
 # source is the one measured.
 MEASURED_TRAFFIC = {
     "kernel": "k_lg5<1024>",
     "source": "paper_2011_03135_amd/csrc/local_graph.hip",
-    "source_sha256_prefix": "0929cc93784b2dcc",
+    "source_sha256_prefix": "e851ec9e997d9794",
     "lg5_slice": 1 << 20,   # the task size the counters were taken at
-    "bytes_read": 4307177 * 128,
-    "bytes_written": 30690 * 32,
+    "bytes_read": 5056276 * 128,
+    "bytes_written": 3198720,
 }
 
 

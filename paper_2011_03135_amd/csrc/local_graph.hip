@@ -40,8 +40,9 @@ constexpr int kHalfMaxD = 512;
 constexpr int kHalfThreads = 512;
 constexpr int kHalfBlocksPerCu = 3;
 // Threads and workgroups per CU of the 5-clique kernel: by registers, 4 waves a
-// SIMD for local graphs of up to 8 words a row and 3 up to 16 (RMAT-20: 8.4 ms;
-// 9.2 with 2 waves).  The descents of larger cliques and the listing, whose
+// SIMD for local graphs of up to 8 words a row and 3 up to 16 (RMAT-20: 8.4 ms,
+// 9.2 with 2 waves, both before the operands of 10 words and more left scratch
+// memory; 6.5 now).  The descents of larger cliques and the listing, whose
 // tasks differ more, take one workgroup of 16 waves (6-cliques of RMAT-16: 6.4
 // ms in this class; 11.3 with two of 8).
 template <int DMAX, bool TILES> struct Lg5Block {
@@ -529,9 +530,9 @@ __device__ __forceinline__ void down_to(int32_t first, F &&f) {
 // Sums stay whole: an entry is below 2^24 units and a lane adds at most
 // 528 tiles x 16 entries x 1021.  The last tile repeats the last member, whose
 // row has nothing inside R: it adds nothing on either side.
-// Bound by the vector units (about 95 operations a wave and tile of 2.7 steps, two
-// thirds of its time) and the latency of the gathered rows; the matrix cores take a
-// fifth.  RMAT-20, 3.7e7 tiles: 8.4 ms; by population counts, as lg5_sweep, 15.1.
+// Bound by the vector units: about 90 operations a wave and tile of 2.7 steps,
+// 85 % of its time; the matrix cores take 28 %.  RMAT-20, 3.7e7 tiles: 6.5 ms; by
+// population counts, as lg5_sweep, 15.1.
 template <int W, int S>
 __device__ __forceinline__ uint64_t lg5_tiles(const uint64_t *rows, const uint64_t *ri, int32_t c,
                                               int16_t *mem) {
