@@ -53,8 +53,8 @@ OPS_PER_LOCAL_TRIANGLE = 4
 
 
 # Bytes beyond L2 per call of the dominant kernel (k_lg5: both its launches, one
-# span) from two rocprofv3 counter runs: TCC EA read requests x 128 B (32 B for TCC_EA0_RDREQ_32B) and write
-# requests x 64 B (TCC_EA0_WRREQ_64B) or 32 B
+# span) from two rocprofv3 counter runs: TCC EA read requests x 128 B (32 B for
+# TCC_EA0_RDREQ_32B) and write requests x 64 B (TCC_EA0_WRREQ_64B) or 32 B
 # (profiles/rmat20_cliques_hbm_traffic.md); valid only while the kernel's
 # source is the one measured.
 MEASURED_TRAFFIC = {

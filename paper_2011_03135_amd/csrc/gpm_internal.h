@@ -87,14 +87,14 @@ struct WordRun {
 hipError_t zero_words(hipStream_t s, std::initializer_list<WordRun> runs);
 // Work cursors.  A kernel whose workers (a workgroup, or a wave) take their
 // tasks as they become free does so from kCursors counters, each in a cache
-// line of its own.  One counter serves a task about every 12 ns whatever the
-// grid (24 ns in kernels that also load), so that it bounds a kernel of many
-// small tasks: 65,536 of them take 750 us at one counter, 120 us at 8, and 18
-// us at 64 (8 counters in one line are no better than one).  Beside the kernels'
-// own work the number matters little from a few on: with 4, 8, 16 and 24
-// 4-motif enumeration of 1,024 vertices takes 488, 475, 468 and 479 us, and
-// triangles, cliques, motifs and the 5-motif formulas of RMAT-12 to RMAT-20
-// agree within 2 %.
+// line of its own, unless it says why one is better.  One counter serves a task
+// about every 12 ns whatever the grid (24 ns in kernels that also load), so that
+// it bounds a kernel of many small tasks: 65,536 of them take 750 us at one
+// counter, 120 us at 8, and 18 us at 64 (8 counters in one line are no better
+// than one).  Beside the kernels' own work the number matters little from a few
+// on: with 4, 8, 16 and 24, 4-motif enumeration of 1,024 vertices takes 488, 475,
+// 468 and 479 us, and triangles, cliques, motifs and the 5-motif formulas of
+// RMAT-12 to RMAT-20 agree within 2 %.
 constexpr int kCursors = 16, kCursorStride = 16;          // u64 words
 constexpr uint64_t kCursorWords = 2ull * kCursors * kCursorStride;   // 32-bit words, zero on entry
 // The words at the front of the local-graph workspace that must be zero when
