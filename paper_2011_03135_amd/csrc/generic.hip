@@ -215,8 +215,10 @@ __global__ void k_gen_total(const int64_t *__restrict__ total, unsigned long lon
     if (threadIdx.x == 0) out[0] = (unsigned long long)*total;
 }
 
+// (The listing takes 95 registers, so that five waves fit a SIMD: with the 99
+// it takes if let, 4-paths of 10,000 vertices are 98.6 ms, 90.8 with 95.)
 template <bool MNC, bool LIST>
-__global__ void __launch_bounds__(kGenNT) k_generic(const int32_t *__restrict__ off,
+__global__ void __launch_bounds__(kGenNT, LIST ? 5 : 1) k_generic(const int32_t *__restrict__ off,
                                                     const int32_t *__restrict__ adj, int32_t n,
                                                     GenPlan P, const int64_t *__restrict__ chunk_off,
                                                     unsigned long long *cursor, int32_t map_stride,
@@ -367,27 +369,16 @@ __global__ void __launch_bounds__(kGenNT) k_generic(const int32_t *__restrict__ 
         return (uint64_t)total;
     };
     // a work unit is one 64-candidate chunk of step 2 below one arc (steps
-    // 0 and 1), with the whole search below it; units come from work cursors,
-    // so a hub's arcs and chunks spread over the grid.  Counts take spread
-    // cursors: with short units one counter is the bound (4-paths of a uniform
-    // graph of 1,000,000 vertices and 3,000,000 edges 36.1 ms, 21.6 with them;
-    // induced 6-cycles of 1,024 vertices 179 and 177).  Listings keep one: the
-    // cursors' registers cost them one of five waves a SIMD (the same 4-paths
-    // 43.8 ms, not 38.1; those of 10,000 vertices 99, not 89).
-    constexpr bool kSpread = !LIST;
+    // 0 and 1), with the whole search below it; units come from
+    // work cursors, so a hub's arcs and chunks spread over the grid (with short
+    // units one counter is the bound: 4-paths of a uniform graph of 1,000,000
+    // vertices and 3,000,000 edges 36.1 ms, 21.6 so; listed in 5,000 cliques of
+    // 20 11.6 ms, 2.6 so)
     TaskQueue queue(cursor, nchunks, wib * gridDim.x + blockIdx.x,
                     gridDim.x * (kGenNT / kWave));
     for (;;) {
-        int64_t c;   // wave-uniform
-        if constexpr (kSpread) {
-            c = queue.next();
-            if (c < 0) break;
-        } else {
-            unsigned long long got = 0;
-            if (lane == 0) got = atomicAdd(cursor, 1ull);
-            c = (int64_t)__shfl(got, 0);
-            if (c >= nchunks) break;
-        }
+        const int64_t c = queue.next();
+        if (c < 0) break;   // wave-uniform
         int64_t lo = 0, hi = narcs;   // the arc of unit c: last a with chunk_off[a] <= c
         while (hi - lo > 1) {
             const int64_t mid = (lo + hi) >> 1;
