@@ -556,13 +556,22 @@ __global__ void __launch_bounds__(kBlock, MODE == TC_COUNT ? 8 : 4)
                             if (!more) break;
                         }
                     } else {
+                        int32_t p[TU];   // HUB: last entry of N+(x) up to w, or the first;
+                        if constexpr (HUB) {   // the tiles' searches advance together
+#pragma unroll
+                            for (int q = 0; q < TU; q++) p[q] = 0;
+                            for (int32_t len = d; len > 1; len -= len >> 1) {
+#pragma unroll
+                                for (int q = 0; q < TU; q++)
+                                    p[q] += dag_adj[s + p[q] + (len >> 1)] <= w[q] ? len >> 1 : 0;
+                            }
+                        }
 #pragma unroll
                         for (int q = 0; q < TU; q++) {
                             int32_t at = -1;   // slot of w (HUB: position in N+(x))
                             if ((pend[q] >> lane) & 1ull) {
                                 if constexpr (HUB) {
-                                    const int32_t p = lower_bound_i32(dag_adj + s, d, w[q]);
-                                    at = p < d && dag_adj[s + p] == w[q] ? p : -1;
+                                    at = dag_adj[s + p[q]] == w[q] ? p[q] : -1;
                                 } else {
                                     uint32_t h = lds_hash_slot(w[q], hb);
                                     for (;;) {
