@@ -769,9 +769,11 @@ __device__ __forceinline__ uint64_t lgk_set(const uint64_t *rows, const uint64_t
 // Stride of a class's rows in LDS for W words: odd, so that a column of them is
 // spread over the banks; but not for the descents above 512, where the room for
 // more waves is worth more (6-cliques of 7,000 vertices, out-degrees up to 986:
-// 260 ms with 8 waves, 213 with 10).
+// 260 ms with 8 waves, 213 with 10), nor up to 256, where they gain nothing by it
+// (RMAT-16: 6-cliques 21.8 ms in this class, 20.4 without; 7-cliques 570 and 510;
+// from 257 to 512 6.46 and 6.58 ms).
 template <int DMAX> __host__ __device__ constexpr int32_t row_stride(int32_t W, bool deep) {
-    return deep && DMAX > kHalfMaxD ? W : W | 1;
+    return deep && DMAX != kHalfMaxD ? W : W | 1;
 }
 
 template <int WLO, int WHI, bool DEEP>
@@ -933,7 +935,8 @@ __global__ void __launch_bounds__(NT, DEEP ? 7 : kMidWaves) k_lg5_mid(const int3
         __syncthreads();
         if (r >= nroots) break;
         const int32_t u = roots[r];
-        const int32_t d = dag_off[u + 1] - dag_off[u], W = (d + 63) >> 6, S = W | 1;
+        const int32_t d = dag_off[u + 1] - dag_off[u], W = (d + 63) >> 6;
+        const int32_t S = row_stride<DMAX>(W, DEEP);
         build_rows<DMAX, NT, true>(off, okey, dag_off, dag_adj, u, d, S, rows, keys, vals, pre, offj,
                                    lidx, sh.s_sum, verts);
         if (res3 || res4) {
